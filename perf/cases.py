@@ -137,9 +137,10 @@ def prepare(c, seed):
     s = {"path": c["path"], "net": net, "x": x}
     if c["path"] == "train":
         s["labels"] = torch.randint(0, CLASSES, (n,), generator=gen, device=DEVICE, dtype=torch.int32)
-        # views of the updated weights and of the weight gradients inside the parameter buffer
+        # views of the updated weights, and in fp32 of the weight gradients, inside the parameter buffer (in bf16 the gradients
+        # of two correct implementations differ by up to 0.25, see tolerance(): nothing to compare)
         s["trained"] = [net.tensor(i, which) for i, l in enumerate(layers) if l["kind"] in ("conv", "linear")
-                        for which in (sol.NT_W, sol.NT_GRAD_W)]
+                        for which in ((sol.NT_W,) if dt == sol.BF16 else (sol.NT_W, sol.NT_GRAD_W))]
     return s
 
 
@@ -201,11 +202,11 @@ def work(c):
 
 
 def tolerance(c):
-    """Four times what the library's own kernels of different summation orders differ by from one another.  A training
-    step's gradients differ by far more than its sums: a rounding of relative size d puts about 0.4 d of the ReLU
-    decisions on the other side of zero, each of them a whole term, so an activation gradient moves by the square root
-    of that per layer, which adds up to 0.25 in bf16 (d = 0.005) and 0.005 in fp32 in the first layers of the list."""
+    """Four times what the library's own kernels of different summation orders differ by from one another (three steps of
+    training included: logits 0.009 in bf16, gradients 0.006 in fp32).  Gradients differ by far more than sums do: a
+    rounding of relative size d puts about 0.4 d of the ReLU decisions on the other side of zero, each of them a whole
+    term, so an activation gradient moves by the square root of that per layer."""
     bf16 = c["dtype"] == "bf16"
     if c["path"] == "train":
-        return {"rel": 0.6 if bf16 else 0.03}
+        return {"rel": 0.03}
     return {"rel": 0.017 if bf16 else 5e-6}
