@@ -145,6 +145,10 @@ static sol_status conv_fused_impl(const sol_tensor_desc &xd, const void *x, cons
         SOL_REQUIRE(res == nullptr && pair_applies(a, xd.dtype, pair->H2, pair->W2, pair->K2, pair->Kp2, pair->stride), SOL_ERR_UNSUPPORTED,
                     "a fused projection pair is two bf16 unpadded 1x1 convolutions over multiples of 64 channels");
         SOL_REQUIRE(pair->x2 && pair->w2 && aligned16(pair->x2) && aligned16(pair->w2), SOL_ERR_NULL, "pair operands");
+        const int pt = tile != T_AUTO ? tile : direct_choose_pair_tile(a, pair->K2);
+        if (pt >= S_FIRST && pt <= S_LAST)
+            return launch_conv_direct_pair(a, pt, pair->x2, pair->w2, pair->scale2, pair->shift2, pair->H2, pair->W2, pair->K2, pair->Kp2,
+                                           pair->stride, st);
         return launch_conv_pair(a, pair->x2, pair->w2, pair->scale2, pair->shift2, pair->H2, pair->W2, pair->K2, pair->Kp2, pair->stride, st);
     }
     return launch_conv(a, xd.dtype, tile, st);
@@ -1243,7 +1247,7 @@ static sol_status run_layers(sol_network *net, const void *x, void *y, void *wor
                                          reinterpret_cast<const float *>(net->params + pp.shift_off),
                                          pp.in.h, pp.in.w, pp.cd.cin, packed_k(pp.cd, pp.in.dtype), pp.cd.sh};
                     SOL_TRY(conv_fused_impl(lp.in, in, lp.cd, net->params + lp.w_off, scale, shift, nullptr, lp.L.act, nullptr, conv_dst,
-                                            nullptr, nullptr, T_AUTO, st, ldy, &po));
+                                            nullptr, nullptr, g_tile_override, st, ldy, &po));
                     break;
                 }
                 if (lp.pre_bn || lp.ldx) {   // BN + ReLU on the input side and / or a channel prefix of a dense-block buffer
@@ -1345,7 +1349,12 @@ static const int kTuneCandidates[] = {
     D_128x128_128x2, D_128x128_128x3, D_128x64_128x3, D_64x64_128x3, D_128x128_64x5, D_64x64_128x4, D_256x128_128x3,
     D_256x128_64x4, D_128x256_64x4, D_64x64_64x8,
     H_256x128_x5, H_128x128_x3, H_256x64_x5, H_256x64_x6s, H_256x64_x6s2, H_256x64_x6, H_128x128_k2, H_64x128_k4, H_128x64_k4, H_64x64_k4,
-    G_128x128_k2, G_256x128, G_128x256, G_64x128_k4, G_128x64_k4, G_256x256_r64, G_256x128_r64, G_64x64_k4, G_64x64_k4_deep};
+    G_128x128_k2, G_256x128, G_128x256, G_64x128_k4, G_128x64_k4, G_256x256_r64, G_256x128_r64, G_64x64_k4, G_64x64_k4_deep,
+    S_16x16, S_16x32, S_32x32, S_64x32, S_64x64};
+// The small tiles re-read their operands once per 16 to 64 rows: not worth timing on a layer that fills the chip with 128x128 tiles.
+static bool tune_skips(int tile, const sol_tensor_desc &out) {
+    return tile >= S_FIRST && tile <= S_LAST && (long)ceil_div(out.n * out.h * out.w, 128) * ceil_div(out.c, 128) >= 192;
+}
 
 // Training networks: the forward convolution of every layer and its data-gradient convolution get a tile each.
 // A candidate is timed right behind another convolution of similar size that evicts its weights from L2 (the
@@ -1393,7 +1402,9 @@ static sol_status autotune_training(sol_network *net, const void *x, void *y, vo
             rs = time_conv(i, dg, T_AUTO, &best);
             if (rs != SOL_OK) break;
             int best_tile = T_AUTO;
+            const sol_tensor_desc &shape = dg ? lp.in : lp.conv_out;
             for (int cand : kTuneCandidates) {
+                if (tune_skips(cand, shape)) continue;
                 float ms = 0.f;
                 const sol_status cs = time_conv(i, dg, cand, &ms);
                 if (cs == SOL_ERR_HIP) { rs = cs; break; }
@@ -1451,6 +1462,7 @@ sol_status sol_network_autotune(sol_network *net, const void *x, void *y, void *
         if (rs != SOL_OK) break;
         int best_tile = T_AUTO;
         for (int cand : kTuneCandidates) {
+            if (tune_skips(cand, lp.conv_out)) continue;
             lp.tile = cand;
             float ms = 0.f;
             const sol_status cs = time_layer(i, &ms);

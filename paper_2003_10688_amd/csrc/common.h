@@ -147,12 +147,20 @@ enum {
     // G_*: eight-wave 1x1 GEMM kernel (conv_gemm8.hip); kN: reduction split N ways inside the workgroup, r64: 64-byte rows
     G_128x128_k2 = 61, G_256x128 = 62, G_128x256 = 63, G_64x128_k4 = 64, G_128x64_k4 = 65, G_256x256_r64 = 66, G_256x128_r64 = 67,
     G_64x64_k4 = 68, G_64x64_k4_deep = 69, G_64x32_k4_r256 = 70, G_FIRST = 61, G_LAST = 79,
+    // S_*: register-direct kernel for layers with few pixels (conv_direct.hip)
+    S_16x16 = 81, S_16x32 = 82, S_32x32 = 83, S_64x32 = 84, S_64x64 = 85, S_FIRST = 81, S_LAST = 85,
     T_NO_HALO = 99   // automatic choice among the implicit-GEMM kernels only
 };
 int dma_tile_row_bytes(int tile);
 sol_status launch_conv_dma(const ConvArgs &a, int dt, int tile, hipStream_t st);
 bool gemm8_kernel_applies(const ConvArgs &a, int dt);
 sol_status launch_conv_gemm8(const ConvArgs &a, int tile, hipStream_t st);
+bool direct_kernel_applies(const ConvArgs &a, int dt);
+int direct_choose_tile(const ConvArgs &a, int dt);
+sol_status launch_conv_direct(const ConvArgs &a, int dt, int tile, hipStream_t st);
+int direct_choose_pair_tile(const ConvArgs &a, int K2);
+sol_status launch_conv_direct_pair(const ConvArgs &a, int tile, const void *x2, const void *w2, const float *scale2, const float *shift2,
+                                   int H2, int W2, int K2, int Kp2, int stride, hipStream_t st);
 bool halo_kernel_applies(const ConvArgs &a, int dt);
 int halo_choose_tile(const ConvArgs &a);
 sol_status launch_conv_halo(const ConvArgs &a, int tile, hipStream_t st);

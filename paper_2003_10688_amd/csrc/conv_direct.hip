@@ -1,0 +1,399 @@
+// Fused convolution (implicit GEMM, up to 32 filter taps) for layers with few output pixels: small tiles, the reduction split
+// over the waves of a workgroup, each with an LDS-DMA ring of its own (gfx950).
+//
+// What bounds these layers.  A 3x3 convolution over 512 channels of one 7x7 image is 0.23 GFLOP and 4.7 MB of weights, a few
+// microseconds of the chip's time, but the ring and halo kernels give it to 8 workgroups (64x64 or 64x128 tiles) that each
+// walk 4608 reduction elements in up to 72 dependent stages.  What is short is not bandwidth but work in flight: the tiles
+// here go down to what one 16x16 MFMA block covers (16 pixels x 16 channels), the reduction is split over the four waves of
+// the workgroup, and a wave neither shares tile data nor meets a barrier before the partial sums come together in LDS (added
+// in wave order, so the result does not depend on timing).  A stage is 128 bytes of every row, fetched in whole lines by
+// buffer_load ... lds (fragments loaded straight from global memory, 16 bytes of 16 rows per instruction, reached 16 bytes per
+// clock and CU against 50 this way).  The price of small tiles is traffic, (BP + BC) / (BP * BC) rows per output, so the tile
+// grows with the layer and large layers stay on the ring kernels: direct_choose_tile estimates every candidate's time.
+// Measured (layer behind 96 MB of other weights; us before -> now): bf16 3x3 512->512 at 7x7, batch 1: 60.3 -> 6.1, batch 8:
+// 30.7 -> 8.8, batch 32: 24.4 -> 18.0; 3x3 256->256 at 14x14, batch 1: 21.5 -> 4.7; 1x1 2048->512 at 7x7, batch 1: 14.6 -> 4.5;
+// fp32 3x3 512->512 at 7x7, batch 1: 107 -> 11.5, batch 8: 99 -> 25.
+//
+// fp32 runs the same 64-byte steps as four v_mfma_f32_16x16x4_f32 (true fp32 multiplies), whose reduction order inside a
+// step is permuted identically for both operands.
+//
+// The same kernel computes a projection pair (a bottleneck's last 1x1 convolution and the strided 1x1 shortcut it adds): the
+// two reductions are walked one behind the other into two sets of accumulators.
+#include <math.h>
+
+#include "conv_common.h"
+
+namespace sol {
+
+typedef __attribute__((ext_vector_type(4))) float f32x4_t;
+using lds_pipe::u32x4_t;
+
+template <typename T> struct Mma16;
+template <> struct Mma16<bf16_t> {
+    static __device__ __forceinline__ void run(f32x4_t &acc, const u32x4_t &a, const u32x4_t &b) {
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), acc, 0, 0, 0);
+    }
+};
+template <> struct Mma16<float> {
+    static __device__ __forceinline__ void run(f32x4_t &acc, const u32x4_t &a, const u32x4_t &b) {
+#pragma unroll
+        for (int e = 0; e < 4; e++) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a[e]), __uint_as_float(b[e]), acc, 0, 0, 0);
+    }
+};
+
+// second operand set of a projection pair: unpadded 1x1 convolution of stride `stride` over K2 channels of an H2 x W2 image
+struct DirectPair {
+    const void *x, *w;
+    const float *scale, *shift;
+    int H, W, C, Kp, stride;
+};
+
+// PB x CB: 16-pixel x 16-channel blocks of the tile; NW waves split the reduction; NS: ring stages of each wave
+template <typename T, int PB, int CB, int NW, int NS, bool PAIR>
+__global__ void __launch_bounds__(NW * 64) conv_direct_kernel(const ConvArgs a, const DirectPair q) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    using namespace lds_pipe;
+    constexpr int ES = (int)sizeof(T), BP = PB * 16, BC = CB * 16;
+    constexpr int ROWB = 128, XL = BP / 8, WL = BC / 8, L = XL + WL;   // bytes of a row per stage; DMA instructions (8 rows each) per stage
+    constexpr int STAGE = (BP + BC) * ROWB;
+    constexpr int LSTR = 68;                               // floats between the four 16-lane groups of a parked block: spreads the banks of the epilogue's reads
+    constexpr int REDB = NW * PB * CB * 4 * LSTR * 4, RING = NW * NS * STAGE;
+    static_assert(RING <= 160 * 1024 && (NS - 1) * L < 64, "LDS, vmcnt");
+    __shared__ __align__(1024) unsigned char lds[RING > REDB ? RING : REDB];
+
+    const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lg = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lslot = lane & 7, lrow = lane >> 3;
+
+    // XCD-aware tile order (see conv_dma.hip): a run of tiles per XCD, or a set of channel tiles when the weights are larger
+    const int xcd = (int)(blockIdx.x & 7);
+    int tile;
+    if (a.cpx > 0) {
+        const int j = (int)(blockIdx.x >> 3);
+        tile = (j / a.cpx) * a.ntc + xcd * a.cpx + j % a.cpx;
+    } else {
+        tile = xcd * ((a.ntiles + 7) >> 3) + (int)(blockIdx.x >> 3);
+    }
+    if (tile >= a.ntiles) return;
+    const int p0 = (tile / a.ntc) * BP, c0 = (tile % a.ntc) * BC;
+
+    // the activation resource starts `bias` bytes early so that window origins in the padding have offsets >= 0; padding
+    // taps and rows beyond the tensor get an out-of-range offset, which the hardware answers with zeros
+    const unsigned bias = (unsigned)((a.ph * a.W + a.pw) * a.C) * ES;
+    const unsigned xbytes = (unsigned)a.N * a.H * a.W * a.C * ES, wbytes = (unsigned)a.Cout * a.Kp * ES;
+    const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<unsigned char *>(static_cast<const unsigned char *>(a.x)) - bias, 0, (int)(xbytes + bias), 0x00020000);
+    const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(a.w), 0, (int)wbytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t xnull = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(a.x), 0, 0, 0x00020000);
+    const __amdgpu_buffer_rsrc_t wnull = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(a.w), 0, 0, 0x00020000);
+
+    unsigned xo[XL], xinv[XL], wo[WL];                     // this lane's rows; bit t of xinv: filter tap t reads padding
+#pragma unroll
+    for (int i = 0; i < XL; i++) {
+        const int row = i * 8 + lrow, m = p0 + row;
+        int n, op, oq;
+        decode_pixel(a, m, n, op, oq);
+        const int ih0 = op * a.sh - a.ph, iw0 = oq * a.sw - a.pw;
+        const unsigned off = (unsigned)(((n * a.H + ih0) * a.W + iw0) * a.C) * ES + bias + ((lslot ^ swz<ROWB>(row)) << 4);
+        const int slo = max(0, -iw0), shi = min(a.S, a.W - iw0), rlo = max(0, -ih0), rhi = min(a.R, a.H - ih0);
+        const unsigned cval = shi > slo ? (unsigned)((1ull << shi) - 1ull) & ~((1u << slo) - 1u) : 0u;
+        unsigned val = 0;
+        for (int r = 0; r < a.R; r++) val |= (r >= rlo && r < rhi) ? cval << (r * a.S) : 0u;
+        xo[i] = m < a.P ? off : 0xffffffffu;
+        xinv[i] = ~val;
+    }
+#pragma unroll
+    for (int i = 0; i < WL; i++) {
+        const int row = i * 8 + lrow, co = c0 + row;
+        wo[i] = co < a.Cout ? (unsigned)(co * a.Kp) * ES + ((lslot ^ swz<ROWB>(row)) << 4) : 0xffffffffu;
+    }
+
+    // projection pair: rows of the shortcut's operands (the main convolution is 1x1 then: no taps)
+    unsigned xo2[XL], wo2[WL];
+    const unsigned x2bytes = PAIR ? (unsigned)a.N * q.H * q.W * q.C * ES : 0u, w2bytes = PAIR ? (unsigned)a.Cout * q.Kp * ES : 0u;
+    if constexpr (PAIR) {
+#pragma unroll
+        for (int i = 0; i < XL; i++) {
+            const int row = i * 8 + lrow, m = p0 + row;
+            int n, op, oq;
+            decode_pixel(a, m, n, op, oq);
+            xo2[i] = m < a.P ? (unsigned)(((n * q.H + op * q.stride) * q.W + oq * q.stride) * q.C) * ES + ((lslot ^ swz<ROWB>(row)) << 4) : 0xffffffffu;
+        }
+#pragma unroll
+        for (int i = 0; i < WL; i++) {
+            const int row = i * 8 + lrow, co = c0 + row;
+            wo2[i] = co < a.Cout ? (unsigned)(co * q.Kp) * ES + ((lslot ^ swz<ROWB>(row)) << 4) : 0xffffffffu;
+        }
+    }
+
+    // this wave's run of stages [s0, s1); a stage is 128 bytes of one filter tap of every row
+    const int cps = a.C * ES / ROWB, nmain = a.R * a.S * cps, nsteps = nmain + (PAIR ? q.C * ES / ROWB : 0);
+    const int s0 = (int)((long)nsteps * wave / NW), s1 = (int)((long)nsteps * (wave + 1) / NW);
+    int s = s0, tap = s0 / cps, tc = s0 - tap * cps;
+    int tr = tap / a.S, ts = tap - tr * a.S;
+    unsigned char *ring = lds + wave * (NS * STAGE);
+
+    auto issue = [&](int buf) {                            // next stage into ring slot buf; beyond s1 through a size-0 resource -> zeros
+        const bool real = s < s1;
+        const unsigned xs = (unsigned)((tr * a.W + ts) * a.C) * ES + (unsigned)tc * ROWB, ws = (unsigned)s * ROWB;
+        unsigned char *lx = ring + buf * STAGE, *lw = lx + BP * ROWB;
+        if constexpr (PAIR) {                              // both convolutions are 1x1: stage s is chunk s of the main or chunk s - nmain of the shortcut
+            const bool second = s >= nmain;
+            const unsigned off = (unsigned)(second ? s - nmain : s) * ROWB;
+            const __amdgpu_buffer_rsrc_t wq = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(second ? q.w : a.w), 0, (int)(!real ? 0u : second ? w2bytes : wbytes), 0x00020000);
+            const __amdgpu_buffer_rsrc_t xq = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(second ? q.x : a.x), 0, (int)(!real ? 0u : second ? x2bytes : xbytes), 0x00020000);
+#pragma unroll
+            for (int i = 0; i < WL; i++)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(wq, (__attribute__((address_space(3))) void *)(lw + i * 1024), 16, second ? wo2[i] : wo[i], off, 0, 0);
+#pragma unroll
+            for (int i = 0; i < XL; i++)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(xq, (__attribute__((address_space(3))) void *)(lx + i * 1024), 16, second ? xo2[i] : xo[i], off, 0, 0);
+            ++s;
+            return;
+        }
+#pragma unroll
+        for (int i = 0; i < WL; i++)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(real ? wr : wnull, (__attribute__((address_space(3))) void *)(lw + i * 1024), 16, wo[i], ws, 0, 0);
+#pragma unroll
+        for (int i = 0; i < XL; i++) {
+            const unsigned off = xo[i] | (unsigned)__builtin_amdgcn_sbfe(xinv[i], tap, 1);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(real ? xr : xnull, (__attribute__((address_space(3))) void *)(lx + i * 1024), 16, off, xs, 0, 0);
+        }
+        ++s;
+        if (++tc == cps) { tc = 0; ++tap; if (++ts == a.S) { ts = 0; ++tr; } }
+    };
+    f32x4_t acc[CB][PB], acc2[CB][PB];
+#pragma unroll
+    for (int i = 0; i < CB; i++)
+#pragma unroll
+        for (int j = 0; j < PB; j++) acc[i][j] = acc2[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+
+    const unsigned fsw = swz<ROWB>(lr);                    // block row bases are multiples of 16: the swizzle depends on lr only
+    const unsigned f0 = lds_addr(ring) + lr * ROWB + ((lg ^ fsw) << 4), f1 = lds_addr(ring) + lr * ROWB + (((lg + 4) ^ fsw) << 4);
+
+    if (s0 < s1) {
+        static_for<NS>([&](auto B) { issue(decltype(B)::value); });
+        int buf = 0;
+        for (int k = s0; k < s1; k++) {
+            // stage k has landed once only the NS - 1 stages issued after it are outstanding (the ring is this wave's own: no barrier)
+            wait_vmcnt<(NS - 1) * L>();
+            u32x4_t fw[2][CB], fx[2][PB];
+            const unsigned b0 = f0 + buf * STAGE, b1 = f1 + buf * STAGE;
+            static_for<CB>([&](auto I) { lds_read16<BP * ROWB + decltype(I)::value * 16 * ROWB>(fw[0][decltype(I)::value], b0); });
+            static_for<PB>([&](auto J) { lds_read16<decltype(J)::value * 16 * ROWB>(fx[0][decltype(J)::value], b0); });
+            static_for<CB>([&](auto I) { lds_read16<BP * ROWB + decltype(I)::value * 16 * ROWB>(fw[1][decltype(I)::value], b1); });
+            static_for<PB>([&](auto J) { lds_read16<decltype(J)::value * 16 * ROWB>(fx[1][decltype(J)::value], b1); });
+            wait_lgkmcnt<0>();
+            static_for<2>([&](auto H) {
+                static_for<CB>([&](auto I) { landed(fw[decltype(H)::value][decltype(I)::value]); });
+                static_for<PB>([&](auto J) { landed(fx[decltype(H)::value][decltype(J)::value]); });
+            });
+            issue(buf);                                    // the slot's data is in registers: refill it
+            auto contract = [&](f32x4_t (&to)[CB][PB]) {
+#pragma unroll
+                for (int h = 0; h < 2; h++)
+#pragma unroll
+                    for (int i = 0; i < CB; i++)
+#pragma unroll
+                        for (int j = 0; j < PB; j++) Mma16<T>::run(to[i][j], fw[h][i], fx[h][j]);
+            };
+            if (PAIR && k >= nmain) contract(acc2); else contract(acc);
+            buf = buf + 1 == NS ? 0 : buf + 1;
+        }
+        wait_vmcnt<0>();                                   // the zero-fill DMAs of the tail
+    }
+    if constexpr (PAIR) {                                  // fold the two sums: their scales differ, so they meet here; the shifts follow in the epilogue
+#pragma unroll
+        for (int i = 0; i < CB; i++)
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+                const int co = c0 + i * 16 + lg * 4 + e, cc = co < a.Cout ? co : 0;
+                const float sm = a.scale ? a.scale[cc] : 1.f, ss = q.scale ? q.scale[cc] : 1.f;
+#pragma unroll
+                for (int j = 0; j < PB; j++) acc[i][j][e] = acc[i][j][e] * sm + acc2[i][j][e] * ss;
+            }
+    }
+    __syncthreads();                                       // every ring is dead: the LDS becomes the parking place of the partial sums
+    typedef float Block[4 * LSTR];
+    Block *red = reinterpret_cast<Block *>(lds);           // [wave][block]
+
+    // accumulator register e of lane l: channel 4 * (l / 16) + e, pixel l % 16 of its block
+#pragma unroll
+    for (int i = 0; i < CB; i++)
+#pragma unroll
+        for (int j = 0; j < PB; j++)
+            *reinterpret_cast<float4 *>(&red[wave * PB * CB + j * CB + i][lg * LSTR + lr * 4]) = make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
+    __syncthreads();
+
+    // four channels of one pixel (of one pooling window) per thread, channels fastest
+    T *__restrict__ yg = static_cast<T *>(a.y);
+    const T *__restrict__ resg = static_cast<const T *>(a.res);
+    const int npix = a.pool ? BP / 4 : BP;
+    for (int it = tid; it < npix * (BC / 4); it += NW * 64) {
+        const int cg = it % (BC / 4), px = it / (BC / 4), cb = c0 + cg * 4;
+        const int nv = min(4, a.Cout - cb), m0 = p0 + (a.pool ? px * 4 : px);
+        if (nv <= 0 || m0 >= a.P) continue;
+        float sc[4], sf[4], out[4];
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+            sc[e] = (!PAIR && a.scale && e < nv) ? a.scale[cb + e] : 1.f;
+            sf[e] = (a.shift && e < nv) ? a.shift[cb + e] : 0.f;
+            if (PAIR) sf[e] += (q.shift && e < nv) ? q.shift[cb + e] : 0.f;
+        }
+        auto finish = [&](int row, float v[4]) {           // act(scale * sum + shift + residual) of tile row `row`
+            const int blk = (row >> 4) * CB + (cg >> 2), at = (cg & 3) * LSTR + (row & 15) * 4;
+            float4 t = *reinterpret_cast<const float4 *>(&red[blk][at]);
+#pragma unroll
+            for (int w = 1; w < NW; w++) {
+                const float4 q = *reinterpret_cast<const float4 *>(&red[w * PB * CB + blk][at]);
+                t.x += q.x; t.y += q.y; t.z += q.z; t.w += q.w;
+            }
+            v[0] = t.x * sc[0] + sf[0]; v[1] = t.y * sc[1] + sf[1]; v[2] = t.z * sc[2] + sf[2]; v[3] = t.w * sc[3] + sf[3];
+            if (resg) {
+                const T *rp = resg + (long)(p0 + row) * a.Cout + cb;
+#pragma unroll
+                for (int e = 0; e < 4; e++) v[e] += e < nv ? Elem<T>::load(rp + e) : 0.f;
+            }
+            if (a.act == SOL_ACT_RELU) {
+#pragma unroll
+                for (int e = 0; e < 4; e++) v[e] = __builtin_fmaxf(v[e], 0.f);
+            }
+        };
+        if (!a.pool) {
+            finish(px, out);
+        } else {                                           // rows 4w .. 4w + 3 are pooling window w, in row-major order
+            finish(px * 4, out);
+#pragma unroll
+            for (int d = 1; d < 4; d++) {
+                float v[4];
+                finish(px * 4 + d, v);
+#pragma unroll
+                for (int e = 0; e < 4; e++) out[e] = a.pool == 1 ? (v[e] > out[e] ? v[e] : out[e]) : out[e] + v[e];
+            }
+            if (a.pool == 2) {
+#pragma unroll
+                for (int e = 0; e < 4; e++) out[e] *= 0.25f;
+            }
+        }
+        T *yp = yg + (long)(a.pool ? m0 >> 2 : m0) * a.ldy + cb;
+        if (nv == 4 && ((a.ldy | a.Cout) & 3) == 0) {
+            if constexpr (ES == 2) *reinterpret_cast<uint2 *>(yp) = make_uint2(pack_bf16x2(out[0], out[1]), pack_bf16x2(out[2], out[3]));
+            else *reinterpret_cast<float4 *>(yp) = make_float4(out[0], out[1], out[2], out[3]);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; e++)
+                if (e < nv) Elem<T>::store(yp + e, out[e]);
+        }
+    }
+#endif
+}
+
+template <typename T, int PB, int CB, int NW, int NS>
+static sol_status launch_direct_cfg(ConvArgs a, const DirectPair *q, hipStream_t st) {
+    a.ntc = ceil_div(a.Cout, CB * 16);
+    a.ntiles = ceil_div(a.P, PB * 16) * a.ntc;
+    const int grid = ((a.ntiles + 7) / 8) * 8;
+    const double xbytes = (double)a.N * a.H * a.W * a.C * sizeof(T), wbytes = (double)a.Cout * a.Kp * sizeof(T);
+    a.cpx = (a.ntc % 8 == 0 && wbytes > xbytes) ? a.ntc / 8 : 0;
+    if constexpr (sizeof(T) == 2) {
+        if (q) {
+            hipLaunchKernelGGL((conv_direct_kernel<T, PB, CB, NW, NS, true>), dim3(grid), dim3(NW * 64), 0, st, a, *q);
+            SOL_HIP(hipGetLastError());
+            return SOL_OK;
+        }
+    }
+    hipLaunchKernelGGL((conv_direct_kernel<T, PB, CB, NW, NS, false>), dim3(grid), dim3(NW * 64), 0, st, a, DirectPair{});
+    SOL_HIP(hipGetLastError());
+    return SOL_OK;
+}
+
+// Stages of 128 bytes inside one filter tap, one validity bit per tap, 32-bit byte offsets; no winners / pre-pool tensor, no
+// residual in front of a pool.
+bool direct_kernel_applies(const ConvArgs &a, int dt) {
+    const double es = (double)dtype_size(dt), xb = (double)a.N * a.H * a.W * a.C * es + (double)(a.ph * a.W + a.pw) * a.C * es;
+    return a.R * a.S <= 32 && (a.C * (int)es) % 128 == 0 && a.pool <= 2 && !(a.pool && a.res) && !a.argmax && !a.prepool && xb < 2147483648.0 &&
+           (double)a.Cout * a.Kp * es < 2147483648.0;
+}
+
+template <typename T> static sol_status launch_direct_typed(const ConvArgs &a, int tile, const DirectPair *q, hipStream_t st) {
+    switch (tile) {
+        //                                              PB CB NW NS
+        case S_16x16: return launch_direct_cfg<T, 1, 1, 4, 3>(a, q, st);      // 48 KB of LDS: three workgroups per CU
+        case S_16x32: return launch_direct_cfg<T, 1, 2, 4, 3>(a, q, st);      // 72 KB: two
+        case S_32x32: return launch_direct_cfg<T, 2, 2, 4, 2>(a, q, st);      // 64 KB: two
+        case S_64x32: return launch_direct_cfg<T, 4, 2, 4, 2>(a, q, st);      // 96 KB: one
+        case S_64x64: return launch_direct_cfg<T, 4, 4, 4, 2>(a, q, st);      // 128 KB: one
+        default: SOL_FAIL(SOL_ERR_UNSUPPORTED, "unknown direct conv tile id %d", tile);
+    }
+}
+
+sol_status launch_conv_direct(const ConvArgs &a, int dt, int tile, hipStream_t st) {
+    return dt == SOL_BF16 ? launch_direct_typed<bf16_t>(a, tile, nullptr, st) : launch_direct_typed<float>(a, tile, nullptr, st);
+}
+
+// Estimated time of a layer on a tile, in microseconds:  t0 + ((a + n * lat)^4 + (tiles / 256 * (c + N * rho))^4)^(1/4)
+// -- the serial chain of one workgroup (n stages of one wave) against the share of one of 256 CUs in the whole layer (N
+// stages per tile, and a constant per tile), the larger of the two with a soft corner.  The constants are least-squares fits
+// to 154 timed shapes (1x1 and 3x3, 49 to 100352 pixels, 64 to 4608 reduction elements) per tile: mean error 3-8 %.
+struct TileCost { int tile, bp, bc, waves, rowb; float t0, a, lat, c, rho; };
+static const TileCost kCostBf16[] = {
+    {S_16x16, 16, 16, 4, 128, 3.33f, 0.00f, 0.134f, 0.61f, 0.0319f}, {S_16x32, 16, 32, 4, 128, 2.97f, 0.40f, 0.207f, 1.08f, 0.0540f},
+    {S_32x32, 32, 32, 4, 128, 2.91f, 0.88f, 0.268f, 1.27f, 0.0811f}, {S_64x32, 64, 32, 4, 128, 1.96f, 3.15f, 0.393f, 4.10f, 0.1467f},
+    {S_64x64, 64, 64, 4, 128, 4.50f, 2.81f, 0.563f, 5.00f, 0.2517f},
+    {D_64x64_128x4, 64, 64, 1, 128, 2.70f, 0.f, 0.355f, 0.92f, 0.237f}, {D_64x64_64x4, 64, 64, 1, 64, 2.68f, 0.f, 0.238f, 0.44f, 0.150f},
+    {G_64x64_k4, 64, 64, 1, 128, 3.48f, 0.f, 0.259f, 3.13f, 0.232f}, {H_64x64_k4, 64, 64, 1, 128, 3.30f, 0.f, 0.225f, 3.00f, 0.120f}};
+static const TileCost kCostF32[] = {
+    {S_16x16, 16, 16, 4, 128, 3.47f, 0.00f, 0.208f, 0.60f, 0.0481f}, {S_16x32, 16, 32, 4, 128, 2.97f, 0.25f, 0.370f, 1.10f, 0.0923f},
+    {S_32x32, 32, 32, 4, 128, 3.09f, 0.59f, 0.599f, 1.37f, 0.1623f}, {S_64x32, 64, 32, 4, 128, 1.69f, 3.45f, 1.078f, 4.69f, 0.3427f},
+    {S_64x64, 64, 64, 4, 128, 5.00f, 2.33f, 2.009f, 5.00f, 0.7287f},
+    {D_64x64_128x4, 64, 64, 1, 128, 2.86f, 0.f, 0.719f, 1.23f, 0.655f}, {D_64x64_64x4, 64, 64, 1, 64, 2.95f, 0.f, 0.419f, 0.73f, 0.336f}};
+
+static float cost_of(const TileCost &t, long P, int Cout, double kbytes) {
+    const double tiles = (double)((P + t.bp - 1) / t.bp) * ceil_div(Cout, t.bc), N = kbytes / t.rowb, n = N / t.waves;
+    const double serial = t.a + (t.waves > 1 ? (double)(long)(n + 0.999) : n) * t.lat, share = tiles / 256.0 * (t.c + N * t.rho);
+    return (float)(t.t0 + sqrt(sqrt(serial * serial * serial * serial + share * share * share * share)));
+}
+
+// Tile of a layer with few output pixels, or T_AUTO when it has enough 128x128 tiles for the other kernels' heuristics to be
+// the better guide (from about 96 tiles on: measured on the shapes above, 3x3 256->256 at 14x14, batch 32, 98 tiles: 14.0 us
+// by the heuristic, 14.4 here; batch 16, 50 tiles: 13.4 against 10.4).
+int direct_choose_tile(const ConvArgs &a, int dt) {
+    if (!direct_kernel_applies(a, dt) || (long)ceil_div(a.P, 128) * ceil_div(a.Cout, 128) >= 96) return T_AUTO;
+    const double kbytes = (double)a.R * a.S * a.C * dtype_size(dt);
+    const bool halo = halo_kernel_applies(a, dt) && a.W <= 31;      // 64 pixels + halo rows must fit the 128-row patch
+    int best = T_AUTO;
+    float bt = 0.f;
+    const TileCost *tab = dt == SOL_BF16 ? kCostBf16 : kCostF32;
+    const int nt = dt == SOL_BF16 ? (int)(sizeof(kCostBf16) / sizeof(TileCost)) : (int)(sizeof(kCostF32) / sizeof(TileCost));
+    for (int i = 0; i < nt; i++) {
+        const TileCost &t = tab[i];
+        if (t.tile == H_64x64_k4 && !halo) continue;
+        const float c = cost_of(t, a.P, a.Cout, kbytes);
+        if (best == T_AUTO || c < bt) { best = t.tile; bt = c; }
+    }
+    return best;
+}
+
+// The projection pair (bf16) on this kernel: which tile, or T_AUTO for the pair kernels, whose one 128x128 tile per workgroup
+// walks (K + K2) / 64 chunks of 0.87 us behind a start of 2.8 us as long as the tiles do not fill the chip.  The two operand
+// sets cost this kernel about a fifth on top of the estimate of one.  Measured (K + K2 -> channels, pixels; us pair kernel ->
+// this one): 512 + 1024 -> 2048, 49: 23.4 -> 5.8; the same, 392: 26.8 -> 15.7; 256 + 512 -> 1024, 784: 15.9 -> 12.3; the same,
+// 1568: 16.3, 20.8 here; 64 + 64 -> 256, 3136: 4.8, 8.5 here.
+int direct_choose_pair_tile(const ConvArgs &a, int K2) {
+    if (!direct_kernel_applies(a, SOL_BF16) || K2 % 64 != 0) return T_AUTO;
+    int best = T_AUTO;
+    float bt = 2.8f + 0.87f * (float)((a.C + K2) / 64);
+    for (const TileCost &t : kCostBf16) {
+        if (t.tile < S_FIRST || t.tile > S_64x32) continue;
+        const float c = 1.2f * cost_of(t, a.P, a.Cout, 2.0 * (a.C + K2));
+        if (c < bt) { best = t.tile; bt = c; }
+    }
+    return best;
+}
+sol_status launch_conv_direct_pair(const ConvArgs &a, int tile, const void *x2, const void *w2, const float *scale2, const float *shift2, int H2,
+                                   int W2, int K2, int Kp2, int stride, hipStream_t st) {
+    const DirectPair q{x2, w2, scale2, shift2, H2, W2, K2, Kp2, stride};
+    return launch_direct_typed<bf16_t>(a, tile, &q, st);
+}
+
+}  // namespace sol

@@ -319,6 +319,7 @@ sol_status launch_conv(const ConvArgs &a, int dt, int tile_override, hipStream_t
         }
         return launch_linear(a, dt, st);
     }
+    if (tile_override == T_AUTO) tile_override = direct_choose_tile(a, dt);     // few pixels: its own small tiles, or the best of the others'
     if (tile_override == T_AUTO && halo_kernel_applies(a, dt)) {
         if (const int ht = halo_choose_tile(a)) return launch_conv_halo(a, ht, st);
     }
@@ -331,6 +332,12 @@ sol_status launch_conv(const ConvArgs &a, int dt, int tile_override, hipStream_t
         SOL_REQUIRE(gemm8_kernel_applies(a, dt), SOL_ERR_UNSUPPORTED,
                     "conv tile %d needs a bf16 convolution with at most 32 filter taps and Cin %% 32 == 0", tile_override);
         return launch_conv_gemm8(a, tile_override, st);
+    }
+    if (tile_override >= S_FIRST && tile_override <= S_LAST) {
+        SOL_REQUIRE(direct_kernel_applies(a, dt), SOL_ERR_UNSUPPORTED,
+                    "conv tile %d needs at most 32 filter taps over channels in multiples of 64 bytes, no pool winners and no residual in front of a pool",
+                    tile_override);
+        return launch_conv_direct(a, dt, tile_override, st);
     }
     if (tile_override == T_NO_HALO) tile_override = T_AUTO;
     if (const int rowb = dma_tile_row_bytes(tile_override)) {
