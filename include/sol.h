@@ -337,8 +337,11 @@ void sol_graph_destroy(sol_graph *graph);
  *     shortcut) whose only reader is the residual input of a later unpadded 1x1 stride-1 convolution over a multiple
  *     of 64 channels runs inside that convolution's launch; its output is never stored, and never rounded to the storage type either (the result differs from
  *     the two-launch result by at most one rounding of the shortcut term).
+ *   - a 1x1 stride-1 convolution with an input-side BN + ReLU (pre_bn), 128 filters and ReLU whose only reader is a 3x3 stride-1
+ *     pad-1 convolution of 32 filters without pool or residual (a dense layer) runs inside that convolution's launch; its
+ *     output, rounded to bf16 as it would be stored, stays in on-chip memory.
  * *into = index of the layer whose launch produces `layer`'s output: `layer` itself, the layer in front for such a
- * pool layer, the later convolution for such a shortcut, the last convolution of a bottleneck that runs as one launch
+ * pool layer, the later convolution for such a shortcut or such a 1x1 convolution, the last convolution of a bottleneck that runs as one launch
  * (see sol_network_set_layer_block) for its first two, the first layer of an expand -> reduce pair (see
  * sol_network_set_layer_xr) for its second (sol_network_run_layer on a fused layer launches nothing). */
 sol_status sol_network_layer_fused_into(const sol_network *net, int layer, int *into);

@@ -214,6 +214,7 @@ struct LayerPlan {
     bool use_block;                 // on the last convolution: the plan runs the bottleneck as one launch (heuristic or sol_network_autotune)
     int xr_next, xr_from;           // CONV (last 1x1 of a bottleneck): the next bottleneck's first 1x1, which the same launch can compute (conv_xr.hip); on that layer: the former (-1: none)
     bool use_xr;                    // on the former: the plan runs the two as one launch
+    int dense_c1;                   // CONV (3x3 of a dense layer): the pre-activated 1x1 convolution that its launch also computes (-1: none)
     bool pre_bn, pre_set;           // CONV: BN + ReLU on the input side; its folded constants have been set
     size_t pre_scale_off, pre_shift_off;
     int ldx;                        // CONV: input pixel pitch when the input is a channel prefix of a dense-block buffer (0: dense)
@@ -394,7 +395,7 @@ static sol_status plan_network(sol_network *net, const sol_layer *layers, int n_
         lp.concat_into = -1;
         lp.pair = -1;
         lp.block_c1 = lp.block_c2 = lp.block_c3 = -1;
-        lp.xr_next = lp.xr_from = -1;
+        lp.xr_next = lp.xr_from = lp.dense_c1 = -1;
         lp.chain_owner = -1;
         lp.fused_into = i;
         lp.in = lp.src < 0 ? net->input : net->layers[lp.src].out;
@@ -637,6 +638,27 @@ static sol_status plan_network(sol_network *net, const sol_layer *layers, int n_
                 off += p.out.c;
                 k++;
             }
+        }
+
+    // Dense layer (depth-first again): a pre-activated 1x1 convolution + ReLU whose only reader is a 3x3 convolution runs inside
+    // that convolution's launch, its output is never stored (conv_dense.hip).  Measured faster than the two launches at every
+    // size tried (one image of 7x7 to 64 of 56x56), so the plan needs no second opinion.
+    if (!net->training && !net->keep && dt == SOL_BF16)
+        for (int i = 0; i < n_layers; i++) {
+            LayerPlan &c2 = net->layers[i];
+            const auto plain = [](const LayerPlan &l) {
+                return l.L.kind == SOL_LAYER_CONV && l.L.pool.kind == SOL_POOL_NONE && l.res < 0 && !l.cout_real && l.pair < 0 && !l.elided &&
+                       !l.absorbs_next && l.cd.sh == 1 && l.cd.sw == 1;
+            };
+            if (!plain(c2) || c2.cin_real || c2.pre_bn || c2.ldx || c2.src < 0 || c2.cd.kh != 3 || c2.cd.kw != 3 || c2.cd.ph != 1 || c2.cd.pw != 1) continue;
+            LayerPlan &c1 = net->layers[c2.src];
+            if (!plain(c1) || !c1.pre_bn || c1.L.act != SOL_ACT_RELU || c1.nuse != 1 || c1.concat_into >= 0 || c1.cd.kh != 1 || c1.cd.kw != 1 || c1.cd.ph || c1.cd.pw) continue;
+            const int ldy = c2.concat_into >= 0 ? net->layers[c2.concat_into].out.c : c2.cd.cout;
+            if (!dense_kernel_applies(dt, c1.in.n, c1.in.h, c1.in.w, (int)round_up((size_t)c1.cd.cin, 64), c1.ldx ? c1.ldx : c1.cd.cin, c1.cd.cout, c2.cd.cout, ldy)) continue;
+            c2.dense_c1 = c2.src;
+            c1.elided = c1.no_buffer = true;
+            c1.fused_into = i;
+            if (c1.src >= 0) net->layers[c1.src].last_use = std::max(net->layers[c1.src].last_use, i);   // read by layer i now
         }
 
     // Depth-first bottleneck (the paper's layer-chain fusion, Sec. III-A, across three contractions): 1x1 reduce + ReLU,
@@ -1250,6 +1272,15 @@ static sol_status run_layers(sol_network *net, const void *x, void *y, void *wor
                                             nullptr, nullptr, g_tile_override, st, ldy, &po));
                     break;
                 }
+                if (lp.dense_c1 >= 0) {      // a dense layer: this launch also computes the pre-activated 1x1 convolution in front
+                    const LayerPlan &c1 = net->layers[lp.dense_c1];
+                    const auto fp = [&](size_t off) { return reinterpret_cast<const float *>(net->params + off); };
+                    const DenseLaunch dl{layer_in(net, c1.src, x, ws), c1.ldx ? c1.ldx : c1.cd.cin, (int)round_up((size_t)c1.cd.cin, 64), c1.cin_real ? c1.cin_real : c1.cd.cin,
+                                         fp(c1.pre_scale_off), fp(c1.pre_shift_off), net->params + c1.w_off, packed_k(c1.cd, lp.in.dtype), fp(c1.scale_off),
+                                         fp(c1.shift_off), net->params + lp.w_off, scale, shift, conv_dst, ldy ? ldy : lp.cd.cout, lp.L.act, lp.in.n, lp.in.h, lp.in.w};
+                    SOL_TRY(launch_conv_dense(dl, g_tile_override >= B_FIRST && g_tile_override <= B_LAST ? g_tile_override - B_FIRST : -1, st));
+                    break;
+                }
                 if (lp.pre_bn || lp.ldx) {   // BN + ReLU on the input side and / or a channel prefix of a dense-block buffer
                     sol_tensor_desc xin = lp.in;
                     xin.c = lp.cd.cin;
@@ -1456,7 +1487,7 @@ sol_status sol_network_autotune(sol_network *net, const void *x, void *y, void *
         LayerPlan &lp = net->layers[i];
         if (lp.L.kind != SOL_LAYER_CONV || lp.in.n == 0) continue;
         if (lp.absorbs_next || (lp.fuse_pool && !pool_is_fusable(lp.L.pool))) continue;   // stem + pool: one kernel, nothing to choose
-        if (lp.elided || lp.pair >= 0) continue;                                          // projection pair: likewise
+        if (lp.elided || lp.pair >= 0 || lp.dense_c1 >= 0) continue;                      // projection pair, dense layer: likewise
         float best = 0.f;
         rs = time_layer(i, &best);                            // the shape heuristic's choice is the incumbent
         if (rs != SOL_OK) break;

@@ -149,6 +149,8 @@ enum {
     G_64x64_k4 = 68, G_64x64_k4_deep = 69, G_64x32_k4_r256 = 70, G_FIRST = 61, G_LAST = 79,
     // S_*: register-direct kernel for layers with few pixels (conv_direct.hip)
     S_16x16 = 81, S_16x32 = 82, S_32x32 = 83, S_64x32 = 84, S_64x64 = 85, S_FIRST = 81, S_LAST = 85,
+    // B_*: patch rows of the dense-layer kernel (conv_dense.hip); not a choice of any other layer
+    B_64 = 91, B_96 = 92, B_128 = 93, B_192 = 94, B_256 = 95, B_384 = 96, B_FIRST = 91, B_LAST = 96,
     T_NO_HALO = 99   // automatic choice among the implicit-GEMM kernels only
 };
 int dma_tile_row_bytes(int tile);
@@ -189,6 +191,17 @@ struct XrLaunch {
 };
 bool xr_kernel_applies(int dt, long P, int WM, int C4, int WZ);
 sol_status launch_conv_xr(const XrLaunch &b, hipStream_t st);
+// a dense layer (BN + ReLU, 1x1 to 128 channels, BN + ReLU, 3x3 to 32 channels) in one kernel (conv_dense.hip)
+struct DenseLaunch {
+    const void *x; int ldx, C, Cvalid;               // block buffer, its pixel pitch, channels read (a multiple of 64), real ones among them
+    const float *ps, *ph;                            // input-side scale / shift [C]
+    const void *w1; int Kp1; const float *s1, *h1;   // packed 1x1 weights [128][Kp1], folded scale / shift
+    const void *w2; const float *s2, *h2;            // packed 3x3 weights [32][9*128], folded scale / shift
+    void *y; int ldy, act;
+    int N, H, W;
+};
+bool dense_kernel_applies(int dt, int N, int H, int W, int C, int ldx, int mid, int cout, int ldy);
+sol_status launch_conv_dense(const DenseLaunch &d, int variant, hipStream_t st);
 bool linear_kernel_applies(const ConvArgs &a, int dt);
 sol_status launch_linear(const ConvArgs &a, int dt, hipStream_t st);
 sol_status launch_conv(const ConvArgs &a, int dt, int tile_override, hipStream_t st);
