@@ -9,6 +9,7 @@ namespace sol {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 typedef __attribute__((ext_vector_type(16))) float f32x16_t;
+typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 
 template <typename T> struct Mma;
 template <> struct Mma<bf16_t> {
@@ -61,6 +62,21 @@ __device__ __forceinline__ unsigned xor_add(unsigned a, unsigned x, unsigned b) 
 template <int ROWB> __device__ __forceinline__ int swz(int row) { return ROWB == 256 ? (row & 15) : ROWB == 128 ? ((row >> 1) & 7) : ((row >> 2) & 3); }
 
 }  // namespace lds_pipe
+
+// one 64-byte step of a 16 x 16 block: v_mfma_f32_16x16x32_bf16, or four v_mfma_f32_16x16x4_f32 (true fp32 multiplies, the
+// reduction order inside the step permuted identically for both operands)
+template <typename T> struct Mma16;
+template <> struct Mma16<bf16_t> {
+    static __device__ __forceinline__ void run(f32x4_t &acc, const lds_pipe::u32x4_t &a, const lds_pipe::u32x4_t &b) {
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), acc, 0, 0, 0);
+    }
+};
+template <> struct Mma16<float> {
+    static __device__ __forceinline__ void run(f32x4_t &acc, const lds_pipe::u32x4_t &a, const lds_pipe::u32x4_t &b) {
+#pragma unroll
+        for (int e = 0; e < 4; e++) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a[e]), __uint_as_float(b[e]), acc, 0, 0, 0);
+    }
+};
 
 // Warms this XCD's L2 with a range of the layer's packed weights.  Inside a network the weights of a layer are
 // cold when it starts, every workgroup streams the same rows in lock step, and each stage would stall on an HBM

@@ -25,21 +25,7 @@
 
 namespace sol {
 
-typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 using lds_pipe::u32x4_t;
-
-template <typename T> struct Mma16;
-template <> struct Mma16<bf16_t> {
-    static __device__ __forceinline__ void run(f32x4_t &acc, const u32x4_t &a, const u32x4_t &b) {
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), acc, 0, 0, 0);
-    }
-};
-template <> struct Mma16<float> {
-    static __device__ __forceinline__ void run(f32x4_t &acc, const u32x4_t &a, const u32x4_t &b) {
-#pragma unroll
-        for (int e = 0; e < 4; e++) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a[e]), __uint_as_float(b[e]), acc, 0, 0, 0);
-    }
-};
 
 // second operand set of a projection pair: unpadded 1x1 convolution of stride `stride` over K2 channels of an H2 x W2 image
 struct DirectPair {

@@ -308,8 +308,9 @@ sol_status launch_conv(const ConvArgs &a, int dt, int tile_override, hipStream_t
     if (a.P <= 0) return SOL_OK;   // empty batch: nothing to do
     if (a.pre_scale || a.ldx != a.C || a.Cvalid != a.C) return launch_conv_staged(a, dt, tile_override, st);
     if (tile_override == T_AUTO && stem_kernel_applies(a, dt)) return launch_conv_stem(a, st);
+    if (tile_override == T_AUTO && linear_stream_applies(a, dt)) return launch_linear_stream(a, dt, st);
     if (tile_override == T_AUTO && linear_kernel_applies(a, dt)) {
-        // few rows, but a weight matrix of many megabytes (the MLP workload): the job is streaming the weights, which the
+        // more rows than linear_stream_applies takes, and a weight matrix of many megabytes: the job is streaming the weights, which the
         // eight-wave ring kernel does with whole 128-byte lines and eight stages in flight
         const double wbytes = (double)a.Cout * a.Kp * dtype_size(dt);
         if (wbytes >= 16.0 * 1048576 && gemm8_kernel_applies(a, dt) && a.C % 64 == 0) {
