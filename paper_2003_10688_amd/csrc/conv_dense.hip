@@ -15,7 +15,7 @@
 //    to a zero row); w2 continues in the same ring, two taps to a stage.  The waves split the reduction KSB ways, and
 //    the partial sums meet in LDS in a fixed order.
 // Measured (batch 64, two launches -> one): 56x56, 64..224 channels: 76 -> 41..66 us; 28x28, 128..480: 30 -> 14..22; 14x14,
-// 256..992: 29 -> 10..18; 7x7, 512..992: 24 -> 10..13; DenseNet-121-shaped pass 2276 -> 1302 us.  A chunk of phase A costs a
+// 256..992: 29 -> 10..18; 7x7, 512..992: 24 -> 10..13; DenseNet-121-shaped pass 2343 -> 1292 us.  A chunk of phase A costs a
 // workgroup 0.4 us (64 rows) to 1.5 us (384): BN + ReLU, fragment reads, MFMAs and DMA issue of a chunk take about a
 // quarter of that each and hardly overlap, since all eight waves run the same sequence between two barriers.  (Half of the
 // waves in the other order, transform against multiply: slower, 18.0 -> 20.2 us at 14x14; it doubles the code and the registers.)
@@ -29,7 +29,9 @@ typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 using lds_pipe::u32x4_t;
 typedef __attribute__((ext_vector_type(2))) unsigned u32x2_t;
 
-__device__ __forceinline__ void lds_write16(unsigned addr, const u32x4_t &v) { asm volatile("ds_write_b128 %0, %1" ::"v"(addr), "v"(v) : "memory"); }
+template <int O> __device__ __forceinline__ void lds_write16(unsigned addr, const u32x4_t &v) {
+    asm volatile("ds_write_b128 %0, %1 offset:%2" ::"v"(addr), "v"(v), "n"(O) : "memory");
+}
 __device__ __forceinline__ void lds_write8(unsigned addr, const u32x2_t &v) { asm volatile("ds_write_b64 %0, %1" ::"v"(addr), "v"(v) : "memory"); }
 __device__ __forceinline__ void mma(f32x4_t &acc, const u32x4_t &a, const u32x4_t &b) {
     acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), acc, 0, 0, 0);
@@ -94,19 +96,22 @@ __global__ void __launch_bounds__(512) conv_dense_kernel(const DenseArgs a) {
     };
     // ---- x rows: piece i of this thread = 16-byte slot (tid & 7) of patch row (tid >> 3) + 64 * i
     const int xslot = tid & 7;
-    unsigned xo[XR], xl[XR];                               // byte offset in x (out of range: zeros); LDS offset inside a chunk buffer
-#pragma unroll
-    for (int i = 0; i < XR; i++) {
-        const int row = (tid >> 3) + 64 * i, p = p0 - W - 1 + row;
-        xo[i] = (row < PR && p >= 0 && p < P) ? (unsigned)(p * d.ldx) * 2 + (xslot << 4) : 0xffffffffu;
-        xl[i] = (unsigned)min(row, PR - 1) * 128 + ((xslot ^ swz<128>(row)) << 4);
-    }
+    // byte offset of piece 0 in x; rows outside x wrap or run past its end, where the buffer's own check returns zeros (nothing reads
+    // what becomes of them: their taps are padding).  The other pieces' offsets are added up at each load and not kept in registers.
+    const unsigned xo = (unsigned)((p0 - W - 1 + (tid >> 3)) * d.ldx) * 2 + (xslot << 4), xstep = (unsigned)d.ldx * 128;
+    // LDS offset of piece 0 inside a chunk buffer; piece i lies 64 rows on, where the slot permutation is the same: an immediate
+    // offset (an address per piece took the 384-row variant over 256 registers, 16 bytes of scratch per lane;
+    // without them the DenseNet-121-shaped pass, batch 64, takes 1292 us instead of 1300)
+    const unsigned xl = (unsigned)(tid >> 3) * 128 + ((xslot ^ swz<128>(tid >> 3)) << 4);
     u32x4_t xv[DX][XR];
     auto load_x = [&](auto S, int c) {
         constexpr int s = decltype(S)::value;
         const unsigned so = (unsigned)min(c, nc - 1) * 128u;
+        unsigned off = xo, by = xstep;
+        asm volatile("" : "+s"(by));                       // not an invariant of the loop, to the compiler
 #pragma unroll
-        for (int i = 0; i < XR; i++) xv[s][i] = __builtin_amdgcn_raw_buffer_load_b128(xr, xo[i], so, 0);
+        for (int i = 0; i < XR; i++, off += by)
+            xv[s][i] = __builtin_amdgcn_raw_buffer_load_b128(xr, XR * 64 == PR || (tid >> 3) + 64 * i < PR ? off : 0xffffffffu, so, 0);
     };
     // input-side constants of this thread's eight channels of the next chunk to go to LDS; fetched one iteration ahead
     u32x4_t q[4];
@@ -124,9 +129,9 @@ __global__ void __launch_bounds__(512) conv_dense_kernel(const DenseArgs a) {
     // relu(scale * x + shift) of chunk c from register set S into chunk buffer c & 1; channels past the prefix are zeros
     auto put_x = [&](auto S, int c) {
         constexpr int s = decltype(S)::value;
-        const unsigned xb = lbase + (c & 1) * (PR * 128);
-#pragma unroll
-        for (int i = 0; i < XR; i++) {
+        const unsigned xb = lbase + (c & 1) * (PR * 128) + xl;
+        static_for<XR>([&](auto I) {
+            constexpr int i = decltype(I)::value;
             u32x4_t o;
 #pragma unroll
             for (int e = 0; e < 4; e++) {
@@ -141,8 +146,8 @@ __global__ void __launch_bounds__(512) conv_dense_kernel(const DenseArgs a) {
 #pragma unroll
                 for (int e = 0; e < 4; e++) o[e] = left >= 2 * e + 2 ? o[e] : left == 2 * e + 1 ? o[e] & 0xffffu : 0u;
             }
-            if (XR * 64 == PR || (tid >> 3) + 64 * i < PR) lds_write16(xb + xl[i], o);
-        }
+            if (XR * 64 == PR || (tid >> 3) + 64 * i < PR) lds_write16<i * 8192>(xb, o);
+        });
     };
 
     // ---- prologue
@@ -169,8 +174,8 @@ __global__ void __launch_bounds__(512) conv_dense_kernel(const DenseArgs a) {
 #pragma unroll
         for (int j = 0; j < PA; j++) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     const int wpa = wave % WPA, wca = wave / WPA;
-    const unsigned fsw = swz<128>(lr);
-    const unsigned fx = lbase + (wpa * PA * 16 + lr) * 128, fw = lbase + RING0 + (wca * CA * 16 + lr) * 128;
+    // slot of the first k-step's fragment included; the second one's is four slots away: bit 6 of the address flipped
+    const unsigned so0 = (lg ^ swz<128>(lr)) << 4, fx = lbase + (wpa * PA * 16 + lr) * 128 + so0, fw = lbase + RING0 + (wca * CA * 16 + lr) * 128 + so0;
 
     read_pre(0);
     wait_lgkmcnt<0>();
@@ -189,9 +194,9 @@ __global__ void __launch_bounds__(512) conv_dense_kernel(const DenseArgs a) {
         u32x4_t fa[BOTH ? 2 : 1][CA], fb[BOTH ? 2 : 1][PA];
         auto read = [&](auto H, auto F) {
             constexpr int f = decltype(F)::value;
-            const unsigned so = ((decltype(H)::value * 4 + lg) ^ fsw) << 4;
-            static_for<CA>([&](auto I) { lds_read16<decltype(I)::value * 2048>(fa[f][decltype(I)::value], wb + so); });
-            static_for<PA>([&](auto J) { lds_read16<decltype(J)::value * 2048>(fb[f][decltype(J)::value], xb + so); });
+            constexpr unsigned flip = decltype(H)::value * 64;
+            static_for<CA>([&](auto I) { lds_read16<decltype(I)::value * 2048>(fa[f][decltype(I)::value], wb ^ flip); });
+            static_for<PA>([&](auto J) { lds_read16<decltype(J)::value * 2048>(fb[f][decltype(J)::value], xb ^ flip); });
         };
         auto frags_landed = [&](auto F) {
             constexpr int f = decltype(F)::value;
