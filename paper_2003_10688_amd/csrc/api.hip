@@ -70,7 +70,8 @@ static sol_status conv_fused_impl(const sol_tensor_desc &xd, const void *x, cons
                                   const float *scale, const float *shift, const void *res, int act,
                                   const sol_pool_desc *pool, void *y, int32_t *argmax, void *prepool, int tile,
                                   hipStream_t st, int ldy = 0,     // ldy: elements between output pixels in y, 0 = cout (dense)
-                                  const PairOperand *pair = nullptr, const InputSide *ins = nullptr) {
+                                  const PairOperand *pair = nullptr, const InputSide *ins = nullptr,
+                                  bool one_order = false) {       // see launch_conv
     SOL_REQUIRE(cd.cin == xd.c, SOL_ERR_SHAPE, "conv cin %d != input channels %d", cd.cin, xd.c);
     SOL_REQUIRE(act == SOL_ACT_NONE || act == SOL_ACT_RELU, SOL_ERR_SHAPE, "bad activation %d", act);
     const int Ho = out_size(xd.h, cd.kh, cd.sh, cd.ph), Wo = out_size(xd.w, cd.kw, cd.sw, cd.pw);
@@ -151,7 +152,7 @@ static sol_status conv_fused_impl(const sol_tensor_desc &xd, const void *x, cons
                                            pair->stride, st);
         return launch_conv_pair(a, pair->x2, pair->w2, pair->scale2, pair->shift2, pair->H2, pair->W2, pair->K2, pair->Kp2, pair->stride, st);
     }
-    return launch_conv(a, xd.dtype, tile, st);
+    return launch_conv(a, xd.dtype, tile, st, one_order);
 }
 
 static sol_status pool_impl(const sol_tensor_desc &xd, const void *x, const sol_pool_desc &pd, void *y, int32_t *argmax,
@@ -1018,12 +1019,13 @@ static sol_status train_conv_fwd(const sol_network *net, const LayerPlan &lp, co
     const void *in = layer_in(net, lp.src, x, ws);
     const bool bn = lp.L.kind == SOL_LAYER_CONV && lp.L.has_bn;
     const float *bias = vec_ptr(net, lp, VEC_BIAS);
+    const bool one_order = lp.in.dtype == SOL_F32;
     if (bn)
         return conv_fused_impl(lp.in, in, lp.cd, net->params + lp.w_off, nullptr, bias, nullptr, SOL_ACT_NONE, nullptr, ws + lp.z_off,
-                               nullptr, nullptr, tile, st);
+                               nullptr, nullptr, tile, st, 0, nullptr, nullptr, one_order);
     const void *res = lp.res >= 0 ? layer_in(net, lp.res, x, ws) : nullptr;
     return conv_fused_impl(lp.in, in, lp.cd, net->params + lp.w_off, nullptr, bias, res, lp.L.act, nullptr, ws + lp.out_off, nullptr,
-                           nullptr, tile, st);
+                           nullptr, tile, st, 0, nullptr, nullptr, one_order);
 }
 
 static sol_status train_conv_dgrad(const sol_network *net, const LayerPlan &lp, const void *g, unsigned char *ws, int tile,
@@ -1435,7 +1437,7 @@ static sol_status autotune_training(sol_network *net, const void *x, void *y, vo
             int best_tile = T_AUTO;
             const sol_tensor_desc &shape = dg ? lp.in : lp.conv_out;
             for (int cand : kTuneCandidates) {
-                if (tune_skips(cand, shape)) continue;
+                if (tune_skips(cand, shape) || (!dg && lp.in.dtype == SOL_F32 && cand >= S_FIRST && cand <= S_LAST)) continue;   // (see launch_conv: one_order)
                 float ms = 0.f;
                 const sol_status cs = time_conv(i, dg, cand, &ms);
                 if (cs == SOL_ERR_HIP) { rs = cs; break; }

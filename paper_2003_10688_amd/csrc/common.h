@@ -206,7 +206,7 @@ bool linear_kernel_applies(const ConvArgs &a, int dt);
 sol_status launch_linear(const ConvArgs &a, int dt, hipStream_t st);
 bool linear_stream_applies(const ConvArgs &a, int dt);   // up to 128 rows, weights streamed (linear.hip)
 sol_status launch_linear_stream(const ConvArgs &a, int dt, hipStream_t st);
-sol_status launch_conv(const ConvArgs &a, int dt, int tile_override, hipStream_t st);
+sol_status launch_conv(const ConvArgs &a, int dt, int tile_override, hipStream_t st, bool one_order = false);
 sol_status launch_pool(const PoolArgs &a, int dt, hipStream_t st);
 sol_status launch_dwconv(const DwArgs &a, int dt, hipStream_t st);
 sol_status launch_pack_dw(int C, int taps, int dt, const float *w, void *packed, hipStream_t st);

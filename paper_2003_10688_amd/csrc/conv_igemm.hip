@@ -304,11 +304,16 @@ static sol_status launch_conv_staged(const ConvArgs &a, int dt, int tile, hipStr
     SOL_FAIL(SOL_ERR_DTYPE, "unknown dtype %d", dt);
 }
 
-sol_status launch_conv(const ConvArgs &a, int dt, int tile_override, hipStream_t st) {
+// one_order: the automatic choice leaves out the kernels that split a reduction by the size of the layer (the small tiles, the
+// weight-streaming linear kernel), so that in fp32, where every remaining one walks a reduction the same way, an output does not
+// depend on how many pixels or rows stand beside it, to the last bit.  The forward pass of an fp32 training step asks for it: a
+// pre-activation or pooling candidate within a rounding of its threshold, decided the other way, moves a whole term of a weight
+// gradient (9 images of 113x113, ResNet-18-shaped: up to 0.02 of a gradient's norm, 2.5 of its rms in one element).
+sol_status launch_conv(const ConvArgs &a, int dt, int tile_override, hipStream_t st, bool one_order) {
     if (a.P <= 0) return SOL_OK;   // empty batch: nothing to do
     if (a.pre_scale || a.ldx != a.C || a.Cvalid != a.C) return launch_conv_staged(a, dt, tile_override, st);
     if (tile_override == T_AUTO && stem_kernel_applies(a, dt)) return launch_conv_stem(a, st);
-    if (tile_override == T_AUTO && linear_stream_applies(a, dt)) return launch_linear_stream(a, dt, st);
+    if (tile_override == T_AUTO && !one_order && linear_stream_applies(a, dt)) return launch_linear_stream(a, dt, st);
     if (tile_override == T_AUTO && linear_kernel_applies(a, dt)) {
         // more rows than linear_stream_applies takes, and a weight matrix of many megabytes: the job is streaming the weights, which the
         // eight-wave ring kernel does with whole 128-byte lines and eight stages in flight
@@ -320,7 +325,7 @@ sol_status launch_conv(const ConvArgs &a, int dt, int tile_override, hipStream_t
         }
         return launch_linear(a, dt, st);
     }
-    if (tile_override == T_AUTO) tile_override = direct_choose_tile(a, dt);     // few pixels: its own small tiles, or the best of the others'
+    if (tile_override == T_AUTO && !one_order) tile_override = direct_choose_tile(a, dt);     // few pixels: its own small tiles, or the best of the others'
     if (tile_override == T_AUTO && halo_kernel_applies(a, dt)) {
         if (const int ht = halo_choose_tile(a)) return launch_conv_halo(a, ht, st);
     }

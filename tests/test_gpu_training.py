@@ -178,6 +178,24 @@ def test_train_step_after_autotune(sol, dtype):
         compare(got[s], ref[s], layers, dtype, elementwise=dtype == "f32", tag=f"wide/{dtype} tuned step {s}")
 
 
+def test_fp32_forward_does_not_depend_on_the_batch(sol):
+    """fp32: the forward sums of a training step run in one order whatever stands beside them (ReLU and pool decisions hang on
+    their last bits, and whole terms of the gradients on those): three images alone and among 130 give the same bits."""
+    c = wl.conv
+    layers = [c(64, 3, bn=False), c(128, 3, bn=False), c(64, 1, p=0, bn=False), wl.gap(), wl.linear(520, act="relu"), wl.linear(10)]
+    params = wl.make_params(layers, 32, 5, False, bias_std=0.2)
+    x = wl.make_input((130, 32, 12, 12), 6, "normal", False)
+    outs = []
+    for n in (3, 130):
+        net = sol.Network(layers, (n,) + x.shape[1:], sol.F32, flags=sol.NET_TRAINING)
+        net.set_params(params)
+        net.forward(sol.to_device_nhwc(x[:n], sol.F32))
+        torch.cuda.synchronize()
+        outs.append([sol.to_host_nchw(net.layer_output(i))[:3] for i in range(len(layers))])
+    for i, (a, b) in enumerate(zip(*outs)):
+        assert np.array_equal(a, b), f"layer {i}: {np.abs(a - b).max()}"
+
+
 def test_train_step_deterministic(sol):
     layers, params, x, labels = _make("wide", "bf16", N=8, H=24, W=24)
     _, a = gpu_train(sol, layers, params, x, labels, "bf16", steps=2)
