@@ -295,7 +295,9 @@ __global__ void __launch_bounds__(512) conv_dense_kernel(const DenseArgs a) {
             u32x4_t fa[QG][2], fb[QG][NB];
             static_for<QG>([&](auto Q) {
                 constexpr int q = decltype(Q)::value;
-                const int ks = kq * KPW + q0 + q, tap = min(2 * j + (ks >> 2), 8);       // the tenth tap reads zeros of w2 and any pixels
+                // the tenth tap of the last stage reads zeros of w2 and, as bit 9 is never set, the zero row: any pixel there
+                // could be an infinity, and its product with zero a NaN
+                const int ks = kq * KPW + q0 + q, t = 2 * j + (ks >> 2), tap = min(t, 8);
                 const int r = tap / 3, s = tap - 3 * r, toff = r * W + s;
                 const unsigned slot = (ks & 3) * 4 + lg, wa = wb + (ks >> 2) * 8192 + ((slot ^ lr) << 4);
                 lds_read16<0>(fa[q][0], wa);
@@ -303,7 +305,7 @@ __global__ void __launch_bounds__(512) conv_dense_kernel(const DenseArgs a) {
                 // the pixel blocks of a wave lie 16 rows apart: one address (the slot permutation depends on row % 16), block b at
                 // an immediate offset; lanes whose tap is padding go to the zero row instead
                 const int row0 = wpb * NB * 16 + lr + toff;
-                const unsigned at = lbase + row0 * 256 + ((slot ^ (row0 & 15)) << 4), zero = lbase + ZROW + (slot << 4), bit = 1u << tap;
+                const unsigned at = lbase + row0 * 256 + ((slot ^ (row0 & 15)) << 4), zero = lbase + ZROW + (slot << 4), bit = 1u << t;
                 static_for<NB>([&](auto B) {
                     constexpr int b = decltype(B)::value;
                     lds_read16<b * 4096>(fb[q][b], (val[b] & bit) ? at : zero - b * 4096);

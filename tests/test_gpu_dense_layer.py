@@ -55,3 +55,37 @@ def test_dense_layer(sol, case, variant):  # noqa: F811
     torch.cuda.synchronize()
     # the last convolution sums the features of every layer; two roundings (t1, the feature) lie between it and the input
     assert rel_err(sol.to_host_nchw(net.y).reshape(outs[-1].shape), outs[-1]) <= TOL["bf16"]
+
+
+@pytest.mark.parametrize("variant", [91, 92, 93, 94, 95, 96])
+def test_dense_layer_infinity(sol, variant):  # noqa: F811
+    """One pixel of the 1x1's output overflows to +inf: the 3x3 window around it is +inf (its weights are positive), all else finite."""
+    N, H, W, C = 2, 9, 11, 64
+    layers = [wl.conv(C, 1, p=0, bn=False, act="none"), wl.conv(128, 1, p=0, src=0, pre_bn=True), wl.conv(32, 3, bn=False, act="none"), wl.concat(0, 2),
+              wl.conv(8, 1, p=0, bn=False, act="none")]
+    rng = np.random.default_rng(variant)
+    prm = wl.make_params(layers, 64, 7, bf16=True)
+    prm[0]["w"] = np.eye(64, dtype=np.float32).reshape(64, 64, 1, 1)
+    prm[1]["w"][:] = np.abs(prm[1]["w"])
+    prm[1]["w"][1:, 0] = 0.0                     # the huge input channel reaches one of the 128 channels only
+    prm[1]["w"][0, 0] = 2.0 ** 120
+    prm[2]["w"][:] = np.abs(prm[2]["w"])
+    x = wl.to_bf16_grid(np.abs(rng.standard_normal((N, 64, H, W))))
+    x[:, 0] = 0.0
+    prm[1]["pre_beta"][0] = prm[1]["pre_mean"][0] = 0.0
+    x[1, 0, 4, 6] = 2.0 ** 100
+    net = sol.Network(layers, x.shape, sol.BF16)
+    net.set_params(prm)
+    xd = sol.to_device_nhwc(x, sol.BF16)
+    net.forward(xd)
+    assert net.fused_into(1) == 2
+    sol.sol_debug_set_conv_tile(variant)
+    try:
+        net.run_layer(2, xd)
+    finally:
+        sol.sol_debug_set_conv_tile(0)
+    torch.cuda.synchronize()
+    y = sol.to_host_nchw(net.layer_output(3))[:, 64:]        # the new features, written in place behind the block's input
+    inside = np.zeros(y.shape, bool)
+    inside[1, :, 3:6, 5:8] = True
+    assert np.isposinf(y[inside]).all() and np.isfinite(y[~inside]).all()
