@@ -39,6 +39,21 @@ __device__ __forceinline__ void mma(f32x4_t &acc, const u32x4_t &a, const u32x4_
 
 constexpr int DN_MID = 128, DN_OUT = 32, DN_CMAX = 1024;   // filters of the 1x1 / of the 3x3 convolution; widest input prefix
 
+// Taps of pixel m of a workgroup's bp pixels, bit t = 3 r + s: those inside the image (cols: bits of the three columns; up, down:
+// the rows above and below exist).  A pixel past bp has none: its tap (r, s) would be patch row m + r W + s, and with
+// bp = rows - 2 W - 2 that lies behind the patch, in the ring that a DMA is filling or past the end of LDS.
+__host__ __device__ constexpr unsigned dense_taps(int m, int bp, unsigned cols, bool up, bool down) {
+    return m < bp ? (up ? cols : 0u) | cols << 3 | (down ? cols << 6 : 0u) : 0u;
+}
+constexpr bool dense_taps_inside(int rows) {               // the ninth tap is the farthest
+    for (int W = 1; W < rows / 2; W++)
+        for (int m = 0; m < rows; m++)
+            if ((dense_taps(m, rows - 2 * W - 2, 7u, true, true) >> 8 & 1u) && m + 2 * W + 2 >= rows) return false;
+    return true;
+}
+static_assert(dense_taps_inside(64) && dense_taps_inside(96) && dense_taps_inside(128) && dense_taps_inside(192) && dense_taps_inside(256) &&
+              dense_taps_inside(384), "every tap read lies in the patch");
+
 struct DenseArgs {
     DenseLaunch d;
     int bp, ntiles, nc;        // pixels per workgroup; workgroups; chunks of 64 input channels
@@ -268,7 +283,7 @@ __global__ void __launch_bounds__(512) conv_dense_kernel(const DenseArgs a) {
 
     // ---- phase B
     const int wpb = wave % WPB, kq = wave / WPB;
-    unsigned val[NB];                                      // bit t: tap t of this lane's pixel of block b lies inside the image
+    unsigned val[NB];                                      // the taps of this lane's pixel of block b
     f32x4_t acc2[NB][2];
     {
         int m = wpb * NB * 16 + lr, p = min(p0 + m, P - 1);
@@ -276,7 +291,7 @@ __global__ void __launch_bounds__(512) conv_dense_kernel(const DenseArgs a) {
 #pragma unroll
         for (int b = 0; b < NB; b++) {
             const unsigned cm = (w > 0 ? 1u : 0u) | 2u | (w + 1 < W ? 4u : 0u);
-            val[b] = (p0 + m < P) ? ((h > 0 ? cm : 0u) | cm << 3 | (h + 1 < d.H ? cm << 6 : 0u)) : 0u;
+            val[b] = dense_taps(m, bp, cm, h > 0, h + 1 < d.H);
             m += 16;
             w += 16;
             while (w >= W) { w -= W; h = h + 1 == d.H ? 0 : h + 1; }

@@ -17,6 +17,7 @@ CASES = [
     (2, 14, 13, 160, 2),
     (1, 3, 61, 64, 2),       # wide rows: the larger patches only
     (1, 2, 130, 128, 1),     # halo as large as the patch allows
+    (1, 3, 183, 64, 1),      # the widest image: 16 pixels to a patch of 384 rows
     (1, 5, 9, 992, 1),       # sixteen chunks, the last one half masked
 ]
 
