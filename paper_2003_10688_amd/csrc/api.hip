@@ -706,6 +706,10 @@ static sol_status plan_network(sol_network *net, const sol_layer *layers, int n_
             c3.use_xr = (long)c3.in.n * c3.in.h * c3.in.w >= 128 * 64;   // heuristic: a workgroup per 64 pixels; worth it once those fill half the chip
         }
 
+    // the one buffer of a dense chain lives until the last reader of any of its joins, which need not be a reader of the last one
+    for (auto &lp : net->layers)
+        if (lp.chain_owner >= 0) net->layers[lp.chain_owner].last_use = std::max(net->layers[lp.chain_owner].last_use, lp.last_use);
+
     // activation layout: inference reuses buffers once their last consumer has run, training keeps all
     Arena ar;
     for (int i = 0; i < n_layers; i++) {

@@ -280,3 +280,33 @@ def test_no_kernel_spills_registers():
     spills = {k: v["scratch_bytes_per_lane"] for k, v in res.items() if v.get("scratch_bytes_per_lane", 0) != 0}
     assert not spills, spills
     assert all(v.get("lds_bytes", 0) <= 160 * 1024 for v in res.values())
+
+
+@pytest.mark.parametrize("dt,late", [("f32", "pointwise"), ("bf16", "pointwise"), ("bf16", "dense")])
+def test_dense_chain_buffer_outlives_its_last_reader(sol, dt, late):
+    """The joins of a dense block share one buffer.  A layer that reads an inner join after everything has read the last one
+    (on its own, or inside the launch of the 3x3 convolution behind it) still finds it: no other output takes its place."""
+    L, c = sol.lib(), wl.conv
+    layers = [c(64, 1, p=0), c(128, 1, p=0, src=0, pre_bn=True), c(32, 3, bn=False, act="none"), wl.concat(0, 2),
+              c(128, 1, p=0, src=3, pre_bn=True), c(32, 3, bn=False, act="none"), wl.concat(3, 5)]
+    if late == "dense":
+        layers += [c(128, 1, p=0, src=3, pre_bn=True), c(256, 1, p=0, src=6), c(64, 1, p=0), c(128, 1, p=0, src=9), c(32, 3, src=7), c(8, 1, p=0, src=10)]
+    else:
+        layers += [c(256, 1, p=0, src=6), c(64, 1, p=0), c(128, 1, p=0, src=8), c(64, 1, p=0, src=3), c(8, 1, p=0, src=9)]
+    d = sol.BF16 if dt == "bf16" else sol.F32
+    st, h = _create(sol, layers, (2, 64, 14, 14), d)
+    assert st == 0
+    last = max(i for i in range(len(layers) - 1) if layers[i].get("src", -1) == (7 if late == "dense" else 3))   # launches the late read
+    es, got = 2 if dt == "bf16" else 4, {}
+    for i in range(6, last):
+        p, od, into = C.c_void_p(), sol.TensorDesc(), C.c_int()
+        assert L.sol_network_layer_fused_into(h, i, C.byref(into)) == 0
+        if into.value != i:
+            continue
+        assert L.sol_network_layer_output(h, i, C.c_void_p(1 << 40), C.byref(p)) == 0
+        assert L.sol_network_output_desc(h, i, C.byref(od)) == 0
+        got[i] = (p.value, p.value + od.n * od.h * od.w * od.c * es)
+    for i in range(7, last):
+        if i in got:
+            assert got[i][0] >= got[6][1] or got[i][1] <= got[6][0], f"layer {i} is written over the block's buffer"
+    L.sol_network_destroy(h)
