@@ -253,8 +253,9 @@ sol_status sol_network_forward(sol_network *net, const void *x, void *y, void *w
  * tight serving loops, harnesses that forbid hipMalloc): sol_network_forward with the activations between the layers
  * kept in a static device array of the library, SOL_STATIC_WORKSPACE_BYTES per GPU, resident from the library's load
  * until the process ends.  The call allocates nothing (no hipMalloc / hipFree, no allocating library routine).
- *   net     an inference network (SOL_ERR_UNSUPPORTED for SOL_NET_TRAINING) whose sol_network_workspace_bytes() is at
- *           most SOL_STATIC_WORKSPACE_BYTES (else SOL_ERR_WORKSPACE, nothing launched)
+ *   net     an inference network (SOL_ERR_UNSUPPORTED for SOL_NET_TRAINING) whose sol_network_workspace_bytes() (less what
+ *           sol_network_set_layer_dense says a pass can go without) is at most SOL_STATIC_WORKSPACE_BYTES (else
+ *           SOL_ERR_WORKSPACE, nothing launched)
  *   x, y    device pointers as for sol_network_forward (caller-owned input and output of the last layer)
  * Runs on the current device (the stream must belong to it).  Results are those of sol_network_forward bit for bit.
  * Every call on one GPU uses the same array, which keeps the previous call's contents; every buffer of a pass is
@@ -317,6 +318,18 @@ sol_status sol_network_layer_block(const sol_network *net, int layer, int *state
 sol_status sol_network_layer_xr(const sol_network *net, int layer, int *state);
 sol_status sol_network_set_layer_xr(sol_network *net, int layer, int fused);
 
+/* Dense layers in one launch.  When a network keeps no activations (flags 0), bf16: a 1x1 stride-1 convolution with an
+ * input-side BN + ReLU (pre_bn), 128 filters and ReLU over at most 1024 channels whose only reader is a 3x3 stride-1 pad-1
+ * convolution of 32 filters without pool or residual can run inside that convolution's launch; its output, rounded to bf16
+ * as it would be stored, then stays in on-chip memory.  The plan decides by a rule on the image width (the halo of a tile is
+ * computed twice), sol_network_autotune by timing both ways.  sol_network_layer_fused_into reports the 3x3 convolution's
+ * index for the 1x1 while the two run as one.  *state = -1: `layer` is not the 3x3 convolution of such a pair; 0: two
+ * launches; 1: one.  sol_network_set_layer_dense restores / forces the choice (SOL_ERR_UNSUPPORTED if there is none).
+ * sol_network_workspace_bytes counts the buffer between the two launches; a pass in which every such pair runs as one
+ * accepts a workspace without it (it lies behind all others), and sol_network_autotune then leaves them as they are. */
+sol_status sol_network_layer_dense(const sol_network *net, int layer, int *state);
+sol_status sol_network_set_layer_dense(sol_network *net, int layer, int fused);
+
 /* One forward pass recorded as a HIP graph (launch-bound inner loops: the about forty launches of a ResNet-50-shaped
  * pass replay as one submission).  sol_network_graph_create runs the pass once eagerly, then records the same
  * launches with the given pointers baked in: x, y, workspace, the bound parameter buffer and the network must
@@ -338,8 +351,8 @@ void sol_graph_destroy(sol_graph *graph);
  *     of 64 channels runs inside that convolution's launch; its output is never stored, and never rounded to the storage type either (the result differs from
  *     the two-launch result by at most one rounding of the shortcut term).
  *   - a 1x1 stride-1 convolution with an input-side BN + ReLU (pre_bn), 128 filters and ReLU whose only reader is a 3x3 stride-1
- *     pad-1 convolution of 32 filters without pool or residual (a dense layer) runs inside that convolution's launch; its
- *     output, rounded to bf16 as it would be stored, stays in on-chip memory.
+ *     pad-1 convolution of 32 filters without pool or residual (a dense layer) may run inside that convolution's launch, see
+ *     sol_network_set_layer_dense.
  * *into = index of the layer whose launch produces `layer`'s output: `layer` itself, the layer in front for such a
  * pool layer, the later convolution for such a shortcut or such a 1x1 convolution, the last convolution of a bottleneck that runs as one launch
  * (see sol_network_set_layer_block) for its first two, the first layer of an expand -> reduce pair (see

@@ -215,14 +215,15 @@ struct LayerPlan {
     bool use_block;                 // on the last convolution: the plan runs the bottleneck as one launch (heuristic or sol_network_autotune)
     int xr_next, xr_from;           // CONV (last 1x1 of a bottleneck): the next bottleneck's first 1x1, which the same launch can compute (conv_xr.hip); on that layer: the former (-1: none)
     bool use_xr;                    // on the former: the plan runs the two as one launch
-    int dense_c1;                   // CONV (3x3 of a dense layer): the pre-activated 1x1 convolution that its launch also computes (-1: none)
+    int dense_c1, dense_into;       // CONV (3x3 of a dense layer): the pre-activated 1x1 convolution that one launch can compute with it (-1: none); on that layer: the former
+    bool use_dense;                 // on the former: the plan runs the two as one launch
     bool pre_bn, pre_set;           // CONV: BN + ReLU on the input side; its folded constants have been set
     size_t pre_scale_off, pre_shift_off;
     int ldx;                        // CONV: input pixel pitch when the input is a channel prefix of a dense-block buffer (0: dense)
     int chain_owner;                // CONCAT: last CONCAT of the dense chain whose buffer this layer is a prefix of (-1: none; itself for the last)
     bool part_inplace[2];           // CONCAT: src / res part already sits in the output buffer when the layer runs
     int fused_into;                 // index of the layer whose launch produces this layer's output (itself unless elided)
-    bool no_buffer;                 // elided, and nobody allocates an output for it either
+    bool no_buffer;                 // no output of its own among the buffers that are laid out by lifetime
     size_t w_off, scale_off, shift_off;
     size_t out_off, tmp_off;        // workspace offsets; out_off unused for the last layer
     int last_use;
@@ -251,6 +252,7 @@ struct sol_network {
     sol_tensor_desc input;
     int training, keep;
     size_t param_bytes, ws_bytes;
+    size_t ws_apart;                // ws_bytes plus what stands behind it: the buffers between the two launches of dense layers
     unsigned char *params;
     size_t params_size;
     size_t dz_off, dil_off, part_off, loss_off;   // training: shared scratch inside the workspace
@@ -361,6 +363,16 @@ static bool stem_pool_plan_ok(const sol_tensor_desc &in, const sol_conv_desc &cd
     return L.res < 0 && stem_pool_applies(a, in.dtype, p);
 }
 
+// The plan's own choice for a dense layer whose 3x3 convolution is c2: see dense_one_launch_pays
+static bool dense_one_launch(const sol_network *net, const LayerPlan &c2) {
+    const LayerPlan &c1 = net->layers[c2.dense_c1];
+    return dense_one_launch_pays(c2.in.n, c2.in.h, c2.in.w, (int)round_up((size_t)c1.cd.cin, 64), (c1.cin_real ? c1.cin_real : c1.cd.cin) % 64 != 0);
+}
+// Does the 3x3 convolution c2 compute the 1x1 in front with it?
+static bool dense_fused(const LayerPlan &c2) {
+    return c2.dense_c1 >= 0 && (c2.use_dense || (g_tile_override >= B_FIRST && g_tile_override <= B_LAST));
+}
+
 static sol_status plan_network(sol_network *net, const sol_layer *layers, int n_layers) {
     const int dt = net->input.dtype;
     net->layers.resize(n_layers);
@@ -396,7 +408,7 @@ static sol_status plan_network(sol_network *net, const sol_layer *layers, int n_
         lp.concat_into = -1;
         lp.pair = -1;
         lp.block_c1 = lp.block_c2 = lp.block_c3 = -1;
-        lp.xr_next = lp.xr_from = lp.dense_c1 = -1;
+        lp.xr_next = lp.xr_from = lp.dense_c1 = lp.dense_into = -1;
         lp.chain_owner = -1;
         lp.fused_into = i;
         lp.in = lp.src < 0 ? net->input : net->layers[lp.src].out;
@@ -642,8 +654,8 @@ static sol_status plan_network(sol_network *net, const sol_layer *layers, int n_
         }
 
     // Dense layer (depth-first again): a pre-activated 1x1 convolution + ReLU whose only reader is a 3x3 convolution runs inside
-    // that convolution's launch, its output is never stored (conv_dense.hip).  Measured faster than the two launches at every
-    // size tried (one image of 7x7 to 64 of 56x56), so the plan needs no second opinion.
+    // that convolution's launch, its output is never stored (conv_dense.hip).  Its buffer stands behind all others, so the
+    // plan can run the two one by one as well: a rule on the image width picks, sol_network_autotune measures.
     if (!net->training && !net->keep && dt == SOL_BF16)
         for (int i = 0; i < n_layers; i++) {
             LayerPlan &c2 = net->layers[i];
@@ -657,8 +669,9 @@ static sol_status plan_network(sol_network *net, const sol_layer *layers, int n_
             const int ldy = c2.concat_into >= 0 ? net->layers[c2.concat_into].out.c : c2.cd.cout;
             if (!dense_kernel_applies(dt, c1.in.n, c1.in.h, c1.in.w, (int)round_up((size_t)c1.cd.cin, 64), c1.ldx ? c1.ldx : c1.cd.cin, c1.cd.cout, c2.cd.cout, ldy)) continue;
             c2.dense_c1 = c2.src;
-            c1.elided = c1.no_buffer = true;
-            c1.fused_into = i;
+            c1.dense_into = i;
+            c1.no_buffer = true;
+            c2.use_dense = dense_one_launch(net, c2);
             if (c1.src >= 0) net->layers[c1.src].last_use = std::max(net->layers[c1.src].last_use, i);   // read by layer i now
         }
 
@@ -711,9 +724,11 @@ static sol_status plan_network(sol_network *net, const sol_layer *layers, int n_
         if (lp.chain_owner >= 0) net->layers[lp.chain_owner].last_use = std::max(net->layers[lp.chain_owner].last_use, lp.last_use);
 
     // activation layout: inference reuses buffers once their last consumer has run, training keeps all
-    Arena ar;
+    Arena ar, apart;                 // apart: the 1x1 outputs of dense layers, behind everything else, for a pass that stores them
     for (int i = 0; i < n_layers; i++) {
         LayerPlan &lp = net->layers[i];
+        if (lp.dense_into >= 0) lp.out_off = apart.alloc(tensor_bytes(lp.out));
+        if (lp.dense_c1 >= 0) apart.release(net->layers[lp.dense_c1].out_off);
         if (lp.split_pool) lp.tmp_off = ar.alloc(tensor_bytes(lp.conv_out));
         if (lp.chain_owner >= 0) {       // a join of a dense chain: a prefix of the chain's one buffer, laid out at the first touch
             LayerPlan &ow = net->layers[lp.chain_owner];
@@ -724,7 +739,7 @@ static sol_status plan_network(sol_network *net, const sol_layer *layers, int n_
         } else if (lp.concat_into >= 0) {   // ... and so does the concatenation's, from its first in-place producer on
             LayerPlan &cc = net->layers[lp.concat_into];
             if (!cc.prealloc && lp.concat_into + 1 < n_layers) { cc.out_off = ar.alloc(tensor_bytes(cc.out)); cc.prealloc = true; }
-        } else if (!lp.elided && !lp.prealloc && (i + 1 < n_layers || net->training)) {
+        } else if (!lp.elided && !lp.no_buffer && !lp.prealloc && (i + 1 < n_layers || net->training)) {
             lp.out_off = ar.alloc(tensor_bytes(lp.out));
         }
         if (lp.xr_next >= 0 && lp.xr_next + 1 < n_layers) {   // this launch may also write the next layer's output: that buffer exists from here on
@@ -743,6 +758,9 @@ static sol_status plan_network(sol_network *net, const sol_layer *layers, int n_
     }
     if (net->training) SOL_TRY(plan_training(net, ar));
     net->ws_bytes = ar.top;
+    net->ws_apart = ar.top + apart.top;
+    for (auto &lp : net->layers)
+        if (lp.dense_into >= 0) lp.out_off += ar.top;
     return SOL_OK;
 }
 
@@ -919,7 +937,7 @@ sol_status sol_network_create(const sol_layer *layers, int n_layers, const sol_t
 
 void sol_network_destroy(sol_network *net) { delete net; }
 size_t sol_network_param_bytes(const sol_network *net) { return net ? net->param_bytes : 0; }
-size_t sol_network_workspace_bytes(const sol_network *net) { return net ? net->ws_bytes : 0; }
+size_t sol_network_workspace_bytes(const sol_network *net) { return net ? net->ws_apart : 0; }
 int sol_network_num_layers(const sol_network *net) { return net ? (int)net->layers.size() : 0; }
 
 sol_status sol_network_output_desc(const sol_network *net, int layer, sol_tensor_desc *out) {
@@ -1215,7 +1233,10 @@ static sol_status run_layers(sol_network *net, const void *x, void *y, void *wor
     if (net->input.n == 0) return SOL_OK;                  // empty batch: every tensor is empty (allocators hand out NULL for them)
     SOL_REQUIRE(x && y, SOL_ERR_NULL, "x and y must not be NULL");
     SOL_REQUIRE(workspace || net->ws_bytes == 0, SOL_ERR_NULL, "workspace is NULL");
-    SOL_REQUIRE(workspace_bytes >= net->ws_bytes, SOL_ERR_WORKSPACE, "workspace has %zu bytes, %zu needed", workspace_bytes, net->ws_bytes);
+    size_t need = net->ws_bytes;
+    for (const auto &lp : net->layers)
+        if (lp.dense_c1 >= 0 && !dense_fused(lp)) need = net->ws_apart;
+    SOL_REQUIRE(workspace_bytes >= need, SOL_ERR_WORKSPACE, "workspace has %zu bytes, %zu needed", workspace_bytes, need);
     SOL_REQUIRE(aligned16(x) && aligned16(y) && aligned16(workspace), SOL_ERR_ALIGN, "device pointers must be 16-byte aligned");
     const int nl = (int)net->layers.size();
     SOL_REQUIRE(first >= 0 && first <= last && last < nl, SOL_ERR_SHAPE, "bad layer range [%d,%d]", first, last);
@@ -1234,6 +1255,7 @@ static sol_status run_layers(sol_network *net, const void *x, void *y, void *wor
         if (lp.elided) continue;                            // computed by the convolution in front of it
         if (lp.block_c3 >= 0 && net->layers[lp.block_c3].use_block && !g_tile_override) continue;   // ... by the bottleneck launch behind it
         if (lp.xr_from >= 0 && net->layers[lp.xr_from].use_xr && !g_tile_override) continue;        // ... by the expand-reduce launch in front of it
+        if (lp.dense_into >= 0 && dense_fused(net->layers[lp.dense_into])) continue;                // ... by the 3x3 convolution behind it
         const void *in = layer_in(net, lp.src, x, ws);
         const int oi = lp.absorbs_next ? i + 1 : lp.concat_into >= 0 ? lp.concat_into : lp.chain_owner >= 0 ? lp.chain_owner : i;   // the layer whose buffer this launch writes
         void *out = oi + 1 == nl ? y : static_cast<void *>(ws + net->layers[oi].out_off);
@@ -1278,7 +1300,7 @@ static sol_status run_layers(sol_network *net, const void *x, void *y, void *wor
                                             nullptr, nullptr, g_tile_override, st, ldy, &po));
                     break;
                 }
-                if (lp.dense_c1 >= 0) {      // a dense layer: this launch also computes the pre-activated 1x1 convolution in front
+                if (dense_fused(lp)) {       // a dense layer: this launch also computes the pre-activated 1x1 convolution in front
                     const LayerPlan &c1 = net->layers[lp.dense_c1];
                     const auto fp = [&](size_t off) { return reinterpret_cast<const float *>(net->params + off); };
                     const DenseLaunch dl{layer_in(net, c1.src, x, ws), c1.ldx ? c1.ldx : c1.cd.cin, (int)round_up((size_t)c1.cd.cin, 64), c1.cin_real ? c1.cin_real : c1.cd.cin,
@@ -1370,7 +1392,7 @@ static sol_status static_scratch(unsigned char **out) {
 sol_status sol_network_forward_static(sol_network *net, const void *x, void *y, void *stream) {
     SOL_REQUIRE(net, SOL_ERR_NULL, "net is NULL");
     SOL_REQUIRE(!net->training, SOL_ERR_UNSUPPORTED, "the static-workspace forward runs inference networks only (a backward pass needs the caller's workspace)");
-    SOL_REQUIRE(net->ws_bytes <= (size_t)SOL_STATIC_WORKSPACE_BYTES, SOL_ERR_WORKSPACE,
+    SOL_REQUIRE(net->ws_bytes <= (size_t)SOL_STATIC_WORKSPACE_BYTES, SOL_ERR_WORKSPACE,   // run_layers checks for ws_apart where that is needed
                 "network needs %zu bytes of workspace, the static workspace holds %zu (SOL_STATIC_WORKSPACE_BYTES); use sol_network_forward", net->ws_bytes,
                 (size_t)SOL_STATIC_WORKSPACE_BYTES);
     unsigned char *ws = nullptr;
@@ -1463,7 +1485,9 @@ sol_status sol_network_autotune(sol_network *net, const void *x, void *y, void *
     if (net->training) return autotune_training(net, x, y, workspace, workspace_bytes, reps, (hipStream_t)stream);
     hipStream_t st = (hipStream_t)stream;
     const int nl = (int)net->layers.size();
-    for (auto &lp : net->layers) { lp.tile = T_AUTO; lp.use_block = false; lp.use_xr = false; }   // every layer is tuned on its own first
+    // every layer is tuned on its own first; a workspace without the buffers between them leaves dense layers in one launch
+    const bool apart = workspace_bytes >= net->ws_apart;
+    for (auto &lp : net->layers) { lp.tile = T_AUTO; lp.use_block = false; lp.use_xr = false; lp.use_dense = lp.dense_c1 >= 0 && !apart; }
     // one whole pass: validates the arguments and leaves finite activations of the right shape in every buffer
     SOL_TRY(run_layers(net, x, y, workspace, workspace_bytes, 0, nl - 1, st));
     hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -1489,11 +1513,40 @@ sol_status sol_network_autotune(sol_network *net, const void *x, void *y, void *
         *ms = total;
         return SOL_OK;
     };
+    // dense layers: one depth-first launch against two, behind the producer of their input; clearly the faster one (more than
+    // tuning the two gains) it needs no tiles
+    auto time_dense = [&](int i, float (&t)[2]) -> sol_status {
+        LayerPlan &lp = net->layers[i];
+        const int c1 = lp.dense_c1, prod = net->layers[c1].src;
+        for (int fused = 0; fused < 2; fused++) {
+            lp.use_dense = fused != 0;
+            t[fused] = 0.f;
+            for (int r = 0; r < reps + 1; r++) {
+                if (prod >= 0) SOL_TRY(run_layers(net, x, y, workspace, workspace_bytes, prod, prod, st));
+                SOL_HIP(hipEventRecord(e0, st));
+                for (int j : {c1, i}) SOL_TRY(run_layers(net, x, y, workspace, workspace_bytes, j, j, st));
+                SOL_HIP(hipEventRecord(e1, st));
+                SOL_HIP(hipEventSynchronize(e1));
+                float ms = 0.f;
+                SOL_HIP(hipEventElapsedTime(&ms, e0, e1));
+                if (r > 0) t[fused] += ms;
+            }
+        }
+        return SOL_OK;
+    };
+    for (int i = 0; i < nl && rs == SOL_OK && apart; i++) {
+        LayerPlan &lp = net->layers[i];
+        if (lp.dense_c1 < 0 || lp.in.n == 0) continue;
+        float t[2];
+        rs = time_dense(i, t);
+        lp.use_dense = rs == SOL_OK && t[1] < 0.7f * t[0];
+    }
     for (int i = 0; i < nl && rs == SOL_OK; i++) {
         LayerPlan &lp = net->layers[i];
         if (lp.L.kind != SOL_LAYER_CONV || lp.in.n == 0) continue;
+        if (lp.use_dense || (lp.dense_into >= 0 && net->layers[lp.dense_into].use_dense)) continue;
         if (lp.absorbs_next || (lp.fuse_pool && !pool_is_fusable(lp.L.pool))) continue;   // stem + pool: one kernel, nothing to choose
-        if (lp.elided || lp.pair >= 0 || lp.dense_c1 >= 0) continue;                      // projection pair, dense layer: likewise
+        if (lp.elided || lp.pair >= 0) continue;                                          // projection pair: likewise
         float best = 0.f;
         rs = time_layer(i, &best);                            // the shape heuristic's choice is the incumbent
         if (rs != SOL_OK) break;
@@ -1507,6 +1560,13 @@ sol_status sol_network_autotune(sol_network *net, const void *x, void *y, void *
             if (cs == SOL_OK && ms < 0.97f * best) { best = ms; best_tile = cand; }   // 3 % margin against timing noise
         }
         lp.tile = best_tile;
+    }
+    for (int i = 0; i < nl && rs == SOL_OK; i++) {             // the dense layers still open, against the two tuned launches
+        LayerPlan &lp = net->layers[i];
+        if (lp.dense_c1 < 0 || lp.use_dense || lp.in.n == 0) continue;
+        float t[2];
+        rs = time_dense(i, t);
+        lp.use_dense = rs == SOL_OK && t[1] < t[0];
     }
     // bottlenecks: one depth-first launch against the three tuned launches, both right behind the block's producer
     for (int i = 0; i < nl && rs == SOL_OK; i++) {
@@ -1556,7 +1616,10 @@ sol_status sol_network_autotune(sol_network *net, const void *x, void *y, void *
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
-    if (rs != SOL_OK) for (auto &lp : net->layers) lp.tile = T_AUTO;
+    if (rs != SOL_OK) {
+        for (auto &lp : net->layers) lp.tile = T_AUTO;
+        for (auto &lp : net->layers) lp.use_dense = lp.dense_c1 >= 0 && dense_one_launch(net, lp);
+    }
     return rs;
 }
 
@@ -1574,6 +1637,23 @@ sol_status sol_network_set_layer_xr(sol_network *net, int layer, int fused) {
     LayerPlan &lp = net->layers[layer];
     SOL_REQUIRE(lp.xr_next >= 0 || !fused, SOL_ERR_UNSUPPORTED, "layer %d is not the first layer of an expand-reduce pair the depth-first kernel can run", layer);
     lp.use_xr = fused != 0;
+    return SOL_OK;
+}
+
+sol_status sol_network_layer_dense(const sol_network *net, int layer, int *state) {
+    SOL_REQUIRE(net && state, SOL_ERR_NULL, "net and state must not be NULL");
+    SOL_REQUIRE(layer >= 0 && layer < (int)net->layers.size(), SOL_ERR_SHAPE, "no layer %d", layer);
+    const LayerPlan &lp = net->layers[layer];
+    *state = lp.dense_c1 < 0 ? -1 : (lp.use_dense ? 1 : 0);
+    return SOL_OK;
+}
+
+sol_status sol_network_set_layer_dense(sol_network *net, int layer, int fused) {
+    SOL_REQUIRE(net, SOL_ERR_NULL, "net is NULL");
+    SOL_REQUIRE(layer >= 0 && layer < (int)net->layers.size(), SOL_ERR_SHAPE, "no layer %d", layer);
+    LayerPlan &lp = net->layers[layer];
+    SOL_REQUIRE(lp.dense_c1 >= 0 || !fused, SOL_ERR_UNSUPPORTED, "layer %d is not the 3x3 convolution of a dense layer the depth-first kernel can run", layer);
+    lp.use_dense = fused != 0;
     return SOL_OK;
 }
 
@@ -1659,6 +1739,7 @@ sol_status sol_network_layer_fused_into(const sol_network *net, int layer, int *
     const LayerPlan &lp = net->layers[layer];
     *into = (lp.block_c3 >= 0 && net->layers[lp.block_c3].use_block) ? lp.block_c3
             : (lp.xr_from >= 0 && net->layers[lp.xr_from].use_xr)        ? lp.xr_from
+            : (lp.dense_into >= 0 && net->layers[lp.dense_into].use_dense) ? lp.dense_into
                                                                          : lp.fused_into;
     return SOL_OK;
 }

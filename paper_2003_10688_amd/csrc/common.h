@@ -201,6 +201,7 @@ struct DenseLaunch {
     int N, H, W;
 };
 bool dense_kernel_applies(int dt, int N, int H, int W, int C, int ldx, int mid, int cout, int ldy);
+bool dense_one_launch_pays(int N, int H, int W, int C, bool masked);   // masked: the real channels end inside a chunk of 64
 sol_status launch_conv_dense(const DenseLaunch &d, int variant, hipStream_t st);
 bool linear_kernel_applies(const ConvArgs &a, int dt);
 sol_status launch_linear(const ConvArgs &a, int dt, hipStream_t st);

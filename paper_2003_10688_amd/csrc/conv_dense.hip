@@ -396,20 +396,43 @@ bool dense_kernel_applies(int dt, int N, int H, int W, int C, int ldx, int mid, 
            (double)N * H * W * ldx * 2 < 2147483648.0 && (double)N * H * W * ldy * 2 < 4294967296.0;
 }
 
-sol_status launch_conv_dense(const DenseLaunch &d, int variant, hipStream_t st) {
-    const int P = d.N * d.H * d.W;
-    if (P <= 0) return SOL_OK;
+namespace {
+// The variant and the rounds of the 256 CUs it takes.  variant >= 0: forced, the first one from there on that the width allows.
+int choose_variant(int P, int W, int C, int variant, int *rounds) {
     // Larger patches recompute less of the halo (2 W + 2 rows per tile) and take longer each: the fewest rounds of the 256 CUs,
     // weighted with the time of a round.  (14x14, 640 channels, 64 images: 64 rows 21.0 us, 96 rows 14.2, 128 rows 15.3.)
     int v = -1;
     float best = 0.f;
     for (int i = 0; i < 6; i++) {
-        const int px = kVariant[i].rows - 2 * d.W - 2;
+        const int px = kVariant[i].rows - 2 * W - 2;
         if (px < 16 && i < 5) continue;
-        const float t = (float)ceil_div(ceil_div(P, px), 256) * (kVariant[i].base + kVariant[i].chunk * (d.C / 64));
-        if (i >= variant && variant >= 0) { v = i; break; }      // forced: the first one from there on that the image width allows
-        if (v < 0 || t < best) { v = i; best = t; }
+        const int n = ceil_div(ceil_div(P, px), 256);
+        const float t = (float)n * (kVariant[i].base + kVariant[i].chunk * (C / 64));
+        if (v < 0 || t < best || (variant >= 0 && i >= variant)) { v = i; best = t; *rounds = n; }
+        if (variant >= 0 && i >= variant) break;
     }
+    return v;
+}
+}  // namespace
+
+// A patch recomputes 2 W + 2 rows of the 1x1 convolution for its pixels, so wide images lose by one launch what it saves.  Two
+// launches -> one, us, launches and events included, 64 images unless stated: W = 56, C = 64: 65 -> 45; 84, 512: 262 -> 251; 96, 64:
+// 180 -> 167; 96, 512: 338 -> 344; 112, 512: 457 -> 511; 128, 64: 348 -> 430; 160, 64: 497 -> 1267.  A prefix that ends inside
+// a chunk of 64 channels costs the 1x1 convolution on its own about three times as much, and the line lies further out:
+// 148, 96: 927 -> 921; 152, 96: 976 -> 1072; 144, 224: 1362 -> 1041; 160, 224: 1665 -> 1934; 16 images, 144, 992: 1151 -> 564; 176, 224: 530 -> 1138.  One round of
+// workgroups is about as fast as two launches at any width (one image, 144, 64: 31 -> 25; 84, 64: 20 -> 22; only strips such as
+// 2 x 130 pixels, 19 -> 25, are not, which the auto-tuner finds).
+bool dense_one_launch_pays(int N, int H, int W, int C, bool masked) {
+    int rounds = 1;
+    choose_variant(N * H * W, W, C, -1, &rounds);
+    return rounds <= 1 || W <= (masked ? 148 : 104);
+}
+
+sol_status launch_conv_dense(const DenseLaunch &d, int variant, hipStream_t st) {
+    const int P = d.N * d.H * d.W;
+    if (P <= 0) return SOL_OK;
+    int rounds;
+    const int v = choose_variant(P, d.W, d.C, variant, &rounds);
     int bp = kVariant[v].rows - 2 * d.W - 2;
     const int nt = ceil_div(P, bp);
     bp = min(bp, (int)round_up(ceil_div(P, nt), 4));       // equal shares

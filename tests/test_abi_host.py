@@ -310,3 +310,39 @@ def test_dense_chain_buffer_outlives_its_last_reader(sol, dt, late):
         if i in got:
             assert got[i][0] >= got[6][1] or got[i][1] <= got[6][0], f"layer {i} is written over the block's buffer"
     L.sol_network_destroy(h)
+
+
+def _dense_net(sol, shape, c=64):
+    layers = [wl.conv(c, 1, p=0), wl.conv(128, 1, p=0, src=0, pre_bn=True), wl.conv(32, 3, bn=False, act="none"), wl.concat(0, 2),
+              wl.conv(8, 1, p=0, bn=False, act="none")]
+    st, h = _create(sol, layers, shape, sol.BF16)
+    assert st == 0
+    return h
+
+
+@pytest.mark.parametrize("shape,c,fused", [((64, 64, 56, 56), 64, 1), ((64, 64, 104, 104), 64, 1), ((64, 64, 105, 105), 64, 0), ((64, 64, 144, 144), 96, 1),
+                                           ((16, 64, 149, 149), 96, 0), ((8, 64, 183, 183), 64, 0), ((1, 64, 144, 144), 64, 1), ((1, 64, 176, 176), 64, 0)])
+def test_dense_layer_one_launch_or_two(sol, shape, c, fused):
+    """Wide images, whose tiles are mostly halo, keep the two launches; the choice can be set both ways, and only a pass that
+    stores the 1x1 convolution's output needs the buffer for it."""
+    L, h, v = sol.lib(), _dense_net(sol, shape, c), C.c_int()
+
+    def state():
+        assert L.sol_network_layer_dense(h, 2, C.byref(v)) == 0
+        d = v.value
+        assert L.sol_network_layer_fused_into(h, 1, C.byref(v)) == 0 and v.value == (2 if d else 1)
+        return d
+
+    assert state() == fused
+    assert L.sol_network_layer_dense(h, 1, C.byref(v)) == 0 and v.value == -1
+    assert L.sol_network_set_layer_dense(h, 1, 1) == 6
+    n, _, hh, ww = shape
+    buf, need = n * hh * ww * 128 * 2, L.sol_network_workspace_bytes(h)
+    fake = C.c_void_p(0x1000)
+    for f in (0, 1):
+        assert L.sol_network_set_layer_dense(h, 2, f) == 0 and state() == f
+        # parameters are not set: a workspace that is large enough is refused for that, a smaller one for its size
+        for size, what in ((need, "parameters"), (need - buf, "parameters" if f else "workspace"), (need - buf - (buf + 255) // 256 * 256, "workspace")):
+            assert L.sol_network_forward(h, fake, fake, fake, C.c_size_t(size), None) == 5
+            assert what in L.sol_last_error().decode(), (f, size)
+    L.sol_network_destroy(h)

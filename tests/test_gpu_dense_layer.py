@@ -90,3 +90,33 @@ def test_dense_layer_infinity(sol, variant):  # noqa: F811
     inside = np.zeros(y.shape, bool)
     inside[1, :, 3:6, 5:8] = True
     assert np.isposinf(y[inside]).all() and np.isfinite(y[~inside]).all()
+
+
+@pytest.mark.parametrize("case", [(5, 7, 7, 96), (1, 3, 183, 64), (16, 20, 160, 64)])
+def test_dense_layer_two_launches(sol, case):  # noqa: F811
+    """The same layer one by one, as one launch, in the plan's own choice and in the auto-tuner's."""
+    N, H, W, C = case
+    layers = [wl.conv(C, 1, p=0), wl.conv(128, 1, p=0, src=0, pre_bn=True), wl.conv(32, 3, bn=False, act="none"), wl.concat(0, 2),
+              wl.conv(8, 1, p=0, bn=False, act="none")]
+    x = wl.to_bf16_grid(np.random.default_rng(case).standard_normal((N, 64, H, W)))
+    prm = wl.make_params(layers, 64, 3 + C, bf16=True, bias_std=0.3)
+    outs, _ = orc.network_forward(layers, prm, x, bf16=True, return_all=True)
+    net = sol.Network(layers, x.shape, sol.BF16)
+    net.set_params(prm)
+    assert net.dense_state(2) == (W != 160)                 # 51200 pixels of images 160 wide are more than one round of tiles
+    xd = sol.to_device_nhwc(x, sol.BF16)
+    for choice in (0, 1, "tuned", "restored"):
+        if choice == "tuned":
+            tiles = net.autotune(xd, reps=2)
+            assert tiles["2d"] == net.dense_state(2)
+        elif choice == "restored":
+            net.set_tiles(tiles)
+            assert tiles["2d"] == net.dense_state(2)
+        else:
+            net.set_dense(2, choice)
+        net.workspace.fill_(0xff)
+        net.forward(xd)
+        torch.cuda.synchronize()
+        assert rel_err(sol.to_host_nchw(net.y).reshape(outs[-1].shape), outs[-1]) <= TOL["bf16"], choice
+        if choice == 0:
+            assert rel_err(sol.to_host_nchw(net.layer_output(1)), outs[1]) <= TOL["bf16"]
