@@ -295,7 +295,8 @@ sol_status sol_network_autotune(sol_network *net, const void *x, void *y, void *
 sol_status sol_network_layer_tile(const sol_network *net, int layer, int *tile);
 /* Restores a choice that sol_network_autotune made earlier (same network, same machine): `tile` as reported by
  * sol_network_layer_tile, 0 = shape heuristic.  An id that does not fit the layer makes the next forward fail with
- * SOL_ERR_UNSUPPORTED before anything is launched for that layer. */
+ * SOL_ERR_UNSUPPORTED before anything is launched for that layer.  A tile for either convolution of a dense layer (see
+ * sol_network_set_layer_dense) runs the two one by one; with 0 for both the plan's own choice is back. */
 sol_status sol_network_set_layer_tile(sol_network *net, int layer, int tile);
 
 /* Whole bottlenecks in one launch.  When a network keeps no activations (flags 0), bf16: a 1x1 convolution + ReLU, a

@@ -366,11 +366,11 @@ static bool stem_pool_plan_ok(const sol_tensor_desc &in, const sol_conv_desc &cd
 // The plan's own choice for a dense layer whose 3x3 convolution is c2: see dense_one_launch_pays
 static bool dense_one_launch(const sol_network *net, const LayerPlan &c2) {
     const LayerPlan &c1 = net->layers[c2.dense_c1];
-    return dense_one_launch_pays(c2.in.n, c2.in.h, c2.in.w, (int)round_up((size_t)c1.cd.cin, 64), (c1.cin_real ? c1.cin_real : c1.cd.cin) % 64 != 0);
+    return c1.tile == T_AUTO && c2.tile == T_AUTO && dense_one_launch_pays(c2.in.n, c2.in.h, c2.in.w, (int)round_up((size_t)c1.cd.cin, 64), (c1.cin_real ? c1.cin_real : c1.cd.cin) % 64 != 0);
 }
-// Does the 3x3 convolution c2 compute the 1x1 in front with it?
+// Does the 3x3 convolution c2 compute the 1x1 in front with it?  A tile forced on every layer runs them one by one.
 static bool dense_fused(const LayerPlan &c2) {
-    return c2.dense_c1 >= 0 && (c2.use_dense || (g_tile_override >= B_FIRST && g_tile_override <= B_LAST));
+    return c2.dense_c1 >= 0 && ((c2.use_dense && !g_tile_override) || (g_tile_override >= B_FIRST && g_tile_override <= B_LAST));
 }
 
 static sol_status plan_network(sol_network *net, const sol_layer *layers, int n_layers) {
@@ -1678,7 +1678,12 @@ sol_status sol_network_set_layer_tile(sol_network *net, int layer, int tile) {
     SOL_REQUIRE(net, SOL_ERR_NULL, "net is NULL");
     SOL_REQUIRE(layer >= 0 && layer < (int)net->layers.size(), SOL_ERR_SHAPE, "no layer %d", layer);
     SOL_REQUIRE(tile >= 0 && tile < 100, SOL_ERR_SHAPE, "tile id %d out of range", tile);
-    net->layers[layer].tile = tile;
+    LayerPlan &lp = net->layers[layer];
+    lp.tile = tile;
+    if (lp.dense_c1 >= 0 || lp.dense_into >= 0) {     // a tile for either convolution of a dense layer runs the two one by one
+        LayerPlan &c2 = lp.dense_c1 >= 0 ? lp : net->layers[lp.dense_into];
+        c2.use_dense = dense_one_launch(net, c2);
+    }
     return SOL_OK;
 }
 

@@ -346,3 +346,20 @@ def test_dense_layer_one_launch_or_two(sol, shape, c, fused):
             assert L.sol_network_forward(h, fake, fake, fake, C.c_size_t(size), None) == 5
             assert what in L.sol_last_error().decode(), (f, size)
     L.sol_network_destroy(h)
+
+
+def test_dense_layer_tile_runs_two_launches(sol):
+    """A tile set for either convolution of a dense layer is used: the pair runs one by one until both are automatic again."""
+    L, h, v = sol.lib(), _dense_net(sol, (4, 64, 14, 14)), C.c_int()
+
+    def state():
+        assert L.sol_network_layer_dense(h, 2, C.byref(v)) == 0
+        return v.value
+
+    assert state() == 1
+    for layer in (1, 2):
+        assert L.sol_network_set_layer_tile(h, layer, 5) == 0 and state() == 0
+        assert L.sol_network_set_layer_tile(h, 3 - layer, 0) == 0 and state() == 0
+        assert L.sol_network_set_layer_tile(h, layer, 0) == 0 and state() == 1
+    assert L.sol_network_set_layer_tile(h, 0, 5) == 0 and state() == 1       # any other layer's tile leaves it alone
+    L.sol_network_destroy(h)

@@ -120,3 +120,35 @@ def test_dense_layer_two_launches(sol, case):  # noqa: F811
         assert rel_err(sol.to_host_nchw(net.y).reshape(outs[-1].shape), outs[-1]) <= TOL["bf16"], choice
         if choice == 0:
             assert rel_err(sol.to_host_nchw(net.layer_output(1)), outs[1]) <= TOL["bf16"]
+
+
+def test_dense_layer_tiles_are_used(sol):  # noqa: F811
+    """Tiles set for, or forced on, the two convolutions of a dense layer are used (and one that cannot apply is refused)."""
+    layers = [wl.conv(64, 1, p=0), wl.conv(128, 1, p=0, src=0, pre_bn=True), wl.conv(32, 3, bn=False, act="none"), wl.concat(0, 2),
+              wl.conv(8, 1, p=0, bn=False, act="none")]
+    x = wl.to_bf16_grid(np.random.default_rng(4).standard_normal((3, 64, 9, 10)))
+    prm = wl.make_params(layers, 64, 5, bf16=True, bias_std=0.3)
+    outs, _ = orc.network_forward(layers, prm, x, bf16=True, return_all=True)
+    net = sol.Network(layers, x.shape, sol.BF16)
+    net.set_params(prm)
+    xd = sol.to_device_nhwc(x, sol.BF16)
+
+    def check():
+        net.workspace.fill_(0xff)
+        net.forward(xd)
+        torch.cuda.synchronize()
+        assert rel_err(sol.to_host_nchw(net.y).reshape(outs[-1].shape), outs[-1]) <= TOL["bf16"]
+        assert rel_err(sol.to_host_nchw(net.layer_output(1)), outs[1]) <= TOL["bf16"]       # stored: two launches
+
+    net.set_tiles({1: 3, 2: 6})
+    check()
+    sol.sol_debug_set_conv_tile(5)
+    try:
+        net.set_tiles({})
+        check()
+    finally:
+        sol.sol_debug_set_conv_tile(0)
+    net.set_tiles({1: 11})                                   # a DMA ring tile cannot apply BN + ReLU to its input
+    with pytest.raises(sol.SolError) as e:
+        net.forward(xd)
+    assert e.value.status == 6
