@@ -376,7 +376,9 @@ sol_status sol_network_run_layer(sol_network *net, int layer, const void *x, voi
                                  size_t workspace_bytes, void *hip_stream);
 
 /* Device address (inside the workspace passed to the last forward) of a layer's output; only
- * meaningful after a forward of a network created with SOL_NET_KEEP_ACTIVATIONS. */
+ * meaningful after a forward of a network created with SOL_NET_KEEP_ACTIVATIONS.  Without that flag SOL_ERR_UNSUPPORTED for a
+ * layer that has no tensor of its own there: a projection shortcut or a stem convolution that is never stored, a
+ * convolution that writes a channel range of a concatenation. */
 sol_status sol_network_layer_output(const sol_network *net, int layer, void *workspace, void **ptr);
 
 /* ---- training step (networks created with SOL_NET_TRAINING) ----------------------------------------

@@ -1767,7 +1767,11 @@ sol_status sol_network_layer_output(const sol_network *net, int layer, void *wor
     SOL_REQUIRE(net && workspace && ptr, SOL_ERR_NULL, "net, workspace and ptr must not be NULL");
     SOL_REQUIRE(layer >= 0 && layer + (net->training ? 0 : 1) < (int)net->layers.size(), SOL_ERR_SHAPE,
                 "layer %d has no workspace buffer (the last layer writes to y)", layer);
-    *ptr = static_cast<unsigned char *>(workspace) + net->layers[layer].out_off;
+    const LayerPlan &lp = net->layers[layer];
+    SOL_REQUIRE(!(lp.no_buffer && lp.dense_into < 0) && !lp.absorbs_next, SOL_ERR_UNSUPPORTED,
+                "the output of layer %d is never stored: one launch computes it and the layer that reads it", layer);
+    SOL_REQUIRE(lp.concat_into < 0, SOL_ERR_UNSUPPORTED, "the output of layer %d is a channel range of concatenation %d's", layer, lp.concat_into);
+    *ptr = static_cast<unsigned char *>(workspace) + lp.out_off;
     return SOL_OK;
 }
 

@@ -363,3 +363,25 @@ def test_dense_layer_tile_runs_two_launches(sol):
         assert L.sol_network_set_layer_tile(h, layer, 0) == 0 and state() == 1
     assert L.sol_network_set_layer_tile(h, 0, 5) == 0 and state() == 1       # any other layer's tile leaves it alone
     L.sol_network_destroy(h)
+
+
+def test_layer_output_only_of_stored_layers(sol):
+    """A layer without a tensor of its own in the workspace has no address (it used to be another layer's)."""
+    L, c = sol.lib(), wl.conv
+    layers = [c(64, 7, 2, 3, bn=False), wl.pool("max", 3, 2, 1),                              # stem + pool in one launch
+              c(64, 1, p=0), c(64, 1, p=0, src=1, act="none"), c(64, 1, p=0, src=2, res=3),  # projection shortcut inside the expand
+              c(32, 3), c(32, 3, src=4), wl.concat(5, 6), c(128, 1, p=0, src=7, pre_bn=True), c(32, 3), c(8, 1, p=0)]
+    own = {0: False, 3: False, 5: False, 6: False}
+    for flags in (0, sol.NET_KEEP_ACTIVATIONS):
+        st, h = _create(sol, layers, (2, 3, 64, 64), sol.BF16, flags)
+        assert st == 0, L.sol_last_error()
+        ws, seen = 1 << 40, []
+        for i in range(len(layers) - 1):
+            p = C.c_void_p()
+            st = L.sol_network_layer_output(h, i, C.c_void_p(ws), C.byref(p))
+            assert st == (0 if flags or own.get(i, True) else 6), (flags, i, st)
+            if st == 0:
+                assert ws <= p.value < ws + L.sol_network_workspace_bytes(h)
+                seen.append(p.value)
+        assert not flags or len(set(seen)) == len(seen)
+        L.sol_network_destroy(h)
