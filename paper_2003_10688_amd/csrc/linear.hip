@@ -149,8 +149,9 @@ __global__ void __launch_bounds__(512) linear_stream_kernel(const ConvArgs a, in
     const int nst = (a.C * ES + ROWB - 1) / ROWB, tail = a.C * ES - (nst - 1) * ROWB;    // stages; bytes of the last one
     const int s0 = (int)((long)nst * wave / NW), s1 = (int)((long)nst * (wave + 1) / NW);
     const int n = s1 - s0;
-    // every workgroup starts at a stage of its own: 39.1 -> 35.6 us (64 rows, 8192x8192), or all ask for the same columns of x at once
-    int s = n > 0 ? s0 + ((int)(blockIdx.x >> 3) + wave) % n : s0, left = n;
+    // the workgroups start at different stages: 39.1 -> 35.6 us (64 rows, 8192x8192), or all ask for the same columns of x at once.
+    // The row tiles of one feature tile start at the same one: they share its weights, and equal rows give equal bits
+    int s = n > 0 ? s0 + (grp + wave) % n : s0, left = n;
     unsigned char *ring = lds + wave * (NS * XST), *strip = lds + NW * NS * XST + wave * WST;
 
     u32x4_t wq[NS][WL];

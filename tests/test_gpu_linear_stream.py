@@ -34,3 +34,16 @@ def test_linear_stream(sol, dt, rows, kin, out):  # noqa: F811
         if act == sol.ACT_RELU:
             want = np.maximum(want, 0)
         assert rel_err(sol.to_host_nchw(y).reshape(rows, out), want) <= TOL[dt]
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("rows,kin,out", [(65, 4096, 40), (128, 2304, 600)])
+def test_linear_equal_rows_equal_bits(sol, dt, rows, kin, out):  # noqa: F811
+    """A row's sums run in one order wherever it stands: the rows of the second row tile repeat those of the first."""
+    rng = np.random.default_rng([rows, kin, out])
+    d = sol.BF16 if dt == "bf16" else sol.F32
+    x = rng.standard_normal((64, kin))[np.arange(rows) % 64]
+    cd = sol.ConvDesc(out, kin, 1, 1, 1, 1, 0, 0)
+    wp = sol.sol_pack_conv_weights(cd, d, sol.dev_f32((rng.standard_normal((out, kin)) / np.sqrt(kin)).reshape(out, kin, 1, 1)))
+    y = sol.to_host_nchw(sol.sol_linear(sol.to_device_nhwc(x, d), wp, None, out, sol.ACT_NONE)).reshape(rows, out)
+    assert np.array_equal(y[64:], y[:rows - 64])
