@@ -315,7 +315,7 @@ sol_status launch_conv(const ConvArgs &a, int dt, int tile_override, hipStream_t
     if (tile_override == T_AUTO && stem_kernel_applies(a, dt)) return launch_conv_stem(a, st);
     if (tile_override == T_AUTO && !one_order && linear_stream_applies(a, dt)) return launch_linear_stream(a, dt, st);
     if (tile_override == T_AUTO && linear_kernel_applies(a, dt)) {
-        // more rows than linear_stream_applies takes, and a weight matrix of many megabytes: the job is streaming the weights, which the
+        // not one for linear_stream_applies, and a weight matrix of many megabytes: the job is streaming the weights, which the
         // eight-wave ring kernel does with whole 128-byte lines and eight stages in flight
         const double wbytes = (double)a.Cout * a.Kp * dtype_size(dt);
         if (wbytes >= 16.0 * 1048576 && gemm8_kernel_applies(a, dt) && a.C % 64 == 0) {

@@ -150,7 +150,8 @@ __global__ void __launch_bounds__(512) linear_stream_kernel(const ConvArgs a, in
     const int s0 = (int)((long)nst * wave / NW), s1 = (int)((long)nst * (wave + 1) / NW);
     const int n = s1 - s0;
     // the workgroups start at different stages: 39.1 -> 35.6 us (64 rows, 8192x8192), or all ask for the same columns of x at once.
-    // The row tiles of one feature tile start at the same one: they share its weights, and equal rows give equal bits
+    // The row tiles of one feature tile start at the same one, so that equal rows give equal bits (one stage apart was up to
+    // 6 % faster with 65 to 128 rows: 65, bf16 3072 -> 16384, 44.3 against 47.1; 128, 8192 -> 8192, 54.9 against 55.9)
     int s = n > 0 ? s0 + (grp + wave) % n : s0, left = n;
     unsigned char *ring = lds + wave * (NS * XST), *strip = lds + NW * NS * XST + wave * WST;
 
@@ -258,13 +259,30 @@ __global__ void __launch_bounds__(512) linear_stream_kernel(const ConvArgs a, in
 #endif
 }
 
+// Matrices of 16 MB and more belong to the ring kernel when the rows are many for the length of the reduction: x is most of what
+// a workgroup fetches, and 64 features share it there, 32 here.  Each side counts for as much as the rounds of 256 workgroups that
+// it makes are full.  The line is a fit to 624 timed layers (33..128 rows, 2048..8192 -> 4096..16384 in steps of 512), on which the choice
+// is 0.6 % slower than the better of the two on average and 14 % at worst; always here: 2.9 % and 27 %.  bf16, ring kernel
+// against here, us: 128 rows, 2048 -> 6656 16.4, 20.5; 2048 -> 8192 17.8, 20.9; 2048 -> 12800 30.1, 38.1; 4096 -> 8192 30.2, 32.7;
+// 4096 -> 16384 65.5, 63.4; 8192 -> 8192 55.0, 54.5; 64 rows, 2048 -> 12800 21.1, 23.4; 4096 -> 8192 25.1, 21.7; 4096 -> 12800 37.2, 38.2.
+// Features in multiples of 512: eight sets of tiles, one per XCD (128 rows, 2048 -> 6400, where every XCD reads the whole matrix:
+// 39.4, 20.2).
+static bool ring_kernel_is_better(const ConvArgs &a, int dt) {
+    if (dt != SOL_BF16 || a.C % 128 != 0 || a.Cout % 512 != 0 || a.P <= 32 || (double)a.Cout * a.Kp * 2.0 < 16.0 * 1048576) return false;
+    const auto fill = [](int n) { return (float)n / (float)(256 * ceil_div(n, 256)); };      // of the rounds that n workgroups make
+    const int here = ceil_div(a.P, 64) * ceil_div(a.Cout, 32), tiles = ceil_div(a.P, 64) * ceil_div(a.Cout, 64);
+    if (tiles < 200 && here <= 256) return false;
+    const float e = here <= 256 ? 1.f : fill(here), er = fill(tiles);
+    return (float)a.C * e * e * e <= (float)(tiles <= 256 ? 44 * a.P : 32 * a.P + 512) * er * er;
+}
+
 // Up to 128 rows (above, the 64-row tiles re-read the weights too often), and reductions that linear_kernel does not finish in
 // one round trip: from 4 KB per row in bf16 (64 rows: 1024 -> 1000 features 6.6 against 6.3 us here, 2048 -> 1000 10.4 against 7.9;
 // 13 rows, 512 -> 1000: 4.2 against 5.2; 128 rows, 1528 -> 1528: 7.7 against 8.5), from 2 KB in fp32, where its 32x32 blocks are a
 // long chain of matrix instructions (9 rows, 512 -> 1000: 7.3 against 5.5; 64 rows, 128 -> 10: 4.8 against 5.6).
 bool linear_stream_applies(const ConvArgs &a, int dt) {
     const double es = (double)dtype_size(dt);
-    return linear_kernel_applies(a, dt) && a.P <= 128 && a.C * (int)es >= (dt == SOL_BF16 ? 4096 : 2048) && (double)a.P * a.C * es < 2147483648.0 && (double)a.Cout * a.Kp * es < 2147483648.0;
+    return linear_kernel_applies(a, dt) && a.P <= 128 && !ring_kernel_is_better(a, dt) && a.C * (int)es >= (dt == SOL_BF16 ? 4096 : 2048) && (double)a.P * a.C * es < 2147483648.0 && (double)a.Cout * a.Kp * es < 2147483648.0;
 }
 
 template <typename T> static sol_status launch_stream_typed(const ConvArgs &a, hipStream_t st) {

@@ -19,6 +19,8 @@ pytestmark = pytest.mark.gpu
     (64, 2048, 4104),     # 32-feature tiles with a remainder
     (65, 2088, 72),       # two row tiles sharing their weights
     (128, 2048, 4100),    # both at their largest
+    (128, 2048, 6656),    # bf16: many rows for the reduction, the eight-wave ring kernel's
+    (64, 2048, 12800),    # the first width of one row tile that is
 ])
 def test_linear_stream(sol, dt, rows, kin, out):  # noqa: F811
     rng = np.random.default_rng([rows, kin, out])
@@ -37,7 +39,7 @@ def test_linear_stream(sol, dt, rows, kin, out):  # noqa: F811
 
 
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
-@pytest.mark.parametrize("rows,kin,out", [(65, 4096, 40), (128, 2304, 600)])
+@pytest.mark.parametrize("rows,kin,out", [(65, 4096, 40), (128, 2304, 600), (128, 2048, 6656)])
 def test_linear_equal_rows_equal_bits(sol, dt, rows, kin, out):  # noqa: F811
     """A row's sums run in one order wherever it stands: the rows of the second row tile repeat those of the first."""
     rng = np.random.default_rng([rows, kin, out])
