@@ -20,6 +20,10 @@ pytestmark = pytest.mark.gpu
     (65, 2088, 72),       # two row tiles sharing their weights
     (128, 2048, 4100),    # both at their largest
     (128, 2048, 6656),    # bf16: many rows for the reduction, the eight-wave ring kernel's
+    (1, 2048, 4104),      # up to 16 and up to 32 rows on 32-feature tiles (more than 4096 features), with remainders of all three
+    (16, 2056, 8200),
+    (17, 2056, 4104),
+    (32, 2112, 4100),
     (64, 2048, 12800),    # the first width of one row tile that is
 ])
 def test_linear_stream(sol, dt, rows, kin, out):  # noqa: F811
