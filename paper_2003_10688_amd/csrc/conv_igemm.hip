@@ -341,7 +341,7 @@ sol_status launch_conv(const ConvArgs &a, int dt, int tile_override, hipStream_t
     }
     if (tile_override >= S_FIRST && tile_override <= S_LAST) {
         SOL_REQUIRE(direct_kernel_applies(a, dt), SOL_ERR_UNSUPPORTED,
-                    "conv tile %d needs at most 32 filter taps over channels in multiples of 64 bytes, no pool winners and no residual in front of a pool",
+                    "conv tile %d needs at most 32 filter taps over channels in multiples of 128 bytes, operands below 2 GiB, no pool winners and no residual in front of a pool",
                     tile_override);
         return launch_conv_direct(a, dt, tile_override, st);
     }

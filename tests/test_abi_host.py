@@ -385,3 +385,15 @@ def test_layer_output_only_of_stored_layers(sol):
                 seen.append(p.value)
         assert not flags or len(set(seen)) == len(seen)
         L.sol_network_destroy(h)
+
+
+def test_small_tile_refusal_names_its_condition(sol):
+    """32 bf16 channels are 64 bytes: a small tile forced on them is refused with the rule that they miss."""
+    fake, null = C.c_void_p(0x1000), C.c_void_p(0)
+    sol.sol_debug_set_conv_tile(81)
+    try:
+        st = sol.lib().sol_conv2d_fused(C.byref(sol.TensorDesc(1, 8, 8, 32, sol.BF16)), fake, C.byref(sol.ConvDesc(32, 32, 3, 3, 1, 1, 1, 1)), fake, null,
+                                        null, null, 0, None, fake, null, null, null)
+    finally:
+        sol.sol_debug_set_conv_tile(0)
+    assert st == 6 and "multiples of 128 bytes" in sol.lib().sol_last_error().decode()
