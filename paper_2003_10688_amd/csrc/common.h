@@ -147,7 +147,7 @@ enum {
     // G_*: eight-wave 1x1 GEMM kernel (conv_gemm8.hip); kN: reduction split N ways inside the workgroup, r64: 64-byte rows
     G_128x128_k2 = 61, G_256x128 = 62, G_128x256 = 63, G_64x128_k4 = 64, G_128x64_k4 = 65, G_256x256_r64 = 66, G_256x128_r64 = 67,
     G_64x64_k4 = 68, G_64x64_k4_deep = 69, G_64x32_k4_r256 = 70, G_FIRST = 61, G_LAST = 79,
-    // S_*: register-direct kernel for layers with few pixels (conv_direct.hip)
+    // S_*: small tiles, one LDS-DMA ring per wave, for layers with few pixels (conv_direct.hip)
     S_16x16 = 81, S_16x32 = 82, S_32x32 = 83, S_64x32 = 84, S_64x64 = 85, S_FIRST = 81, S_LAST = 85,
     // B_*: patch rows of the dense-layer kernel (conv_dense.hip); not a choice of any other layer
     B_64 = 91, B_96 = 92, B_128 = 93, B_192 = 94, B_256 = 95, B_384 = 96, B_FIRST = 91, B_LAST = 96,

@@ -25,7 +25,6 @@
 namespace sol {
 
 namespace {
-typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 using lds_pipe::u32x4_t;
 typedef __attribute__((ext_vector_type(2))) unsigned u32x2_t;
 
@@ -33,9 +32,6 @@ template <int O> __device__ __forceinline__ void lds_write16(unsigned addr, cons
     asm volatile("ds_write_b128 %0, %1 offset:%2" ::"v"(addr), "v"(v), "n"(O) : "memory");
 }
 __device__ __forceinline__ void lds_write8(unsigned addr, const u32x2_t &v) { asm volatile("ds_write_b64 %0, %1" ::"v"(addr), "v"(v) : "memory"); }
-__device__ __forceinline__ void mma(f32x4_t &acc, const u32x4_t &a, const u32x4_t &b) {
-    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), acc, 0, 0, 0);
-}
 
 constexpr int DN_MID = 128, DN_OUT = 32, DN_CMAX = 1024;   // filters of the 1x1 / of the 3x3 convolution; widest input prefix
 
@@ -223,7 +219,7 @@ __global__ void __launch_bounds__(512) conv_dense_kernel(const DenseArgs a) {
 #pragma unroll
             for (int i = 0; i < CA; i++)
 #pragma unroll
-                for (int j = 0; j < PA; j++) mma(acc[i][j], fa[f][i], fb[f][j]);
+                for (int j = 0; j < PA; j++) Mma16<bf16_t>::run(acc[i][j], fa[f][i], fb[f][j]);
         };
         using I0 = std::integral_constant<int, 0>;
         using I1 = std::integral_constant<int, 1>;
@@ -334,8 +330,8 @@ __global__ void __launch_bounds__(512) conv_dense_kernel(const DenseArgs a) {
                 static_for<NB>([&](auto B) { landed(fb[q][decltype(B)::value]); });
 #pragma unroll
                 for (int b = 0; b < NB; b++) {
-                    mma(acc2[b][0], fa[q][0], fb[q][b]);
-                    mma(acc2[b][1], fa[q][1], fb[q][b]);
+                    Mma16<bf16_t>::run(acc2[b][0], fa[q][0], fb[q][b]);
+                    Mma16<bf16_t>::run(acc2[b][1], fa[q][1], fb[q][b]);
                 }
             });
         }

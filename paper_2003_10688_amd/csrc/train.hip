@@ -696,9 +696,10 @@ __global__ void pack_weights_flip_kernel(const float *__restrict__ w, T *__restr
 // ---- weight gradient -------------------------------------------------------------------------------------
 // dW[k][r][s][c] = sum over output pixels of dz[pixel][k] * x[pixel shifted by tap (r,s)][c]: a GEMM whose
 // reduction runs over pixels, the slow axis of both NHWC operands.  The general kernel: a workgroup owns 64 filters x
-// 64 columns j = (r, s, c) -- a lane keeps the tap and channel of its columns for the whole loop, so a stem of three
-// channels fills its tiles: 7x7 over 9 images of 113x113, fp32, @STEM@ -- and a contiguous range of pixel groups; MFMA
-// fragments (16 bytes of consecutive pixels for one column) are gathered element-wise straight from global memory with
+// 64 columns j = (r, s, c) -- a lane keeps the tap and channel of its columns for the whole loop, so few or odd channels
+// fill its tiles (before, with a tile per tap and 64 channels; us -> now): fp32 7x7 of 3 channels, 9 images of 113x113, 171 -> 27;
+// bf16 3x3, 66 -> 66 at 28x28, 32 images, 74 -> 41; whole 64-channel blocks pay for it: 64 -> 10, 21.9 -> 24.1; 1x1, 70 -> 130 at
+// 14x14, 10.3 -> 11.2 -- and a contiguous range of pixel groups; MFMA fragments (16 bytes of consecutive pixels for one column) are gathered element-wise straight from global memory with
 // out-of-range taps, column tails and row tails turned into zeros by the buffer range check.  Pixels are enumerated in groups of GP along an
 // output row (GP = elements per 16 bytes); each half-wave takes one group per step, so one step reduces
 // 2*GP pixels.  The four waves interleave steps and their accumulators are summed through LDS at the end;
