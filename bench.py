@@ -126,7 +126,7 @@ def main():
     t0 = time.perf_counter()
     if a.load_plan:
         with open(a.load_plan) as f:
-            tuned = {(k if k[-1] in "bx" else int(k)): v for k, v in json.load(f).items()}
+            tuned = {(int(k) if k.isdigit() else k): v for k, v in json.load(f).items()}
         net.set_tiles(tuned)
     else:
         tuned = net.autotune(x, reps=a.tune_reps, stream=stream) if a.tune_reps > 0 else {}
@@ -376,7 +376,7 @@ def main():
         "submission": "HIP graph replay" if a.graph else "eager launches", "eager_ms_per_step": round(eager_ms, 4), "higher_is_better": True, "scaling": "weak",
         "vs_baseline": None, "dtype": "bf16" if wk.bf16 else "f32", "data": "synthetic",
         "config": {"workload": f"{wk.name} batch {batch} input {wk.in_shape[1]}x{wk.in_shape[2]}x{wk.in_shape[3]} (seeded synthetic, He-normal weights)",
-                   "launches_per_step": sum(1 for r in rows if r["kind"] != "fused"), "autotuned_layers": sum(1 for k in tuned if str(k)[-1] not in "bx"), "fused_bottlenecks": sum(1 for k, v in tuned.items() if str(k).endswith("b") and v),
+                   "launches_per_step": sum(1 for r in rows if r["kind"] != "fused"), "autotuned_layers": sum(1 for k in tuned if str(k).isdigit()), "fused_bottlenecks": sum(1 for k, v in tuned.items() if str(k).endswith("b") and v),
                    "fused_expand_reduce_pairs": sum(1 for k, v in tuned.items() if str(k).endswith("x") and v), "autotune_seconds": round(tune_s, 2)},
         "roofline": roofline, "cpu_baseline": cpu, "parity": parity, "training_step": training,
     }
