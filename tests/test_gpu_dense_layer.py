@@ -152,3 +152,22 @@ def test_dense_layer_tiles_are_used(sol):  # noqa: F811
     with pytest.raises(sol.SolError) as e:
         net.forward(xd)
     assert e.value.status == 6
+
+
+def test_dense_layer_static_workspace(sol):  # noqa: F811
+    """A pass that stores no 1x1 output needs no buffer for it: 31 MiB of the static workspace's 32 do, 55 would not."""
+    layers = [wl.conv(64, 1, p=0), wl.conv(128, 1, p=0, src=0, pre_bn=True), wl.conv(32, 3, bn=False, act="none"), wl.concat(0, 2),
+              wl.conv(8, 1, p=0, bn=False, act="none")]
+    net = sol.Network(layers, (32, 64, 56, 56), sol.BF16)
+    net.set_params(wl.make_params(layers, 64, 9, bf16=True))
+    x = torch.randn((32, 56, 56, 64), device="cuda:0").bfloat16()
+    y = net.forward(x).clone()
+    net.y.zero_()
+    assert torch.equal(net.forward_static(x), y)
+    net.set_dense(2, 0)
+    with pytest.raises(sol.SolError) as e:
+        net.forward_static(x)
+    assert e.value.status == 5
+    net.workspace = net.workspace[:net.workspace.numel() - 32 * 56 * 56 * 128 * 2]      # one launch: accepted, and left alone by the auto-tuner
+    net.set_dense(2, 1)
+    assert torch.equal(net.forward(x), y) and net.autotune(x, reps=1)["2d"] == 1
