@@ -238,30 +238,22 @@ sol_status launch_gap_bwd(const void *dy, void *dx, int N, int HW, int C, int fi
 sol_status launch_softmax_ce(const void *logits, const int32_t *labels, void *dlogits, float *row_loss, float *loss, int N,
                              int C, int dt, hipStream_t st);
 
-// Batched parameter update: up to SGD_MAX_SEG tensors updated, and up to PACK_MAX_SEG packed weight buffers rebuilt,
-// by one launch each (a ResNet-18-shaped step otherwise spends ~100 launches on them).  The segment tables travel
-// in the kernel arguments, so nothing is allocated or copied.
-constexpr int SGD_MAX_SEG = 96, PACK_MAX_SEG = 64;
-struct SgdBatch {
+// Parameter update: up to UPD_MAX_SEG tensors by one launch (the segment table travels in the kernel arguments, so nothing is
+// allocated or copied).  A segment with packed copies is a weight tensor [K][C][RS]; one without is a run of C values.
+constexpr int UPD_MAX_SEG = 48, UPD_PLANE = 9216;     // UPD_PLANE: weights of one block's tile
+struct UpdateBatch {
     int nseg;
-    int first_block[SGD_MAX_SEG + 1];     // blocks [first_block[i], first_block[i+1]) work on segment i
-    float *w[SGD_MAX_SEG], *v[SGD_MAX_SEG];
-    const float *g[SGD_MAX_SEG];
-    long n[SGD_MAX_SEG];
+    int first_block[UPD_MAX_SEG + 1];      // blocks [first_block[i], first_block[i+1]) work on segment i
+    float *w[UPD_MAX_SEG], *v[UPD_MAX_SEG];
+    const float *g[UPD_MAX_SEG];
+    void *out[UPD_MAX_SEG], *outT[UPD_MAX_SEG];     // packed weights in forward order / flipped and transposed; NULL: not kept
+    int K[UPD_MAX_SEG], C[UPD_MAX_SEG], RS[UPD_MAX_SEG], Kp[UPD_MAX_SEG], KpT[UPD_MAX_SEG];
+    int TK[UPD_MAX_SEG], TC[UPD_MAX_SEG];  // filters x input channels of a block's tile; TK == 0: a run
 };
-struct PackBatch {
-    int nseg;
-    int first_block[PACK_MAX_SEG + 1];
-    const float *w[PACK_MAX_SEG];          // fp32 master, framework layout [K][C][R][S]
-    void *out[PACK_MAX_SEG];
-    int K[PACK_MAX_SEG], C[PACK_MAX_SEG], R[PACK_MAX_SEG], S[PACK_MAX_SEG], Kp[PACK_MAX_SEG], flip[PACK_MAX_SEG];
-    int mode[PACK_MAX_SEG];                // how the segment's blocks are cut, set by pack_segment_blocks
-};
-// number of workgroups a segment takes in pack_batch_kernel (and the block-cutting mode, written to *mode)
-int pack_segment_blocks(int K, int C, int R, int S, int Kp, int flip, int *mode);
-constexpr int SGD_ELEMS_PER_BLOCK = 256 * 8, PACK_ELEMS_PER_BLOCK = 256 * 8;
-sol_status launch_sgd_batch(const SgdBatch &b, float lr, float mu, hipStream_t st);
-sol_status launch_pack_batch(const PackBatch &b, int dt, hipStream_t st);
+// Cuts the segment whose w, v, g, out, outT, K, C, RS, Kp and KpT are set into blocks; false: a filter larger than a block's tile
+bool update_segment_blocks(UpdateBatch &b, int i);
+constexpr int UPD_ELEMS_PER_BLOCK = 256 * 8;
+sol_status launch_update_batch(const UpdateBatch &b, int dt, float lr, float mu, hipStream_t st);
 sol_status launch_pack_flip(const sol_conv_desc &cd, int dt, const float *w, void *packed, hipStream_t st);
 void wgrad_plan(const sol_tensor_desc &xd, const sol_conv_desc &cd, int Ho, int Wo, int *nsplit, size_t *part_floats);
 // deferred_nsplit != NULL: only the first stage runs (split partials into `part`) and the number of splits is

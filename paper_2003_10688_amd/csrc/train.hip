@@ -558,122 +558,126 @@ __global__ void loss_mean_kernel(const float *__restrict__ row_loss, int N, floa
     }
 }
 
-// ---- SGD with momentum: v <- mu v + g ; w <- w - lr v ---------------------------------------------------------
-// All parameter tensors of a network in one launch: block -> segment by a scan of the (scalar) block table.
-__global__ void __launch_bounds__(256) sgd_batch_kernel(const SgdBatch b, float lr, float mu) {
+// ---- SGD with momentum: v <- mu v + g ; w <- w - lr v, and the packed copies of the new weights ---------------------
+// All parameter tensors of a network in one launch: block -> segment by a scan of the (scalar) block table.  What bounds it
+// is memory: weight, velocity and gradient in, weight, velocity and two packed copies out.  An update launch followed by a
+// repacking launch reads every weight once more and fetched it in an order that suits only one of the two copies; here a
+// block takes a tile of TK filters x TC input channels x all taps, whose master rows are runs of TC * taps floats, updates it,
+// leaves the new weights in LDS and writes from there both copies, a tap's TC channels in a row of the forward pack and its
+// TK filters in a row of the flipped one (element maps of pack_weights_kernel / pack_weights_flip_kernel; the padding of packed
+// rows was zeroed when the weights were set and stays).  32 x 32 for 3x3 filters makes both writes 64 bytes long (bf16).
+// ResNet-18-shaped, 11.7 M weights, bf16 / fp32: 54 + 60 / 54 + 61 us as two launches, 50 / 58 us here (281 / 328 MB).
+template <typename T, int V, bool VEC>
+__device__ __forceinline__ void write_packed(const float *tile, int pitch, T *__restrict__ out, int rows, int row0, int cols, int col0, int ncol, int RS,
+                                             int Kp, int srow, int scol, bool flip) {
+    // out row (row0 + r), tap position t, columns col0 ..: tile element r * srow + c * scol + tap
+    constexpr int W = VEC ? V : 1;
+    const int pieces = cols / W, per_row = RS * pieces;
+    for (int i = threadIdx.x; i < rows * per_row; i += 256) {
+        const int r = i / per_row, rem = i - r * per_row, t = rem / pieces, c = (rem - t * pieces) * W;
+        const float *src = tile + r * srow + c * scol + (flip ? RS - 1 - t : t);
+        T *dst = out + (size_t)(row0 + r) * Kp + (size_t)t * ncol + col0 + c;
+        if constexpr (VEC) {
+            float f[V];
+#pragma unroll
+            for (int e = 0; e < V; e++) f[e] = src[e * scol];
+            VecIO<T, V>::store(dst, f);
+        } else {
+            Elem<T>::store(dst, *src);
+        }
+    }
+}
+template <typename T>
+__global__ void __launch_bounds__(256) update_batch_kernel(const UpdateBatch b, float lr, float mu) {
+    constexpr int V = 16 / (int)sizeof(T);
+    __shared__ float tile[UPD_PLANE + 64];             // rows of one filter's TC * taps weights, padded to an odd length
     int seg = 0;
     while (seg + 1 < b.nseg && (int)blockIdx.x >= b.first_block[seg + 1]) seg++;
+    const int blk = (int)blockIdx.x - b.first_block[seg];
     float *__restrict__ w = b.w[seg], *__restrict__ v = b.v[seg];
     const float *__restrict__ g = b.g[seg];
-    const long n = b.n[seg];
-    const long i0 = (long)((int)blockIdx.x - b.first_block[seg]) * SGD_ELEMS_PER_BLOCK;
+    const int K = b.K[seg], C = b.C[seg], RS = b.RS[seg], TK = b.TK[seg], TC = b.TC[seg];
+    if (TK == 0) {
+        const int i0 = blk * UPD_ELEMS_PER_BLOCK;
 #pragma unroll
-    for (int u = 0; u < SGD_ELEMS_PER_BLOCK / 256; u++) {
-        const long i = i0 + u * 256 + threadIdx.x;
-        if (i < n) {
-            const float vel = mu * v[i] + g[i];
-            v[i] = vel;
-            w[i] -= lr * vel;
-        }
-    }
-}
-
-// All packed weight buffers of a network (forward order and, for the data gradient, flipped / transposed) rebuilt
-// from the fp32 masters in one launch; same element maps as pack_weights_kernel / pack_weights_flip_kernel.
-// Both maps transpose the channel axis against the filter taps, so a segment is cut into blocks whose reads AND
-// writes are contiguous runs, with the transposition done in LDS:
-//   mode 1 (forward pack): one block per output channel k; its [C][taps] plane is one contiguous run of the
-//          master and becomes the contiguous packed row [taps][C] (+ zero padding);
-//   mode 2 (flipped pack, C % 8 == 0, K % 64 == 0): one block per 8 input channels x KT output channels; the master
-//          is read in runs of 8 x taps floats (one per k), the packed rows are written in runs of KT elements;
-//   mode 0: any other shape, one gathered element per thread.
-constexpr int PACK_PLANE = 9216;                   // floats of LDS per block
-template <typename T>
-__global__ void __launch_bounds__(256) pack_batch_kernel(const PackBatch b) {
-    __shared__ float tile[PACK_PLANE + 128];
-    int seg = 0;
-    while (seg + 1 < b.nseg && (int)blockIdx.x >= b.first_block[seg + 1]) seg++;
-    const float *__restrict__ w = b.w[seg];
-    T *__restrict__ out = static_cast<T *>(b.out[seg]);
-    const int K = b.K[seg], C = b.C[seg], R = b.R[seg], S = b.S[seg], Kp = b.Kp[seg], flip = b.flip[seg], mode = b.mode[seg];
-    const int blk = (int)blockIdx.x - b.first_block[seg], RS = R * S;
-    if (mode == 1) {
-        const int n = C * RS;
-        const float *src = w + (size_t)blk * n;
-        // eight loads in flight per thread (a plain copy loop waits for every load before it issues the next)
-        for (int i0 = threadIdx.x; i0 < n; i0 += 256 * 8) {                        // i = c * RS + tap
-            float v[8];
-#pragma unroll
-            for (int u = 0; u < 8; u++) v[u] = src[min(i0 + u * 256, n - 1)];
-#pragma unroll
-            for (int u = 0; u < 8; u++)
-                if (i0 + u * 256 < n) tile[i0 + u * 256] = v[u];
-        }
-        __syncthreads();
-        T *dst = out + (size_t)blk * Kp;
-        for (int j = threadIdx.x; j < Kp; j += 256) {                               // j = tap * C + c
-            const int tap = j / C, c = j - tap * C;
-            Elem<T>::store(dst + j, j < n ? tile[c * RS + tap] : 0.f);
+        for (int u = 0; u < UPD_ELEMS_PER_BLOCK / 256; u++) {
+            const int i = i0 + u * 256 + threadIdx.x;
+            if (i < C) {
+                const float vel = mu * v[i] + g[i];
+                v[i] = vel;
+                w[i] -= lr * vel;
+            }
         }
         return;
     }
-    if (mode == 2) {
-        const int KT = K % 128 == 0 ? 128 : 64, nkb = K / KT, run = 8 * RS, pitch = run + 1;
-        const int cb = blk / nkb, kb = blk - cb * nkb, c0 = cb * 8, k0 = kb * KT;
-        for (int i0 = threadIdx.x; i0 < KT * run; i0 += 256 * 8) {                // eight loads in flight per thread
-            float v[8];
-            int dst[8];
+    const int ncb = (C + TC - 1) / TC, kb = blk / ncb, cb = blk - kb * ncb;
+    const int k0 = kb * TK, c0 = cb * TC, nk = min(TK, K - k0), nc = min(TC, C - c0);
+    const int run = nc * RS, pitch = (TC * RS) | 1;
+    const size_t base = ((size_t)k0 * C + c0) * RS, rowlen = (size_t)C * RS;
+    if (((C * RS) & 3) == 0 && ((TC * RS) & 3) == 0) {  // every run starts and ends on 16 bytes (the tensors lie on 256)
+        const int q = run >> 2, n = nk * q;
+        for (int i0 = threadIdx.x; i0 < n; i0 += 256 * 3) {       // three groups of 16 bytes of each tensor in flight per thread
+            float4 wv[3], vv[3], gv[3];
+            size_t off[3];
+            int lo[3];
 #pragma unroll
-            for (int u = 0; u < 8; u++) {
-                const int i = min(i0 + u * 256, KT * run - 1);
-                const int kk = i / run, rem = i - kk * run;                         // rem = cc * RS + tap
-                dst[u] = kk * pitch + rem;
-                v[u] = w[((size_t)(k0 + kk) * C + c0) * RS + rem];
+            for (int u = 0; u < 3; u++) {
+                const int i = min(i0 + u * 256, n - 1), kk = i / q, j = (i - kk * q) * 4;
+                off[u] = base + kk * rowlen + j;
+                lo[u] = kk * pitch + j;
+                wv[u] = *reinterpret_cast<const float4 *>(w + off[u]);
+                vv[u] = *reinterpret_cast<const float4 *>(v + off[u]);
+                gv[u] = *reinterpret_cast<const float4 *>(g + off[u]);
             }
 #pragma unroll
-            for (int u = 0; u < 8; u++)
-                if (i0 + u * 256 < KT * run) tile[dst[u]] = v[u];
+            for (int u = 0; u < 3; u++) {
+                if (i0 + u * 256 >= n) continue;
+                vv[u].x = mu * vv[u].x + gv[u].x; vv[u].y = mu * vv[u].y + gv[u].y; vv[u].z = mu * vv[u].z + gv[u].z; vv[u].w = mu * vv[u].w + gv[u].w;
+                wv[u].x -= lr * vv[u].x; wv[u].y -= lr * vv[u].y; wv[u].z -= lr * vv[u].z; wv[u].w -= lr * vv[u].w;
+                *reinterpret_cast<float4 *>(v + off[u]) = vv[u];
+                *reinterpret_cast<float4 *>(w + off[u]) = wv[u];
+                tile[lo[u]] = wv[u].x; tile[lo[u] + 1] = wv[u].y; tile[lo[u] + 2] = wv[u].z; tile[lo[u] + 3] = wv[u].w;
+            }
         }
-        __syncthreads();
-        for (int o = threadIdx.x; o < KT * run; o += 256) {
-            const int kk = o % KT, t2 = o / KT, tap = t2 % RS, cc = t2 / RS;        // tap: position in the flipped filter
-            Elem<T>::store(out + (size_t)(c0 + cc) * Kp + (size_t)tap * K + k0 + kk, tile[kk * pitch + cc * RS + (RS - 1 - tap)]);
+    } else {
+        for (int i = threadIdx.x; i < nk * run; i += 256) {
+            const int kk = i / run, j = i - kk * run;
+            const size_t o = base + kk * rowlen + j;
+            const float vel = mu * v[o] + g[o], nw = w[o] - lr * vel;
+            v[o] = vel;
+            w[o] = nw;
+            tile[kk * pitch + j] = nw;
         }
-        return;
     }
-    const long total = (long)(flip ? C : K) * Kp;
-    const long i0 = (long)blk * PACK_ELEMS_PER_BLOCK;
-#pragma unroll
-    for (int u = 0; u < PACK_ELEMS_PER_BLOCK / 256; u++) {
-        const long i = i0 + u * 256 + threadIdx.x;
-        if (i >= total) break;
-        const unsigned row = (unsigned)i / (unsigned)Kp, j = (unsigned)i % (unsigned)Kp;    // packed buffers hold < 2^31 elements
-        float v = 0.f;
-        if (!flip) {                               // out[k][(r*S+s)*C + c]
-            if (j < R * S * C) {
-                const int c = j % C, tap = j / C, s = tap % S, r = tap / S;
-                v = w[(((long)row * C + c) * R + r) * S + s];
-            }
-        } else {                                   // out[c][((R-1-r)*S + (S-1-s))*K + k]
-            if (j < R * S * K) {
-                const int k = j % K, tap = j / K, s = S - 1 - tap % S, r = R - 1 - tap / S;
-                v = w[(((long)k * C + row) * R + r) * S + s];
-            }
-        }
-        Elem<T>::store(out + i, v);
+    __syncthreads();
+    T *out = static_cast<T *>(b.out[seg]), *outT = static_cast<T *>(b.outT[seg]);
+    if (out) {
+        if (C % V == 0 && TC % V == 0) write_packed<T, V, true>(tile, pitch, out, nk, k0, nc, c0, C, RS, b.Kp[seg], pitch, RS, false);
+        else write_packed<T, V, false>(tile, pitch, out, nk, k0, nc, c0, C, RS, b.Kp[seg], pitch, RS, false);
+    }
+    if (outT) {
+        if (K % V == 0 && TK % V == 0) write_packed<T, V, true>(tile, pitch, outT, nc, c0, nk, k0, K, RS, b.KpT[seg], RS, pitch, true);
+        else write_packed<T, V, false>(tile, pitch, outT, nc, c0, nk, k0, K, RS, b.KpT[seg], RS, pitch, true);
     }
 }
 
-int pack_segment_blocks(int K, int C, int R, int S, int Kp, int flip, int *mode) {
-    const int RS = R * S;
-    if (!flip && (long)C * RS <= PACK_PLANE) { *mode = 1; return K; }
-    if (flip && C % 8 == 0 && K % 64 == 0 && (K % 128 == 0 ? 128 : 64) * (8 * RS + 1) <= PACK_PLANE + 128 && Kp == RS * K) {
-        *mode = 2;
-        return (C / 8) * (K / (K % 128 == 0 ? 128 : 64));
+bool update_segment_blocks(UpdateBatch &b, int i) {
+    int blocks;
+    if (!b.out[i]) {
+        b.TK[i] = b.TC[i] = 0;
+        blocks = ceil_div(b.C[i], UPD_ELEMS_PER_BLOCK);
+    } else {
+        const int RS = b.RS[i];
+        if (RS > UPD_PLANE) return false;
+        // rows of a tile are padded to an odd length: at most TK <= 64 floats on top of the plane
+        if (RS == 1) { b.TK[i] = 64; b.TC[i] = 64; }
+        else if (RS <= 9) { b.TK[i] = 32; b.TC[i] = 32; }
+        else if (RS <= UPD_PLANE / 32) { b.TK[i] = 32; b.TC[i] = std::min(b.C[i], UPD_PLANE / 32 / RS); }
+        else { b.TK[i] = UPD_PLANE / RS; b.TC[i] = 1; }
+        blocks = ceil_div(b.K[i], b.TK[i]) * ceil_div(b.C[i], b.TC[i]);
     }
-    *mode = 0;
-    const long total = (long)(flip ? C : K) * Kp;
-    return (int)((total + PACK_ELEMS_PER_BLOCK - 1) / PACK_ELEMS_PER_BLOCK);
+    b.first_block[i + 1] = b.first_block[i] + blocks;
+    return true;
 }
 
 // Weights for the data-gradient: framework layout w[k][c][r][s] -> packed rows [c][((R-1-r)*S + (S-1-s))*K + k],
@@ -1662,19 +1666,12 @@ sol_status launch_softmax_ce(const void *logits, const int32_t *labels, void *dl
     return SOL_OK;
 }
 
-sol_status launch_sgd_batch(const SgdBatch &b, float lr, float mu, hipStream_t st) {
-    if (b.nseg <= 0 || b.first_block[b.nseg] <= 0) return SOL_OK;
-    hipLaunchKernelGGL(sgd_batch_kernel, dim3(b.first_block[b.nseg]), dim3(256), 0, st, b, lr, mu);
-    SOL_HIP(hipGetLastError());
-    return SOL_OK;
-}
-
-sol_status launch_pack_batch(const PackBatch &b, int dt, hipStream_t st) {
+sol_status launch_update_batch(const UpdateBatch &b, int dt, float lr, float mu, hipStream_t st) {
     if (b.nseg <= 0 || b.first_block[b.nseg] <= 0) return SOL_OK;
     if (dt == SOL_BF16)
-        hipLaunchKernelGGL((pack_batch_kernel<bf16_t>), dim3(b.first_block[b.nseg]), dim3(256), 0, st, b);
+        hipLaunchKernelGGL((update_batch_kernel<bf16_t>), dim3(b.first_block[b.nseg]), dim3(256), 0, st, b, lr, mu);
     else
-        hipLaunchKernelGGL((pack_batch_kernel<float>), dim3(b.first_block[b.nseg]), dim3(256), 0, st, b);
+        hipLaunchKernelGGL((update_batch_kernel<float>), dim3(b.first_block[b.nseg]), dim3(256), 0, st, b, lr, mu);
     SOL_HIP(hipGetLastError());
     return SOL_OK;
 }
