@@ -354,6 +354,8 @@ sol_status launch_conv(const ConvArgs &a, int dt, int tile_override, hipStream_t
                     rowb / (int)dtype_size(dt));
         return launch_conv_dma(a, dt, tile_override, st);
     }
+    // fewer than 192 tiles of 128x128 and 32-channel chunks: the ring kernel's 64x64 tile, or the same sums on smaller ones
+    if (one_order && dt == SOL_F32 && tile_override == T_AUTO && choose_tile(a, 4) == D_64x64_128x3 && chain_kernel_applies(a)) return launch_conv_chain(a, st);
     if (dt == SOL_BF16) return launch_typed<bf16_t>(a, tile_override, st);
     if (dt == SOL_F32) return launch_typed<float>(a, tile_override, st);
     SOL_FAIL(SOL_ERR_DTYPE, "unknown dtype %d", dt);
