@@ -331,6 +331,16 @@ sol_status sol_network_set_layer_xr(sol_network *net, int layer, int fused);
 sol_status sol_network_layer_dense(const sol_network *net, int layer, int *state);
 sol_status sol_network_set_layer_dense(sol_network *net, int layer, int fused);
 
+/* Depthwise + pointwise pairs in one launch.  When a network keeps no activations (flags 0), bf16: a depthwise 3x3 convolution
+ * (pad 1, stride 1 or 2, no residual) of 32, 64, 128, 256 or 512 channels whose only reader is an unpadded 1x1 stride-1
+ * convolution of a multiple of 64 filters without pool or residual can run inside that convolution's launch; its output, rounded
+ * to bf16 as it would be stored, then stays in on-chip memory.  The plan decides by a rule on the sizes, sol_network_autotune by
+ * timing both ways; a tile for the 1x1 convolution runs the two one by one.  sol_network_layer_fused_into reports the 1x1
+ * convolution's index for the depthwise one while the two run as one.  *state = -1: `layer` is not the 1x1 convolution of such a
+ * pair; 0: two launches; 1: one.  sol_network_set_layer_dwpw restores / forces the choice (SOL_ERR_UNSUPPORTED if there is none). */
+sol_status sol_network_layer_dwpw(const sol_network *net, int layer, int *state);
+sol_status sol_network_set_layer_dwpw(sol_network *net, int layer, int fused);
+
 /* One forward pass recorded as a HIP graph (launch-bound inner loops: the about forty launches of a ResNet-50-shaped
  * pass replay as one submission).  sol_network_graph_create runs the pass once eagerly, then records the same
  * launches with the given pointers baked in: x, y, workspace, the bound parameter buffer and the network must
@@ -353,7 +363,9 @@ void sol_graph_destroy(sol_graph *graph);
  *     the two-launch result by at most one rounding of the shortcut term).
  *   - a 1x1 stride-1 convolution with an input-side BN + ReLU (pre_bn), 128 filters and ReLU whose only reader is a 3x3 stride-1
  *     pad-1 convolution of 32 filters without pool or residual (a dense layer) may run inside that convolution's launch, see
- *     sol_network_set_layer_dense.
+ *     sol_network_set_layer_dense;
+ *   - a depthwise 3x3 convolution whose only reader is a plain 1x1 convolution may run inside that convolution's launch, see
+ *     sol_network_set_layer_dwpw.
  * *into = index of the layer whose launch produces `layer`'s output: `layer` itself, the layer in front for such a
  * pool layer, the later convolution for such a shortcut or such a 1x1 convolution, the last convolution of a bottleneck that runs as one launch
  * (see sol_network_set_layer_block) for its first two, the first layer of an expand -> reduce pair (see

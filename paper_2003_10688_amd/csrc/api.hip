@@ -217,6 +217,8 @@ struct LayerPlan {
     bool use_xr;                    // on the former: the plan runs the two as one launch
     int dense_c1, dense_into;       // CONV (3x3 of a dense layer): the pre-activated 1x1 convolution that one launch can compute with it (-1: none); on that layer: the former
     bool use_dense;                 // on the former: the plan runs the two as one launch
+    int dw_c1, dw_into;             // CONV (1x1): the depthwise convolution in front that one launch can compute with it (-1: none); on that layer: the former
+    bool use_dw;                    // on the former: the plan runs the two as one launch
     bool pre_bn, pre_set;           // CONV: BN + ReLU on the input side; its folded constants have been set
     size_t pre_scale_off, pre_shift_off;
     int ldx;                        // CONV: input pixel pitch when the input is a channel prefix of a dense-block buffer (0: dense)
@@ -368,6 +370,11 @@ static bool dense_one_launch(const sol_network *net, const LayerPlan &c2) {
     const LayerPlan &c1 = net->layers[c2.dense_c1];
     return c1.tile == T_AUTO && c2.tile == T_AUTO && dense_one_launch_pays(c2.in.n, c2.in.h, c2.in.w, (int)round_up((size_t)c1.cd.cin, 64), (c1.cin_real ? c1.cin_real : c1.cd.cin) % 64 != 0);
 }
+// The plan's own choice for a depthwise + 1x1 pair whose 1x1 convolution is c2: see dwpw_pays
+static bool dw_one_launch(const sol_network *net, const LayerPlan &c2) {
+    const LayerPlan &c1 = net->layers[c2.dw_c1];
+    return c2.tile == T_AUTO && dwpw_pays(c1.in.n, c1.in.h, c1.in.w, c1.in.c, c1.cd.sh, c2.cd.cout);
+}
 // Does the 3x3 convolution c2 compute the 1x1 in front with it?  A tile forced on every layer runs them one by one.
 static bool dense_fused(const LayerPlan &c2) {
     return c2.dense_c1 >= 0 && ((c2.use_dense && !g_tile_override) || (g_tile_override >= B_FIRST && g_tile_override <= B_LAST));
@@ -408,7 +415,7 @@ static sol_status plan_network(sol_network *net, const sol_layer *layers, int n_
         lp.concat_into = -1;
         lp.pair = -1;
         lp.block_c1 = lp.block_c2 = lp.block_c3 = -1;
-        lp.xr_next = lp.xr_from = lp.dense_c1 = lp.dense_into = -1;
+        lp.xr_next = lp.xr_from = lp.dense_c1 = lp.dense_into = lp.dw_c1 = lp.dw_into = -1;
         lp.chain_owner = -1;
         lp.fused_into = i;
         lp.in = lp.src < 0 ? net->input : net->layers[lp.src].out;
@@ -675,6 +682,23 @@ static sol_status plan_network(sol_network *net, const sol_layer *layers, int n_
             if (c1.src >= 0) net->layers[c1.src].last_use = std::max(net->layers[c1.src].last_use, i);   // read by layer i now
         }
 
+    // Separable block (depth-first again): a depthwise 3x3 convolution whose only reader is a plain 1x1 convolution can run inside that
+    // convolution's launch, its output is then never stored (conv_dwpw.hip).  Both layers keep their buffers; a rule decides,
+    // sol_network_autotune measures.
+    if (!net->training && !net->keep && dt == SOL_BF16)
+        for (int i = 0; i < n_layers; i++) {
+            LayerPlan &c2 = net->layers[i];
+            if (c2.L.kind != SOL_LAYER_CONV || c2.L.pool.kind != SOL_POOL_NONE || c2.res >= 0 || c2.cin_real || c2.pre_bn || c2.ldx || c2.elided || c2.pair >= 0 ||
+                c2.absorbs_next || c2.src < 0 || c2.cd.kh != 1 || c2.cd.kw != 1 || c2.cd.ph || c2.cd.pw || c2.cd.sh != 1 || c2.cd.sw != 1) continue;
+            LayerPlan &c1 = net->layers[c2.src];
+            if (c1.L.kind != SOL_LAYER_DWCONV || c1.res >= 0 || c1.nuse != 1 || c1.cd.kh != 3 || c1.cd.kw != 3 || c1.cd.ph != 1 || c1.cd.pw != 1 || c1.cd.sh != c1.cd.sw) continue;
+            const int ldy = c2.concat_into >= 0 ? net->layers[c2.concat_into].out.c : c2.cd.cout;
+            if (!dwpw_kernel_applies(dt, c1.in.n, c1.in.h, c1.in.w, c1.in.c, c1.cd.sh, c2.cd.cout, ldy)) continue;
+            c2.dw_c1 = c2.src;
+            c1.dw_into = i;
+            c2.use_dw = dw_one_launch(net, c2);
+        }
+
     // Depth-first bottleneck (the paper's layer-chain fusion, Sec. III-A, across three contractions): 1x1 reduce + ReLU,
     // 3x3 stride 1 + ReLU, 1x1 expand + identity shortcut + ReLU, every intermediate read by the next layer only, can run
     // as one launch that never stores the two intermediates (conv_block.hip).  The three layers keep their buffers, so
@@ -725,36 +749,60 @@ static sol_status plan_network(sol_network *net, const sol_layer *layers, int n_
 
     // activation layout: inference reuses buffers once their last consumer has run, training keeps all
     Arena ar, apart;                 // apart: the 1x1 outputs of dense layers, behind everything else, for a pass that stores them
-    for (int i = 0; i < n_layers; i++) {
-        LayerPlan &lp = net->layers[i];
-        if (lp.dense_into >= 0) lp.out_off = apart.alloc(tensor_bytes(lp.out));
-        if (lp.dense_c1 >= 0) apart.release(net->layers[lp.dense_c1].out_off);
-        if (lp.split_pool) lp.tmp_off = ar.alloc(tensor_bytes(lp.conv_out));
-        if (lp.chain_owner >= 0) {       // a join of a dense chain: a prefix of the chain's one buffer, laid out at the first touch
-            LayerPlan &ow = net->layers[lp.chain_owner];
-            if (!ow.prealloc) { ow.out_off = ar.alloc(tensor_bytes(ow.out)); ow.prealloc = true; }
-            lp.out_off = ow.out_off;
-        } else if (lp.absorbs_next) {   // writes the pool layer's output: that buffer has to exist while this layer runs
-            if (i + 2 < n_layers) net->layers[i + 1].out_off = ar.alloc(tensor_bytes(net->layers[i + 1].out));
-        } else if (lp.concat_into >= 0) {   // ... and so does the concatenation's, from its first in-place producer on
-            LayerPlan &cc = net->layers[lp.concat_into];
-            if (!cc.prealloc && lp.concat_into + 1 < n_layers) { cc.out_off = ar.alloc(tensor_bytes(cc.out)); cc.prealloc = true; }
-        } else if (!lp.elided && !lp.no_buffer && !lp.prealloc && (i + 1 < n_layers || net->training)) {
-            lp.out_off = ar.alloc(tensor_bytes(lp.out));
+    auto lay_out = [&]() {
+        ar = Arena(); apart = Arena();
+        std::vector<int> last(n_layers);
+        for (int i = 0; i < n_layers; i++) { last[i] = net->layers[i].last_use; net->layers[i].prealloc = false; }
+        for (int i = 0; i < n_layers; i++) {         // the input of a depthwise + 1x1 pair may be read when the 1x1 convolution runs
+            if (net->layers[i].dw_c1 < 0) continue;
+            const int in = net->layers[net->layers[i].dw_c1].src;
+            if (in < 0) continue;
+            const int owner = net->layers[in].chain_owner >= 0 ? net->layers[in].chain_owner : in;
+            last[in] = std::max(last[in], i);
+            last[owner] = std::max(last[owner], i);
         }
-        if (lp.xr_next >= 0 && lp.xr_next + 1 < n_layers) {   // this launch may also write the next layer's output: that buffer exists from here on
-            LayerPlan &nx = net->layers[lp.xr_next];
-            nx.out_off = ar.alloc(tensor_bytes(nx.out));
-            nx.prealloc = true;
-        }
-        if (lp.split_pool && !net->keep) ar.release(lp.tmp_off);
-        if (!net->keep)
-            for (int j = 0; j < i; j++) {
-                const LayerPlan &lj = net->layers[j];
-                if (lj.last_use == i && j + 1 < n_layers && !lj.absorbs_next && lj.concat_into < 0 && !lj.no_buffer &&
-                    !(lj.chain_owner >= 0 && lj.chain_owner != j))
-                    ar.release(lj.out_off);
+        for (int i = 0; i < n_layers; i++) {
+            LayerPlan &lp = net->layers[i];
+            if (lp.dense_into >= 0) lp.out_off = apart.alloc(tensor_bytes(lp.out));
+            if (lp.dense_c1 >= 0) apart.release(net->layers[lp.dense_c1].out_off);
+            if (lp.split_pool) lp.tmp_off = ar.alloc(tensor_bytes(lp.conv_out));
+            if (lp.chain_owner >= 0) {       // a join of a dense chain: a prefix of the chain's one buffer, laid out at the first touch
+                LayerPlan &ow = net->layers[lp.chain_owner];
+                if (!ow.prealloc) { ow.out_off = ar.alloc(tensor_bytes(ow.out)); ow.prealloc = true; }
+                lp.out_off = ow.out_off;
+            } else if (lp.absorbs_next) {   // writes the pool layer's output: that buffer has to exist while this layer runs
+                if (i + 2 < n_layers) net->layers[i + 1].out_off = ar.alloc(tensor_bytes(net->layers[i + 1].out));
+            } else if (lp.concat_into >= 0) {   // ... and so does the concatenation's, from its first in-place producer on
+                LayerPlan &cc = net->layers[lp.concat_into];
+                if (!cc.prealloc && lp.concat_into + 1 < n_layers) { cc.out_off = ar.alloc(tensor_bytes(cc.out)); cc.prealloc = true; }
+            } else if (!lp.elided && !lp.no_buffer && !lp.prealloc && (i + 1 < n_layers || net->training)) {
+                lp.out_off = ar.alloc(tensor_bytes(lp.out));
             }
+            if (lp.xr_next >= 0 && lp.xr_next + 1 < n_layers) {   // this launch may also write the next layer's output: that buffer exists from here on
+                LayerPlan &nx = net->layers[lp.xr_next];
+                nx.out_off = ar.alloc(tensor_bytes(nx.out));
+                nx.prealloc = true;
+            }
+            if (lp.split_pool && !net->keep) ar.release(lp.tmp_off);
+            if (!net->keep)
+                for (int j = 0; j < i; j++) {
+                    const LayerPlan &lj = net->layers[j];
+                    if (last[j] == i && j + 1 < n_layers && !lj.absorbs_next && lj.concat_into < 0 && !lj.no_buffer &&
+                        !(lj.chain_owner >= 0 && lj.chain_owner != j))
+                        ar.release(lj.out_off);
+                }
+        }
+    };
+    lay_out();
+    // A pair keeps its input alive for one layer more.  Where that alone would take the network out of the static workspace, it runs
+    // as two launches.
+    bool pairs = false;
+    for (const auto &lp : net->layers) pairs = pairs || lp.dw_c1 >= 0;
+    if (pairs && ar.top > (size_t)SOL_STATIC_WORKSPACE_BYTES) {
+        const std::vector<LayerPlan> with = net->layers;
+        for (auto &lp : net->layers) { lp.dw_c1 = lp.dw_into = -1; lp.use_dw = false; }
+        lay_out();
+        if (ar.top > (size_t)SOL_STATIC_WORKSPACE_BYTES) { net->layers = with; lay_out(); }
     }
     if (net->training) SOL_TRY(plan_training(net, ar));
     net->ws_bytes = ar.top;
@@ -1256,6 +1304,7 @@ static sol_status run_layers(sol_network *net, const void *x, void *y, void *wor
         if (lp.block_c3 >= 0 && net->layers[lp.block_c3].use_block && !g_tile_override) continue;   // ... by the bottleneck launch behind it
         if (lp.xr_from >= 0 && net->layers[lp.xr_from].use_xr && !g_tile_override) continue;        // ... by the expand-reduce launch in front of it
         if (lp.dense_into >= 0 && dense_fused(net->layers[lp.dense_into])) continue;                // ... by the 3x3 convolution behind it
+        if (lp.dw_into >= 0 && net->layers[lp.dw_into].use_dw && !g_tile_override) continue;        // ... by the 1x1 convolution behind it
         const void *in = layer_in(net, lp.src, x, ws);
         const int oi = lp.absorbs_next ? i + 1 : lp.concat_into >= 0 ? lp.concat_into : lp.chain_owner >= 0 ? lp.chain_owner : i;   // the layer whose buffer this launch writes
         void *out = oi + 1 == nl ? y : static_cast<void *>(ws + net->layers[oi].out_off);
@@ -1307,6 +1356,15 @@ static sol_status run_layers(sol_network *net, const void *x, void *y, void *wor
                                          fp(c1.pre_scale_off), fp(c1.pre_shift_off), net->params + c1.w_off, packed_k(c1.cd, lp.in.dtype), fp(c1.scale_off),
                                          fp(c1.shift_off), net->params + lp.w_off, scale, shift, conv_dst, ldy ? ldy : lp.cd.cout, lp.L.act, lp.in.n, lp.in.h, lp.in.w};
                     SOL_TRY(launch_conv_dense(dl, g_tile_override >= B_FIRST && g_tile_override <= B_LAST ? g_tile_override - B_FIRST : -1, st));
+                    break;
+                }
+                if (lp.dw_c1 >= 0 && lp.use_dw && !g_tile_override) {     // this launch also computes the depthwise convolution in front
+                    const LayerPlan &c1 = net->layers[lp.dw_c1];
+                    const auto fp = [&](size_t off) { return reinterpret_cast<const float *>(net->params + off); };
+                    const DwPwLaunch dl{layer_in(net, c1.src, x, ws), net->params + c1.w_off, fp(c1.scale_off), fp(c1.shift_off), c1.L.act,
+                                        net->params + lp.w_off, scale, shift, lp.L.act, conv_dst, ldy ? ldy : lp.cd.cout,
+                                        c1.in.n, c1.in.h, c1.in.w, c1.in.c, c1.cd.sh, lp.cd.cout};
+                    SOL_TRY(launch_conv_dwpw(dl, st));
                     break;
                 }
                 if (lp.pre_bn || lp.ldx) {   // BN + ReLU on the input side and / or a channel prefix of a dense-block buffer
@@ -1487,7 +1545,7 @@ sol_status sol_network_autotune(sol_network *net, const void *x, void *y, void *
     const int nl = (int)net->layers.size();
     // every layer is tuned on its own first; a workspace without the buffers between them leaves dense layers in one launch
     const bool apart = workspace_bytes >= net->ws_apart;
-    for (auto &lp : net->layers) { lp.tile = T_AUTO; lp.use_block = false; lp.use_xr = false; lp.use_dense = lp.dense_c1 >= 0 && !apart; }
+    for (auto &lp : net->layers) { lp.tile = T_AUTO; lp.use_block = false; lp.use_xr = false; lp.use_dw = false; lp.use_dense = lp.dense_c1 >= 0 && !apart; }
     // one whole pass: validates the arguments and leaves finite activations of the right shape in every buffer
     SOL_TRY(run_layers(net, x, y, workspace, workspace_bytes, 0, nl - 1, st));
     hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -1614,11 +1672,36 @@ sol_status sol_network_autotune(sol_network *net, const void *x, void *y, void *
         }
         lp.use_xr = t[1] < t[0];
     }
+    // depthwise + 1x1 pairs: one launch against the depthwise and the tuned 1x1 launch, behind the producer of the pair's input
+    for (int i = 0; i < nl && rs == SOL_OK; i++) {
+        LayerPlan &lp = net->layers[i];
+        if (lp.dw_c1 < 0 || lp.in.n == 0) continue;
+        const int prod = net->layers[lp.dw_c1].src;
+        float t[2] = {0.f, 0.f};
+        for (int fused = 0; fused < 2 && rs == SOL_OK; fused++) {
+            lp.use_dw = fused != 0;
+            for (int r = 0; r < reps + 1 && rs == SOL_OK; r++) {
+                if (prod >= 0) rs = run_layers(net, x, y, workspace, workspace_bytes, prod, prod, st);
+                if (rs != SOL_OK) break;
+                SOL_HIP(hipEventRecord(e0, st));
+                for (int j : {lp.dw_c1, i})
+                    if (rs == SOL_OK) rs = run_layers(net, x, y, workspace, workspace_bytes, j, j, st);
+                SOL_HIP(hipEventRecord(e1, st));
+                SOL_HIP(hipEventSynchronize(e1));
+                float ms = 0.f;
+                SOL_HIP(hipEventElapsedTime(&ms, e0, e1));
+                if (r > 0) t[fused] += ms;
+            }
+        }
+        lp.use_dw = t[1] < t[0];
+        if (lp.use_dw) lp.tile = T_AUTO;                       // a tile asks for two launches
+    }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (rs != SOL_OK) {
         for (auto &lp : net->layers) lp.tile = T_AUTO;
         for (auto &lp : net->layers) lp.use_dense = lp.dense_c1 >= 0 && dense_one_launch(net, lp);
+        for (auto &lp : net->layers) lp.use_dw = lp.dw_c1 >= 0 && dw_one_launch(net, lp);
     }
     return rs;
 }
@@ -1657,6 +1740,23 @@ sol_status sol_network_set_layer_dense(sol_network *net, int layer, int fused) {
     return SOL_OK;
 }
 
+sol_status sol_network_layer_dwpw(const sol_network *net, int layer, int *state) {
+    SOL_REQUIRE(net && state, SOL_ERR_NULL, "net and state must not be NULL");
+    SOL_REQUIRE(layer >= 0 && layer < (int)net->layers.size(), SOL_ERR_SHAPE, "no layer %d", layer);
+    const LayerPlan &lp = net->layers[layer];
+    *state = lp.dw_c1 < 0 ? -1 : (lp.use_dw ? 1 : 0);
+    return SOL_OK;
+}
+
+sol_status sol_network_set_layer_dwpw(sol_network *net, int layer, int fused) {
+    SOL_REQUIRE(net, SOL_ERR_NULL, "net is NULL");
+    SOL_REQUIRE(layer >= 0 && layer < (int)net->layers.size(), SOL_ERR_SHAPE, "no layer %d", layer);
+    LayerPlan &lp = net->layers[layer];
+    SOL_REQUIRE(lp.dw_c1 >= 0 || !fused, SOL_ERR_UNSUPPORTED, "layer %d is not the 1x1 convolution of a depthwise pair the depth-first kernel can run", layer);
+    lp.use_dw = fused != 0;
+    return SOL_OK;
+}
+
 sol_status sol_network_layer_block(const sol_network *net, int layer, int *state) {
     SOL_REQUIRE(net && state, SOL_ERR_NULL, "net and state must not be NULL");
     SOL_REQUIRE(layer >= 0 && layer < (int)net->layers.size(), SOL_ERR_SHAPE, "no layer %d", layer);
@@ -1684,6 +1784,7 @@ sol_status sol_network_set_layer_tile(sol_network *net, int layer, int tile) {
         LayerPlan &c2 = lp.dense_c1 >= 0 ? lp : net->layers[lp.dense_into];
         c2.use_dense = dense_one_launch(net, c2);
     }
+    if (lp.dw_c1 >= 0) lp.use_dw = dw_one_launch(net, lp);      // likewise the 1x1 convolution of a depthwise pair
     return SOL_OK;
 }
 
@@ -1745,6 +1846,7 @@ sol_status sol_network_layer_fused_into(const sol_network *net, int layer, int *
     *into = (lp.block_c3 >= 0 && net->layers[lp.block_c3].use_block) ? lp.block_c3
             : (lp.xr_from >= 0 && net->layers[lp.xr_from].use_xr)        ? lp.xr_from
             : (lp.dense_into >= 0 && net->layers[lp.dense_into].use_dense) ? lp.dense_into
+            : (lp.dw_into >= 0 && net->layers[lp.dw_into].use_dw)        ? lp.dw_into
                                                                          : lp.fused_into;
     return SOL_OK;
 }

@@ -205,6 +205,16 @@ struct DenseLaunch {
 bool dense_kernel_applies(int dt, int N, int H, int W, int C, int ldx, int mid, int cout, int ldy);
 bool dense_one_launch_pays(int N, int H, int W, int C, bool masked);   // masked: the real channels end inside a chunk of 64
 sol_status launch_conv_dense(const DenseLaunch &d, int variant, hipStream_t st);
+// a depthwise 3x3 convolution (pad 1, stride S) and the 1x1 convolution behind it in one kernel (conv_dwpw.hip)
+struct DwPwLaunch {
+    const void *x, *wd; const float *sd, *hd; int act_d;   // input [N][H][W][C], packed depthwise weights [9][C], their folded scale / shift
+    const void *w; const float *s, *h; int act;            // packed 1x1 weights [K][C rounded up to 64], folded scale / shift
+    void *y; int ldy;
+    int N, H, W, C, S, K;
+};
+bool dwpw_kernel_applies(int dt, int N, int H, int W, int C, int S, int K, int ldy);
+bool dwpw_pays(int N, int H, int W, int C, int S, int K);
+sol_status launch_conv_dwpw(const DwPwLaunch &d, hipStream_t st);
 bool linear_kernel_applies(const ConvArgs &a, int dt);
 sol_status launch_linear(const ConvArgs &a, int dt, hipStream_t st);
 bool linear_stream_applies(const ConvArgs &a, int dt);   // up to 128 rows, weights streamed (linear.hip)

@@ -394,6 +394,9 @@ class Network:
             b = self.dense_state(i)
             if b >= 0:
                 out[f"{i}d"] = b          # dense layer whose 3x3 convolution is layer i: 1 = one launch, 0 = two
+            b = self.dwpw_state(i)
+            if b >= 0:
+                out[f"{i}p"] = b          # depthwise + 1x1 pair whose 1x1 convolution is layer i: 1 = one launch, 0 = two
         return out
 
     def set_tiles(self, tiles):
@@ -406,6 +409,8 @@ class Network:
                 self.set_xr(i, tiles[f"{i}x"])
             if f"{i}d" in tiles:
                 self.set_dense(i, tiles[f"{i}d"])
+            if f"{i}p" in tiles:
+                self.set_dwpw(i, tiles[f"{i}p"])
 
     def graph(self, x, stream):
         """Records one forward pass on `stream` (a torch.cuda.Stream other than the default one) as a HIP graph;
@@ -450,6 +455,16 @@ class Network:
     def set_dense(self, layer, fused):
         """Runs convolution `layer` and the pre-activated 1x1 convolution in front as one depth-first launch (fused) or one by one."""
         _check(lib().sol_network_set_layer_dense(self._h, C.c_int(layer), C.c_int(int(bool(fused)))))
+
+    def dwpw_state(self, layer):
+        """-1: `layer` is not the 1x1 convolution of a depthwise pair the depth-first kernel can run; 0: two launches; 1: one."""
+        t = C.c_int(0)
+        _check(lib().sol_network_layer_dwpw(self._h, C.c_int(layer), C.byref(t)))
+        return t.value
+
+    def set_dwpw(self, layer, fused):
+        """Runs 1x1 convolution `layer` and the depthwise convolution in front as one depth-first launch (fused) or one by one."""
+        _check(lib().sol_network_set_layer_dwpw(self._h, C.c_int(layer), C.c_int(int(bool(fused)))))
 
     def fused_into(self, layer):
         """Index of the layer whose launch produces `layer`'s output (itself unless the plan fused it into

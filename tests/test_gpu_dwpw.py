@@ -1,0 +1,99 @@
+"""The depth-first depthwise + pointwise kernel (3x3 depthwise of stride 1 or 2, then 1x1, one launch) in each of its channel counts,
+against the CPU checker, and the plan's handling of such pairs."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as orc
+from paper_2003_10688_amd import workloads as wl
+from test_gpu_parity import TOL, rel_err, sol  # noqa: F401  (sol: the module fixture)
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # N, H, W, K, activations (depthwise, 1x1)
+    (1, 1, 1, 64, ("relu", "relu")),          # one pixel: every tap but one in the padding
+    (3, 8, 8, 128, ("relu", "none")),         # whole 8-column tiles (stride 1)
+    (2, 17, 15, 192, ("none", "relu")),       # remainders of rows and columns, of a pass of 128 channels
+    (1, 33, 9, 320, ("relu", "relu")),        # several tiles of 16 rows, a last pass that is half empty
+    (2, 2, 31, 64, ("none", "none")),
+]
+
+
+def build(sol, layers, x, prm):  # noqa: F811
+    net = sol.Network(layers, x.shape, sol.BF16)
+    net.set_params(prm)
+    net.workspace.fill_(0xff)                    # NaNs: nothing that was not written may be looked at
+    return net, sol.to_device_nhwc(x, sol.BF16)
+
+
+@pytest.mark.parametrize("stride", [1, 2])
+@pytest.mark.parametrize("c", [32, 64, 128, 256, 512])
+@pytest.mark.parametrize("case", CASES)
+def test_pair(sol, case, c, stride):  # noqa: F811
+    N, H, W, K, (a1, a2) = case
+    layers = [wl.conv(c, 1, p=0), wl.conv(c, 3, s=stride, dw=True, act=a1), wl.conv(K, 1, p=0, act=a2), wl.conv(8, 1, p=0, bn=False, act="none")]
+    rng = np.random.default_rng([N, H, W, c, stride])
+    x = wl.to_bf16_grid(rng.standard_normal((N, 32, H, W)))
+    prm = wl.make_params(layers, 32, 5 + c, bf16=True, bias_std=0.3)
+    outs, _ = orc.network_forward(layers, prm, x, bf16=True, return_all=True)
+    net, xd = build(sol, layers, x, prm)
+    net.set_dwpw(2, True)
+    assert net.dwpw_state(2) == 1 and net.fused_into(1) == 2 and net.dwpw_state(3) == -1
+    net.forward(xd)
+    torch.cuda.synchronize()
+    # one rounding (t) lies between the pair's input and its output, both sides make it at the same place
+    got = sol.to_host_nchw(net.layer_output(2))
+    assert rel_err(got.reshape(outs[2].shape), outs[2]) <= TOL["bf16"]
+    assert rel_err(sol.to_host_nchw(net.y).reshape(outs[3].shape), outs[3]) <= TOL["bf16"]
+    net.set_tiles({2: 99})                       # a tile for the 1x1 convolution: two launches
+    assert net.dwpw_state(2) == 0 and net.fused_into(1) == 1
+    net.forward(xd)
+    torch.cuda.synchronize()
+    assert rel_err(got, sol.to_host_nchw(net.layer_output(2))) <= TOL["bf16"]
+
+
+def test_pair_into_concatenation(sol):  # noqa: F811
+    """The 1x1 convolution writes its channels into a joined tensor (output pitch above its channel count)."""
+    layers = [wl.conv(64, 1, p=0), wl.conv(64, 3, dw=True), wl.conv(64, 1, p=0), wl.conv(72, 1, p=0, src=0), wl.concat(3, 2), wl.conv(8, 1, p=0, bn=False, act="none")]
+    rng = np.random.default_rng(3)
+    x = wl.to_bf16_grid(rng.standard_normal((2, 32, 11, 10)))
+    prm = wl.make_params(layers, 32, 9, bf16=True, bias_std=0.3)
+    outs, _ = orc.network_forward(layers, prm, x, bf16=True, return_all=True)
+    net, xd = build(sol, layers, x, prm)
+    net.set_dwpw(2, True)
+    net.forward(xd)
+    torch.cuda.synchronize()
+    assert net.concat_in_place(4) == 2
+    assert rel_err(sol.to_host_nchw(net.layer_output(4)), outs[4]) <= TOL["bf16"]
+
+
+def test_infinity_stays_where_it_belongs(sol):  # noqa: F811
+    """An infinity in one input pixel reaches the 3x3 outputs around it and no others (padding channels and tile rows included)."""
+    layers = [wl.conv(32, 3, dw=True, bn=False, act="none"), wl.conv(64, 1, p=0, bn=False, act="none"), wl.conv(64, 1, p=0, bn=False, act="none")]
+    prm = wl.make_params(layers, 32, 1, bf16=True)
+    prm[0]["w"][:] = 1.0
+    prm[1]["w"][:] = np.abs(prm[1]["w"]) + 0.125
+    x = np.ones((1, 32, 9, 11), dtype=np.float32)
+    x[0, 5, 4, 6] = np.inf
+    net, xd = build(sol, layers, x, prm)
+    net.set_dwpw(1, True)
+    net.forward(xd)
+    torch.cuda.synchronize()
+    got = sol.to_host_nchw(net.layer_output(1))[0]
+    want = np.zeros((9, 11), dtype=bool)
+    want[3:6, 5:8] = True
+    assert (np.isposinf(got) == want[None]).all() and np.isfinite(got[:, ~want]).all()
+
+
+def test_pairs_do_not_cost_the_static_workspace(sol):  # noqa: F811
+    """A list that fits the static workspace layer by layer keeps fitting; one that does not fit either way runs in pairs."""
+    layers = [wl.conv(64, 1, p=0, bn=False), wl.conv(64, 3, s=2, dw=True, bn=False), wl.conv(128, 1, p=0, bn=False), wl.conv(8, 1, p=0, bn=False)]
+    limit = 32 << 20
+    def mb(n):   # input of the pair, its middle, its output
+        return [n * 64 * 64 * 64 * 2, n * 32 * 32 * 64 * 2, n * 32 * 32 * 128 * 2]
+    n = next(n for n in range(1, 200) if sum(mb(n)) > limit and sum(mb(n)[:2]) <= limit and sum(mb(n)[1:]) <= limit)
+    net = sol.Network(layers, (n, 32, 64, 64), sol.BF16)
+    assert net.workspace.numel() <= limit and net.dwpw_state(2) == -1
+    assert sol.Network(layers, (4 * n, 32, 64, 64), sol.BF16).dwpw_state(2) >= 0
+    assert sol.Network(layers, (1, 32, 64, 64), sol.BF16).dwpw_state(2) >= 0
