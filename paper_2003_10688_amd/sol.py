@@ -79,6 +79,12 @@ def lib():
         L.sol_debug_probe_copy.argtypes = [C.c_void_p, C.c_void_p, C.c_size_t, C.c_void_p]
         L.sol_debug_probe_mfma.argtypes = [C.c_int, C.c_int, C.c_void_p, C.POINTER(C.c_double), C.c_void_p]
         L.sol_network_forward_static.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p]
+        # the calls that a program repeats: with their argument types known, plain integers are marshalled without wrapper objects
+        vp, sz, i = C.c_void_p, C.c_size_t, C.c_int
+        L.sol_conv2d_fused.argtypes = [C.POINTER(TensorDesc), vp, C.POINTER(ConvDesc), vp, vp, vp, vp, i, C.POINTER(PoolDesc), vp, vp, vp, vp]
+        L.sol_network_forward.argtypes = [vp, vp, vp, vp, sz, vp]
+        L.sol_network_backward.argtypes = [vp, vp, vp, vp, vp, sz, vp]
+        L.sol_network_sgd_step.argtypes = [vp, C.c_float, C.c_float, vp]
         _lib = L
     return _lib
 
@@ -88,18 +94,29 @@ def _check(status):
         raise SolError(status, lib().sol_last_error().decode())
 
 
-def _ptr(t):
+def _addr(t):
     if t is None:
-        return C.c_void_p(0)
+        return 0
     if isinstance(t, torch.Tensor):
         assert t.is_cuda and t.is_contiguous(), "device tensors must be contiguous GPU tensors"
-        return C.c_void_p(t.data_ptr())
-    return C.c_void_p(int(t))
+        return t.data_ptr()
+    return int(t)
+
+
+def _ptr(t):
+    return C.c_void_p(_addr(t))
+
+
+def _stream_handle(stream=None):
+    if stream is not None:
+        return stream.cuda_stream
+    if torch.cuda.is_initialized():      # the current device's current stream, without the object around it
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return torch.cuda.current_stream().cuda_stream
 
 
 def _stream(stream=None):
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return C.c_void_p(s.cuda_stream)
+    return C.c_void_p(_stream_handle(stream))
 
 
 def torch_dtype(dt):
@@ -148,6 +165,15 @@ def sol_out_size(n, k, s, p):
     return lib().sol_out_size(C.c_int(n), C.c_int(k), C.c_int(s), C.c_int(p))
 
 
+def _conv_out(h, w, d):
+    """Output extent of a window description (kh, kw, sh, sw, ph, pw) on an h x w image, as sol_out_size gives it: quotients towards zero."""
+    kh, kw, sh, sw, ph, pw = d.kh, d.kw, d.sh, d.sw, d.ph, d.pw
+    if sh <= 0 or sw <= 0:           # refused by the library, with its own message
+        return 0, 0
+    a, b = h + 2 * ph - kh, w + 2 * pw - kw
+    return (a // sh if a >= 0 else -(-a // sh)) + 1, (b // sw if b >= 0 else -(-b // sw)) + 1
+
+
 def sol_packed_weight_bytes(cd, dt):
     return lib().sol_packed_weight_bytes(C.byref(cd), C.c_int(dt))
 
@@ -176,19 +202,18 @@ def sol_fold_bn(c, gamma, beta, mean, var, bias, eps, device="cuda:0", stream=No
 def sol_conv2d_fused(x, cd, w_packed, scale=None, shift=None, residual=None, act=ACT_NONE, pool=None,
                      want_argmax=False, want_prepool=False, stream=None):
     """x: NHWC device tensor.  Returns (y, argmax or None, prepool or None)."""
-    n, h, w, _ = x.shape
-    ho, wo = sol_out_size(h, cd.kh, cd.sh, cd.ph), sol_out_size(w, cd.kw, cd.sw, cd.pw)
+    n, h, w, c = x.shape
+    ho, wo = _conv_out(h, w, cd)
     hy, wy = ho, wo
     pd = pool if isinstance(pool, PoolDesc) or pool is None else pool_desc(pool)
     if pd is not None and pd.kind != POOL_NONE:
-        hy, wy = sol_out_size(ho, pd.kh, pd.sh, pd.ph), sol_out_size(wo, pd.kw, pd.sw, pd.pw)
-    y = torch.empty((n, max(hy, 0), max(wy, 0), cd.cout), dtype=x.dtype, device=x.device)
+        hy, wy = _conv_out(ho, wo, pd)
+    cout = cd.cout
+    y = torch.empty((n, max(hy, 0), max(wy, 0), cout), dtype=x.dtype, device=x.device)
     arg = torch.empty(y.shape, dtype=torch.int32, device=x.device) if want_argmax else None
-    pre = torch.empty((n, max(ho, 0), max(wo, 0), cd.cout), dtype=x.dtype, device=x.device) if want_prepool else None
-    xd = tensor_desc(x)
-    _check(lib().sol_conv2d_fused(C.byref(xd), _ptr(x), C.byref(cd), _ptr(w_packed), _ptr(scale), _ptr(shift),
-                                  _ptr(residual), C.c_int(act), C.byref(pd) if pd is not None else None,
-                                  _ptr(y), _ptr(arg), _ptr(pre), _stream(stream)))
+    pre = torch.empty((n, max(ho, 0), max(wo, 0), cout), dtype=x.dtype, device=x.device) if want_prepool else None
+    _check(lib().sol_conv2d_fused(TensorDesc(n, h, w, c, dtype_of(x)), _addr(x), cd, _addr(w_packed), _addr(scale), _addr(shift),
+                                  _addr(residual), act, pd, _addr(y), _addr(arg), _addr(pre), _stream_handle(stream)))
     return y, arg, pre
 
 
@@ -366,8 +391,7 @@ class Network:
 
     def forward(self, x, stream=None):
         """x: NHWC device tensor; returns the (reused) output tensor of the last layer."""
-        _check(lib().sol_network_forward(self._h, _ptr(x), _ptr(self.y), _ptr(self.workspace),
-                                         C.c_size_t(self.workspace.numel()), _stream(stream)))
+        _check(lib().sol_network_forward(self._h, _addr(x), _addr(self.y), _addr(self.workspace), self.workspace.numel(), _stream_handle(stream)))
         return self.y
 
     def forward_static(self, x, stream=None):
@@ -499,12 +523,12 @@ class Network:
         Returns the device scalar holding the mean cross-entropy."""
         if not hasattr(self, "loss"):
             self.loss = torch.zeros(4, dtype=torch.float32, device=self.device)
-        _check(lib().sol_network_backward(self._h, _ptr(x), _ptr(labels), _ptr(self.loss), _ptr(self.workspace),
-                                          C.c_size_t(self.workspace.numel()), _stream(stream)))
+        _check(lib().sol_network_backward(self._h, _addr(x), _addr(labels), _addr(self.loss), _addr(self.workspace), self.workspace.numel(),
+                                          _stream_handle(stream)))
         return self.loss[:1]
 
     def sgd_step(self, lr, momentum, stream=None):
-        _check(lib().sol_network_sgd_step(self._h, C.c_float(lr), C.c_float(momentum), _stream(stream)))
+        _check(lib().sol_network_sgd_step(self._h, lr, momentum, _stream_handle(stream)))
 
     def tensor(self, layer, which):
         """fp32 view (inside the parameter buffer) of a layer's master parameter, gradient or batch statistic."""
