@@ -165,6 +165,8 @@ sol_status launch_conv_direct_pair(const ConvArgs &a, int tile, const void *x2, 
                                    int H2, int W2, int K2, int Kp2, int stride, hipStream_t st);
 bool chain_kernel_applies(const ConvArgs &a);            // fp32, the sums of D_64x64_128x3 on smaller tiles (conv_chain.hip)
 sol_status launch_conv_chain(const ConvArgs &a, hipStream_t st);
+bool small_kernel_applies(const ConvArgs &a, int dt);    // three input channels on the vector units (conv_small.hip)
+sol_status launch_conv_small(const ConvArgs &a, int dt, hipStream_t st);
 bool halo_kernel_applies(const ConvArgs &a, int dt);
 int halo_choose_tile(const ConvArgs &a);
 sol_status launch_conv_halo(const ConvArgs &a, int tile, hipStream_t st);

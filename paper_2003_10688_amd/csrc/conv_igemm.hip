@@ -313,6 +313,7 @@ sol_status launch_conv(const ConvArgs &a, int dt, int tile_override, hipStream_t
     if (a.P <= 0) return SOL_OK;   // empty batch: nothing to do
     if (a.pre_scale || a.ldx != a.C || a.Cvalid != a.C) return launch_conv_staged(a, dt, tile_override, st);
     if (tile_override == T_AUTO && stem_kernel_applies(a, dt)) return launch_conv_stem(a, st);
+    if (tile_override == T_AUTO && !one_order && small_kernel_applies(a, dt)) return launch_conv_small(a, dt, st);
     if (tile_override == T_AUTO && !one_order && linear_stream_applies(a, dt)) return launch_linear_stream(a, dt, st);
     if (tile_override == T_AUTO && linear_kernel_applies(a, dt)) {
         // not one for linear_stream_applies, and a weight matrix of many megabytes: the job is streaming the weights, which the
