@@ -341,6 +341,16 @@ sol_status sol_network_set_layer_dense(sol_network *net, int layer, int fused);
 sol_status sol_network_layer_dwpw(const sol_network *net, int layer, int *state);
 sol_status sol_network_set_layer_dwpw(sol_network *net, int layer, int fused);
 
+/* Fire modules in one launch.  When a network keeps no activations (flags 0), bf16: a 1x1 stride-1 convolution (squeeze, stored with 32
+ * channels, padding included, over a multiple of 64) whose only readers are an unpadded 1x1 and a 3x3 pad-1 convolution of
+ * stride 1, multiples of 64 filters each, that are joined by one concatenation, can run with both inside the launch of the 3x3; its
+ * output, rounded to bf16 as it would be stored, then stays in on-chip memory.  The plan decides by a rule on the sizes,
+ * sol_network_autotune by timing both ways; a tile for any of the three runs them one by one.  sol_network_layer_fused_into reports
+ * the 3x3 convolution's index for the other two while they run as one.  *state = -1: `layer` is not the 3x3 expand of such a module; 0: layer
+ * by layer; 1: one launch.  sol_network_set_layer_fire restores / forces the choice (SOL_ERR_UNSUPPORTED if there is none). */
+sol_status sol_network_layer_fire(const sol_network *net, int layer, int *state);
+sol_status sol_network_set_layer_fire(sol_network *net, int layer, int fused);
+
 /* One forward pass recorded as a HIP graph (launch-bound inner loops: the about forty launches of a ResNet-50-shaped
  * pass replay as one submission).  sol_network_graph_create runs the pass once eagerly, then records the same
  * launches with the given pointers baked in: x, y, workspace, the bound parameter buffer and the network must
@@ -365,7 +375,8 @@ void sol_graph_destroy(sol_graph *graph);
  *     pad-1 convolution of 32 filters without pool or residual (a dense layer) may run inside that convolution's launch, see
  *     sol_network_set_layer_dense;
  *   - a depthwise 3x3 convolution whose only reader is a plain 1x1 convolution may run inside that convolution's launch, see
- *     sol_network_set_layer_dwpw.
+ *     sol_network_set_layer_dwpw;
+ *   - the squeeze and the 1x1 expand of a fire module may run inside the launch of its 3x3 expand, see sol_network_set_layer_fire.
  * *into = index of the layer whose launch produces `layer`'s output: `layer` itself, the layer in front for such a
  * pool layer, the later convolution for such a shortcut or such a 1x1 convolution, the last convolution of a bottleneck that runs as one launch
  * (see sol_network_set_layer_block) for its first two, the first layer of an expand -> reduce pair (see

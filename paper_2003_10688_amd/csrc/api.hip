@@ -219,6 +219,8 @@ struct LayerPlan {
     bool use_dense;                 // on the former: the plan runs the two as one launch
     int dw_c1, dw_into;             // CONV (1x1): the depthwise convolution in front that one launch can compute with it (-1: none); on that layer: the former
     bool use_dw;                    // on the former: the plan runs the two as one launch
+    int fire_s, fire_e1, fire_into; // CONV (3x3 expand of a fire module): its squeeze and its 1x1 expand, which one launch can compute with it (-1: none); on those two: the former
+    bool use_fire;                  // on the former: the plan runs the three as one launch
     bool pre_bn, pre_set;           // CONV: BN + ReLU on the input side; its folded constants have been set
     size_t pre_scale_off, pre_shift_off;
     int ldx;                        // CONV: input pixel pitch when the input is a channel prefix of a dense-block buffer (0: dense)
@@ -375,6 +377,11 @@ static bool dw_one_launch(const sol_network *net, const LayerPlan &c2) {
     const LayerPlan &c1 = net->layers[c2.dw_c1];
     return c2.tile == T_AUTO && dwpw_pays(c1.in.n, c1.in.h, c1.in.w, c1.in.c, c1.cd.sh, c2.cd.cout);
 }
+// The plan's own choice for a fire module whose 3x3 expand is c3: see fire_pays
+static bool fire_one_launch(const sol_network *net, const LayerPlan &c3) {
+    const LayerPlan &sq = net->layers[c3.fire_s], &e1 = net->layers[c3.fire_e1];
+    return c3.tile == T_AUTO && sq.tile == T_AUTO && e1.tile == T_AUTO && fire_pays(sq.in.n, sq.in.h, sq.in.w, sq.in.c);
+}
 // Does the 3x3 convolution c2 compute the 1x1 in front with it?  A tile forced on every layer runs them one by one.
 static bool dense_fused(const LayerPlan &c2) {
     return c2.dense_c1 >= 0 && ((c2.use_dense && !g_tile_override) || (g_tile_override >= B_FIRST && g_tile_override <= B_LAST));
@@ -415,7 +422,7 @@ static sol_status plan_network(sol_network *net, const sol_layer *layers, int n_
         lp.concat_into = -1;
         lp.pair = -1;
         lp.block_c1 = lp.block_c2 = lp.block_c3 = -1;
-        lp.xr_next = lp.xr_from = lp.dense_c1 = lp.dense_into = lp.dw_c1 = lp.dw_into = -1;
+        lp.xr_next = lp.xr_from = lp.dense_c1 = lp.dense_into = lp.dw_c1 = lp.dw_into = lp.fire_s = lp.fire_e1 = lp.fire_into = -1;
         lp.chain_owner = -1;
         lp.fused_into = i;
         lp.in = lp.src < 0 ? net->input : net->layers[lp.src].out;
@@ -699,6 +706,31 @@ static sol_status plan_network(sol_network *net, const sol_layer *layers, int n_
             c2.use_dw = dw_one_launch(net, c2);
         }
 
+    // Fire module (depth-first again): a 1x1 convolution whose only readers are a 1x1 and a 3x3 convolution of the same concatenation can
+    // run inside the latter's launch together with the former (conv_fire.hip).  All layers keep their buffers; a rule decides,
+    // sol_network_autotune measures.
+    if (!net->training && !net->keep && dt == SOL_BF16)
+        for (int i = 0; i < n_layers; i++) {
+            LayerPlan &c3 = net->layers[i];
+            const auto plain = [](const LayerPlan &l) {
+                return l.L.kind == SOL_LAYER_CONV && l.L.pool.kind == SOL_POOL_NONE && l.res < 0 && l.pair < 0 && !l.elided && !l.absorbs_next && !l.pre_bn && !l.ldx && l.cd.sh == 1 &&
+                       l.cd.sw == 1 && l.block_c3 < 0 && l.dw_c1 < 0;
+            };
+            const auto pointwise = [](const LayerPlan &l) { return l.cd.kh == 1 && l.cd.kw == 1 && l.cd.ph == 0 && l.cd.pw == 0; };
+            if (!plain(c3) || c3.cd.kh != 3 || c3.cd.kw != 3 || c3.cd.ph != 1 || c3.cd.pw != 1 || c3.concat_into < 0 || c3.cout_real || c3.src < 0) continue;
+            LayerPlan &sq = net->layers[c3.src];
+            if (!plain(sq) || !pointwise(sq) || sq.cin_real || sq.nuse != 2 || sq.concat_into >= 0 || sq.fire_into >= 0) continue;
+            int e1 = -1;
+            for (int j = 0; j < n_layers; j++)
+                if (j != i && net->layers[j].src == c3.src) e1 = j;
+            if (e1 < 0 || e1 > i || !plain(net->layers[e1]) || !pointwise(net->layers[e1]) || net->layers[e1].concat_into != c3.concat_into || net->layers[e1].cout_real) continue;
+            if (!fire_kernel_applies(dt, sq.in.n, sq.in.h, sq.in.w, sq.in.c, sq.cd.cout, net->layers[e1].cd.cout, c3.cd.cout, net->layers[c3.concat_into].out.c)) continue;
+            c3.fire_s = c3.src;
+            c3.fire_e1 = e1;
+            sq.fire_into = net->layers[e1].fire_into = i;
+            c3.use_fire = fire_one_launch(net, c3);
+        }
+
     // Depth-first bottleneck (the paper's layer-chain fusion, Sec. III-A, across three contractions): 1x1 reduce + ReLU,
     // 3x3 stride 1 + ReLU, 1x1 expand + identity shortcut + ReLU, every intermediate read by the next layer only, can run
     // as one launch that never stores the two intermediates (conv_block.hip).  The three layers keep their buffers, so
@@ -753,9 +785,10 @@ static sol_status plan_network(sol_network *net, const sol_layer *layers, int n_
         ar = Arena(); apart = Arena();
         std::vector<int> last(n_layers);
         for (int i = 0; i < n_layers; i++) { last[i] = net->layers[i].last_use; net->layers[i].prealloc = false; }
-        for (int i = 0; i < n_layers; i++) {         // the input of a depthwise + 1x1 pair may be read when the 1x1 convolution runs
-            if (net->layers[i].dw_c1 < 0) continue;
-            const int in = net->layers[net->layers[i].dw_c1].src;
+        for (int i = 0; i < n_layers; i++) {         // the input of a depthwise + 1x1 pair or of a fire module may be read when its last layer runs
+            const LayerPlan &lp = net->layers[i];
+            const int first = lp.dw_c1 >= 0 ? lp.dw_c1 : lp.fire_s;
+            const int in = first >= 0 ? net->layers[first].src : -1;
             if (in < 0) continue;
             const int owner = net->layers[in].chain_owner >= 0 ? net->layers[in].chain_owner : in;
             last[in] = std::max(last[in], i);
@@ -794,13 +827,13 @@ static sol_status plan_network(sol_network *net, const sol_layer *layers, int n_
         }
     };
     lay_out();
-    // A pair keeps its input alive for one layer more.  Where that alone would take the network out of the static workspace, it runs
-    // as two launches.
+    // A pair or a fire module keeps its input alive for a layer or two more.  Where that alone would take the network out of the static
+    // workspace, they run layer by layer.
     bool pairs = false;
-    for (const auto &lp : net->layers) pairs = pairs || lp.dw_c1 >= 0;
+    for (const auto &lp : net->layers) pairs = pairs || lp.dw_c1 >= 0 || lp.fire_s >= 0;
     if (pairs && ar.top > (size_t)SOL_STATIC_WORKSPACE_BYTES) {
         const std::vector<LayerPlan> with = net->layers;
-        for (auto &lp : net->layers) { lp.dw_c1 = lp.dw_into = -1; lp.use_dw = false; }
+        for (auto &lp : net->layers) { lp.dw_c1 = lp.dw_into = lp.fire_s = lp.fire_e1 = lp.fire_into = -1; lp.use_dw = lp.use_fire = false; }
         lay_out();
         if (ar.top > (size_t)SOL_STATIC_WORKSPACE_BYTES) { net->layers = with; lay_out(); }
     }
@@ -1305,6 +1338,7 @@ static sol_status run_layers(sol_network *net, const void *x, void *y, void *wor
         if (lp.xr_from >= 0 && net->layers[lp.xr_from].use_xr && !g_tile_override) continue;        // ... by the expand-reduce launch in front of it
         if (lp.dense_into >= 0 && dense_fused(net->layers[lp.dense_into])) continue;                // ... by the 3x3 convolution behind it
         if (lp.dw_into >= 0 && net->layers[lp.dw_into].use_dw && !g_tile_override) continue;        // ... by the 1x1 convolution behind it
+        if (lp.fire_into >= 0 && net->layers[lp.fire_into].use_fire && !g_tile_override) continue;  // ... by the 3x3 expand of the fire module
         const void *in = layer_in(net, lp.src, x, ws);
         const int oi = lp.absorbs_next ? i + 1 : lp.concat_into >= 0 ? lp.concat_into : lp.chain_owner >= 0 ? lp.chain_owner : i;   // the layer whose buffer this launch writes
         void *out = oi + 1 == nl ? y : static_cast<void *>(ws + net->layers[oi].out_off);
@@ -1356,6 +1390,16 @@ static sol_status run_layers(sol_network *net, const void *x, void *y, void *wor
                                          fp(c1.pre_scale_off), fp(c1.pre_shift_off), net->params + c1.w_off, packed_k(c1.cd, lp.in.dtype), fp(c1.scale_off),
                                          fp(c1.shift_off), net->params + lp.w_off, scale, shift, conv_dst, ldy ? ldy : lp.cd.cout, lp.L.act, lp.in.n, lp.in.h, lp.in.w};
                     SOL_TRY(launch_conv_dense(dl, g_tile_override >= B_FIRST && g_tile_override <= B_LAST ? g_tile_override - B_FIRST : -1, st));
+                    break;
+                }
+                if (lp.fire_s >= 0 && lp.use_fire && !g_tile_override) {  // a fire module: this launch also computes the squeeze and the 1x1 expand
+                    const LayerPlan &sq = net->layers[lp.fire_s], &e1 = net->layers[lp.fire_e1];
+                    const auto fp = [&](size_t off) { return reinterpret_cast<const float *>(net->params + off); };
+                    unsigned char *joined = static_cast<unsigned char *>(out) - (size_t)lp.concat_off * es;      // the concatenation's buffer
+                    const FireLaunch fl{layer_in(net, sq.src, x, ws), net->params + sq.w_off, fp(sq.scale_off), fp(sq.shift_off), sq.L.act,
+                                        net->params + e1.w_off, fp(e1.scale_off), fp(e1.shift_off), e1.L.act, net->params + lp.w_off, scale, shift, lp.L.act,
+                                        joined + (size_t)e1.concat_off * es, out, ldy, sq.in.n, sq.in.h, sq.in.w, sq.in.c, sq.cd.cout, e1.cd.cout, lp.cd.cout};
+                    SOL_TRY(launch_conv_fire(fl, st));
                     break;
                 }
                 if (lp.dw_c1 >= 0 && lp.use_dw && !g_tile_override) {     // this launch also computes the depthwise convolution in front
@@ -1545,7 +1589,7 @@ sol_status sol_network_autotune(sol_network *net, const void *x, void *y, void *
     const int nl = (int)net->layers.size();
     // every layer is tuned on its own first; a workspace without the buffers between them leaves dense layers in one launch
     const bool apart = workspace_bytes >= net->ws_apart;
-    for (auto &lp : net->layers) { lp.tile = T_AUTO; lp.use_block = false; lp.use_xr = false; lp.use_dw = false; lp.use_dense = lp.dense_c1 >= 0 && !apart; }
+    for (auto &lp : net->layers) { lp.tile = T_AUTO; lp.use_block = false; lp.use_xr = false; lp.use_dw = false; lp.use_fire = false; lp.use_dense = lp.dense_c1 >= 0 && !apart; }
     // one whole pass: validates the arguments and leaves finite activations of the right shape in every buffer
     SOL_TRY(run_layers(net, x, y, workspace, workspace_bytes, 0, nl - 1, st));
     hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -1672,20 +1716,22 @@ sol_status sol_network_autotune(sol_network *net, const void *x, void *y, void *
         }
         lp.use_xr = t[1] < t[0];
     }
-    // depthwise + 1x1 pairs: one launch against the depthwise and the tuned 1x1 launch, behind the producer of the pair's input
+    // depthwise + 1x1 pairs and fire modules: one launch against the tuned layers one by one, behind the producer of their input
     for (int i = 0; i < nl && rs == SOL_OK; i++) {
         LayerPlan &lp = net->layers[i];
-        if (lp.dw_c1 < 0 || lp.in.n == 0) continue;
-        const int prod = net->layers[lp.dw_c1].src;
+        if ((lp.dw_c1 < 0 && lp.fire_s < 0) || lp.in.n == 0) continue;
+        const bool dw = lp.dw_c1 >= 0;
+        const int first = dw ? lp.dw_c1 : lp.fire_s, prod = net->layers[first].src;
+        bool &use = dw ? lp.use_dw : lp.use_fire;
         float t[2] = {0.f, 0.f};
         for (int fused = 0; fused < 2 && rs == SOL_OK; fused++) {
-            lp.use_dw = fused != 0;
+            use = fused != 0;
             for (int r = 0; r < reps + 1 && rs == SOL_OK; r++) {
                 if (prod >= 0) rs = run_layers(net, x, y, workspace, workspace_bytes, prod, prod, st);
                 if (rs != SOL_OK) break;
                 SOL_HIP(hipEventRecord(e0, st));
-                for (int j : {lp.dw_c1, i})
-                    if (rs == SOL_OK) rs = run_layers(net, x, y, workspace, workspace_bytes, j, j, st);
+                for (int j : {first, dw ? -1 : lp.fire_e1, i})
+                    if (rs == SOL_OK && j >= 0) rs = run_layers(net, x, y, workspace, workspace_bytes, j, j, st);
                 SOL_HIP(hipEventRecord(e1, st));
                 SOL_HIP(hipEventSynchronize(e1));
                 float ms = 0.f;
@@ -1693,8 +1739,9 @@ sol_status sol_network_autotune(sol_network *net, const void *x, void *y, void *
                 if (r > 0) t[fused] += ms;
             }
         }
-        lp.use_dw = t[1] < t[0];
-        if (lp.use_dw) lp.tile = T_AUTO;                       // a tile asks for two launches
+        use = t[1] < t[0];
+        if (use) lp.tile = T_AUTO;                              // a tile asks for the layers one by one
+        if (use && !dw) net->layers[first].tile = net->layers[lp.fire_e1].tile = T_AUTO;
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
@@ -1702,6 +1749,7 @@ sol_status sol_network_autotune(sol_network *net, const void *x, void *y, void *
         for (auto &lp : net->layers) lp.tile = T_AUTO;
         for (auto &lp : net->layers) lp.use_dense = lp.dense_c1 >= 0 && dense_one_launch(net, lp);
         for (auto &lp : net->layers) lp.use_dw = lp.dw_c1 >= 0 && dw_one_launch(net, lp);
+        for (auto &lp : net->layers) lp.use_fire = lp.fire_s >= 0 && fire_one_launch(net, lp);
     }
     return rs;
 }
@@ -1757,6 +1805,23 @@ sol_status sol_network_set_layer_dwpw(sol_network *net, int layer, int fused) {
     return SOL_OK;
 }
 
+sol_status sol_network_layer_fire(const sol_network *net, int layer, int *state) {
+    SOL_REQUIRE(net && state, SOL_ERR_NULL, "net and state must not be NULL");
+    SOL_REQUIRE(layer >= 0 && layer < (int)net->layers.size(), SOL_ERR_SHAPE, "no layer %d", layer);
+    const LayerPlan &lp = net->layers[layer];
+    *state = lp.fire_s < 0 ? -1 : (lp.use_fire ? 1 : 0);
+    return SOL_OK;
+}
+
+sol_status sol_network_set_layer_fire(sol_network *net, int layer, int fused) {
+    SOL_REQUIRE(net, SOL_ERR_NULL, "net is NULL");
+    SOL_REQUIRE(layer >= 0 && layer < (int)net->layers.size(), SOL_ERR_SHAPE, "no layer %d", layer);
+    LayerPlan &lp = net->layers[layer];
+    SOL_REQUIRE(lp.fire_s >= 0 || !fused, SOL_ERR_UNSUPPORTED, "layer %d is not the 3x3 expand of a fire module the depth-first kernel can run", layer);
+    lp.use_fire = fused != 0;
+    return SOL_OK;
+}
+
 sol_status sol_network_layer_block(const sol_network *net, int layer, int *state) {
     SOL_REQUIRE(net && state, SOL_ERR_NULL, "net and state must not be NULL");
     SOL_REQUIRE(layer >= 0 && layer < (int)net->layers.size(), SOL_ERR_SHAPE, "no layer %d", layer);
@@ -1785,6 +1850,10 @@ sol_status sol_network_set_layer_tile(sol_network *net, int layer, int tile) {
         c2.use_dense = dense_one_launch(net, c2);
     }
     if (lp.dw_c1 >= 0) lp.use_dw = dw_one_launch(net, lp);      // likewise the 1x1 convolution of a depthwise pair
+    if (lp.fire_s >= 0 || lp.fire_into >= 0) {                  // ... and each convolution of a fire module
+        LayerPlan &c3 = lp.fire_s >= 0 ? lp : net->layers[lp.fire_into];
+        c3.use_fire = fire_one_launch(net, c3);
+    }
     return SOL_OK;
 }
 
@@ -1847,6 +1916,7 @@ sol_status sol_network_layer_fused_into(const sol_network *net, int layer, int *
             : (lp.xr_from >= 0 && net->layers[lp.xr_from].use_xr)        ? lp.xr_from
             : (lp.dense_into >= 0 && net->layers[lp.dense_into].use_dense) ? lp.dense_into
             : (lp.dw_into >= 0 && net->layers[lp.dw_into].use_dw)        ? lp.dw_into
+            : (lp.fire_into >= 0 && net->layers[lp.fire_into].use_fire)  ? lp.fire_into
                                                                          : lp.fused_into;
     return SOL_OK;
 }

@@ -217,6 +217,17 @@ struct DwPwLaunch {
 bool dwpw_kernel_applies(int dt, int N, int H, int W, int C, int S, int K, int ldy);
 bool dwpw_pays(int N, int H, int W, int C, int S, int K);
 sol_status launch_conv_dwpw(const DwPwLaunch &d, hipStream_t st);
+// a fire module -- 1x1 squeeze, 1x1 and 3x3 expand of it side by side -- in one kernel (conv_fire.hip)
+struct FireLaunch {
+    const void *x, *ws; const float *ss, *hs; int act_s;   // input [N][H][W][C], packed squeeze weights [SP][C], folded scale / shift
+    const void *w1; const float *s1, *h1; int act1;        // packed 1x1 expand weights [E1][64]
+    const void *w3; const float *s3, *h3; int act3;        // packed 3x3 expand weights [E3][9 * SP rounded up to 64]
+    void *y1, *y3; int ldy;                                // where each expand's first channel goes; output pixel pitch
+    int N, H, W, C, SP, E1, E3;
+};
+bool fire_kernel_applies(int dt, int N, int H, int W, int C, int SP, int E1, int E3, int ldy);
+bool fire_pays(int N, int H, int W, int C);
+sol_status launch_conv_fire(const FireLaunch &f, hipStream_t st);
 bool linear_kernel_applies(const ConvArgs &a, int dt);
 sol_status launch_linear(const ConvArgs &a, int dt, hipStream_t st);
 bool linear_stream_applies(const ConvArgs &a, int dt);   // up to 128 rows, weights streamed (linear.hip)

@@ -259,6 +259,9 @@ static int choose_tile(const ConvArgs &a, int esize) {
     if (a.Cout <= 32 || !dma64) return a.C % (128 / esize) == 0 ? (a.Cout <= 32 ? T_128x32 : T_128x64)
                                                                  : (a.Cout <= 32 ? T_128x32 : T_128x64);
     const bool wide = a.R * a.S > 1;
+    // chunks of 64 bytes, one channel tile: twice the pixels per weight row once there are four rounds of them (64 images of 55x55, us,
+    // 64 pixels / 128: 3x3 32 -> 64 22.8 / 17.6, 1x1 32 -> 64 11.2 / 8.9)
+    if (a.Cout <= 64 && !dma128 && esize == 2 && a.P >= 128 * 1024) return D_128x64_64x4;
     if (a.Cout <= 64) return (wide && dma128) ? D_64x64_128x3 : D_64x64_64x4;
     const long nt = (long)ceil_div(a.P, 128) * ceil_div(a.Cout, 128);
     if (nt >= 1024) return a.res ? D_64x64_64x4 : D_128x64_64x4;   // HBM-bound: many small workgroups in flight

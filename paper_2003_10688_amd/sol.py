@@ -421,6 +421,9 @@ class Network:
             b = self.dwpw_state(i)
             if b >= 0:
                 out[f"{i}p"] = b          # depthwise + 1x1 pair whose 1x1 convolution is layer i: 1 = one launch, 0 = two
+            b = self.fire_state(i)
+            if b >= 0:
+                out[f"{i}f"] = b          # fire module whose 3x3 expand is layer i: 1 = one launch, 0 = layer by layer
         return out
 
     def set_tiles(self, tiles):
@@ -435,6 +438,8 @@ class Network:
                 self.set_dense(i, tiles[f"{i}d"])
             if f"{i}p" in tiles:
                 self.set_dwpw(i, tiles[f"{i}p"])
+            if f"{i}f" in tiles:
+                self.set_fire(i, tiles[f"{i}f"])
 
     def graph(self, x, stream):
         """Records one forward pass on `stream` (a torch.cuda.Stream other than the default one) as a HIP graph;
@@ -489,6 +494,16 @@ class Network:
     def set_dwpw(self, layer, fused):
         """Runs 1x1 convolution `layer` and the depthwise convolution in front as one depth-first launch (fused) or one by one."""
         _check(lib().sol_network_set_layer_dwpw(self._h, C.c_int(layer), C.c_int(int(bool(fused)))))
+
+    def fire_state(self, layer):
+        """-1: `layer` is not the 3x3 expand of a fire module the depth-first kernel can run; 0: layer by layer; 1: one launch."""
+        t = C.c_int(0)
+        _check(lib().sol_network_layer_fire(self._h, C.c_int(layer), C.byref(t)))
+        return t.value
+
+    def set_fire(self, layer, fused):
+        """Runs the fire module whose 3x3 expand is `layer` as one depth-first launch (fused) or layer by layer."""
+        _check(lib().sol_network_set_layer_fire(self._h, C.c_int(layer), C.c_int(int(bool(fused)))))
 
     def fused_into(self, layer):
         """Index of the layer whose launch produces `layer`'s output (itself unless the plan fused it into
