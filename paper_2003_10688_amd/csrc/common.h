@@ -167,6 +167,8 @@ bool chain_kernel_applies(const ConvArgs &a);            // fp32, the sums of D_
 sol_status launch_conv_chain(const ConvArgs &a, hipStream_t st);
 bool small_kernel_applies(const ConvArgs &a, int dt);    // three input channels on the vector units (conv_small.hip)
 sol_status launch_conv_small(const ConvArgs &a, int dt, hipStream_t st);
+bool pre_kernel_applies(const ConvArgs &a, int dt);      // 1x1 with BN + ReLU on the input side over whole 64-channel chunks (conv_pre.hip)
+sol_status launch_conv_pre(const ConvArgs &a, hipStream_t st);
 bool halo_kernel_applies(const ConvArgs &a, int dt);
 int halo_choose_tile(const ConvArgs &a);
 sol_status launch_conv_halo(const ConvArgs &a, int tile, hipStream_t st);

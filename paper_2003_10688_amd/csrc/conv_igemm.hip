@@ -296,6 +296,7 @@ template <typename T> static sol_status launch_typed(const ConvArgs &a, int tile
 // Input-side BN + ReLU, a strided input (channel prefix of a wider tensor) or masked padding channels: the
 // register-staged kernel is the one that can transform what it fetches on its way to LDS.
 static sol_status launch_conv_staged(const ConvArgs &a, int dt, int tile, hipStream_t st) {
+    if (tile == T_AUTO && pre_kernel_applies(a, dt)) return launch_conv_pre(a, st);
     if (!(tile >= T_256x128 && tile <= T_64x128)) {
         SOL_REQUIRE(tile == T_AUTO || tile == T_NO_HALO, SOL_ERR_UNSUPPORTED,
                     "conv tile %d cannot apply an input-side BN + ReLU or read a channel prefix; the register-staged tiles 1..8 can", tile);
