@@ -293,8 +293,9 @@ template <typename T> static sol_status launch_typed(const ConvArgs &a, int tile
     }
 }
 
-// Input-side BN + ReLU, a strided input (channel prefix of a wider tensor) or masked padding channels: the
-// register-staged kernel is the one that can transform what it fetches on its way to LDS.
+// Input-side BN + ReLU, a strided input (channel prefix of a wider tensor) or masked padding channels: what is fetched has to pass
+// through registers before it is multiplied.  A pre-activated 1x1 convolution of whole chunks takes its fragments from memory
+// directly (conv_pre); everything else, and a tile asked for, the register-staged kernel, which transforms on the way to LDS.
 static sol_status launch_conv_staged(const ConvArgs &a, int dt, int tile, hipStream_t st) {
     if (tile == T_AUTO && pre_kernel_applies(a, dt)) return launch_conv_pre(a, st);
     if (!(tile >= T_256x128 && tile <= T_64x128)) {

@@ -510,6 +510,59 @@ __global__ void __launch_bounds__(256) pool_bwd_kernel(const PoolArgs a, const T
     }
 }
 
+// The same for a 3x3 stride-2 pad-1 max pool, by 2 x 2 input pixels (rows 2 i, 2 i + 1, columns 2 j, 2 j + 1): only the windows
+// (i .. i + 1) x (j .. j + 1) hold them, four gradients and winners read for four pixels, where a thread per pixel reads nine
+// (1 + 2 + 2 + 4) and issues sixteen.  Bound by those reads from L2 before, by its 90 MB of memory now (4.2 TB/s); the windows of a
+// pixel are added in the same order.  32 images of 112x112, 64 channels, bf16: 36 -> 21.6 us.
+template <typename T, int V>
+__global__ void __launch_bounds__(256) pool3x3s2_bwd_kernel(const PoolArgs a, const T *__restrict__ dy, T *dx, int first, uint32_t total,
+                                                            FastDiv dcg, FastDiv dw, FastDiv dh) {
+    for (uint32_t i = blockIdx.x * 256u + threadIdx.x; i < total; i += gridDim.x * 256u) {
+        uint32_t rest, g, qj, n, qi;
+        dcg.divmod(i, rest, g);
+        dw.divmod(rest, rest, qj);
+        dh.divmod(rest, n, qi);
+        float d[4][V];
+        int win[4][V];
+        bool on[4];
+#pragma unroll
+        for (int u = 0; u < 4; u++) {                      // unconditional loads from clamped addresses, masked afterwards
+            const int p = (int)qi + (u >> 1), q = (int)qj + (u & 1);
+            on[u] = p < a.Ho && q < a.Wo;
+            const long o = (((long)n * a.Ho + min(p, a.Ho - 1)) * a.Wo + min(q, a.Wo - 1)) * a.C + (long)g * V;
+            VecIO<T, V>::load(dy + o, d[u]);
+#pragma unroll
+            for (int e = 0; e < V; e += 4) {
+                const int4 w4 = *reinterpret_cast<const int4 *>(a.argmax + o + e);
+                win[u][e] = w4.x; win[u][e + 1] = w4.y; win[u][e + 2] = w4.z; win[u][e + 3] = w4.w;
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < 4; s++) {
+            const int ih = 2 * (int)qi + (s >> 1), iw = 2 * (int)qj + (s & 1);
+            if (ih >= a.H || iw >= a.W) continue;
+            float sum[V];
+#pragma unroll
+            for (int e = 0; e < V; e++) sum[e] = 0.f;
+#pragma unroll
+            for (int u = 0; u < 4; u++) {                  // row-major window order
+                if ((u >> 1) > (s >> 1) || (u & 1) > (s & 1)) continue;
+#pragma unroll
+                for (int e = 0; e < V; e++)
+                    if (on[u] && win[u][e] == ih * a.W + iw) sum[e] += d[u][e];
+            }
+            const long o = (((long)n * a.H + ih) * a.W + iw) * a.C + (long)g * V;
+            if (!first) {
+                float old[V];
+                VecIO<T, V>::load(dx + o, old);
+#pragma unroll
+                for (int e = 0; e < V; e++) sum[e] += old[e];
+            }
+            VecIO<T, V>::store(dx + o, sum);
+        }
+    }
+}
+
 // dx[n][p][c] (+)= dy[n][c] / HW
 template <typename T, int V>
 __global__ void __launch_bounds__(256) gap_bwd_kernel(const T *__restrict__ dy, T *dx, int N, int HW, int C, int first) {
@@ -1653,8 +1706,21 @@ sol_status launch_dilate(const void *dz, void *out, int N, int Ho, int Wo, int K
 
 sol_status launch_pool_bwd(const PoolArgs &a, const void *dy, void *dx, int first, int dt, hipStream_t st) {
     const long total = (long)a.N * a.H * a.W * a.C;
-    SOL_DISPATCH_TV(dt, a.C, hipLaunchKernelGGL((pool_bwd_kernel<T, V>), dim3(grid_for(total / V)), dim3(256), 0, st, a,
-                                                static_cast<const T *>(dy), static_cast<T *>(dx), first));
+    SOL_DISPATCH_TV(dt, a.C, {
+        if constexpr (V % 4 == 0) {
+            const long quads = (long)a.N * ((a.H + 1) / 2) * ((a.W + 1) / 2) * (a.C / V);
+            if (a.kind == SOL_POOL_MAX && a.kh == 3 && a.kw == 3 && a.sh == 2 && a.sw == 2 && a.ph == 1 && a.pw == 1 &&
+                quads < (1L << 31)) {
+                hipLaunchKernelGGL((pool3x3s2_bwd_kernel<T, V>), dim3(grid_for(quads)), dim3(256), 0, st, a, static_cast<const T *>(dy),
+                                   static_cast<T *>(dx), first, (uint32_t)quads, FastDiv((uint32_t)(a.C / V)),
+                                   FastDiv((uint32_t)((a.W + 1) / 2)), FastDiv((uint32_t)((a.H + 1) / 2)));
+                SOL_HIP(hipGetLastError());
+                return SOL_OK;
+            }
+        }
+        hipLaunchKernelGGL((pool_bwd_kernel<T, V>), dim3(grid_for(total / V)), dim3(256), 0, st, a, static_cast<const T *>(dy),
+                           static_cast<T *>(dx), first);
+    });
     SOL_HIP(hipGetLastError());
     return SOL_OK;
 }

@@ -168,6 +168,25 @@ def test_train_step_bf16(sol, name):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("ch,n,h,w", [(8, 3, 1, 1), (8, 2, 2, 5), (16, 5, 9, 6), (24, 2, 15, 14), (64, 1, 8, 3)])
+def test_max_pool_3x3_stride_2_backward(sol, dtype, ch, n, h, w):
+    """`pool3x3s2_bwd_kernel`, which works by 2 x 2 input pixels: odd and even extents, a single pixel, one and several channel groups;
+    as the second contribution to its input's gradient (the strided convolution's is written before it) and as the only one."""
+    bf = dtype == "bf16"
+    layers = [wl.conv(ch, 3, act="none"), wl.pool("max", 3, 2, 1), wl.conv(ch, 3, s=2, src=0, res=1), wl.pool("max", 3, 2, 1),
+              wl.gap(), wl.linear(5)]
+    params = wl.make_params(layers, 3, ch + h, bf, bias_std=0.2)
+    for l, prm in zip(layers, params):
+        if l["kind"] == "conv" and l["bn"]:
+            prm["bias"] = np.zeros_like(prm["bias"])
+    x = wl.make_input((n, 3, h, w), ch + w, "normal", bf)
+    labels = wl.make_labels(n, 5, ch)
+    _, got = gpu_train(sol, layers, params, x, labels, dtype)
+    ref = oracle_train(layers, params, x, labels, dtype)
+    compare(got[0], ref[0], layers, dtype, elementwise=not bf, tag=f"pool/{dtype}")
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_train_step_after_autotune(sol, dtype):
     """The plan-time auto-tune of a training network (one tile for each forward and each data-gradient convolution)
     changes kernels, not results: the step that follows it meets the same bounds as an untuned one."""
