@@ -1,5 +1,5 @@
 """The depth-first depthwise + pointwise kernel (3x3 depthwise of stride 1 or 2, then 1x1, one launch) in each of its channel counts,
-against the CPU checker, and the plan's handling of such pairs."""
+against the CPU oracle, and the plan's handling of such pairs."""
 import numpy as np
 import pytest
 import torch

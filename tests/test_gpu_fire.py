@@ -1,4 +1,4 @@
-"""The depth-first fire-module kernel (1x1 squeeze, 1x1 and 3x3 expand, joined; one launch) against the CPU checker, and the plan's
+"""The depth-first fire-module kernel (1x1 squeeze, 1x1 and 3x3 expand, joined; one launch) against the CPU oracle, and the plan's
 handling of such modules."""
 import numpy as np
 import pytest

@@ -1,4 +1,4 @@
-"""1x1 convolutions with BN + ReLU on the input side over whole 64-channel chunks (`conv_pre_kernel`) against the CPU checker."""
+"""1x1 convolutions with BN + ReLU on the input side over whole 64-channel chunks (`conv_pre_kernel`) against the CPU oracle."""
 import numpy as np
 import pytest
 import torch

@@ -1,4 +1,4 @@
-"""Convolutions of three input channels on the vector units (`conv_small_kernel`) against the CPU checker."""
+"""Convolutions of three input channels on the vector units (`conv_small_kernel`) against the CPU oracle."""
 import numpy as np
 import pytest
 import torch
