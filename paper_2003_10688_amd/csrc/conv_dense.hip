@@ -412,8 +412,10 @@ int choose_variant(int P, int W, int C, int variant, int *rounds) {
 }  // namespace
 
 // A patch recomputes 2 W + 2 rows of the 1x1 convolution for its pixels, so wide images lose by one launch what it saves.  Two
-// launches -> one, us, launches and events included, 64 images unless stated: W = 56, C = 64: 65 -> 45; 84, 512: 262 -> 251; 96, 64:
-// 180 -> 167; 96, 512: 338 -> 344; 112, 512: 457 -> 511; 128, 64: 348 -> 430; 160, 64: 497 -> 1267.  A prefix that ends inside
+// launches (the 1x1 convolution on conv_pre) -> one, us, launches and events included, 64 images: W = 56, C = 64: 66 -> 46; 88, 256:
+// 216 -> 200; 88, 512: 278 -> 273; 104, 64: 224 -> 200; 104, 128: 256 -> 236; 104, 256: 291 -> 307; 104, 512: 378 -> 418; 112, 128: 299 -> 298;
+// 112, 256: 333 -> 374; 112, 512: 433 -> 517.  The line is where the narrow prefixes, which images so wide have, cross; for wide ones it is
+// up to 11 % late between 88 and 104, which the auto-tuner finds.  A prefix that ends inside
 // a chunk of 64 channels costs the 1x1 convolution on its own about three times as much, and the line lies further out:
 // 148, 96: 927 -> 921; 152, 96: 976 -> 1072; 144, 224: 1362 -> 1041; 160, 224: 1665 -> 1934; 16 images, 144, 992: 1151 -> 564; 176, 224: 530 -> 1138.  One round of
 // workgroups is about as fast as two launches at any width (one image, 144, 64: 31 -> 25; 84, 64: 20 -> 22; only strips such as
