@@ -723,7 +723,12 @@ static sol_status plan_network(sol_network *net, const sol_layer *layers, int n_
             int e1 = -1;
             for (int j = 0; j < n_layers; j++)
                 if (j != i && net->layers[j].src == c3.src) e1 = j;
-            if (e1 < 0 || e1 > i || !plain(net->layers[e1]) || !pointwise(net->layers[e1]) || net->layers[e1].concat_into != c3.concat_into || net->layers[e1].cout_real) continue;
+            // One concatenation has to join the two: in a dense chain the parts of different joins are written into the same buffer, and
+            // what reads the earlier join runs before the 3x3 expand, in whose launch the 1x1 expand would only then be computed.
+            bool joined = false;
+            for (const LayerPlan &l : net->layers)
+                joined = joined || (l.L.kind == SOL_LAYER_CONCAT && ((l.src == e1 && l.res == i) || (l.src == i && l.res == e1)));
+            if (e1 < 0 || e1 > i || !joined || !plain(net->layers[e1]) || !pointwise(net->layers[e1]) || net->layers[e1].concat_into < 0 || net->layers[e1].cout_real) continue;
             if (!fire_kernel_applies(dt, sq.in.n, sq.in.h, sq.in.w, sq.in.c, sq.cd.cout, net->layers[e1].cd.cout, c3.cd.cout, net->layers[c3.concat_into].out.c)) continue;
             c3.fire_s = c3.src;
             c3.fire_e1 = e1;

@@ -365,6 +365,24 @@ def test_dense_layer_tile_runs_two_launches(sol):
     L.sol_network_destroy(h)
 
 
+@pytest.mark.parametrize("first", [0, 1])
+def test_fire_module_of_one_join_only(sol, first):
+    """Expands that different joins of one dense chain take are no module: the layer that reads the earlier join (here layer 4) runs
+    between them.  The same expands under one join of a chain are one."""
+    L, c, cat, v = sol.lib(), wl.conv, wl.concat, C.c_int()
+    head = [c(64, 1, p=0), c(32, 1, p=0, src=0), c(64, 1, p=0, src=1)]
+    join = cat(0, 2) if first == 0 else cat(2, 0)
+    apart = head + [join, c(64, 1, p=0, src=3), c(64, 3, src=1), cat(3, 5), c(64, 1, p=0, src=6, res=4), c(8, 1, p=0)]
+    one = head + [c(64, 3, src=1), cat(2, 3), c(64, 1, p=0, src=4), cat(4, 5), c(8, 1, p=0)]
+    for layers, expand, state in ((apart, 5, -1), (one, 3, 1)):
+        st, h = _create(sol, layers, (1, 64, 8, 8), sol.BF16)
+        assert st == 0
+        assert L.sol_network_layer_fire(h, expand, C.byref(v)) == 0 and v.value == state
+        for i in (1, 2):
+            assert L.sol_network_layer_fused_into(h, i, C.byref(v)) == 0 and v.value == (expand if state == 1 else i)
+        L.sol_network_destroy(h)
+
+
 def test_layer_output_only_of_stored_layers(sol):
     """A layer without a tensor of its own in the workspace has no address (it used to be another layer's)."""
     L, c = sol.lib(), wl.conv

@@ -74,7 +74,7 @@ def test_infinity_stays_where_it_belongs(sol):  # noqa: F811
 
 
 def test_other_readers_keep_the_layers_apart(sol):  # noqa: F811
-    """A squeeze that a third layer reads, expands of different joins, kept activations: no module."""
+    """A squeeze that a third layer reads, kept activations, fp32, a squeeze of 64 channels: no module."""
     base = module(64, 32, 64, 64)
     assert sol.Network(base, (1, 32, 8, 8), sol.BF16).fire_state(3) >= 0
     assert sol.Network(base, (1, 32, 8, 8), sol.BF16, flags=sol.NET_KEEP_ACTIVATIONS).fire_state(3) == -1
@@ -82,3 +82,22 @@ def test_other_readers_keep_the_layers_apart(sol):  # noqa: F811
     third = base[:5] + [wl.conv(64, 1, p=0, src=1), wl.concat(4, 5), wl.conv(8, 1, p=0, bn=False, act="none")]
     assert sol.Network(third, (1, 32, 8, 8), sol.BF16).fire_state(3) == -1
     assert sol.Network(module(64, 64, 64, 64), (1, 32, 8, 8), sol.BF16).fire_state(3) == -1
+
+
+def test_expands_of_different_joins(sol):  # noqa: F811
+    """Expands of two joins of one dense chain: layer 4 reads the earlier join, with the 1x1 expand in it, before the 3x3 expand runs."""
+    c = wl.conv
+    layers = [c(64, 1, p=0), c(32, 1, p=0, src=0), c(64, 1, p=0, src=1), wl.concat(0, 2), c(64, 1, p=0, src=3), c(64, 3, src=1), wl.concat(3, 5),
+              c(64, 1, p=0, src=6, res=4), c(8, 1, p=0, bn=False, act="none")]
+    rng = np.random.default_rng(8)
+    x = wl.to_bf16_grid(rng.standard_normal((2, 64, 8, 9)))
+    prm = wl.make_params(layers, 64, 6, bf16=True, bias_std=0.3)
+    outs, _ = orc.network_forward(layers, prm, x, bf16=True, return_all=True)
+    net = sol.Network(layers, x.shape, sol.BF16)
+    net.set_params(prm)
+    net.workspace.fill_(0xff)                    # NaNs: nothing that was not written may be looked at
+    assert net.fire_state(5) == -1
+    net.forward(sol.to_device_nhwc(x, sol.BF16))
+    torch.cuda.synchronize()
+    assert rel_err(sol.to_host_nchw(net.layer_output(7)), outs[7]) <= TOL["bf16"]
+    assert rel_err(sol.to_host_nchw(net.y).reshape(outs[8].shape), outs[8]) <= TOL["bf16"]
