@@ -9,7 +9,7 @@
 // the tile straight from global memory -- every load of a thread's window is in flight at once -- and parks it in LDS as bf16,
 // the rounding point of the stored tensor; phase 2 takes it into registers as MFMA fragments and contracts it with W, whose rows
 // come through an LDS ring that fills by DMA while phase 1 runs, in passes of WC * TC * 32 output channels.  Every W row travels once per
-// tile, so the pair pays where tiles are many and K * C is small next to a tile's pixels: see dwpw_pays.
+// tile, so the pair pays where pixels are many next to the output channels: see dwpw_pays.
 // What bounds it: phase 1's vector instructions (about 16 per element of t: nine products, the widening, addresses, the epilogue) and,
 // from 256 channels on, the W rows, which a CU takes into LDS at 50 bytes per clock; the two follow each other inside a workgroup.
 // Tiles of other heights, one or two 32-channel blocks per wave, one to four rows per thread and more workgroups per CU all
@@ -246,15 +246,22 @@ bool dwpw_kernel_applies(int dt, int N, int H, int W, int C, int S, int K, int l
            (double)K * round_up((size_t)C, 64) * 2 < 2147483648.0;
 }
 
-// A workgroup streams all of W, so a launch takes at least that long (9 us for 128 KB, 15 for 256 or 512 KB, 24 for 1 MB) however few
-// tiles there are; two launches put few tiles on the small-tile kernels, 9 to 11 us in all and 1.5 to 2 for the gap.  Measured, two
-// launches without the gap / one: 256 -> 256 at 28x28, 1 image 9.1 / 9.6, 16 images 16.8 / 12.0; 256 -> 512 stride 2, 64 tiles
-// 10.6 / 15.6, 128 tiles 16.3 / 16.1, 256 tiles 20.2 / 19.0; 512 -> 512, 32 tiles 11.7 / 14.0, 64 tiles 14.4 / 14.5, 128 tiles
-// 19.8 / 15.7; 512 -> 1024, 64 tiles 18.7 / 25.8.  Up to 128 KB one launch was the faster at every size.
+// A workgroup passes all of W, so a launch takes at least that long however few its tiles are, while two launches spread the output
+// channels of few pixels over the chip.  The line is therefore one of output channels against output pixels, K <= few + pixels / per, both
+// fitted for each channel count and stride on 4000 pairs of random sizes (1 to 64 images of 4x4 to 160x160, K of 64 to 2048; launches replayed
+// from a graph, the gap between two of them included) and looked at on 2500 others: of those 6500 one launch is the slower by more than 5 % in
+// 21 that the rule takes (at most 23 %, just beyond a whole round of workgroups), and they take 0.920 of the time of two launches,
+// 0.914 if every pair went its faster way.  us, two launches / one: stride 1, 2 images of 7x8, 32 -> 192 8.3 / 7.9; 1 of 7x7, 32 -> 256 8.5 / 8.9, 128 -> 128
+// 9.2 / 8.5, 128 -> 256 9.4 / 11.3; 1 of 14x14, 32 -> 1024 8.1 / 24.7, 256 -> 128 9.0 / 8.0, 512 -> 64 8.9 / 9.5; 3 of 120x120, 64 -> 384 20.4 / 18.1; 3 of 125x125,
+// 128 -> 512 33.7 / 26.4; 7 of 40x28, 256 -> 512 13.8 / 15.2; 2 of 45x31, 512 -> 128 13.0 / 9.8; stride 2, 2 of 11x11, 128 -> 384 8.6 / 10.1; 24 of 12x12,
+// 256 -> 64 8.8 / 9.7; 8 of 20x20, 512 -> 64 9.3 / 13.9.  At 512 channels and stride 2 a tile takes 14 us for any K: two launches (the auto-tuner tries one).
 bool dwpw_pays(int N, int H, int W, int C, int S, int K) {
+    const int Ho = out_size(H, 3, S, 1), Wo = out_size(W, 3, S, 1);
     const long wk = (long)C * K;
-    const long tiles = (long)N * ceil_div(out_size(H, 3, S, 1), 8) * ceil_div(out_size(W, 3, S, 1), 8);
-    return wk <= 65536 || (wk <= 262144 && tiles >= 128);
+    if (wk > 262144 || (wk > 65536 && (long)N * ceil_div(Ho, 8) * ceil_div(Wo, 8) < 128)) return false;
+    const int i = C <= 32 ? 0 : C <= 64 ? 1 : C <= 128 ? 2 : C <= 256 ? 3 : 4;
+    constexpr int few[2][5] = {{192, 192, 128, 128, 0}, {128, 128, 192, 0, 0}}, per[2][5] = {{160, 100, 100, 25, 12}, {150, 100, 25, 34, 0}};
+    return per[S - 1][i] > 0 && K <= few[S - 1][i] + (long)N * Ho * Wo / per[S - 1][i];
 }
 
 template <int C, int S, int TH, int WP, int WC, int TC, int NS, int RR> static void launch_dwpw_cfg(const DwPwLaunch &d, hipStream_t st) {

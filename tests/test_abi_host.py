@@ -365,6 +365,21 @@ def test_dense_layer_tile_runs_two_launches(sol):
     L.sol_network_destroy(h)
 
 
+@pytest.mark.parametrize("n,hw,c,s,k,fused", [
+    (1, 7, 32, 1, 192, 1), (1, 7, 32, 1, 256, 0), (1, 14, 32, 1, 2048, 0), (16, 112, 32, 1, 1024, 1), (4, 56, 64, 1, 1024, 0), (64, 56, 64, 1, 128, 1),
+    (1, 7, 128, 1, 128, 1), (1, 7, 128, 1, 256, 0), (64, 28, 256, 1, 256, 1), (1, 28, 256, 1, 256, 0), (64, 14, 512, 1, 512, 1), (1, 7, 512, 1, 64, 0),
+    (1, 14, 64, 2, 192, 0), (64, 56, 128, 2, 256, 1), (1, 7, 256, 2, 64, 0), (64, 28, 256, 2, 128, 1), (4, 14, 512, 2, 64, 0), (64, 28, 256, 2, 2048, 0)])
+def test_depthwise_pair_one_launch_or_two(sol, n, hw, c, s, k, fused):
+    """A depthwise convolution and the 1x1 behind it run as one launch where their tiles are many for the output channels that each
+    has to pass; few tiles with many output channels keep the two launches (one was up to five times slower)."""
+    layers = [wl.conv(c, 3, s=s, dw=True), wl.conv(k, 1, p=0), wl.conv(8, 1, p=0)]
+    st, h = _create(sol, layers, (n, c, hw, hw), sol.BF16)
+    v = C.c_int()
+    assert st == 0 and sol.lib().sol_network_layer_dwpw(h, 1, C.byref(v)) == 0
+    sol.lib().sol_network_destroy(h)
+    assert v.value == fused
+
+
 @pytest.mark.parametrize("first", [0, 1])
 def test_fire_module_of_one_join_only(sol, first):
     """Expands that different joins of one dense chain take are no module: the layer that reads the earlier join (here layer 4) runs
