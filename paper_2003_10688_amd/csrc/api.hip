@@ -380,7 +380,7 @@ static bool dw_one_launch(const sol_network *net, const LayerPlan &c2) {
 // The plan's own choice for a fire module whose 3x3 expand is c3: see fire_pays
 static bool fire_one_launch(const sol_network *net, const LayerPlan &c3) {
     const LayerPlan &sq = net->layers[c3.fire_s], &e1 = net->layers[c3.fire_e1];
-    return c3.tile == T_AUTO && sq.tile == T_AUTO && e1.tile == T_AUTO && fire_pays(sq.in.n, sq.in.h, sq.in.w, sq.in.c);
+    return c3.tile == T_AUTO && sq.tile == T_AUTO && e1.tile == T_AUTO && fire_pays(sq.in.n, sq.in.h, sq.in.w, sq.in.c, e1.cd.cout, c3.cd.cout);
 }
 // Does the 3x3 convolution c2 compute the 1x1 in front with it?  A tile forced on every layer runs them one by one.
 static bool dense_fused(const LayerPlan &c2) {

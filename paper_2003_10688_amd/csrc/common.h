@@ -228,7 +228,7 @@ struct FireLaunch {
     int N, H, W, C, SP, E1, E3;
 };
 bool fire_kernel_applies(int dt, int N, int H, int W, int C, int SP, int E1, int E3, int ldy);
-bool fire_pays(int N, int H, int W, int C);
+bool fire_pays(int N, int H, int W, int C, int E1, int E3);
 sol_status launch_conv_fire(const FireLaunch &f, hipStream_t st);
 bool linear_kernel_applies(const ConvArgs &a, int dt);
 sol_status launch_linear(const ConvArgs &a, int dt, hipStream_t st);

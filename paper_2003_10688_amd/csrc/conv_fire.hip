@@ -232,10 +232,17 @@ bool fire_kernel_applies(int dt, int N, int H, int W, int C, int SP, int E1, int
            (double)N * H * W * C * 2 < 2147483648.0 && (double)N * H * W * ldy < 2147483648.0;
 }
 
-// Up to a product of input channels and tiles: the halo is squeezed 1.56 times over.  What one launch gains a pass of the whole
-// SqueezeNet-shaped list, us: 64 channels, 784 tiles 9.9, 3136 tiles 2.5; 128, 49 tiles 5.5, 320 tiles 9.0, 1024 tiles -1.9, 1568 tiles -2.4;
-// 256, 96 tiles 5.6, 512 tiles 1.3, 1024 tiles -4.8.
-bool fire_pays(int N, int H, int W, int C) { return (long)C * N * ceil_div(H, 8) * ceil_div(W, 8) <= (C <= 64 ? 200704 : 102400); }
+// A tile is one path through C / 64 chunks of the squeeze, E1 / 64 stages of the 1x1 expand and five for 64 channels of the 3x3, while the
+// separate launches spread few pixels' channels over the chip; and beyond a tile per CU the halo's 1.56 times the squeeze counts, the
+// more the wider the input.  Fitted on 1700 modules of random sizes (squeezes of 16 and 32, 1 to 128 images of 4x4 to 130x130, replayed from a
+// graph, gaps included) and looked at on 900 others: of those 2600 one launch is the slower by more than 5 % in 13 that the rule takes (at
+// most 14 %), and they take 0.931 of the time of three launches, 0.921 if every module went its faster way.  us, three launches / one: 64 ->
+// 64 + 64, 740 tiles 15.8 / 11.2, 1176 tiles 18.2 / 16.5, 2880 tiles 35.7 / 33.1, 3075 tiles 36.4 / 35.4, 4180 tiles 44.1 / 45.4, 6512 tiles 64.2 / 66.5; 512 -> 256 + 256,
+// 32 tiles 12.3 / 19.0; 512 -> 128 + 256, 18 tiles 12.0 / 17.9; 64 -> 128 + 128, 1404 tiles 23.5 / 26.7.
+bool fire_pays(int N, int H, int W, int C, int E1, int E3) {
+    const long tiles = (long)N * ceil_div(H, 8) * ceil_div(W, 8), over = std::max(0l, tiles - 256);
+    return C + E1 + 2 * E3 + (C <= 64 ? over / 8 : C * over / 128) <= 640;
+}
 
 sol_status launch_conv_fire(const FireLaunch &f, hipStream_t st) {
     if ((long)f.N * f.H * f.W == 0) return SOL_OK;

@@ -380,6 +380,20 @@ def test_depthwise_pair_one_launch_or_two(sol, n, hw, c, s, k, fused):
     assert v.value == fused
 
 
+@pytest.mark.parametrize("n,hw,c,e1,e3,fused", [
+    (1, 13, 64, 64, 64, 1), (1, 13, 64, 256, 256, 0), (64, 55, 64, 64, 64, 1), (80, 55, 64, 64, 64, 0), (8, 55, 64, 128, 128, 1), (64, 55, 64, 128, 128, 0),
+    (1, 27, 256, 128, 128, 1), (1, 27, 512, 128, 128, 0), (16, 27, 128, 128, 128, 1), (64, 27, 128, 128, 128, 0), (1, 13, 512, 256, 256, 0)])
+def test_fire_module_one_launch_or_not(sol, n, hw, c, e1, e3, fused):
+    """A fire module runs as one launch where its tile's path is short -- few input and output channels -- and its tiles are few; wide
+    modules of few tiles were up to 1.5 times slower that way."""
+    layers = [wl.conv(c, 1, p=0), wl.conv(32, 1, p=0), wl.conv(e1, 1, p=0, src=1), wl.conv(e3, 3, src=1), wl.concat(2, 3), wl.conv(8, 1, p=0)]
+    st, h = _create(sol, layers, (n, 64, hw, hw), sol.BF16)
+    v = C.c_int()
+    assert st == 0 and sol.lib().sol_network_layer_fire(h, 3, C.byref(v)) == 0
+    sol.lib().sol_network_destroy(h)
+    assert v.value == fused
+
+
 @pytest.mark.parametrize("first", [0, 1])
 def test_fire_module_of_one_join_only(sol, first):
     """Expands that different joins of one dense chain take are no module: the layer that reads the earlier join (here layer 4) runs
