@@ -270,6 +270,10 @@ sol_status sol_network_forward_static(sol_network *net, const void *x, void *y, 
  * (0 = the library's own choice).  An id that does not fit a layer makes that call fail with SOL_ERR_UNSUPPORTED. */
 void sol_debug_set_conv_tile(int tile);
 
+/* Which kernel the last convolution launched by the CALLING THREAD ran on (test aid): "small" (conv_small), "pre" (conv_pre), "chain"
+ * (conv_chain), or "" for every other one.  Layers that one launch computes together do not count. */
+const char *sol_debug_conv_kernel(void);
+
 /* Measured ceilings for the roofline report (benchmark aid; no layer arithmetic).
  *   sol_debug_probe_copy   a plain device-to-device copy of `bytes` (multiple of 16; 16-byte aligned, non-overlapping
  *                          device buffers) by a simple kernel: what HBM delivers, 2 * bytes of traffic per call;

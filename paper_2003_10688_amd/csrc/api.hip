@@ -862,6 +862,7 @@ int sol_out_size(int in, int k, int stride, int pad) { return out_size(in, k, st
 
 // Debugging / sweeping aid: force the convolution tile for later calls of the calling thread (0 = automatic).
 void sol_debug_set_conv_tile(int tile) { g_tile_override = tile; }
+const char *sol_debug_conv_kernel(void) { return conv_kernel_of_thread(); }
 
 size_t sol_packed_weight_bytes(const sol_conv_desc *cd, sol_dtype dt) {
     if (!cd || cd->cout <= 0 || cd->cin <= 0 || cd->kh <= 0 || cd->kw <= 0) return 0;

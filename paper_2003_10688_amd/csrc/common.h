@@ -163,6 +163,7 @@ sol_status launch_conv_direct(const ConvArgs &a, int dt, int tile, hipStream_t s
 int direct_choose_pair_tile(const ConvArgs &a, int K2);
 sol_status launch_conv_direct_pair(const ConvArgs &a, int tile, const void *x2, const void *w2, const float *scale2, const float *shift2,
                                    int H2, int W2, int K2, int Kp2, int stride, hipStream_t st);
+const char *conv_kernel_of_thread();                     // sol_debug_conv_kernel (conv_igemm.hip)
 bool chain_kernel_applies(const ConvArgs &a);            // fp32, the sums of D_64x64_128x3 on smaller tiles (conv_chain.hip)
 sol_status launch_conv_chain(const ConvArgs &a, hipStream_t st);
 bool small_kernel_applies(const ConvArgs &a, int dt);    // three input channels on the vector units (conv_small.hip)

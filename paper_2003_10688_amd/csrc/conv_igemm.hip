@@ -293,11 +293,14 @@ template <typename T> static sol_status launch_typed(const ConvArgs &a, int tile
     }
 }
 
+static thread_local const char *t_kernel = "";             // see sol_debug_conv_kernel
+const char *conv_kernel_of_thread() { return t_kernel; }
+
 // Input-side BN + ReLU, a strided input (channel prefix of a wider tensor) or masked padding channels: what is fetched has to pass
 // through registers before it is multiplied.  A pre-activated 1x1 convolution of whole chunks takes its fragments from memory
 // directly (conv_pre); everything else, and a tile asked for, the register-staged kernel, which transforms on the way to LDS.
 static sol_status launch_conv_staged(const ConvArgs &a, int dt, int tile, hipStream_t st) {
-    if (tile == T_AUTO && pre_kernel_applies(a, dt)) return launch_conv_pre(a, st);
+    if (tile == T_AUTO && pre_kernel_applies(a, dt)) { t_kernel = "pre"; return launch_conv_pre(a, st); }
     if (!(tile >= T_256x128 && tile <= T_64x128)) {
         SOL_REQUIRE(tile == T_AUTO || tile == T_NO_HALO, SOL_ERR_UNSUPPORTED,
                     "conv tile %d cannot apply an input-side BN + ReLU or read a channel prefix; the register-staged tiles 1..8 can", tile);
@@ -315,10 +318,11 @@ static sol_status launch_conv_staged(const ConvArgs &a, int dt, int tile, hipStr
 // pre-activation or pooling candidate within a rounding of its threshold, decided the other way, moves a whole term of a weight
 // gradient (9 images of 113x113, ResNet-18-shaped: up to 0.02 of a gradient's norm, 2.5 of its rms in one element).
 sol_status launch_conv(const ConvArgs &a, int dt, int tile_override, hipStream_t st, bool one_order) {
+    t_kernel = "";
     if (a.P <= 0) return SOL_OK;   // empty batch: nothing to do
     if (a.pre_scale || a.ldx != a.C || a.Cvalid != a.C) return launch_conv_staged(a, dt, tile_override, st);
     if (tile_override == T_AUTO && stem_kernel_applies(a, dt)) return launch_conv_stem(a, st);
-    if (tile_override == T_AUTO && !one_order && small_kernel_applies(a, dt)) return launch_conv_small(a, dt, st);
+    if (tile_override == T_AUTO && !one_order && small_kernel_applies(a, dt)) { t_kernel = "small"; return launch_conv_small(a, dt, st); }
     if (tile_override == T_AUTO && !one_order && linear_stream_applies(a, dt)) return launch_linear_stream(a, dt, st);
     if (tile_override == T_AUTO && linear_kernel_applies(a, dt)) {
         // not one for linear_stream_applies, and a weight matrix of many megabytes: the job is streaming the weights, which the
@@ -361,7 +365,7 @@ sol_status launch_conv(const ConvArgs &a, int dt, int tile_override, hipStream_t
         return launch_conv_dma(a, dt, tile_override, st);
     }
     // fewer than 192 tiles of 128x128 and 32-channel chunks: the ring kernel's 64x64 tile, or the same sums on smaller ones
-    if (one_order && dt == SOL_F32 && tile_override == T_AUTO && choose_tile(a, 4) == D_64x64_128x3 && chain_kernel_applies(a)) return launch_conv_chain(a, st);
+    if (one_order && dt == SOL_F32 && tile_override == T_AUTO && choose_tile(a, 4) == D_64x64_128x3 && chain_kernel_applies(a)) { t_kernel = "chain"; return launch_conv_chain(a, st); }
     if (dt == SOL_BF16) return launch_typed<bf16_t>(a, tile_override, st);
     if (dt == SOL_F32) return launch_typed<float>(a, tile_override, st);
     SOL_FAIL(SOL_ERR_DTYPE, "unknown dtype %d", dt);

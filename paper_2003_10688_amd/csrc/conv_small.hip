@@ -158,11 +158,27 @@ __global__ void __launch_bounds__(256) conv_small_kernel(const SmallArgs s) {
 #endif
 }
 
+// A thread loads its window again for every four filters, and the gather kernel's 128x64 tiles build a row of the reduction once for 64: with
+// a 2x2 pool, few pixels, few filters, filters that leave the last channel tile part empty or rows that do not store 16 bytes at once this
+// kernel wins at every size measured (1 to 64 images of 12x12 to 256x256, 4 to 512 filters), with full channel tiles the other one, in bf16 from
+// one tile per CU on and in fp32 where the output leaves the caches.  Between one and two tiles per CU, which are one round there, three
+// quarters of a channel tile are enough.  us, gather kernel / here: bf16, 8 images of 64x64, 64 filters (256 tiles) 10.0 / 8.9, 128 filters (512)
+// 11.1 / 14.2; 8 of 51x51, 72 filters (326) 10.9 / 9.3; 64 of 100x100, 48 filters 89 / 72, 64 filters 80 / 93; one of 224x224, 64 filters (392) 10.8 / 14.4, 96
+// filters (784) 18.8 / 18.3; fp32, 8 of 224x224, 128 filters 98 / 84, 256 filters 189 / 225; 64 of 100x100, 192 filters 225 / 251; 31 of 138x138, 224 filters
+// 272 / 256.  Of 1953 layers without a pool 29 go the slower way by more than 4 %, 266 without this line.
+static bool gather_kernel_pays(const ConvArgs &a, int dt) {
+    if (a.pool || a.Cout % 8 != 0) return false;
+    const int ntc = ceil_div(a.Cout, 64);
+    const long tiles = (long)ceil_div(a.P, 128) * ntc;
+    const double full = a.Cout / (64.0 * ntc);
+    return dt == SOL_BF16 ? tiles > 256 && full >= (tiles <= 512 ? 0.7 : 0.9375) : full >= 0.9375 && (double)a.P * a.Cout > 70e6;
+}
+
 // 3x3, stride 1 (with or without a 2x2 pool that keeps no winners) in either type, stride 2 in fp32 (bf16 has the stem kernel)
 bool small_kernel_applies(const ConvArgs &a, int dt) {
     if (a.C != 3 || a.R != 3 || a.S != 3 || a.sh != a.sw || a.Cout % 4 != 0 || a.res || a.argmax || a.prepool || a.pool == 3 || a.pre_scale || a.ldx != a.C || a.Cvalid != a.C) return false;
     if (a.sh != 1 && !(dt == SOL_F32 && a.pool == 0 && a.sh == 2)) return false;
-    return (double)a.N * a.H * a.W * a.C * dtype_size(dt) < 2147483648.0;
+    return !gather_kernel_pays(a, dt) && (double)a.N * a.H * a.W * a.C * dtype_size(dt) < 2147483648.0;
 }
 
 template <typename T, int R, int SH, int TR, int PX, int NCH> static void launch_small_cfg(const ConvArgs &a, hipStream_t st) {

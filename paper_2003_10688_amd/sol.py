@@ -76,6 +76,7 @@ def lib():
         L.sol_graph_destroy.restype = None
         L.sol_graph_launch.argtypes = [C.c_void_p, C.c_void_p]
         L.sol_debug_set_conv_tile.restype = None
+        L.sol_debug_conv_kernel.restype = C.c_char_p
         L.sol_debug_probe_copy.argtypes = [C.c_void_p, C.c_void_p, C.c_size_t, C.c_void_p]
         L.sol_debug_probe_mfma.argtypes = [C.c_int, C.c_int, C.c_void_p, C.POINTER(C.c_double), C.c_void_p]
         L.sol_network_forward_static.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p]
@@ -304,6 +305,11 @@ def sol_global_avgpool(x, stream=None):
 
 def sol_debug_set_conv_tile(tile):
     lib().sol_debug_set_conv_tile(C.c_int(tile))
+
+
+def sol_debug_conv_kernel():
+    """Which kernel this thread's last convolution ran on: "small", "pre", "chain", or "" for every other one."""
+    return lib().sol_debug_conv_kernel().decode()
 
 
 def sol_debug_probe_copy(dst, src, stream=None):
