@@ -646,7 +646,10 @@ __global__ void loss_mean_kernel(const float *__restrict__ row_loss, int N, floa
 // leaves the new weights in LDS and writes from there both copies, a tap's TC channels in a row of the forward pack and its
 // TK filters in a row of the flipped one (element maps of pack_weights_kernel / pack_weights_flip_kernel; the padding of packed
 // rows was zeroed when the weights were set and stays).  32 x 32 for 3x3 filters makes both writes 64 bytes long (bf16).
-// ResNet-18-shaped, 11.7 M weights, bf16 / fp32: 54 + 60 / 54 + 61 us as two launches, 50 / 58 us here (281 / 328 MB).
+// ResNet-18-shaped, 11.7 M weights, bf16 / fp32: 50 + 52 / 50 + 51 us as two launches, 47.6 / 54 us here (281 / 328 MB).  A layer of few tiles
+// takes what one tile takes, so those are cut into smaller ones and values that do not load by 16 bytes come six at a time: two 7x7 layers of 64
+// filters 10.7 us as two launches, 8.2 here (20.5 with whole tiles and one value at a time), 11x11 and 5x5 11.9, 7.8 (23.0), 33, 71 and 35
+// filters 11.2, 6.1 (27.0).
 template <typename T, int V, bool VEC>
 __device__ __forceinline__ void write_packed(const float *tile, int pitch, T *__restrict__ out, int rows, int row0, int cols, int col0, int ncol, int RS,
                                              int Kp, int srow, int scol, bool flip) {
@@ -720,13 +723,28 @@ __global__ void __launch_bounds__(256) update_batch_kernel(const UpdateBatch b, 
             }
         }
     } else {
-        for (int i = threadIdx.x; i < nk * run; i += 256) {
-            const int kk = i / run, j = i - kk * run;
-            const size_t o = base + kk * rowlen + j;
-            const float vel = mu * v[o] + g[o], nw = w[o] - lr * vel;
-            v[o] = vel;
-            w[o] = nw;
-            tile[kk * pitch + j] = nw;
+        const int n = nk * run;
+        for (int i0 = threadIdx.x; i0 < n; i0 += 256 * 6) {       // six values of each tensor in flight per thread
+            float wv[6], vv[6], gv[6];
+            size_t off[6];
+            int lo[6];
+#pragma unroll
+            for (int u = 0; u < 6; u++) {
+                const int i = min(i0 + u * 256, n - 1), kk = i / run, j = i - kk * run;
+                off[u] = base + kk * rowlen + j;
+                lo[u] = kk * pitch + j;
+                wv[u] = w[off[u]];
+                vv[u] = v[off[u]];
+                gv[u] = g[off[u]];
+            }
+#pragma unroll
+            for (int u = 0; u < 6; u++) {
+                if (i0 + u * 256 >= n) continue;
+                const float vel = mu * vv[u] + gv[u], nw = wv[u] - lr * vel;
+                v[off[u]] = vel;
+                w[off[u]] = nw;
+                tile[lo[u]] = nw;
+            }
         }
     }
     __syncthreads();
@@ -749,11 +767,14 @@ bool update_segment_blocks(UpdateBatch &b, int i) {
     } else {
         const int RS = b.RS[i];
         if (RS > UPD_PLANE) return false;
+        const int K = b.K[i], C = b.C[i];
         // rows of a tile are padded to an odd length: at most TK <= 64 floats on top of the plane
-        if (RS == 1) { b.TK[i] = 64; b.TC[i] = 64; }
-        else if (RS <= 9) { b.TK[i] = 32; b.TC[i] = 32; }
-        else if (RS <= UPD_PLANE / 32) { b.TK[i] = 32; b.TC[i] = std::min(b.C[i], UPD_PLANE / 32 / RS); }
-        else { b.TK[i] = UPD_PLANE / RS; b.TC[i] = 1; }
+        int TK = RS == 1 ? 64 : 32, TC = RS == 1 ? 64 : RS <= 9 ? 32 : std::min(C, std::max(UPD_PLANE / 32 / RS, RS * 4 <= UPD_PLANE ? 4 : 1));
+        if (TC > 4 && RS > 9) TC &= ~3;                            // runs of whole 16-byte groups
+        while (TK * TC * RS > UPD_PLANE) TK /= 2;
+        // a layer of few tiles takes as long as one of them: smaller ones, as long as rows of eight values stay
+        while ((long)ceil_div(K, TK) * ceil_div(C, TC) < 64 && TK * TC * RS >= 2048 && std::max(TK, TC) >= 16) (TK >= TC ? TK : TC) /= 2;
+        b.TK[i] = TK; b.TC[i] = TC;
         blocks = ceil_div(b.K[i], b.TK[i]) * ceil_div(b.C[i], b.TC[i]);
     }
     b.first_block[i + 1] = b.first_block[i] + blocks;

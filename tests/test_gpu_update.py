@@ -16,6 +16,7 @@ LISTS = {
     "tiles": [wl.conv(64, 3), wl.conv(96, 3), wl.conv(128, 1, p=0), wl.gap(), wl.linear(64)],
     "remainders": [wl.conv(40, 3), wl.conv(72, 3), wl.conv(100, 1, p=0), wl.gap(), wl.linear(10)],
     "odd": [wl.conv(7, 3), wl.conv(33, 3), wl.conv(65, 1, p=0), wl.gap(), wl.linear(9)],
+    "few_tiles": [wl.conv(40, 3), wl.conv(64, 11, p=5), wl.conv(48, 7), wl.conv(24, 1, p=0), wl.gap(), wl.linear(12)],   # cut into smaller ones
     "large_filters": [wl.conv(36, 7), wl.conv(12, 5), wl.conv(35, 20, p=9), wl.gap(), wl.linear(11)],
 }
 
