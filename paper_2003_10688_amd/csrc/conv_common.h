@@ -42,6 +42,8 @@ template <int N> __device__ __forceinline__ void wait_vmcnt() {
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 template <int N> __device__ __forceinline__ void wait_lgkmcnt() { asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(N) : "memory"); }
+// no memory access crosses this point: a counted wait relies on the order in which DMAs and loads were issued
+__device__ __forceinline__ void keep_order() { asm volatile("" ::: "memory"); }
 template <int OFF> __device__ __forceinline__ void lds_read16(u32x4_t &dst, unsigned addr) {
     asm volatile("ds_read_b128 %0, %1 offset:%2" : "=&v"(dst) : "v"(addr), "n"(OFF));
 }

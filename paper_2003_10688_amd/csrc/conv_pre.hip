@@ -69,10 +69,13 @@ __global__ void __launch_bounds__(256, 2) conv_pre_kernel(const ConvArgs a) {
     const f32x4_t ps = *reinterpret_cast<const f32x4_t *>(a.pre_scale + cc), ph = *reinterpret_cast<const f32x4_t *>(a.pre_shift + cc);
     const float *ap = tid < 128 ? a.scale : a.shift;
     const float av = ap ? ap[c0 + co] : tid < 128 ? 1.f : 0.f;
-    // a chunk's filters, then its pixels: the order in which the loop goes on
+    // a chunk's filters, then its pixels: the order in which the loop goes on, and which its first wait counts on
+    keep_order();
     static_for<PD>([&](auto S) {
         issue(decltype(S)::value);
+        keep_order();
         fetch(raw[decltype(S)::value], decltype(S)::value);
+        keep_order();
     });
     asm volatile("ds_write_b128 %0, %1" ::"v"(cst + (unsigned)cc * 4u), "v"(ps) : "memory");
     asm volatile("ds_write_b128 %0, %1" ::"v"(cst + (unsigned)(a.C + cc) * 4u), "v"(ph) : "memory");
