@@ -89,51 +89,56 @@ __global__ void __launch_bounds__(256, 2) conv_pre_kernel(const ConvArgs a) {
         for (int e = 0; e < 16; e++) acc[i][e] = 0.f;
     const unsigned fsw = swz<128>(lr), fw = lds_addr(lds) + lr * 128, shift_at = (unsigned)(a.C * 4);
     int slot = 0;
-    for (int c = 0; c < nc; c += PD)
-        static_for<PD>([&](auto U) {
-            constexpr int u = decltype(U)::value;
-            if (u == 0 || c + u < nc) {
-                // the chunk's filters have landed once what was issued behind them -- the filters of NS - 2 chunks, the pixels
-                // of NS - 1 -- is all that is outstanding
-                wait_vmcnt<(NS - 2) * WL + (NS - 1) * 4>();
-                __builtin_amdgcn_s_barrier();
-                const unsigned fb = fw + slot * STAGE, cb = cst + (unsigned)((c + u) * 256 + lh * 32);
-                u32x4_t fa[2][TC], k4[2][4];               // filters; scale and shift of the lane's 8 channels
-                auto read = [&](auto KS, u32x4_t (&w)[TC], u32x4_t (&q)[4]) {
-                    constexpr int ks = decltype(KS)::value;
-                    lds_read16<ks * 64>(q[0], cb);
-                    lds_read16<ks * 64 + 16>(q[1], cb);
-                    lds_read16<ks * 64>(q[2], cb + shift_at);
-                    lds_read16<ks * 64 + 16>(q[3], cb + shift_at);
-                    static_for<TC>([&](auto I) { lds_read16<decltype(I)::value * 32 * 128>(w[decltype(I)::value], fb + (((2 * ks + lh) ^ fsw) << 4)); });
-                };
-                read(std::integral_constant<int, 0>{}, fa[0], k4[0]);
-                issue(slot == 0 ? NS - 1 : slot - 1);
-                static_for<4>([&](auto KS) {
-                    constexpr int ks = decltype(KS)::value, cur = ks & 1;
-                    if constexpr (ks < 3) {
-                        read(std::integral_constant<int, ks + 1>{}, fa[cur ^ 1], k4[cur ^ 1]);
-                        wait_lgkmcnt<4 + TC>();
-                    } else {
-                        wait_lgkmcnt<0>();
-                    }
-                    static_for<4>([&](auto I) { landed(k4[cur][decltype(I)::value]); });
-                    static_for<TC>([&](auto I) { landed(fa[cur][decltype(I)::value]); });
-                    u32x4_t b;
-#pragma unroll
-                    for (int d = 0; d < 4; d++) {
-                        const uint32_t v = raw[u][ks][d];
-                        const float s0 = __uint_as_float(k4[cur][d >> 1][2 * (d & 1)]), s1 = __uint_as_float(k4[cur][d >> 1][2 * (d & 1) + 1]);
-                        const float h0 = __uint_as_float(k4[cur][2 + (d >> 1)][2 * (d & 1)]), h1 = __uint_as_float(k4[cur][2 + (d >> 1)][2 * (d & 1) + 1]);
-                        const float f0 = __uint_as_float(v << 16) * s0 + h0, f1 = __uint_as_float(v & 0xffff0000u) * s1 + h1;
-                        b[d] = pack_bf16x2(__builtin_fmaxf(f0, 0.f), __builtin_fmaxf(f1, 0.f));
-                    }
-                    static_for<TC>([&](auto I) { Mma<bf16_t>::run(acc[decltype(I)::value], fa[cur][decltype(I)::value], b); });
-                });
-                fetch(raw[u], c + u + PD);
-                slot = slot + 1 == NS ? 0 : slot + 1;
+    auto chunk = [&](auto U, int at) {                     // chunk `at`, whose pixels are in raw[U]
+        constexpr int u = decltype(U)::value;
+        // the chunk's filters have landed once what was issued behind them -- the filters of NS - 2 chunks, the pixels
+        // of NS - 1 -- is all that is outstanding
+        wait_vmcnt<(NS - 2) * WL + (NS - 1) * 4>();
+        __builtin_amdgcn_s_barrier();
+        const unsigned fb = fw + slot * STAGE, cb = cst + (unsigned)(at * 256 + lh * 32);
+        u32x4_t fa[2][TC], k4[2][4];               // filters; scale and shift of the lane's 8 channels
+        auto read = [&](auto KS, u32x4_t (&w)[TC], u32x4_t (&q)[4]) {
+            constexpr int ks = decltype(KS)::value;
+            lds_read16<ks * 64>(q[0], cb);
+            lds_read16<ks * 64 + 16>(q[1], cb);
+            lds_read16<ks * 64>(q[2], cb + shift_at);
+            lds_read16<ks * 64 + 16>(q[3], cb + shift_at);
+            static_for<TC>([&](auto I) { lds_read16<decltype(I)::value * 32 * 128>(w[decltype(I)::value], fb + (((2 * ks + lh) ^ fsw) << 4)); });
+        };
+        read(std::integral_constant<int, 0>{}, fa[0], k4[0]);
+        issue(slot == 0 ? NS - 1 : slot - 1);
+        static_for<4>([&](auto KS) {
+            constexpr int ks = decltype(KS)::value, cur = ks & 1;
+            if constexpr (ks < 3) {
+                read(std::integral_constant<int, ks + 1>{}, fa[cur ^ 1], k4[cur ^ 1]);
+                wait_lgkmcnt<4 + TC>();
+            } else {
+                wait_lgkmcnt<0>();
             }
+            static_for<4>([&](auto I) { landed(k4[cur][decltype(I)::value]); });
+            static_for<TC>([&](auto I) { landed(fa[cur][decltype(I)::value]); });
+            u32x4_t b;
+#pragma unroll
+            for (int d = 0; d < 4; d++) {
+                const uint32_t v = raw[u][ks][d];
+                const float s0 = __uint_as_float(k4[cur][d >> 1][2 * (d & 1)]), s1 = __uint_as_float(k4[cur][d >> 1][2 * (d & 1) + 1]);
+                const float h0 = __uint_as_float(k4[cur][2 + (d >> 1)][2 * (d & 1)]), h1 = __uint_as_float(k4[cur][2 + (d >> 1)][2 * (d & 1) + 1]);
+                const float f0 = __uint_as_float(v << 16) * s0 + h0, f1 = __uint_as_float(v & 0xffff0000u) * s1 + h1;
+                b[d] = pack_bf16x2(__builtin_fmaxf(f0, 0.f), __builtin_fmaxf(f1, 0.f));
+            }
+            static_for<TC>([&](auto I) { Mma<bf16_t>::run(acc[decltype(I)::value], fa[cur][decltype(I)::value], b); });
         });
+        fetch(raw[u], at + PD);
+        slot = slot + 1 == NS ? 0 : slot + 1;
+    };
+    // Whole turns, then what is left of one: a chunk skipped inside the loop would join its end, and the compiler, which then cannot know
+    // what was requested last, waited at every other chunk for nearly everything (64 images of 7x7, 512 -> 256 11.6 -> 10.5 us without that,
+    // 16 of 28x28, 1024 -> 128 18.1 -> 16.6)
+    int c = 0;
+    for (; c + PD <= nc; c += PD) static_for<PD>([&](auto U) { chunk(U, c + decltype(U)::value); });
+    static_for<PD - 1>([&](auto U) {
+        if (c + decltype(U)::value < nc) chunk(U, c + decltype(U)::value);
+    });
     wait_vmcnt<0>();                                       // the DMAs beyond the last chunk
     __syncthreads();                                       // the ring becomes strips
     static_for<TC / 2>([&](auto H) {                       // 64 channels at a time
