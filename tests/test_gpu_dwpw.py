@@ -53,6 +53,23 @@ def test_pair(sol, case, c, stride):  # noqa: F811
     assert rel_err(got, sol.to_host_nchw(net.layer_output(2))) <= TOL["bf16"]
 
 
+def test_no_less_exact_than_two_launches(sol):  # noqa: F811
+    """The 1x1 sums run in another order than as two launches: as many outputs are the rounded exact value (the oracle's, in 64 bits)."""
+    wrong, total = [0, 0], 0
+    for c, s, K, n, hw in ((32, 1, 64, 2, 28), (64, 2, 128, 2, 28), (128, 1, 128, 2, 20), (128, 2, 256, 2, 28), (256, 1, 256, 2, 20), (512, 1, 512, 2, 14), (512, 2, 64, 2, 28)):
+        layers = [wl.conv(c, 3, s=s, dw=True, act="none", bn=False), wl.conv(K, 1, p=0, act="none", bn=False)]
+        x = wl.to_bf16_grid(np.random.default_rng([c, s, K]).standard_normal((n, c, hw, hw)))
+        prm = wl.make_params(layers, c, 3 + c, bf16=True, bias_std=0.3)
+        want = orc.network_forward(layers, prm, x, bf16=True)
+        net, xd = build(sol, layers, x, prm)
+        for fused in (0, 1):
+            net.set_dwpw(1, fused)
+            wrong[fused] += int((sol.to_host_nchw(net.forward(xd)).reshape(want.shape) != want).sum())
+        total += want.size
+    # a turned rounding is a rare event on its own (about 2 in 10000 here): two counts of the same rate differ by at most four standard deviations
+    assert wrong[1] <= wrong[0] + 4 * (sum(wrong) + 1) ** 0.5 and sum(wrong) < 2e-3 * total, (wrong, total)
+
+
 def test_pair_into_concatenation(sol):  # noqa: F811
     """The 1x1 convolution writes its channels into a joined tensor (output pitch above its channel count)."""
     layers = [wl.conv(64, 1, p=0), wl.conv(64, 3, dw=True), wl.conv(64, 1, p=0), wl.conv(72, 1, p=0, src=0), wl.concat(3, 2), wl.conv(8, 1, p=0, bn=False, act="none")]
