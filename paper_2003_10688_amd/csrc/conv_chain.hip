@@ -31,8 +31,7 @@ template <int NS>
 __global__ void __launch_bounds__(64) conv_chain_kernel(const ConvArgs a) {
 #if defined(__HIP_DEVICE_COMPILE__)
     using namespace lds_pipe;
-    constexpr int PB = 1, CB = 1;                          // 16-row blocks of pixels / channels
-    constexpr int BP = PB * 16, BC = CB * 16, ROWB = 128, BK = 32;
+    constexpr int BP = 16, BC = 16, ROWB = 128, BK = 32;   // pixels, channels; bytes and elements of a stage's row
     constexpr int XL = BP / 8, WL = BC / 8, L = XL + WL;   // DMA instructions (8 rows each) per stage
     constexpr int STAGE = (BP + BC) * ROWB;
     static_assert(NS >= 4 && NS % 2 == 0 && NS * STAGE <= 160 * 1024 && NS * L < 64, "LDS, vmcnt");
@@ -122,13 +121,9 @@ __global__ void __launch_bounds__(64) conv_chain_kernel(const ConvArgs a) {
             __builtin_amdgcn_raw_ptr_buffer_load_lds(xr, (__attribute__((address_space(3))) void *)(lx + (d - WL) * 1024), 16, xov[d - WL], xs, 0, 0);
     };
 
-    f32x4_t acc[CB][PB];
-#pragma unroll
-    for (int i = 0; i < CB; i++)
-#pragma unroll
-        for (int j = 0; j < PB; j++) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
 
-    // fragments of a stage: per 16-row block and 8 reduction elements a lane needs elements 4 (lg & 1) + lg / 2 and that + 2 (the two
+    // fragments of a stage: per 8 reduction elements a lane needs elements 4 (lg & 1) + lg / 2 and that + 2 (the two
     // matrix instructions of those 8 then run through 0 4 1 5 and 2 6 3 7).  It reads the 16 bytes that hold them and picks:
     // two dwords by ds_read2_b32 took LDS 10 cycles per instruction (two rows on one bank), twice the time of the products
     const unsigned fsw = swz<ROWB>(lr);
@@ -137,23 +132,19 @@ __global__ void __launch_bounds__(64) conv_chain_kernel(const ConvArgs a) {
     unsigned fa[4];
 #pragma unroll
     for (int q = 0; q < 4; q++) fa[q] = lds_addr(lds) + lr * ROWB + (((2 * q + (lg & 1)) ^ fsw) << 4);
-    typedef u32x4_t FragsW[CB][4];
-    typedef u32x4_t FragsX[PB][4];
-    FragsW fw[2];
-    FragsX fx[2];
-    // read R of the stage in ring slot BUF: 16 bytes of weight block R % (CB + PB) or of pixel block R % (CB + PB) - CB
-    auto read_one = [&](auto R, auto BUF, FragsW &w, FragsX &x) {
-        constexpr int q = decltype(R)::value / (CB + PB), r = decltype(R)::value % (CB + PB), o = decltype(BUF)::value * STAGE;
-        if constexpr (r < CB) lds_read16<o + (PB + r) * 16 * ROWB>(w[r][q], fa[q]); else lds_read16<o + (r - CB) * 16 * ROWB>(x[r - CB][q], fa[q]);
+    typedef u32x4_t Frags[4];
+    Frags fw[2], fx[2];
+    // read R of the stage in ring slot BUF: 16 bytes of the weights (even R) or of the pixels (odd)
+    auto read_one = [&](auto R, auto BUF, Frags &w, Frags &x) {
+        constexpr int q = decltype(R)::value / 2, o = decltype(BUF)::value * STAGE;
+        if constexpr (decltype(R)::value % 2 == 0) lds_read16<o + BP * ROWB>(w[q], fa[q]); else lds_read16<o>(x[q], fa[q]);
     };
-    auto frags_landed = [](FragsW &w, FragsX &x) {
+    auto frags_landed = [](Frags &w, Frags &x) {
         wait_lgkmcnt<0>();
 #pragma unroll
         for (int q = 0; q < 4; q++) {
-#pragma unroll
-            for (int i = 0; i < CB; i++) landed(w[i][q]);
-#pragma unroll
-            for (int j = 0; j < PB; j++) landed(x[j][q]);
+            landed(w[q]);
+            landed(x[q]);
         }
     };
 
@@ -161,7 +152,7 @@ __global__ void __launch_bounds__(64) conv_chain_kernel(const ConvArgs a) {
         static_for<L>([&](auto D) { issue_one(D, S); });
         next_stage();
     });
-    constexpr int NR = 4 * (CB + PB), SLOTS = 8 * CB * PB;
+    constexpr int NR = 8, SLOTS = 8;                       // fragment reads and matrix instructions of a stage
     wait_vmcnt<(NS - 2) * L>();
     static_for<NR>([&](auto R) { read_one(R, std::integral_constant<int, 0>{}, fw[0], fx[0]); });
     frags_landed(fw[0], fx[0]);
@@ -171,19 +162,17 @@ __global__ void __launch_bounds__(64) conv_chain_kernel(const ConvArgs a) {
             if (u == 0 || __builtin_expect(k + u < nk, 1)) {
                 // stage k + u + 1 has landed; stage k + u is in registers, so the slot of the stage before takes the next one
                 wait_vmcnt<(NS - 3) * L>();
-                float ew[2][CB], ex[2][PB];
+                float ew[2], ex[2];
                 auto picks = [&](auto T) {
                     constexpr int t = decltype(T)::value, q = t / 2, h = t % 2;
-#pragma unroll
-                    for (int i = 0; i < CB; i++) ew[t & 1][i] = pick(fw[cur][i][q][2 * h], fw[cur][i][q][2 * h + 1]);
-#pragma unroll
-                    for (int j = 0; j < PB; j++) ex[t & 1][j] = pick(fx[cur][j][q][2 * h], fx[cur][j][q][2 * h + 1]);
+                    ew[t & 1] = pick(fw[cur][q][2 * h], fw[cur][q][2 * h + 1]);
+                    ex[t & 1] = pick(fx[cur][q][2 * h], fx[cur][q][2 * h + 1]);
                 };
                 picks(std::integral_constant<int, 0>{});
                 static_for<SLOTS>([&](auto Z) {
-                    constexpr int z = decltype(Z)::value, t = z / (CB * PB), b = z % (CB * PB), i = b / PB, j = b % PB;
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(ew[t & 1][i], ex[t & 1][j], acc[i][j], 0, 0, 0);
-                    if constexpr (b == 0 && t < 7) picks(std::integral_constant<int, t + 1>{});
+                    constexpr int z = decltype(Z)::value;
+                    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(ew[z & 1], ex[z & 1], acc, 0, 0, 0);
+                    if constexpr (z < 7) picks(std::integral_constant<int, z + 1>{});
                     // reads in the first half of the stage, to have landed by its end; DMA in the second
                     constexpr int H = SLOTS / 2, N = z < H ? NR : L, y = z % H, lo = y * N / H, hi = (y + 1) * N / H;
                     static_for<hi - lo>([&](auto A) {
@@ -204,35 +193,28 @@ __global__ void __launch_bounds__(64) conv_chain_kernel(const ConvArgs a) {
     const float *__restrict__ resg = static_cast<const float *>(a.res);
     float *__restrict__ yg = static_cast<float *>(a.y);
     const bool vec = (a.Cout & 3) == 0;
+    const int cb = c0 + lg * 4, nv = min(4, a.Cout - cb), m = p0 + lr;
+    float sc[4], sf[4];
 #pragma unroll
-    for (int i = 0; i < CB; i++) {
-        const int cb = c0 + i * 16 + lg * 4, nv = min(4, a.Cout - cb);
-        float sc[4], sf[4];
+    for (int e = 0; e < 4; e++) {
+        sc[e] = (a.scale && e < nv) ? a.scale[cb + e] : 1.f;
+        sf[e] = (a.shift && e < nv) ? a.shift[cb + e] : 0.f;
+    }
+    if (m >= a.P || nv <= 0) return;
+    const size_t o = (size_t)m * a.Cout + cb;
+    float v[4];
 #pragma unroll
-        for (int e = 0; e < 4; e++) {
-            sc[e] = (a.scale && e < nv) ? a.scale[cb + e] : 1.f;
-            sf[e] = (a.shift && e < nv) ? a.shift[cb + e] : 0.f;
-        }
+    for (int e = 0; e < 4; e++) {
+        v[e] = acc[e] * sc[e] + sf[e];
+        if (resg && e < nv) v[e] += resg[o + e];
+        if (a.act == SOL_ACT_RELU) v[e] = __builtin_fmaxf(v[e], 0.f);
+    }
+    if (vec) {
+        *reinterpret_cast<float4 *>(yg + o) = make_float4(v[0], v[1], v[2], v[3]);
+    } else {
 #pragma unroll
-        for (int j = 0; j < PB; j++) {
-            const int m = p0 + j * 16 + lr;
-            if (m >= a.P || nv <= 0) continue;
-            const size_t o = (size_t)m * a.Cout + cb;
-            float v[4];
-#pragma unroll
-            for (int e = 0; e < 4; e++) {
-                v[e] = acc[i][j][e] * sc[e] + sf[e];
-                if (resg && e < nv) v[e] += resg[o + e];
-                if (a.act == SOL_ACT_RELU) v[e] = __builtin_fmaxf(v[e], 0.f);
-            }
-            if (vec) {
-                *reinterpret_cast<float4 *>(yg + o) = make_float4(v[0], v[1], v[2], v[3]);
-            } else {
-#pragma unroll
-                for (int e = 0; e < 4; e++)
-                    if (e < nv) yg[o + e] = v[e];
-            }
-        }
+        for (int e = 0; e < 4; e++)
+            if (e < nv) yg[o + e] = v[e];
     }
 #endif
 }

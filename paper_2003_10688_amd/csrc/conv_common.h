@@ -168,6 +168,15 @@ struct LinearRows {
     __device__ __forceinline__ long operator()(int m) const { return m < P ? (long)m : -1L; }
 };
 
+// Output offsets for conv_epilogue_interior where a wave's 32 rows are 4 image rows of a tile of 8 columns (conv_dwpw.hip, conv_fire.hip)
+struct TileRowOffset {
+    unsigned first, rowpitch, ldy;         // element offset of the wave's first pixel, of an image row, of a pixel
+    int h_left, w_left;                    // image rows / columns that exist from the wave's first pixel on
+    __device__ __forceinline__ bool valid(int r) const { return (r >> 3) < h_left && (r & 7) < w_left; }
+    __device__ __forceinline__ unsigned lane_base(int r) const { return first + (unsigned)(r >> 3) * rowpitch + (unsigned)(r & 7) * ldy; }
+    __device__ __forceinline__ unsigned at(unsigned lb, int r) const { return lb + (unsigned)(r >> 3) * rowpitch; }   // r: a multiple of 8
+};
+
 // Orders this wave's earlier LDS accesses before its later ones (wave-private scratch: the LDS unit
 // executes one wave's instructions in order, so only the compiler has to be kept from reordering).
 __device__ __forceinline__ void wave_lds_fence() {

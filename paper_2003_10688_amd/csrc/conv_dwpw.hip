@@ -35,17 +35,8 @@ struct DwPwArgs {
     FastDiv dtw, dth;
 };
 
-// output pixels of a wave's 32 tile rows (4 image rows of 8 columns) for the shared epilogue
-struct TileRowOffset {
-    unsigned first, rowpitch, ldy;         // element offset of the wave's first pixel, of an image row, of a pixel
-    int h_left, w_left;                    // image rows / columns that exist from the wave's first pixel on
-    __device__ __forceinline__ bool valid(int r) const { return (r >> 3) < h_left && (r & 7) < w_left; }
-    __device__ __forceinline__ unsigned lane_base(int r) const { return first + (unsigned)(r >> 3) * rowpitch + (unsigned)(r & 7) * ldy; }
-    __device__ __forceinline__ unsigned at(unsigned lb, int r) const { return lb + (unsigned)(r >> 3) * rowpitch; }   // r: a multiple of 8
-};
-
-// Phase 1 for one thread: RR x TQ output pixels of four channels.  All loads of the window are issued before the first is used (and,
-// where tiles follow one another, a tile ahead); pixels outside the image are fetched out of range -> zeros.
+// Phase 1 for one thread: RR x TQ output pixels of four channels.  All loads of the window are issued before the first is used; pixels
+// outside the image are fetched out of range -> zeros.
 template <int C, int S, int RR> struct DwWindow {
     static constexpr int TQ = S == 1 ? 4 : 2, NCOL = (TQ - 1) * S + 3, NROW = (RR - 1) * S + 3;
     u32x2_t raw[NROW][NCOL];

@@ -30,21 +30,12 @@ struct FireArgs {
     FastDiv dtw, dth;
 };
 
-// output pixels of a wave's 32 tile rows (4 image rows of 8 columns) for the shared epilogue
-struct FireRowOffset {
-    unsigned first, rowpitch, ldy;
-    int h_left, w_left;                    // image rows / columns that exist from the wave's first pixel on
-    __device__ __forceinline__ bool valid(int r) const { return (r >> 3) < h_left && (r & 7) < w_left; }
-    __device__ __forceinline__ unsigned lane_base(int r) const { return first + (unsigned)(r >> 3) * rowpitch + (unsigned)(r & 7) * ldy; }
-    __device__ __forceinline__ unsigned at(unsigned lb, int r) const { return lb + (unsigned)(r >> 3) * rowpitch; }   // r: a multiple of 8
-};
-
 // ME: room for the affine constants of that many output channels of the two expands together
-template <int SP, int NS, int ME>
+template <int NS, int ME>
 __global__ void __launch_bounds__(256, 2) conv_fire_kernel(const FireArgs a) {
 #if defined(__HIP_DEVICE_COMPILE__)
     using namespace lds_pipe;
-    constexpr int ROWB = SP * 2, KS = SP / 16, SB = SP / 32;           // bytes of a patch row; k-steps of a tap; 32-channel blocks of s
+    constexpr int SP = 32, ROWB = SP * 2, KS = SP / 16;                // stored squeeze channels; bytes of a patch row; k-steps of a tap
     constexpr int NPOS = 100, PATCH = (NPOS * ROWB + 1023) / 1024 * 1024, STAGE = 64 * 128, WL = 2;
     constexpr int ST3 = (9 * SP + 63) / 64;                            // stages of a pass of the 3x3 expand: 64 reduction elements of 64 W3 rows
     constexpr int STRIPS = 4 * 32 * (32 + 4) * 4;
@@ -97,19 +88,16 @@ __global__ void __launch_bounds__(256, 2) conv_fire_kernel(const FireArgs a) {
         const __amdgpu_buffer_rsrc_t sr = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(f.ws), 0, SP * f.C * 2, 0x00020000);
         const unsigned xo = in ? (unsigned)(((int)n * f.H + ih) * f.W + iw) * (unsigned)(f.C * 2) + (unsigned)(lh * 16) : 0x80000000u;
         const unsigned so = (unsigned)lr * (unsigned)(f.C * 2) + (unsigned)(lh * 16);
-        f32x16_t acc[SB];
+        f32x16_t acc;
 #pragma unroll
-        for (int i = 0; i < SB; i++)
-#pragma unroll
-            for (int e = 0; e < 16; e++) acc[i][e] = 0.f;
+        for (int e = 0; e < 16; e++) acc[e] = 0.f;
         typedef __attribute__((ext_vector_type(4))) unsigned q_t;
-        q_t bq[2][4], aq[2][SB][4];
-        auto fetch = [&](q_t (&b)[4], q_t (&w)[SB][4], int kc) {       // 64 reduction elements of the wave's rows and of Ws
+        q_t bq[2][4], aq[2][4];
+        auto fetch = [&](q_t (&b)[4], q_t (&w)[4], int kc) {           // 64 reduction elements of the wave's rows and of Ws
 #pragma unroll
             for (int k = 0; k < 4; k++) {
                 b[k] = __builtin_amdgcn_raw_buffer_load_b128(xr, xo, kc * 128 + k * 32, 0);
-#pragma unroll
-                for (int i = 0; i < SB; i++) w[i][k] = __builtin_amdgcn_raw_buffer_load_b128(sr, so + (unsigned)(i * 32 * f.C * 2), kc * 128 + k * 32, 0);
+                w[k] = __builtin_amdgcn_raw_buffer_load_b128(sr, so, kc * 128 + k * 32, 0);
             }
         };
         const int nc = f.C >> 6;
@@ -118,14 +106,12 @@ __global__ void __launch_bounds__(256, 2) conv_fire_kernel(const FireArgs a) {
         // expands on their way to LDS (a load in front of its use is a trip to L2 on the tile's one path).  The compiler puts these in front
         // and waits for everything at every other chunk below; pinned behind the first operands, with a chunk in flight throughout, 500
         // random modules took 0.998 of the time: three workgroups on a CU cover for one another.
-        float4 sc[SB][4], sf[SB][4];
+        float4 sc[4], sf[4];
 #pragma unroll
-        for (int i = 0; i < SB; i++)
-#pragma unroll
-            for (int g = 0; g < 4; g++) {
-                sc[i][g] = *reinterpret_cast<const float4 *>(f.ss + i * 32 + 8 * g + 4 * lh);
-                sf[i][g] = *reinterpret_cast<const float4 *>(f.hs + i * 32 + 8 * g + 4 * lh);
-            }
+        for (int g = 0; g < 4; g++) {
+            sc[g] = *reinterpret_cast<const float4 *>(f.ss + 8 * g + 4 * lh);
+            sf[g] = *reinterpret_cast<const float4 *>(f.hs + 8 * g + 4 * lh);
+        }
         constexpr int CN = ME / 256;
         float c1[CN], c2[CN];
 #pragma unroll
@@ -140,9 +126,7 @@ __global__ void __launch_bounds__(256, 2) conv_fire_kernel(const FireArgs a) {
                 if (u == 0 || kc + 1 < nc) {
                     fetch(bq[u ^ 1], aq[u ^ 1], min(kc + u + 1, nc - 1));
 #pragma unroll
-                    for (int k = 0; k < 4; k++)
-#pragma unroll
-                        for (int i = 0; i < SB; i++) Mma<bf16_t>::run(acc[i], aq[u][i][k], bq[u][k]);
+                    for (int k = 0; k < 4; k++) Mma<bf16_t>::run(acc, aq[u][k], bq[u][k]);
                 }
             });
         }
@@ -152,16 +136,14 @@ __global__ void __launch_bounds__(256, 2) conv_fire_kernel(const FireArgs a) {
         const float lo = f.act_s == SOL_ACT_RELU ? 0.f : __builtin_nanf("");
         if (pos < NPOS) {
 #pragma unroll
-            for (int i = 0; i < SB; i++)
-#pragma unroll
-                for (int g = 0; g < 4; g++) {
-                    const int c = i * 32 + 8 * g + 4 * lh;
-                    const float4 a4 = sc[i][g], b4 = sf[i][g];
-                    const float v0 = __builtin_fmaxf(acc[i][4 * g] * a4.x + b4.x, lo), v1 = __builtin_fmaxf(acc[i][4 * g + 1] * a4.y + b4.y, lo);
-                    const float v2 = __builtin_fmaxf(acc[i][4 * g + 2] * a4.z + b4.z, lo), v3 = __builtin_fmaxf(acc[i][4 * g + 3] * a4.w + b4.w, lo);
-                    const uint2 u = in ? make_uint2(pack_bf16x2(v0, v1), pack_bf16x2(v2, v3)) : make_uint2(0u, 0u);
-                    *reinterpret_cast<uint2 *>(lds + pos * ROWB + (((unsigned)(c >> 3) ^ (unsigned)swz<ROWB>(pos)) << 4) + (c & 4) * 2) = u;
-                }
+            for (int g = 0; g < 4; g++) {
+                const int c = 8 * g + 4 * lh;
+                const float4 a4 = sc[g], b4 = sf[g];
+                const float v0 = __builtin_fmaxf(acc[4 * g] * a4.x + b4.x, lo), v1 = __builtin_fmaxf(acc[4 * g + 1] * a4.y + b4.y, lo);
+                const float v2 = __builtin_fmaxf(acc[4 * g + 2] * a4.z + b4.z, lo), v3 = __builtin_fmaxf(acc[4 * g + 3] * a4.w + b4.w, lo);
+                const uint2 u = in ? make_uint2(pack_bf16x2(v0, v1), pack_bf16x2(v2, v3)) : make_uint2(0u, 0u);
+                *reinterpret_cast<uint2 *>(lds + pos * ROWB + (((unsigned)(c >> 3) ^ (unsigned)swz<ROWB>(pos)) << 4) + (c & 4) * 2) = u;
+            }
         }
     }
     __syncthreads();
@@ -169,7 +151,7 @@ __global__ void __launch_bounds__(256, 2) conv_fire_kernel(const FireArgs a) {
     // ---- phase B
     const int m = wp * 32 + lr, pos0 = (m >> 3) * 10 + (m & 7);        // position of this lane's pixel under tap (0, 0)
     const unsigned fsw = swz<128>(lr), fw = lds_addr(ring) + (wc * 32 + lr) * 128;
-    const FireRowOffset ro{(unsigned)(((int)n * f.H + oh0 + wp * 4) * f.W + ow0) * (unsigned)f.ldy, (unsigned)f.W * (unsigned)f.ldy, (unsigned)f.ldy,
+    const TileRowOffset ro{(unsigned)(((int)n * f.H + oh0 + wp * 4) * f.W + ow0) * (unsigned)f.ldy, (unsigned)f.W * (unsigned)f.ldy, (unsigned)f.ldy,
                            f.H - oh0 - wp * 4, f.W - ow0};
     ResidualRegs<bf16_t, 1, 1> nores;
     nores.on = false;
@@ -255,8 +237,8 @@ sol_status launch_conv_fire(const FireLaunch &f, hipStream_t st) {
     a.Kp3 = (int)round_up((size_t)9 * f.SP, 64);
     a.dtw = FastDiv((uint32_t)a.tw); a.dth = FastDiv((uint32_t)a.th);
     const dim3 grid(((a.ntiles + 7) / 8) * 8);
-    if (f.E1 + f.E3 <= 256) hipLaunchKernelGGL((conv_fire_kernel<32, 3, 256>), grid, dim3(256), 0, st, a);   // 53 KB: three workgroups per CU
-    else hipLaunchKernelGGL((conv_fire_kernel<32, 3, 512>), grid, dim3(256), 0, st, a);
+    if (f.E1 + f.E3 <= 256) hipLaunchKernelGGL((conv_fire_kernel<3, 256>), grid, dim3(256), 0, st, a);   // 53 KB: three workgroups per CU
+    else hipLaunchKernelGGL((conv_fire_kernel<3, 512>), grid, dim3(256), 0, st, a);
     SOL_HIP(hipGetLastError());
     return SOL_OK;
 }

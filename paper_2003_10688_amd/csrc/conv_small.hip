@@ -1,8 +1,8 @@
-// Convolution of an image of up to four channels on the vector units (gfx950): the first layer of a network.
+// 3x3 convolution of an image of three channels on the vector units (gfx950): the first layer of a network.
 //
 // With three input channels a filter tap is no run that a matrix instruction could take from memory, and the gather kernel pays
-// for building one -- per element a division, an address, a range check, a 4-byte load and a 4-byte LDS store, 9.5 us for a layer of
-// one 32x32 image.  Here a thread computes TR x PX output pixels of NCH channels: the pixels of its window are loaded whole and zero-filled by the range check, every lane of a wave has the same
+// for building one: per element a division, an address, a range check, a 4-byte load and a 4-byte LDS store.  Here a thread computes
+// TR x PX output pixels of NCH channels: the pixels of its window are loaded whole and zero-filled by the range check, every lane of a wave has the same
 // channels, so the filter comes by scalar loads and stands in scalar registers, and there is neither LDS nor a barrier.  fp32 products on
 // the vector units run at half the rate of the fp32 matrix instructions (which is 1/16 of bf16's), and nothing is multiplied
 // that is padding of the reduction: 27 products instead of 32.
@@ -21,24 +21,19 @@ struct SmallArgs {
     FastDiv dcols, drows;
 };
 
-template <typename T, int C> struct PixelIn;               // C channels of one pixel; offset >= 2^31: zeros
-template <int C> struct PixelIn<float, C> {
-    static __device__ __forceinline__ void load(const __amdgpu_buffer_rsrc_t &r, unsigned off, float v[C]) {
-        if constexpr (C == 3) {
-            const auto u = __builtin_amdgcn_raw_buffer_load_b96(r, off, 0, 0);
-            v[0] = __uint_as_float(u[0]); v[1] = __uint_as_float(u[1]); v[2] = __uint_as_float(u[2]);
-        } else {
+constexpr int C = 3, R = 3;                // input channels; filter rows and columns
+constexpr int TR = 2, PX = 2, NCH = 4;     // output rows, columns and channels of a thread
+
+// the channels of one pixel; offset >= 2^31: zeros
+template <typename T> __device__ __forceinline__ void load_pixel(const __amdgpu_buffer_rsrc_t &r, unsigned off, float v[C]);
+template <> __device__ __forceinline__ void load_pixel<float>(const __amdgpu_buffer_rsrc_t &r, unsigned off, float v[C]) {
+    const auto u = __builtin_amdgcn_raw_buffer_load_b96(r, off, 0, 0);
+    v[0] = __uint_as_float(u[0]); v[1] = __uint_as_float(u[1]); v[2] = __uint_as_float(u[2]);
+}
+template <> __device__ __forceinline__ void load_pixel<bf16_t>(const __amdgpu_buffer_rsrc_t &r, unsigned off, float v[C]) {
 #pragma unroll
-            for (int c = 0; c < C; c++) v[c] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, off + 4u * c, 0, 0));
-        }
-    }
-};
-template <int C> struct PixelIn<bf16_t, C> {
-    static __device__ __forceinline__ void load(const __amdgpu_buffer_rsrc_t &r, unsigned off, float v[C]) {
-#pragma unroll
-        for (int c = 0; c < C; c++) v[c] = bf16_to_f32((bf16_t)__builtin_amdgcn_raw_buffer_load_b16(r, off + 2u * c, 0, 0));
-    }
-};
+    for (int c = 0; c < C; c++) v[c] = bf16_to_f32((bf16_t)__builtin_amdgcn_raw_buffer_load_b16(r, off + 2u * c, 0, 0));
+}
 // element i of a packed filter row at a wave-uniform address
 template <typename T> __device__ __forceinline__ float filter_at(const T *row, int i);
 template <> __device__ __forceinline__ float filter_at<float>(const float *row, int i) { return row[i]; }
@@ -47,8 +42,7 @@ template <> __device__ __forceinline__ float filter_at<bf16_t>(const bf16_t *row
     return __uint_as_float((i & 1) ? u & 0xffff0000u : u << 16);
 }
 
-// R x R filter, stride SH; TR x PX output pixels x NCH channels per thread (TR = 2, PX even where a 2x2 pool is fused)
-template <typename T, int C, int R, int SH, int TR, int PX, int NCH>
+template <typename T, int SH>              // SH: stride
 __global__ void __launch_bounds__(256) conv_small_kernel(const SmallArgs s) {
 #if defined(__HIP_DEVICE_COMPILE__)
     constexpr int ES = (int)sizeof(T), NCOL = (PX - 1) * SH + R, NROW = (TR - 1) * SH + R;
@@ -74,7 +68,7 @@ __global__ void __launch_bounds__(256) conv_small_kernel(const SmallArgs s) {
         const int ih = oh * SH - a.ph + j;
         const unsigned rb = (unsigned)ih < (unsigned)a.H ? (unsigned)((int)n * a.H + ih) * (unsigned)(a.W * C * ES) : 0x80000000u;
 #pragma unroll
-        for (int c = 0; c < NCOL; c++) PixelIn<T, C>::load(xr, max(rb + coff[c], max(rb, coff[c])), v[c]);   // both out: the sum wraps, the maximum does not
+        for (int c = 0; c < NCOL; c++) load_pixel<T>(xr, max(rb + coff[c], max(rb, coff[c])), v[c]);   // both out: the sum wraps, the maximum does not
     };
     float acc[TR][PX][NCH];
 #pragma unroll
@@ -126,7 +120,7 @@ __global__ void __launch_bounds__(256) conv_small_kernel(const SmallArgs s) {
             else *reinterpret_cast<uint2 *>(p + e) = make_uint2(pack_bf16x2(v[e], v[e + 1]), pack_bf16x2(v[e + 2], v[e + 3]));
         }
     };
-    if constexpr (TR == 2 && PX % 2 == 0 && SH == 1) {
+    if constexpr (SH == 1) {               // a thread's pixels are a window of a fused 2x2 pool
         if (a.pool) {
 #pragma unroll
             for (int t = 0; t < PX; t += 2) {
@@ -181,20 +175,20 @@ bool small_kernel_applies(const ConvArgs &a, int dt) {
     return !gather_kernel_pays(a, dt) && (double)a.N * a.H * a.W * a.C * dtype_size(dt) < 2147483648.0;
 }
 
-template <typename T, int R, int SH, int TR, int PX, int NCH> static void launch_small_cfg(const ConvArgs &a, hipStream_t st) {
+template <typename T, int SH> static void launch_small_cfg(const ConvArgs &a, hipStream_t st) {
     SmallArgs s;
     s.c = a;
     s.rows = ceil_div(a.pool ? 2 * a.Hy : a.Ho, TR);
     s.cols = ceil_div(a.pool ? 2 * a.Wy : a.Wo, PX);
     s.strips = a.N * s.rows * s.cols;
     s.dcols = FastDiv((uint32_t)s.cols); s.drows = FastDiv((uint32_t)s.rows);
-    hipLaunchKernelGGL((conv_small_kernel<T, 3, R, SH, TR, PX, NCH>), dim3(ceil_div(s.strips, 64), ceil_div(a.Cout, 4 * NCH)), dim3(256), 0, st, s);
+    hipLaunchKernelGGL((conv_small_kernel<T, SH>), dim3(ceil_div(s.strips, 64), ceil_div(a.Cout, 4 * NCH)), dim3(256), 0, st, s);
 }
 
 sol_status launch_conv_small(const ConvArgs &a, int dt, hipStream_t st) {
-    if (a.sh == 2) launch_small_cfg<float, 3, 2, 2, 2, 4>(a, st);
-    else if (dt == SOL_BF16) launch_small_cfg<bf16_t, 3, 1, 2, 2, 4>(a, st);
-    else launch_small_cfg<float, 3, 1, 2, 2, 4>(a, st);
+    if (a.sh == 2) launch_small_cfg<float, 2>(a, st);
+    else if (dt == SOL_BF16) launch_small_cfg<bf16_t, 1>(a, st);
+    else launch_small_cfg<float, 1>(a, st);
     SOL_HIP(hipGetLastError());
     return SOL_OK;
 }
