@@ -36,3 +36,22 @@ def test_same_bits_as_the_ring_kernel(cin, spec, n, hw):
         got[tile] = [y] + [(net.layer_preact(i) if l["bn"] else net.layer_output(i)).clone() for i, l in enumerate(layers) if l["kind"] == "conv"]
     for a, b in zip(got[0], got[RING_64x64]):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("cin,spec,n,hw,kernel", [
+    (32, dict(cout=64, k=3), 3, 13, "chain"), (64, dict(cout=96, k=3, s=2), 3, 13, "chain"), (96, dict(cout=128, k=1, p=0), 3, 7, "chain"),
+    (128, dict(cout=33, k=3), 2, 17, "chain"), (64, dict(cout=160, k=5), 5, 5, "chain"), (512, dict(cout=512, k=3), 9, 4, "chain"),
+    (64, dict(cout=64, k=3), 4, 43, "chain"), (64, dict(cout=64, k=3), 5, 43, ""),        # 1852 and 2312 blocks of 16 x 16
+    (48, dict(cout=64, k=3), 3, 13, ""), (64, dict(cout=32, k=3), 3, 13, ""), (64, dict(cout=64, k=1, p=0), 3, 13, "")])
+def test_which_kernel(cin, spec, n, hw, kernel):
+    """The layers that the ring kernel's 64x64 tile with 128-byte stages would run, of up to 2048 blocks; a tile asked for is used."""
+    layers = [wl.conv(**spec), wl.gap()]
+    net = sol.Network(layers, (n, cin, hw, hw), sol.F32, flags=sol.NET_TRAINING)
+    net.set_params(wl.make_params(layers, cin, 11, False, 0.1))
+    x = torch.ones((n, hw, hw, cin), device="cuda:0")
+    net.forward(x)
+    assert sol.sol_debug_conv_kernel() == kernel
+    net.set_tiles({0: 5})
+    net.forward(x)
+    torch.cuda.synchronize()
+    assert sol.sol_debug_conv_kernel() == ""

@@ -37,6 +37,9 @@ def test_pre_activation_1x1(sol, case):  # noqa: F811
     net.forward(sol.to_device_nhwc(x, sol.BF16))
     torch.cuda.synchronize()
     i = len(layers) - 2
+    net.run_layer(i, sol.to_device_nhwc(x, sol.BF16))
+    torch.cuda.synchronize()
+    assert sol.sol_debug_conv_kernel() == "pre"
     assert rel_err(sol.to_host_nchw(net.layer_output(i)).reshape(outs[i].shape), outs[i]) <= TOL["bf16"]
 
 
@@ -52,6 +55,23 @@ def test_prefix_of_a_wider_tensor(sol):  # noqa: F811
     cd = sol.ConvDesc(K, C, 1, 1, 1, 1, 0, 0)
     wp = sol.sol_pack_conv_weights(cd, sol.BF16, sol.dev_f32(w))
     y = sol.sol_conv2d_preact_fused(xd, cd, wp, sol.dev_f32(ps), sol.dev_f32(ph), channels=C)
+    assert sol.sol_debug_conv_kernel() == "pre"
     t = (xd[..., :C].float() * sol.dev_f32(ps) + sol.dev_f32(ph)).relu().to(torch.bfloat16).double()
     want = t.reshape(-1, C) @ torch.from_numpy(w).cuda().to(torch.bfloat16).double().reshape(K, C).T
     assert rel_err(y.float().cpu().numpy().reshape(-1, K), want.cpu().numpy()) <= TOL["bf16"]
+
+
+@pytest.mark.parametrize("c,k,tile,kernel", [(128, 128, 0, "pre"), (128, 128, 2, ""), (96, 128, 0, ""), (128, 96, 0, ""), (1024, 128, 0, "pre"), (1088, 128, 0, "")])
+def test_which_kernel(sol, c, k, tile, kernel):  # noqa: F811
+    """Whole 64-channel chunks up to 1024, multiples of 128 filters, no tile asked for; what the register-staged kernel computes, bit for bit."""
+    layers = [wl.conv(k, 1, p=0, act="none", bn=False, pre_bn=True)]
+    net = sol.Network(layers, (2, c, 9, 7), sol.BF16)
+    net.set_params(wl.make_params(layers, c, 3, bf16=True, bias_std=0.3))
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(c)
+    x = torch.randn((2, 9, 7, c), generator=gen, device="cuda:0").bfloat16()
+    net.set_tiles({0: tile})
+    y = net.forward(x).clone()
+    assert sol.sol_debug_conv_kernel() == kernel
+    net.set_tiles({0: 99})
+    assert torch.equal(y, net.forward(x)) and sol.sol_debug_conv_kernel() == ""
