@@ -171,3 +171,29 @@ def test_dense_layer_static_workspace(sol):  # noqa: F811
     net.workspace = net.workspace[:net.workspace.numel() - 32 * 56 * 56 * 128 * 2]      # one launch: accepted, and left alone by the auto-tuner
     net.set_dense(2, 1)
     assert torch.equal(net.forward(x), y) and net.autotune(x, reps=1)["2d"] == 1
+
+
+@pytest.mark.parametrize("variant", [91, 92, 93, 94, 95, 96])
+@pytest.mark.parametrize("C", [64, 128, 192, 224, 256, 320, 384, 448, 576])
+def test_dense_layer_chunk_counts(sol, C, variant):  # noqa: F811
+    """Every number of chunks that the pipeline of x chunks and weight stages starts and drains differently for: fewer than are in flight,
+    and each remainder of the register sets behind whole turns of them.  Two rows of images, so that patches reach over their borders."""
+    layers = [wl.conv(C, 1, p=0), wl.conv(128, 1, p=0, src=0, pre_bn=True), wl.conv(32, 3, bn=False, act="none"), wl.concat(0, 2),
+              wl.conv(8, 1, p=0, bn=False, act="none")]
+    rng = np.random.default_rng([variant, C])
+    x = wl.to_bf16_grid(rng.standard_normal((3, 64, 9, 10)))
+    prm = wl.make_params(layers, 64, 5 + C, bf16=True, bias_std=0.3)
+    outs, _ = orc.network_forward(layers, prm, x, bf16=True, return_all=True)
+    net = sol.Network(layers, x.shape, sol.BF16)
+    net.set_params(prm)
+    net.workspace.fill_(0xff)
+    xd = sol.to_device_nhwc(x, sol.BF16)
+    net.forward(xd)
+    assert net.fused_into(1) == 2
+    sol.sol_debug_set_conv_tile(variant)
+    try:
+        net.run_layer(2, xd)
+    finally:
+        sol.sol_debug_set_conv_tile(0)
+    torch.cuda.synchronize()
+    assert rel_err(sol.to_host_nchw(net.layer_output(3)), outs[3]) <= TOL["bf16"]
