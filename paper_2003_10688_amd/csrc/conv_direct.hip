@@ -13,6 +13,12 @@
 // Measured (layer behind 96 MB of other weights; us before -> now): bf16 3x3 512->512 at 7x7, batch 1: 60.3 -> 6.1, batch 8:
 // 30.7 -> 8.8, batch 32: 24.4 -> 18.0; 3x3 256->256 at 14x14, batch 1: 21.5 -> 4.7; 1x1 2048->512 at 7x7, batch 1: 14.6 -> 4.5;
 // fp32 3x3 512->512 at 7x7, batch 1: 107 -> 11.5, batch 8: 99 -> 25.
+// What a launch of one or two stages per wave spends its time on is the way to the first load and the way from the last product to the
+// store (an empty kernel 1.7 us, these 3.7 with warm weights): integer divisions for the tile and the first tap, some 380 instructions
+// before the first load, a round trip for scale and shift and, for the residual, one per element.  With the divisors as
+// multiplications, the weights requested before the pixels' addresses are worked out and the epilogue's operands on their way through the
+// whole reduction: ResNet-50-shaped pass, batch 1, 256.3 -> 244.7 us; ResNet-18-shaped, 13 images of 193x193, 210.0 -> 205.0; fp32,
+// ResNet-50-shaped, batch 8, 1118 -> 1096.
 //
 // fp32 runs the same 64-byte steps as four v_mfma_f32_16x16x4_f32 (true fp32 multiplies), whose reduction order inside a
 // step is permuted identically for both operands.
@@ -34,9 +40,15 @@ struct DirectPair {
     int H, W, C, Kp, stride;
 };
 
+// what the workgroups would otherwise divide for one after the other before their first load (some forty instructions each)
+struct DirectGeom {
+    FastDiv cpx, ntc, cps, S;              // cpx: of ConvArgs, 1 if that is 0; cps: stages per filter tap
+    unsigned taprows;                      // bit r * S for every filter row r
+};
+
 // PB x CB: 16-pixel x 16-channel blocks of the tile; NW waves split the reduction; NS: ring stages of each wave
 template <typename T, int PB, int CB, int NW, int NS, bool PAIR>
-__global__ void __launch_bounds__(NW * 64) conv_direct_kernel(const ConvArgs a, const DirectPair q) {
+__global__ void __launch_bounds__(NW * 64) conv_direct_kernel(const ConvArgs a, const DirectPair q, const DirectGeom g) {
 #if defined(__HIP_DEVICE_COMPILE__)
     using namespace lds_pipe;
     constexpr int ES = (int)sizeof(T), BP = PB * 16, BC = CB * 16;
@@ -47,6 +59,11 @@ __global__ void __launch_bounds__(NW * 64) conv_direct_kernel(const ConvArgs a, 
     static_assert(RING <= 160 * 1024 && (NS - 1) * L < 64, "LDS, vmcnt");
     __shared__ __align__(1024) unsigned char lds[RING > REDB ? RING : REDB];
 
+    // every kernel argument the prologue needs, fetched in one batch
+    asm volatile("" ::"s"(a.x), "s"(a.w), "s"(a.scale), "s"(a.shift), "s"(a.res), "s"(a.P), "s"(a.C), "s"(a.Cout), "s"(a.H), "s"(a.W), "s"(a.Kp),
+                 "s"(a.cpx), "s"(a.dw.mul), "s"(a.dh.mul), "s"(a.sh), "s"(a.pool), "s"(a.ph), "s"(g.cpx.mul), "s"(g.ntc.mul), "s"(g.cps.mul), "s"(g.S.mul), "s"(g.taprows));
+    if constexpr (PAIR) asm volatile("" ::"s"(q.x), "s"(q.w), "s"(q.scale), "s"(q.shift), "s"(q.H), "s"(q.W), "s"(q.C), "s"(q.Kp), "s"(q.stride));
+
     const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lg = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lslot = lane & 7, lrow = lane >> 3;
@@ -55,13 +72,16 @@ __global__ void __launch_bounds__(NW * 64) conv_direct_kernel(const ConvArgs a, 
     const int xcd = (int)(blockIdx.x & 7);
     int tile;
     if (a.cpx > 0) {
-        const int j = (int)(blockIdx.x >> 3);
-        tile = (j / a.cpx) * a.ntc + xcd * a.cpx + j % a.cpx;
+        uint32_t j, c;
+        g.cpx.divmod(blockIdx.x >> 3, j, c);
+        tile = (int)j * a.ntc + xcd * a.cpx + (int)c;
     } else {
         tile = xcd * ((a.ntiles + 7) >> 3) + (int)(blockIdx.x >> 3);
     }
     if (tile >= a.ntiles) return;
-    const int p0 = (tile / a.ntc) * BP, c0 = (tile % a.ntc) * BC;
+    uint32_t ptile, ctile;
+    g.ntc.divmod((uint32_t)tile, ptile, ctile);
+    const int p0 = (int)ptile * BP, c0 = (int)ctile * BC;
 
     // the activation resource starts `bias` bytes early so that window origins in the padding have offsets >= 0; padding
     // taps and rows beyond the tensor get an out-of-range offset, which the hardware answers with zeros
@@ -73,7 +93,77 @@ __global__ void __launch_bounds__(NW * 64) conv_direct_kernel(const ConvArgs a, 
     const __amdgpu_buffer_rsrc_t xnull = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(a.x), 0, 0, 0x00020000);
     const __amdgpu_buffer_rsrc_t wnull = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(a.w), 0, 0, 0x00020000);
 
-    unsigned xo[XL], xinv[XL], wo[WL];                     // this lane's rows; bit t of xinv: filter tap t reads padding
+    // this wave's run of stages [s0, s1); a stage is 128 bytes of one filter tap of every row
+    const int nmain = a.R * a.S * (int)g.cps.d, nsteps = nmain + (PAIR ? q.C * ES / ROWB : 0);
+    const int s0 = (int)((long)nsteps * wave / NW), s1 = (int)((long)nsteps * (wave + 1) / NW);
+    unsigned char *ring = lds + wave * (NS * STAGE);
+    const unsigned x2bytes = PAIR ? (unsigned)a.N * q.H * q.W * q.C * ES : 0u, w2bytes = PAIR ? (unsigned)a.Cout * q.Kp * ES : 0u;
+
+    // The weights go first: their addresses are cheap, and inside a network they come from the farthest memory.
+    unsigned wo[WL], wo2[WL];                              // this lane's rows (wo2: of a projection pair's second convolution)
+#pragma unroll
+    for (int i = 0; i < WL; i++) {
+        const int row = i * 8 + lrow, co = c0 + row;
+        wo[i] = co < a.Cout ? (unsigned)(co * a.Kp) * ES + ((lslot ^ swz<ROWB>(row)) << 4) : 0xffffffffu;
+        if constexpr (PAIR) wo2[i] = co < a.Cout ? (unsigned)(co * q.Kp) * ES + ((lslot ^ swz<ROWB>(row)) << 4) : 0xffffffffu;
+    }
+    auto issue_w = [&](int buf, int s) {                   // weights of stage s into ring slot buf; beyond s1 through a size-0 resource -> zeros
+        const bool real = s < s1;
+        unsigned char *lw = ring + buf * STAGE + BP * ROWB;
+        if constexpr (PAIR) {                              // both convolutions are 1x1: stage s is chunk s of the main or chunk s - nmain of the shortcut
+            const bool second = s >= nmain;
+            const __amdgpu_buffer_rsrc_t wq = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(second ? q.w : a.w), 0, (int)(!real ? 0u : second ? w2bytes : wbytes), 0x00020000);
+#pragma unroll
+            for (int i = 0; i < WL; i++)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(wq, (__attribute__((address_space(3))) void *)(lw + i * 1024), 16, second ? wo2[i] : wo[i],
+                                                         (unsigned)(second ? s - nmain : s) * ROWB, 0, 0);
+        } else {
+#pragma unroll
+            for (int i = 0; i < WL; i++)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(real ? wr : wnull, (__attribute__((address_space(3))) void *)(lw + i * 1024), 16, wo[i], (unsigned)s * ROWB, 0, 0);
+        }
+    };
+    const bool any = s0 < s1;
+    if (any) static_for<NS>([&](auto B) { issue_w(decltype(B)::value, s0 + decltype(B)::value); });
+    keep_order();
+
+    // Epilogue operands of this thread's four channels and IT pixels, behind the weights and ahead of the pixels (the loop's counts of
+    // outstanding loads then need not know of them).  Loaded where they are used they cost a round trip, and the residual, whose
+    // ragged form reads element by element, four more.
+    constexpr int IT = PB * CB > 4 ? PB * CB / 4 : 1;      // pixels per thread without a pool
+    static_assert(NW == 4 && (NW * 64) % (BC / 4) == 0, "a thread keeps its channels");
+    const bool vec = (a.Cout & 3) == 0 && a.Cout <= 1 << 22;
+    typedef __attribute__((ext_vector_type(ES == 2 ? 2 : 4))) unsigned ResVec;
+    const int ecg = tid % (BC / 4), epx = tid / (BC / 4);
+    u32x4_t esc, esf, esf2, psc[PAIR ? CB : 1], psc2[PAIR ? CB : 1];
+    ResVec eres[IT];
+    {
+        auto floats = [&](const float *p) { return __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p), 0, vec && p ? a.Cout * 4 : 0, 0x00020000); };
+        const unsigned co = (unsigned)(c0 + ecg * 4) * 4u;
+        esf = __builtin_amdgcn_raw_buffer_load_b128(floats(a.shift), co, 0, 0);
+        if constexpr (PAIR) {
+            esf2 = __builtin_amdgcn_raw_buffer_load_b128(floats(q.shift), co, 0, 0);
+#pragma unroll
+            for (int i = 0; i < CB; i++) {                 // of the channels of this lane's accumulators
+                psc[i] = __builtin_amdgcn_raw_buffer_load_b128(floats(a.scale), (unsigned)(c0 + i * 16 + lg * 4) * 4u, 0, 0);
+                psc2[i] = __builtin_amdgcn_raw_buffer_load_b128(floats(q.scale), (unsigned)(c0 + i * 16 + lg * 4) * 4u, 0, 0);
+            }
+        } else {
+            esc = __builtin_amdgcn_raw_buffer_load_b128(floats(a.scale), co, 0, 0);
+        }
+        if (a.res && vec) {
+            const __amdgpu_buffer_rsrc_t rr = __builtin_amdgcn_make_buffer_rsrc(const_cast<T *>(static_cast<const T *>(a.res) + (size_t)p0 * a.Cout), 0,
+                                                                                (int)((unsigned)min(BP, a.P - p0) * (unsigned)a.Cout * ES), 0x00020000);
+#pragma unroll
+            for (int u = 0; u < IT; u++) {
+                const unsigned o = ((unsigned)(epx + u * (NW * 64 / (BC / 4))) * (unsigned)a.Cout + (unsigned)(c0 + ecg * 4)) * ES;
+                if constexpr (ES == 2) eres[u] = __builtin_amdgcn_raw_buffer_load_b64(rr, o, 0, 0); else eres[u] = __builtin_amdgcn_raw_buffer_load_b128(rr, o, 0, 0);
+            }
+        }
+    }
+    keep_order();
+
+    unsigned xo[XL], xinv[XL], xo2[XL];                    // this lane's rows; bit t of xinv: filter tap t reads padding
 #pragma unroll
     for (int i = 0; i < XL; i++) {
         const int row = i * 8 + lrow, m = p0 + row;
@@ -83,63 +173,31 @@ __global__ void __launch_bounds__(NW * 64) conv_direct_kernel(const ConvArgs a, 
         const unsigned off = (unsigned)(((n * a.H + ih0) * a.W + iw0) * a.C) * ES + bias + ((lslot ^ swz<ROWB>(row)) << 4);
         const int slo = max(0, -iw0), shi = min(a.S, a.W - iw0), rlo = max(0, -ih0), rhi = min(a.R, a.H - ih0);
         const unsigned cval = shi > slo ? (unsigned)((1ull << shi) - 1ull) & ~((1u << slo) - 1u) : 0u;
-        unsigned val = 0;
-        for (int r = 0; r < a.R; r++) val |= (r >= rlo && r < rhi) ? cval << (r * a.S) : 0u;
+        // filter rows [rlo, rhi) as bits r * S; times the columns' bits, of which a row has S: no carries
+        const unsigned rval = rhi > rlo ? g.taprows & (unsigned)((1ull << (rhi * a.S)) - (1ull << (rlo * a.S))) : 0u;
         xo[i] = m < a.P ? off : 0xffffffffu;
-        xinv[i] = ~val;
+        xinv[i] = ~(cval * rval);
+        if constexpr (PAIR) xo2[i] = m < a.P ? (unsigned)(((n * q.H + op * q.stride) * q.W + oq * q.stride) * q.C) * ES + ((lslot ^ swz<ROWB>(row)) << 4) : 0xffffffffu;
     }
-#pragma unroll
-    for (int i = 0; i < WL; i++) {
-        const int row = i * 8 + lrow, co = c0 + row;
-        wo[i] = co < a.Cout ? (unsigned)(co * a.Kp) * ES + ((lslot ^ swz<ROWB>(row)) << 4) : 0xffffffffu;
-    }
-
-    // projection pair: rows of the shortcut's operands (the main convolution is 1x1 then: no taps)
-    unsigned xo2[XL], wo2[WL];
-    const unsigned x2bytes = PAIR ? (unsigned)a.N * q.H * q.W * q.C * ES : 0u, w2bytes = PAIR ? (unsigned)a.Cout * q.Kp * ES : 0u;
-    if constexpr (PAIR) {
-#pragma unroll
-        for (int i = 0; i < XL; i++) {
-            const int row = i * 8 + lrow, m = p0 + row;
-            int n, op, oq;
-            decode_pixel(a, m, n, op, oq);
-            xo2[i] = m < a.P ? (unsigned)(((n * q.H + op * q.stride) * q.W + oq * q.stride) * q.C) * ES + ((lslot ^ swz<ROWB>(row)) << 4) : 0xffffffffu;
-        }
-#pragma unroll
-        for (int i = 0; i < WL; i++) {
-            const int row = i * 8 + lrow, co = c0 + row;
-            wo2[i] = co < a.Cout ? (unsigned)(co * q.Kp) * ES + ((lslot ^ swz<ROWB>(row)) << 4) : 0xffffffffu;
-        }
-    }
-
-    // this wave's run of stages [s0, s1); a stage is 128 bytes of one filter tap of every row
-    const int cps = a.C * ES / ROWB, nmain = a.R * a.S * cps, nsteps = nmain + (PAIR ? q.C * ES / ROWB : 0);
-    const int s0 = (int)((long)nsteps * wave / NW), s1 = (int)((long)nsteps * (wave + 1) / NW);
-    int s = s0, tap = s0 / cps, tc = s0 - tap * cps;
-    int tr = tap / a.S, ts = tap - tr * a.S;
-    unsigned char *ring = lds + wave * (NS * STAGE);
-
-    auto issue = [&](int buf) {                            // next stage into ring slot buf; beyond s1 through a size-0 resource -> zeros
+    uint32_t utap, utc, utr, uts;
+    g.cps.divmod((uint32_t)s0, utap, utc);
+    g.S.divmod(utap, utr, uts);
+    const int cps = (int)g.cps.d;
+    int s = s0, tap = (int)utap, tc = (int)utc, tr = (int)utr, ts = (int)uts;
+    auto issue_x = [&](int buf) {                          // pixels of the next stage into ring slot buf
         const bool real = s < s1;
-        const unsigned xs = (unsigned)((tr * a.W + ts) * a.C) * ES + (unsigned)tc * ROWB, ws = (unsigned)s * ROWB;
-        unsigned char *lx = ring + buf * STAGE, *lw = lx + BP * ROWB;
-        if constexpr (PAIR) {                              // both convolutions are 1x1: stage s is chunk s of the main or chunk s - nmain of the shortcut
+        unsigned char *lx = ring + buf * STAGE;
+        if constexpr (PAIR) {
             const bool second = s >= nmain;
-            const unsigned off = (unsigned)(second ? s - nmain : s) * ROWB;
-            const __amdgpu_buffer_rsrc_t wq = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(second ? q.w : a.w), 0, (int)(!real ? 0u : second ? w2bytes : wbytes), 0x00020000);
             const __amdgpu_buffer_rsrc_t xq = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(second ? q.x : a.x), 0, (int)(!real ? 0u : second ? x2bytes : xbytes), 0x00020000);
 #pragma unroll
-            for (int i = 0; i < WL; i++)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(wq, (__attribute__((address_space(3))) void *)(lw + i * 1024), 16, second ? wo2[i] : wo[i], off, 0, 0);
-#pragma unroll
             for (int i = 0; i < XL; i++)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(xq, (__attribute__((address_space(3))) void *)(lx + i * 1024), 16, second ? xo2[i] : xo[i], off, 0, 0);
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(xq, (__attribute__((address_space(3))) void *)(lx + i * 1024), 16, second ? xo2[i] : xo[i],
+                                                         (unsigned)(second ? s - nmain : s) * ROWB, 0, 0);
             ++s;
             return;
         }
-#pragma unroll
-        for (int i = 0; i < WL; i++)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(real ? wr : wnull, (__attribute__((address_space(3))) void *)(lw + i * 1024), 16, wo[i], ws, 0, 0);
+        const unsigned xs = (unsigned)((tr * a.W + ts) * a.C) * ES + (unsigned)tc * ROWB;
 #pragma unroll
         for (int i = 0; i < XL; i++) {
             const unsigned off = xo[i] | (unsigned)__builtin_amdgcn_sbfe(xinv[i], tap, 1);
@@ -157,12 +215,13 @@ __global__ void __launch_bounds__(NW * 64) conv_direct_kernel(const ConvArgs a, 
     const unsigned fsw = swz<ROWB>(lr);                    // block row bases are multiples of 16: the swizzle depends on lr only
     const unsigned f0 = lds_addr(ring) + lr * ROWB + ((lg ^ fsw) << 4), f1 = lds_addr(ring) + lr * ROWB + (((lg + 4) ^ fsw) << 4);
 
-    if (s0 < s1) {
-        static_for<NS>([&](auto B) { issue(decltype(B)::value); });
+    if (any) {
+        static_for<NS>([&](auto B) { issue_x(decltype(B)::value); });
         int buf = 0;
-        for (int k = s0; k < s1; k++) {
-            // stage k has landed once only the NS - 1 stages issued after it are outstanding (the ring is this wave's own: no barrier)
-            wait_vmcnt<(NS - 1) * L>();
+        // Stage k has landed once only what was issued after its pixels is outstanding (the ring is this wave's own: no barrier): the
+        // pixels alone of the other stages that the loop found under way, and the stages that it issued.
+        auto stage = [&](int k, auto OUTSTANDING) {
+            wait_vmcnt<decltype(OUTSTANDING)::value>();
             u32x4_t fw[2][CB], fx[2][PB];
             const unsigned b0 = f0 + buf * STAGE, b1 = f1 + buf * STAGE;
             static_for<CB>([&](auto I) { lds_read16<BP * ROWB + decltype(I)::value * 16 * ROWB>(fw[0][decltype(I)::value], b0); });
@@ -174,7 +233,8 @@ __global__ void __launch_bounds__(NW * 64) conv_direct_kernel(const ConvArgs a, 
                 static_for<CB>([&](auto I) { landed(fw[decltype(H)::value][decltype(I)::value]); });
                 static_for<PB>([&](auto J) { landed(fx[decltype(H)::value][decltype(J)::value]); });
             });
-            issue(buf);                                    // the slot's data is in registers: refill it
+            issue_w(buf, s);                               // the slot's data is in registers: refill it
+            issue_x(buf);
             auto contract = [&](f32x4_t (&to)[CB][PB]) {
 #pragma unroll
                 for (int h = 0; h < 2; h++)
@@ -185,7 +245,14 @@ __global__ void __launch_bounds__(NW * 64) conv_direct_kernel(const ConvArgs a, 
             };
             if (PAIR && k >= nmain) contract(acc2); else contract(acc);
             buf = buf + 1 == NS ? 0 : buf + 1;
+        };
+        stage(s0, std::integral_constant<int, (NS - 1) * XL>{});
+        int k = s0 + 1;
+        if constexpr (NS > 2) {
+            static_assert(NS <= 3, "a wait for every stage under way");
+            if (k < s1) stage(k++, std::integral_constant<int, (NS - 2) * XL + L>{});
         }
+        for (; k < s1; k++) stage(k, std::integral_constant<int, (NS - 1) * L>{});
         wait_vmcnt<0>();                                   // the zero-fill DMAs of the tail
     }
     if constexpr (PAIR) {                                  // fold the two sums: their scales differ, so they meet here; the shifts follow in the epilogue
@@ -194,7 +261,8 @@ __global__ void __launch_bounds__(NW * 64) conv_direct_kernel(const ConvArgs a, 
 #pragma unroll
             for (int e = 0; e < 4; e++) {
                 const int co = c0 + i * 16 + lg * 4 + e, cc = co < a.Cout ? co : 0;
-                const float sm = a.scale ? a.scale[cc] : 1.f, ss = q.scale ? q.scale[cc] : 1.f;
+                const float sm = !a.scale ? 1.f : vec ? __uint_as_float(psc[i][e]) : a.scale[cc];
+                const float ss = !q.scale ? 1.f : vec ? __uint_as_float(psc2[i][e]) : q.scale[cc];
 #pragma unroll
                 for (int j = 0; j < PB; j++) acc[i][j][e] = acc[i][j][e] * sm + acc2[i][j][e] * ss;
             }
@@ -214,18 +282,26 @@ __global__ void __launch_bounds__(NW * 64) conv_direct_kernel(const ConvArgs a, 
     // four channels of one pixel (of one pooling window) per thread, channels fastest
     T *__restrict__ yg = static_cast<T *>(a.y);
     const T *__restrict__ resg = static_cast<const T *>(a.res);
-    const int npix = a.pool ? BP / 4 : BP;
-    for (int it = tid; it < npix * (BC / 4); it += NW * 64) {
-        const int cg = it % (BC / 4), px = it / (BC / 4), cb = c0 + cg * 4;
-        const int nv = min(4, a.Cout - cb), m0 = p0 + (a.pool ? px * 4 : px);
-        if (nv <= 0 || m0 >= a.P) continue;
-        float sc[4], sf[4], out[4];
+    const int npix = a.pool ? BP / 4 : BP, cg = ecg, cb = c0 + cg * 4, nv = min(4, a.Cout - cb);
+    if (nv <= 0) return;
+    float sc[4], sf[4];
 #pragma unroll
-        for (int e = 0; e < 4; e++) {
+    for (int e = 0; e < 4; e++) {
+        if (vec) {
+            sc[e] = !PAIR && a.scale ? __uint_as_float(esc[e]) : 1.f;
+            sf[e] = __uint_as_float(esf[e]);
+            if (PAIR) sf[e] += __uint_as_float(esf2[e]);
+        } else {
             sc[e] = (!PAIR && a.scale && e < nv) ? a.scale[cb + e] : 1.f;
             sf[e] = (a.shift && e < nv) ? a.shift[cb + e] : 0.f;
             if (PAIR) sf[e] += (q.shift && e < nv) ? q.shift[cb + e] : 0.f;
         }
+    }
+#pragma unroll
+    for (int u = 0; u < IT; u++) {
+        const int px = epx + u * (NW * 64 / (BC / 4)), m0 = p0 + (a.pool ? px * 4 : px);
+        if (px >= npix || m0 >= a.P) break;
+        float out[4];
         auto finish = [&](int row, float v[4]) {           // act(scale * sum + shift + residual) of tile row `row`
             const int blk = (row >> 4) * CB + (cg >> 2), at = (cg & 3) * LSTR + (row & 15) * 4;
             float4 t = *reinterpret_cast<const float4 *>(&red[blk][at]);
@@ -235,7 +311,13 @@ __global__ void __launch_bounds__(NW * 64) conv_direct_kernel(const ConvArgs a, 
                 t.x += q.x; t.y += q.y; t.z += q.z; t.w += q.w;
             }
             v[0] = t.x * sc[0] + sf[0]; v[1] = t.y * sc[1] + sf[1]; v[2] = t.z * sc[2] + sf[2]; v[3] = t.w * sc[3] + sf[3];
-            if (resg) {
+            if (resg && vec) {
+#pragma unroll
+                for (int e = 0; e < 4; e++) {
+                    if constexpr (ES == 2) v[e] += __uint_as_float(e & 1 ? eres[u][e >> 1] & 0xffff0000u : eres[u][e >> 1] << 16);
+                    else v[e] += __uint_as_float(eres[u][e]);
+                }
+            } else if (resg) {
                 const T *rp = resg + (long)(p0 + row) * a.Cout + cb;
 #pragma unroll
                 for (int e = 0; e < 4; e++) v[e] += e < nv ? Elem<T>::load(rp + e) : 0.f;
@@ -281,14 +363,16 @@ static sol_status launch_direct_cfg(ConvArgs a, const DirectPair *q, hipStream_t
     const int grid = ((a.ntiles + 7) / 8) * 8;
     const double xbytes = (double)a.N * a.H * a.W * a.C * sizeof(T), wbytes = (double)a.Cout * a.Kp * sizeof(T);
     a.cpx = (a.ntc % 8 == 0 && wbytes > xbytes) ? a.ntc / 8 : 0;
+    DirectGeom g{FastDiv((uint32_t)(a.cpx > 0 ? a.cpx : 1)), FastDiv((uint32_t)a.ntc), FastDiv((uint32_t)(a.C * sizeof(T) / 128)), FastDiv((uint32_t)a.S), 0u};
+    for (int r = 0; r < a.R; r++) g.taprows |= 1u << (r * a.S);
     if constexpr (sizeof(T) == 2) {
         if (q) {
-            hipLaunchKernelGGL((conv_direct_kernel<T, PB, CB, NW, NS, true>), dim3(grid), dim3(NW * 64), 0, st, a, *q);
+            hipLaunchKernelGGL((conv_direct_kernel<T, PB, CB, NW, NS, true>), dim3(grid), dim3(NW * 64), 0, st, a, *q, g);
             SOL_HIP(hipGetLastError());
             return SOL_OK;
         }
     }
-    hipLaunchKernelGGL((conv_direct_kernel<T, PB, CB, NW, NS, false>), dim3(grid), dim3(NW * 64), 0, st, a, DirectPair{});
+    hipLaunchKernelGGL((conv_direct_kernel<T, PB, CB, NW, NS, false>), dim3(grid), dim3(NW * 64), 0, st, a, DirectPair{}, g);
     SOL_HIP(hipGetLastError());
     return SOL_OK;
 }

@@ -65,3 +65,22 @@ def test_direct_projection_pair(sol, tile, cp, cm, stride, cout, hw):  # noqa: F
     torch.cuda.synchronize()
     assert net.fused_into(2) == 3
     assert rel_err(sol.to_host_nchw(net.layer_output(3)).reshape(outs[3].shape), outs[3]) <= 2 * TOL["bf16"]
+
+
+@pytest.mark.parametrize("tile", TILES)
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("case", [(1, 128, 4, 4, 512, 3, 1, 1, True, None), (2, 64, 9, 7, 1024, 1, 1, 0, True, None), (1, 192, 6, 5, 256, 3, 2, 1, False, None),
+                                  (1, 64, 2, 3, 264, 3, 1, 3, True, None)])
+def test_direct_channel_slices(sol, dt, case, tile):  # noqa: F811
+    """Weights larger than the input: an XCD takes a set of channel tiles (tile counts that 8 divides, and one that it does not);
+    and windows that lie wholly in a padding as wide as the filter."""
+    N, C, H, W, K, k, s, p, res, pool = case
+    rng = np.random.default_rng([tile, N, C, H, K, k, s, 7])
+    l, x, prm, r = make_block(sol, rng, dt, N, C, H, W, K, k, s, p, res=res, pool=None)
+    want = orc.fused_conv(x, prm, l, r, bf16=(dt == "bf16"))[0]
+    sol.sol_debug_set_conv_tile(tile)
+    try:
+        got, _, _ = run_block(sol, dt, l, x, prm, r)
+    finally:
+        sol.sol_debug_set_conv_tile(0)
+    assert rel_err(got, want) <= TOL[dt]
