@@ -158,7 +158,8 @@ sol_status launch_conv_dma(const ConvArgs &a, int dt, int tile, hipStream_t st);
 bool gemm8_kernel_applies(const ConvArgs &a, int dt);
 sol_status launch_conv_gemm8(const ConvArgs &a, int tile, hipStream_t st);
 bool direct_kernel_applies(const ConvArgs &a, int dt);
-int direct_choose_tile(const ConvArgs &a, int dt);
+int conv_choose_tile(const ConvArgs &a, int dt);         // conv_choose.hip
+float conv_tile_estimate(int tile, int dt, long P, int Cout, float kbytes, float res, float mbytes);
 sol_status launch_conv_direct(const ConvArgs &a, int dt, int tile, hipStream_t st);
 int direct_choose_pair_tile(const ConvArgs &a, int K2);
 sol_status launch_conv_direct_pair(const ConvArgs &a, int tile, const void *x2, const void *w2, const float *scale2, const float *shift2,
@@ -171,7 +172,6 @@ sol_status launch_conv_small(const ConvArgs &a, int dt, hipStream_t st);
 bool pre_kernel_applies(const ConvArgs &a, int dt);      // 1x1 with BN + ReLU on the input side over whole 64-channel chunks (conv_pre.hip)
 sol_status launch_conv_pre(const ConvArgs &a, hipStream_t st);
 bool halo_kernel_applies(const ConvArgs &a, int dt);
-int halo_choose_tile(const ConvArgs &a);
 sol_status launch_conv_halo(const ConvArgs &a, int tile, hipStream_t st);
 bool stem_kernel_applies(const ConvArgs &a, int dt);
 sol_status launch_conv_stem(const ConvArgs &a, hipStream_t st);

@@ -9,7 +9,7 @@
 // in wave order, so the result does not depend on timing).  A stage is 128 bytes of every row, fetched in whole lines by
 // buffer_load ... lds (fragments loaded straight from global memory, 16 bytes of 16 rows per instruction, reached 16 bytes per
 // clock and CU against 50 this way).  The price of small tiles is traffic, (BP + BC) / (BP * BC) rows per output, so the tile
-// grows with the layer and large layers stay on the ring kernels: direct_choose_tile estimates every candidate's time.
+// grows with the layer and large layers stay on the ring kernels (conv_choose.hip).
 // Measured (layer behind 96 MB of other weights; us before -> now): bf16 3x3 512->512 at 7x7, batch 1: 60.3 -> 6.1, batch 8:
 // 30.7 -> 8.8, batch 32: 24.4 -> 18.0; 3x3 256->256 at 14x14, batch 1: 21.5 -> 4.7; 1x1 2048->512 at 7x7, batch 1: 14.6 -> 4.5;
 // fp32 3x3 512->512 at 7x7, batch 1: 107 -> 11.5, batch 8: 99 -> 25.
@@ -401,52 +401,6 @@ sol_status launch_conv_direct(const ConvArgs &a, int dt, int tile, hipStream_t s
     return dt == SOL_BF16 ? launch_direct_typed<bf16_t>(a, tile, nullptr, st) : launch_direct_typed<float>(a, tile, nullptr, st);
 }
 
-// Estimated time of a layer on a tile, in microseconds:  t0 + ((a + n * lat)^4 + (tiles / 256 * (c + N * rho))^4)^(1/4)
-// -- the serial chain of one workgroup (n stages of one wave) against the share of one of 256 CUs in the whole layer (N
-// stages per tile, and a constant per tile), the larger of the two with a soft corner.  The constants are least-squares fits
-// to 154 timed shapes (1x1 and 3x3, 49 to 100352 pixels, 64 to 4608 reduction elements) per tile: mean error 3-8 %.
-// Checked on 483 other layers, drawn at random (both types, 1x1 and 3x3 of stride 1 and 2, 1..64 images of 4..56 pixels,
-// 32..2048 -> 16..2048 channels, some with a pool or a residual): the choice takes 0.55 times as long as the other kernels'
-// heuristics alone (geometric mean); 281 layers are faster by more than 5 %, none is slower when timed again.
-struct TileCost { int tile, bp, bc, waves, rowb; float t0, a, lat, c, rho; };
-static const TileCost kCostBf16[] = {
-    {S_16x16, 16, 16, 4, 128, 3.33f, 0.00f, 0.134f, 0.61f, 0.0319f}, {S_16x32, 16, 32, 4, 128, 2.97f, 0.40f, 0.207f, 1.08f, 0.0540f},
-    {S_32x32, 32, 32, 4, 128, 2.91f, 0.88f, 0.268f, 1.27f, 0.0811f}, {S_64x32, 64, 32, 4, 128, 1.96f, 3.15f, 0.393f, 4.10f, 0.1467f},
-    {S_64x64, 64, 64, 4, 128, 4.50f, 2.81f, 0.563f, 5.00f, 0.2517f},
-    {D_64x64_128x4, 64, 64, 1, 128, 2.70f, 0.f, 0.355f, 0.92f, 0.237f}, {D_64x64_64x4, 64, 64, 1, 64, 2.68f, 0.f, 0.238f, 0.44f, 0.150f},
-    {G_64x64_k4, 64, 64, 1, 128, 3.48f, 0.f, 0.259f, 3.13f, 0.232f}, {H_64x64_k4, 64, 64, 1, 128, 3.30f, 0.f, 0.225f, 3.00f, 0.120f}};
-static const TileCost kCostF32[] = {
-    {S_16x16, 16, 16, 4, 128, 3.47f, 0.00f, 0.208f, 0.60f, 0.0481f}, {S_16x32, 16, 32, 4, 128, 2.97f, 0.25f, 0.370f, 1.10f, 0.0923f},
-    {S_32x32, 32, 32, 4, 128, 3.09f, 0.59f, 0.599f, 1.37f, 0.1623f}, {S_64x32, 64, 32, 4, 128, 1.69f, 3.45f, 1.078f, 4.69f, 0.3427f},
-    {S_64x64, 64, 64, 4, 128, 5.00f, 2.33f, 2.009f, 5.00f, 0.7287f},
-    {D_64x64_128x4, 64, 64, 1, 128, 2.86f, 0.f, 0.719f, 1.23f, 0.655f}, {D_64x64_64x4, 64, 64, 1, 64, 2.95f, 0.f, 0.419f, 0.73f, 0.336f}};
-
-static float cost_of(const TileCost &t, long P, int Cout, double kbytes) {
-    const double tiles = (double)((P + t.bp - 1) / t.bp) * ceil_div(Cout, t.bc), N = kbytes / t.rowb, n = N / t.waves;
-    const double serial = t.a + (t.waves > 1 ? (double)(long)(n + 0.999) : n) * t.lat, share = tiles / 256.0 * (t.c + N * t.rho);
-    return (float)(t.t0 + sqrt(sqrt(serial * serial * serial * serial + share * share * share * share)));
-}
-
-// Tile of a layer with few output pixels, or T_AUTO when it has enough 128x128 tiles for the other kernels' heuristics to be
-// the better guide (from about 96 tiles on: measured on the shapes above, 3x3 256->256 at 14x14, batch 32, 98 tiles: 14.0 us
-// by the heuristic, 14.4 here; batch 16, 50 tiles: 13.4 against 10.4).
-int direct_choose_tile(const ConvArgs &a, int dt) {
-    if (!direct_kernel_applies(a, dt) || (long)ceil_div(a.P, 128) * ceil_div(a.Cout, 128) >= 96) return T_AUTO;
-    const double kbytes = (double)a.R * a.S * a.C * dtype_size(dt);
-    const bool halo = halo_kernel_applies(a, dt) && a.W <= 31;      // 64 pixels + halo rows must fit the 128-row patch
-    int best = T_AUTO;
-    float bt = 0.f;
-    const TileCost *tab = dt == SOL_BF16 ? kCostBf16 : kCostF32;
-    const int nt = dt == SOL_BF16 ? (int)(sizeof(kCostBf16) / sizeof(TileCost)) : (int)(sizeof(kCostF32) / sizeof(TileCost));
-    for (int i = 0; i < nt; i++) {
-        const TileCost &t = tab[i];
-        if (t.tile == H_64x64_k4 && !halo) continue;
-        const float c = cost_of(t, a.P, a.Cout, kbytes);
-        if (best == T_AUTO || c < bt) { best = t.tile; bt = c; }
-    }
-    return best;
-}
-
 // The projection pair (bf16) on this kernel: which tile, or T_AUTO for the pair kernels, whose one 128x128 tile per workgroup
 // walks (K + K2) / 64 chunks of 0.87 us behind a start of 2.8 us as long as the tiles do not fill the chip.  The two operand
 // sets cost this kernel about a fifth on top of the estimate of one.  Measured (K + K2 -> channels, pixels; us pair kernel ->
@@ -456,10 +410,9 @@ int direct_choose_pair_tile(const ConvArgs &a, int K2) {
     if (!direct_kernel_applies(a, SOL_BF16) || K2 % 64 != 0) return T_AUTO;
     int best = T_AUTO;
     float bt = 2.8f + 0.87f * (float)((a.C + K2) / 64);
-    for (const TileCost &t : kCostBf16) {
-        if (t.tile < S_FIRST || t.tile > S_64x32) continue;
-        const float c = 1.2f * cost_of(t, a.P, a.Cout, 2.0 * (a.C + K2));
-        if (c < bt) { best = t.tile; bt = c; }
+    for (int t = S_FIRST; t <= S_64x32; t++) {
+        const float c = 1.2f * conv_tile_estimate(t, SOL_BF16, a.P, a.Cout, 2.f * (float)(a.C + K2), 0.f, 0.f);
+        if (c < bt) { best = t; bt = c; }
     }
     return best;
 }

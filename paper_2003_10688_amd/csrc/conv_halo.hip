@@ -324,18 +324,6 @@ bool halo_kernel_applies(const ConvArgs &a, int dt) {
            a.Cout % 8 == 0 && a.Ho == a.H && a.Wo == a.W && a.W <= 62 && xb < 2147483648.0 && wb < 2147483648.0;
 }
 
-// Shape heuristic (sol_network_autotune refines it by timing): one workgroup per CU wants about 200 tiles or
-// several rounds of them.
-int halo_choose_tile(const ConvArgs &a) {
-    const bool single = a.C == 64;
-    if (a.Cout <= 64) return a.W <= 30 ? H_256x64_x5 : (single ? H_256x64_x6s2 : H_256x64_x6);
-    if (a.W > 30) return 0;
-    const long nt256 = (long)ceil_div(a.P, 256) * ceil_div(a.Cout, 128);
-    if (nt256 >= 160) return H_256x128_x5;
-    if (nt256 >= 80) return H_128x128_k2;
-    return H_64x128_k4;
-}
-
 sol_status launch_conv_halo(const ConvArgs &a, int tile, hipStream_t st) {
     switch (tile) {
         //                                                WP WC KSPL TP TC XL NSW NPB MINW

@@ -337,10 +337,7 @@ sol_status launch_conv(const ConvArgs &a, int dt, int tile_override, hipStream_t
         }
         return launch_linear(a, dt, st);
     }
-    if (tile_override == T_AUTO && !one_order) tile_override = direct_choose_tile(a, dt);     // few pixels: its own small tiles, or the best of the others'
-    if (tile_override == T_AUTO && halo_kernel_applies(a, dt)) {
-        if (const int ht = halo_choose_tile(a)) return launch_conv_halo(a, ht, st);
-    }
+    if (tile_override == T_AUTO && !one_order) tile_override = conv_choose_tile(a, dt);
     if (tile_override >= H_FIRST && tile_override <= H_LAST) {
         SOL_REQUIRE(halo_kernel_applies(a, dt), SOL_ERR_UNSUPPORTED,
                     "conv tile %d needs a bf16 3x3 stride-1 pad-1 convolution with Cin %% 64 == 0 and no fused pool", tile_override);

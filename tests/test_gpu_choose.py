@@ -1,0 +1,65 @@
+"""The automatic choice of kernel and tile by estimated time: whatever it takes computes what the general path (the implicit-GEMM kernels
+alone, tile 99) and the checker compute, over the forms that it accepts and at the limits of the kernels it picks between."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as orc
+from paper_2003_10688_amd import workloads as wl
+from test_gpu_parity import TOL, make_block, rel_err, run_block, sol  # noqa: F401  (sol: the module fixture)
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # N, C, H, W, K, k, s, p, res, pool
+    (2, 64, 31, 31, 128, 3, 1, 1, True, None),      # widest image of the halo tiles, and one column more
+    (2, 64, 31, 32, 128, 3, 1, 1, True, None),
+    (1, 64, 17, 62, 64, 3, 1, 1, False, None),      # the same for the tiles of wide images
+    (1, 64, 17, 63, 64, 3, 1, 1, False, None),
+    (3, 128, 20, 62, 64, 3, 1, 1, True, None),      # wide, two chunks: not the single-chunk tile
+    (40, 256, 14, 14, 256, 3, 1, 1, False, None),   # enough 256-pixel tiles
+    (9, 32, 24, 23, 32, 3, 1, 1, False, None),      # rows of 64 bytes, few filters
+    (9, 32, 24, 24, 32, 3, 1, 1, False, "max"),
+    (5, 96, 19, 19, 40, 3, 2, 1, False, None),      # half a chunk over, ragged filters
+    (50, 64, 33, 33, 16, 1, 1, 0, True, None),      # many pixels, few filters
+    (20, 128, 28, 28, 512, 1, 1, 0, True, None),
+    (33, 256, 15, 15, 1000, 1, 1, 0, False, None),  # channels that no tile divides
+    (16, 512, 14, 14, 512, 3, 2, 1, False, None),
+    (30, 128, 30, 30, 128, 3, 1, 1, False, "avg"),
+    (12, 64, 26, 26, 33, 1, 2, 0, False, None),     # not a multiple of 4
+]
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("case", CASES)
+def test_choice_against_general_path(sol, dt, case):  # noqa: F811
+    N, C, H, W, K, k, s, p, res, pool = case
+    rng = np.random.default_rng([N, C, H, K, k, s])
+    l, x, prm, r = make_block(sol, rng, dt, N, C, H, W, K, k, s, p, res=res, pool=wl.pool_desc(pool, 2, 2, 0) if pool else None)
+    got = run_block(sol, dt, l, x, prm, r)[0]
+    sol.sol_debug_set_conv_tile(99)
+    try:
+        general = run_block(sol, dt, l, x, prm, r)[0]
+    finally:
+        sol.sol_debug_set_conv_tile(0)
+    # two sums of the same terms in different orders, both within the tolerance of the exact one
+    assert rel_err(got, general) <= 2 * TOL[dt]
+    few = np.sort(rng.choice(N, min(N, 2), replace=False))             # the checker's loops take two images
+    want = orc.fused_conv(x[few], prm, l, None if r is None else r[few], bf16=(dt == "bf16"))[0]
+    assert rel_err(got[few], want) <= TOL[dt]
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("n,c,h,w,k", [(2, 64, 9, 7, 40), (33, 128, 20, 21, 64), (40, 32, 24, 24, 32)])
+def test_choice_with_winners(sol, dt, n, c, h, w, k):  # noqa: F811
+    """A fused max pool that also stores its winners and the tensor in front of it: the three fit one another exactly."""
+    rng = np.random.default_rng([n, c, k])
+    l, x, prm, r = make_block(sol, rng, dt, n, c, h, w, k, 3, 1, 1, pool=wl.pool_desc("max", 2, 2, 0))
+    y, arg, pre = run_block(sol, dt, l, x, prm, r, want_argmax=True, want_prepool=True)
+    p, q = h // 2, w // 2
+    assert np.array_equal(y, pre[..., :2 * p, :2 * q].reshape(n, k, p, 2, q, 2).max((3, 5)))
+    assert np.array_equal(y, np.take_along_axis(pre.reshape(n, k, -1), arg.reshape(n, k, -1).astype(np.int64), 2).reshape(y.shape))
+    assert np.array_equal(arg // w // 2, np.broadcast_to(np.arange(p)[:, None], arg.shape)) and np.array_equal(arg % w // 2, np.broadcast_to(np.arange(q), arg.shape))
+    want = orc.fused_conv(x[:1], prm, dict(l, pool=None), None, bf16=(dt == "bf16"))[0]
+    covered = np.s_[..., :2 * p, :2 * q]                    # pixels that no window covers are not stored
+    assert rel_err(pre[:1][covered], want[covered]) <= TOL[dt]
