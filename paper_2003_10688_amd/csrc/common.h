@@ -158,6 +158,7 @@ sol_status launch_conv_dma(const ConvArgs &a, int dt, int tile, hipStream_t st);
 bool gemm8_kernel_applies(const ConvArgs &a, int dt);
 sol_status launch_conv_gemm8(const ConvArgs &a, int tile, hipStream_t st);
 bool direct_kernel_applies(const ConvArgs &a, int dt);
+int direct_choose_pre_tile(const ConvArgs &a, int dt);
 int conv_choose_tile(const ConvArgs &a, int dt);         // conv_choose.hip
 float conv_tile_estimate(int tile, int dt, long P, int Cout, float kbytes, float res, float mbytes);
 sol_status launch_conv_direct(const ConvArgs &a, int dt, int tile, hipStream_t st);

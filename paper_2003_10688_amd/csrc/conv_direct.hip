@@ -47,13 +47,16 @@ struct DirectGeom {
 };
 
 // PB x CB: 16-pixel x 16-channel blocks of the tile; NW waves split the reduction; NS: ring stages of each wave
-template <typename T, int PB, int CB, int NW, int NS, bool PAIR>
+// PRE: relu(pre_scale[c] x + pre_shift[c]) of an unpadded 1x1 convolution's input, applied to the pixels' fragments in registers; the
+// stage's constants travel with its weights (one 4-byte DMA instruction).  x may be a channel prefix (ldx)
+template <typename T, int PB, int CB, int NW, int NS, bool PAIR, bool PRE>
 __global__ void __launch_bounds__(NW * 64) conv_direct_kernel(const ConvArgs a, const DirectPair q, const DirectGeom g) {
 #if defined(__HIP_DEVICE_COMPILE__)
     using namespace lds_pipe;
     constexpr int ES = (int)sizeof(T), BP = PB * 16, BC = CB * 16;
-    constexpr int ROWB = 128, XL = BP / 8, WL = BC / 8, L = XL + WL;   // bytes of a row per stage; DMA instructions (8 rows each) per stage
-    constexpr int STAGE = (BP + BC) * ROWB;
+    constexpr int ROWB = 128, XL = BP / 8, WL = BC / 8, L = XL + WL + (PRE ? 1 : 0);   // bytes of a row per stage; DMA instructions (8 rows each) per stage
+    constexpr int STAGE = (BP + BC) * ROWB + (PRE ? 256 : 0);
+    static_assert(!PRE || (ES == 4 && !PAIR), "32 channels per stage");
     constexpr int LSTR = 68;                               // floats between the four 16-lane groups of a parked block: spreads the banks of the epilogue's reads
     constexpr int REDB = NW * PB * CB * 4 * LSTR * 4, RING = NW * NS * STAGE;
     static_assert(RING <= 160 * 1024 && (NS - 1) * L < 64, "LDS, vmcnt");
@@ -86,7 +89,8 @@ __global__ void __launch_bounds__(NW * 64) conv_direct_kernel(const ConvArgs a, 
     // the activation resource starts `bias` bytes early so that window origins in the padding have offsets >= 0; padding
     // taps and rows beyond the tensor get an out-of-range offset, which the hardware answers with zeros
     const unsigned bias = (unsigned)((a.ph * a.W + a.pw) * a.C) * ES;
-    const unsigned xbytes = (unsigned)a.N * a.H * a.W * a.C * ES, wbytes = (unsigned)a.Cout * a.Kp * ES;
+    const int ldx = PRE ? a.ldx : a.C;
+    const unsigned xbytes = (unsigned)a.N * a.H * a.W * ldx * ES, wbytes = (unsigned)a.Cout * a.Kp * ES;
     const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<unsigned char *>(static_cast<const unsigned char *>(a.x)) - bias, 0, (int)(xbytes + bias), 0x00020000);
     const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(a.w), 0, (int)wbytes, 0x00020000);
@@ -121,6 +125,10 @@ __global__ void __launch_bounds__(NW * 64) conv_direct_kernel(const ConvArgs a, 
 #pragma unroll
             for (int i = 0; i < WL; i++)
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(real ? wr : wnull, (__attribute__((address_space(3))) void *)(lw + i * 1024), 16, wo[i], (unsigned)s * ROWB, 0, 0);
+        }
+        if constexpr (PRE) {                               // 32 factors, 32 summands; beyond s1 the last stage's again, never used
+            const float *src = (lane < 32 ? a.pre_scale : a.pre_shift) + min(s, s1 - 1) * 32 + (lane & 31);
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src, (__attribute__((address_space(3))) void *)(lw + BC * ROWB), 4, 0, 0);
         }
     };
     const bool any = s0 < s1;
@@ -170,7 +178,7 @@ __global__ void __launch_bounds__(NW * 64) conv_direct_kernel(const ConvArgs a, 
         int n, op, oq;
         decode_pixel(a, m, n, op, oq);
         const int ih0 = op * a.sh - a.ph, iw0 = oq * a.sw - a.pw;
-        const unsigned off = (unsigned)(((n * a.H + ih0) * a.W + iw0) * a.C) * ES + bias + ((lslot ^ swz<ROWB>(row)) << 4);
+        const unsigned off = (unsigned)(((n * a.H + ih0) * a.W + iw0) * ldx) * ES + bias + ((lslot ^ swz<ROWB>(row)) << 4);
         const int slo = max(0, -iw0), shi = min(a.S, a.W - iw0), rlo = max(0, -ih0), rhi = min(a.R, a.H - ih0);
         const unsigned cval = shi > slo ? (unsigned)((1ull << shi) - 1ull) & ~((1u << slo) - 1u) : 0u;
         // filter rows [rlo, rhi) as bits r * S; times the columns' bits, of which a row has S: no carries
@@ -228,11 +236,26 @@ __global__ void __launch_bounds__(NW * 64) conv_direct_kernel(const ConvArgs a, 
             static_for<PB>([&](auto J) { lds_read16<decltype(J)::value * 16 * ROWB>(fx[0][decltype(J)::value], b0); });
             static_for<CB>([&](auto I) { lds_read16<BP * ROWB + decltype(I)::value * 16 * ROWB>(fw[1][decltype(I)::value], b1); });
             static_for<PB>([&](auto J) { lds_read16<decltype(J)::value * 16 * ROWB>(fx[1][decltype(J)::value], b1); });
+            u32x4_t pk[PRE ? 4 : 1];                       // this lane's 4 + 4 channels: factors, summands
+            if constexpr (PRE) {
+                const unsigned cb = lds_addr(ring) + buf * STAGE + (BP + BC) * ROWB + lg * 16;
+                lds_read16<0>(pk[0], cb); lds_read16<128>(pk[1], cb); lds_read16<64>(pk[2], cb); lds_read16<192>(pk[3], cb);
+            }
             wait_lgkmcnt<0>();
+            if constexpr (PRE) { landed(pk[0]); landed(pk[1]); landed(pk[2]); landed(pk[3]); }
             static_for<2>([&](auto H) {
                 static_for<CB>([&](auto I) { landed(fw[decltype(H)::value][decltype(I)::value]); });
                 static_for<PB>([&](auto J) { landed(fx[decltype(H)::value][decltype(J)::value]); });
             });
+            if constexpr (PRE) {
+#pragma unroll
+                for (int h = 0; h < 2; h++)
+#pragma unroll
+                    for (int j = 0; j < PB; j++)
+#pragma unroll
+                        for (int e = 0; e < 4; e++)
+                            fx[h][j][e] = __float_as_uint(__builtin_fmaxf(__uint_as_float(fx[h][j][e]) * __uint_as_float(pk[2 * h][e]) + __uint_as_float(pk[2 * h + 1][e]), 0.f));
+            }
             issue_w(buf, s);                               // the slot's data is in registers: refill it
             issue_x(buf);
             auto contract = [&](f32x4_t (&to)[CB][PB]) {
@@ -367,12 +390,19 @@ static sol_status launch_direct_cfg(ConvArgs a, const DirectPair *q, hipStream_t
     for (int r = 0; r < a.R; r++) g.taprows |= 1u << (r * a.S);
     if constexpr (sizeof(T) == 2) {
         if (q) {
-            hipLaunchKernelGGL((conv_direct_kernel<T, PB, CB, NW, NS, true>), dim3(grid), dim3(NW * 64), 0, st, a, *q, g);
+            hipLaunchKernelGGL((conv_direct_kernel<T, PB, CB, NW, NS, true, false>), dim3(grid), dim3(NW * 64), 0, st, a, *q, g);
             SOL_HIP(hipGetLastError());
             return SOL_OK;
         }
     }
-    hipLaunchKernelGGL((conv_direct_kernel<T, PB, CB, NW, NS, false>), dim3(grid), dim3(NW * 64), 0, st, a, DirectPair{}, g);
+    if constexpr (sizeof(T) == 4) {
+        if (a.pre_scale) {
+            hipLaunchKernelGGL((conv_direct_kernel<T, PB, CB, NW, NS, false, true>), dim3(grid), dim3(NW * 64), 0, st, a, DirectPair{}, g);
+            SOL_HIP(hipGetLastError());
+            return SOL_OK;
+        }
+    }
+    hipLaunchKernelGGL((conv_direct_kernel<T, PB, CB, NW, NS, false, false>), dim3(grid), dim3(NW * 64), 0, st, a, DirectPair{}, g);
     SOL_HIP(hipGetLastError());
     return SOL_OK;
 }
@@ -412,6 +442,22 @@ int direct_choose_pair_tile(const ConvArgs &a, int K2) {
     float bt = 2.8f + 0.87f * (float)((a.C + K2) / 64);
     for (int t = S_FIRST; t <= S_64x32; t++) {
         const float c = 1.2f * conv_tile_estimate(t, SOL_BF16, a.P, a.Cout, 2.f * (float)(a.C + K2), 0.f, 0.f);
+        if (c < bt) { best = t; bt = c; }
+    }
+    return best;
+}
+
+// A pre-activated 1x1 convolution in fp32 on this kernel (see PRE), or T_AUTO: whole 32-channel stages, all of them valid, no padding (which
+// the activation would not leave at 0).  The register-staged kernel has one 128-pixel tile per workgroup, one wave per SIMD in step with the
+// others, whatever the layer's size: a DenseNet-121-shaped pass (us, it alone -> here): 1 image of 224x224 3377 -> 698, 3 of 64x64 3331 -> 657,
+// 8 of 100x100 3381 -> 741, 8 of 224x224 3744 -> 1249.
+int direct_choose_pre_tile(const ConvArgs &a, int dt) {
+    if (dt != SOL_F32 || !a.pre_scale || a.R * a.S != 1 || a.ph || a.pw || a.Cvalid != a.C || !direct_kernel_applies(a, dt) ||
+        (double)a.N * a.H * a.W * a.ldx * 4.0 >= 2147483648.0) return T_AUTO;
+    int best = S_FIRST;
+    float bt = INFINITY;
+    for (int t = S_FIRST; t <= S_LAST; t++) {
+        const float c = conv_tile_estimate(t, SOL_F32, a.P, a.Cout, 4.f * (float)a.C, a.res ? 1.f : 0.f, 0.f);
         if (c < bt) { best = t; bt = c; }
     }
     return best;

@@ -241,7 +241,8 @@ static sol_status launch_cfg(ConvArgs a, hipStream_t st) {
     return SOL_OK;
 }
 
-// Planner heuristic: tile per layer shape, from per-layer timing sweeps on MI355X.  Small-Cin layers
+// Tile of what conv_choose_tile leaves over (input channels that are not whole 64-byte chunks, operands of 2 GiB) and of the sums in
+// one order, from per-layer timing sweeps on MI355X.  Small-Cin layers
 // use the element-gather kernel; everything else the LDS-DMA ring kernel with
 //   - 64x64 tiles (many resident workgroups) for narrow outputs and for layers with few tiles,
 //   - 128x64 / 64x64 tiles, 64-byte rows x 4 stages (3-5 workgroups per CU) for the big HBM-bound layers,
@@ -298,9 +299,12 @@ const char *conv_kernel_of_thread() { return t_kernel; }
 
 // Input-side BN + ReLU, a strided input (channel prefix of a wider tensor) or masked padding channels: what is fetched has to pass
 // through registers before it is multiplied.  A pre-activated 1x1 convolution of whole chunks takes its fragments from memory
-// directly (conv_pre); everything else, and a tile asked for, the register-staged kernel, which transforms on the way to LDS.
-static sol_status launch_conv_staged(const ConvArgs &a, int dt, int tile, hipStream_t st) {
+// directly (conv_pre, bf16) or transforms them between LDS and the products (conv_direct, fp32); everything else, and a tile asked for, the
+// register-staged kernel, which transforms on the way to LDS.
+static sol_status launch_conv_staged(const ConvArgs &a, int dt, int tile, hipStream_t st, bool one_order) {
     if (tile == T_AUTO && pre_kernel_applies(a, dt)) { t_kernel = "pre"; return launch_conv_pre(a, st); }
+    if (tile == T_AUTO && !one_order)
+        if (const int t = direct_choose_pre_tile(a, dt)) { t_kernel = "direct"; return launch_conv_direct(a, dt, t, st); }
     if (!(tile >= T_256x128 && tile <= T_64x128)) {
         SOL_REQUIRE(tile == T_AUTO || tile == T_NO_HALO, SOL_ERR_UNSUPPORTED,
                     "conv tile %d cannot apply an input-side BN + ReLU or read a channel prefix; the register-staged tiles 1..8 can", tile);
@@ -320,7 +324,7 @@ static sol_status launch_conv_staged(const ConvArgs &a, int dt, int tile, hipStr
 sol_status launch_conv(const ConvArgs &a, int dt, int tile_override, hipStream_t st, bool one_order) {
     t_kernel = "";
     if (a.P <= 0) return SOL_OK;   // empty batch: nothing to do
-    if (a.pre_scale || a.ldx != a.C || a.Cvalid != a.C) return launch_conv_staged(a, dt, tile_override, st);
+    if (a.pre_scale || a.ldx != a.C || a.Cvalid != a.C) return launch_conv_staged(a, dt, tile_override, st, one_order);
     if (tile_override == T_AUTO && stem_kernel_applies(a, dt)) return launch_conv_stem(a, st);
     if (tile_override == T_AUTO && !one_order && small_kernel_applies(a, dt)) { t_kernel = "small"; return launch_conv_small(a, dt, st); }
     if (tile_override == T_AUTO && !one_order && linear_stream_applies(a, dt)) return launch_linear_stream(a, dt, st);

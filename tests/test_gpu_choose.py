@@ -63,3 +63,37 @@ def test_choice_with_winners(sol, dt, n, c, h, w, k):  # noqa: F811
     want = orc.fused_conv(x[:1], prm, dict(l, pool=None), None, bf16=(dt == "bf16"))[0]
     covered = np.s_[..., :2 * p, :2 * q]                    # pixels that no window covers are not stored
     assert rel_err(pre[:1][covered], want[covered]) <= TOL[dt]
+
+
+@pytest.mark.parametrize("c,ldx,k,hw,n,s,res,pool", [(64, 64, 128, 9, 3, 1, False, None), (96, 256, 40, 7, 2, 1, True, None), (32, 96, 128, 12, 5, 1, False, "avg"),
+                                                     (256, 256, 33, 11, 9, 2, False, None), (1056, 1088, 128, 7, 2, 1, False, None)])
+def test_preact_fp32_small_tiles(sol, c, ldx, k, hw, n, s, res, pool):  # noqa: F811
+    """Pre-activated 1x1 convolutions in fp32 on the small-tile kernel (no tile asked for) against 64 bits and the register-staged kernel:
+    prefixes of a wider tensor (what lies behind is not looked at), strides, pools, ragged channels."""
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(c + k)
+    x = torch.randn((n, hw, hw, ldx), generator=gen, device="cuda:0")
+    x[..., c:] = float("nan")
+    w = torch.randn((k, c, 1, 1), generator=gen, device="cuda:0") / c ** 0.5
+    ps, ph = torch.rand(c, generator=gen, device="cuda:0") + 0.5, torch.rand(c, generator=gen, device="cuda:0") - 0.5
+    cd = sol.ConvDesc(k, c, 1, 1, s, s, 0, 0)
+    wp = sol.sol_pack_conv_weights(cd, sol.F32, w)
+    ho = (hw - 1) // s + 1
+    r = torch.randn((n, ho, ho, k), generator=gen, device="cuda:0") if res else None
+    pd = sol.pool_desc(wl.pool_desc(pool, 2, 2, 0)) if pool else None
+    run = lambda: sol.sol_conv2d_preact_fused(x, cd, wp, ps, ph, residual=r, channels=c, pool=pd)  # noqa: E731
+    y = run()
+    assert sol.sol_debug_conv_kernel() == "direct"
+    sol.sol_debug_set_conv_tile(5)
+    try:
+        staged = run()
+    finally:
+        sol.sol_debug_set_conv_tile(0)
+    t = (x[..., :c].double() * ps.double() + ph.double()).relu()[:, ::s, ::s]
+    want = t.reshape(-1, c) @ w.double().reshape(k, c).T
+    want = want.reshape(n, ho, ho, k) + (r.double() if res else 0)
+    if pool:
+        h2 = ho // 2 * 2
+        want = want[:, :h2, :h2].reshape(n, ho // 2, 2, ho // 2, 2, k).mean((2, 4))
+    for got in (y, staged):
+        assert rel_err(got.cpu().numpy(), want.cpu().numpy()) <= TOL["f32"]
