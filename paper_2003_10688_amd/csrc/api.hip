@@ -71,7 +71,8 @@ static sol_status conv_fused_impl(const sol_tensor_desc &xd, const void *x, cons
                                   const sol_pool_desc *pool, void *y, int32_t *argmax, void *prepool, int tile,
                                   hipStream_t st, int ldy = 0,     // ldy: elements between output pixels in y, 0 = cout (dense)
                                   const PairOperand *pair = nullptr, const InputSide *ins = nullptr,
-                                  bool one_order = false) {       // see launch_conv
+                                  bool one_order = false,        // see launch_conv
+                                  bool planned = false) {         // called by a network's plan
     SOL_REQUIRE(cd.cin == xd.c, SOL_ERR_SHAPE, "conv cin %d != input channels %d", cd.cin, xd.c);
     SOL_REQUIRE(act == SOL_ACT_NONE || act == SOL_ACT_RELU, SOL_ERR_SHAPE, "bad activation %d", act);
     const int Ho = out_size(xd.h, cd.kh, cd.sh, cd.ph), Wo = out_size(xd.w, cd.kw, cd.sw, cd.pw);
@@ -95,12 +96,13 @@ static sol_status conv_fused_impl(const sol_tensor_desc &xd, const void *x, cons
             a.Hy = Ho / 2; a.Wy = Wo / 2;
             SOL_REQUIRE(a.Hy > 0 && a.Wy > 0, SOL_ERR_SHAPE, "conv output %dx%d too small for a 2x2 pool", Ho, Wo);
         } else {
-            SOL_REQUIRE(stem_pool_applies(a, xd.dtype, *pool), SOL_ERR_UNSUPPORTED,
+            // a plan also has the other forms of that kernel: 3x3 filters, fp32, an unpadded pool
+            SOL_REQUIRE(stem_pool_applies(a, xd.dtype, *pool) && (planned || (xd.dtype == SOL_BF16 && cd.kh == 7 && pool->ph == 1)), SOL_ERR_UNSUPPORTED,
                         "a pool fused into the convolution is 2x2 stride 2 unpadded, or a 3x3 stride-2 pad-1 max pool behind a bf16 "
                         "7x7 stride-2 convolution of 3 channels with 64 filters, ReLU and no residual; run sol_pool separately");
             SOL_REQUIRE(!argmax && !prepool, SOL_ERR_UNSUPPORTED, "the fused stem pool stores neither winners nor the pre-pool tensor");
             a.pool = 3;
-            a.Hy = out_size(Ho, 3, 2, 1); a.Wy = out_size(Wo, 3, 2, 1);
+            a.Hy = out_size(Ho, 3, 2, pool->ph); a.Wy = out_size(Wo, 3, 2, pool->pw);
         }
     }
     a.ldy = cd.cout;
@@ -141,7 +143,7 @@ static sol_status conv_fused_impl(const sol_tensor_desc &xd, const void *x, cons
     a.P = quad ? xd.n * a.Hy * a.Wy * 4 : xd.n * Ho * Wo;
     a.dw = FastDiv((uint32_t)(quad ? a.Wy : Wo));
     a.dh = FastDiv((uint32_t)(quad ? a.Hy : Ho));
-    if (a.pool == 3) return launch_conv_stem_pool(a, st);   // one kernel, no tile choice
+    if (a.pool == 3) return launch_conv_stem_pool(a, xd.dtype, pool->ph, st);   // one kernel, no tile choice
     if (pair) {
         SOL_REQUIRE(res == nullptr && pair_applies(a, xd.dtype, pair->H2, pair->W2, pair->K2, pair->Kp2, pair->stride), SOL_ERR_UNSUPPORTED,
                     "a fused projection pair is two bf16 unpadded 1x1 convolutions over multiples of 64 channels");
@@ -1430,7 +1432,7 @@ static sol_status run_layers(sol_network *net, const void *x, void *y, void *wor
                 }
                 SOL_TRY(conv_fused_impl(lp.in, in, lp.cd, net->params + lp.w_off, scale, shift, res, lp.L.act,
                                         fused, conv_dst, nullptr, nullptr,
-                                        g_tile_override ? g_tile_override : lp.tile, st, ldy));
+                                        g_tile_override ? g_tile_override : lp.tile, st, ldy, nullptr, nullptr, false, true));
                 if (lp.split_pool) SOL_TRY(pool_impl(lp.conv_out, conv_dst, lp.L.pool, out, nullptr, st));
                 break;
             }

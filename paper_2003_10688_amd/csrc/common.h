@@ -181,7 +181,7 @@ bool pair_applies(const ConvArgs &a, int dt, int H2, int W2, int K2, int Kp2, in
 sol_status launch_conv_pair(ConvArgs a, const void *x2, const void *w2, const float *scale2, const float *shift2, int H2, int W2, int K2,
                             int Kp2, int stride, hipStream_t st);
 bool stem_pool_applies(const ConvArgs &a, int dt, const sol_pool_desc &p);   // stem + ReLU + 3x3/2 max pool in one kernel
-sol_status launch_conv_stem_pool(const ConvArgs &a, hipStream_t st);
+sol_status launch_conv_stem_pool(const ConvArgs &a, int dt, int pad, hipStream_t st);     // pad: of the pool
 // a whole stride-1 bottleneck (1x1 reduce, 3x3, 1x1 expand + identity shortcut, folded BN and ReLU each) in one kernel (conv_block.hip)
 struct BlockLaunch {
     const void *x; void *y;                          // block input / output, NHWC [N][H][W][C4]

@@ -1,0 +1,75 @@
+"""A planned stem + 3x3 stride-2 max pool in one launch: 3x3 and 7x7 filters, bf16 and fp32, pool padding 0 and 1."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as orc
+from paper_2003_10688_amd import workloads as wl
+from test_gpu_parity import TOL, _grid, make_block, rel_err, run_block, sol  # noqa: F401  (sol: the module fixture)
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # N, H, W, conv padding as a share of the filter    whole blocks, ragged ones, odd extents, tiny images, many tiles per workgroup
+    (2, 64, 64, 0), (1, 61, 75, 1), (3, 30, 44, 2), (2, 17, 19, 1), (1, 11, 11, 0), (24, 97, 90, 1),
+]
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("k", [3, 7])
+@pytest.mark.parametrize("pad", [0, 1])
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "x".join(map(str, c)))
+def test_stem_pool_planned(sol, dt, k, pad, case):  # noqa: F811
+    """Against the checker and against the plan that keeps every activation (convolution stored, then the pool): bit for bit in bf16, where
+    rounding before the maximum is the same; within two summation orders in fp32."""
+    N, H, W, p = case
+    d = sol.BF16 if dt == "bf16" else sol.F32
+    layers = [wl.conv(64, k, s=2, p=p * (k // 2) // 2 if k == 7 else min(p, 2)), wl.pool("max", 3, 2, pad)]
+    rng = np.random.default_rng([N, H, W, k, pad])
+    x = _grid(rng.standard_normal((N, 3, H, W)), dt)
+    prm = wl.make_params(layers, 3, 7 + k, bf16=(dt == "bf16"), bias_std=0.3)
+    ys = {}
+    for keep in (False, True):
+        net = sol.Network(layers, x.shape, d, flags=sol.NET_KEEP_ACTIVATIONS if keep else 0)
+        net.set_params(prm)
+        ys[keep] = sol.to_host_nchw(net.forward(sol.to_device_nhwc(x, d)))
+        torch.cuda.synchronize()
+        assert net.fused_into(1) == (1 if keep else 0)
+    few = np.unique([0, N - 1])                                        # the checker's loops take two images
+    want = orc.network_forward(layers, prm, x[few], bf16=(dt == "bf16"), return_all=True)[0][-1]
+    assert rel_err(ys[False][few].reshape(want.shape), want) <= TOL[dt]
+    if dt == "bf16":
+        assert np.array_equal(ys[False], ys[True])
+    else:
+        assert rel_err(ys[False], ys[True]) <= 2 * TOL[dt]
+
+
+@pytest.mark.parametrize("k", [3, 7])
+def test_nothing_outside_a_window_counts(sol, k):  # noqa: F811
+    """fp32: an infinity or a NaN reaches the outputs whose windows hold it, and no other."""
+    layers = [wl.conv(64, k, s=2, p=k // 2), wl.pool("max", 3, 2, 1)]
+    rng = np.random.default_rng(k)
+    x = rng.standard_normal((1, 3, 60, 60)).astype(np.float32)
+    prm = wl.make_params(layers, 3, 3, bias_std=0.3)
+    net = sol.Network(layers, x.shape, sol.F32)
+    net.set_params(prm)
+    clean = sol.to_host_nchw(net.forward(sol.to_device_nhwc(x, sol.F32)))
+    h, w = 31, 28
+    for bad in (np.inf, np.nan):
+        z = x.copy()
+        z[0, 1, h, w] = bad
+        got = sol.to_host_nchw(net.forward(sol.to_device_nhwc(z, sol.F32)))
+        r = k // 2
+        conv = [np.abs(2 * np.arange(30) - c) <= r for c in (h, w)]     # convolution rows / columns whose windows hold the pixel
+        touched = [np.array([v[max(0, 2 * o - 1):2 * o + 2].any() for o in range(15)]) for v in conv]
+        outside = ~np.outer(*touched)
+        assert np.array_equal(got[0][:, outside], clean[0][:, outside])
+
+
+@pytest.mark.parametrize("dt,k,pad", [("f32", 7, 1), ("bf16", 3, 1), ("bf16", 7, 0)])
+def test_layer_entry_point_refuses_as_before(sol, dt, k, pad):  # noqa: F811
+    rng = np.random.default_rng(5)
+    l, x, prm, r = make_block(sol, rng, dt, 1, 3, 20, 20, 64, k, 2, k // 2, pool=wl.pool_desc("max", 3, 2, pad))
+    with pytest.raises(sol.SolError) as e:
+        run_block(sol, dt, l, x, prm, r)
+    assert e.value.status == 6
