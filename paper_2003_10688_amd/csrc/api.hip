@@ -1165,6 +1165,11 @@ static sol_status train_forward(sol_network *net, const void *x, void *y, unsign
                 void *z = ws + lp.z_off;
                 const int rows = lp.conv_out.n * lp.conv_out.h * lp.conv_out.w, C = lp.cd.cout;
                 if (rows == 0) break;
+                if (bn_small_applies(rows, C)) {
+                    SOL_TRY(launch_bn_small(z, res, out, vec_ptr(net, lp, VEC_GAMMA), vec_ptr(net, lp, VEC_BETA), vec_ptr(net, lp, VEC_MEAN),
+                                            vec_ptr(net, lp, VEC_VAR), vec_ptr(net, lp, VEC_INVSTD), rows, C, lp.eps, lp.L.act == SOL_ACT_RELU, dt, st));
+                    break;
+                }
                 SOL_TRY(launch_bn_stats(z, rows, C, dt, lp.eps, vec_ptr(net, lp, VEC_MEAN), vec_ptr(net, lp, VEC_VAR),
                                         vec_ptr(net, lp, VEC_INVSTD), part, st));
                 SOL_TRY(launch_bn_apply(z, res, out, vec_ptr(net, lp, VEC_MEAN), vec_ptr(net, lp, VEC_INVSTD),
@@ -1261,7 +1266,10 @@ static sol_status train_backward(sol_network *net, const void *x, const int32_t 
                 void *dres = lp.res >= 0 ? static_cast<void *>(ws + net->layers[lp.res].dact_off) : nullptr;
                 unsigned char *dzbuf = ws + lp.dzl_off;
                 const void *dz = dzbuf;
-                if (bn) {
+                if (bn && bn_small_applies(rows, C)) {
+                    SOL_TRY(launch_bn_small_bwd(ws + lp.z_off, dy, yv, vec_ptr(net, lp, VEC_MEAN), vec_ptr(net, lp, VEC_INVSTD), vec_ptr(net, lp, VEC_GAMMA),
+                                                vec_ptr(net, lp, VEC_G_BETA), vec_ptr(net, lp, VEC_G_GAMMA), dzbuf, dres, lp.res_first, rows, C, relu, dt, st));
+                } else if (bn) {
                     const void *z = ws + lp.z_off;
                     SOL_TRY(launch_grad_col_sums(z, dy, yv, vec_ptr(net, lp, VEC_MEAN), vec_ptr(net, lp, VEC_INVSTD), rows, C,
                                                  relu, dt, vec_ptr(net, lp, VEC_G_BETA), vec_ptr(net, lp, VEC_G_GAMMA), part, st));

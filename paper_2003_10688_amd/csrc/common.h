@@ -260,6 +260,12 @@ sol_status launch_grad_col_sums(const void *z, const void *dy, const void *y, co
 sol_status launch_act_bn_bwd(const void *z, const void *dy, const void *y, const float *mean, const float *invstd,
                              const float *gamma, const float *dbeta, const float *dgamma, void *dz, void *dres,
                              int res_first, long total, int C, int relu, int bn, int rows, int dt, hipStream_t st);
+// statistics + apply, and column sums + backward, of a BN layer in one launch each: the results of the launches above, to the last bit
+bool bn_small_applies(int rows, int C);
+sol_status launch_bn_small(const void *z, const void *res, void *y, const float *gamma, const float *beta, float *mean, float *var, float *invstd,
+                           int rows, int C, float eps, int relu, int dt, hipStream_t st);
+sol_status launch_bn_small_bwd(const void *z, const void *dy, const void *y, const float *mean, const float *invstd, const float *gamma, float *dbeta,
+                               float *dgamma, void *dz, void *dres, int res_first, int rows, int C, int relu, int dt, hipStream_t st);
 sol_status launch_dilate(const void *dz, void *out, int N, int Ho, int Wo, int K, int Hd, int Wd, int sh, int sw, int dt,
                          hipStream_t st);
 sol_status launch_pool_bwd(const PoolArgs &a, const void *dy, void *dx, int first, int dt, hipStream_t st);

@@ -397,6 +397,200 @@ __global__ void __launch_bounds__(256) act_bn_bwd_kernel(const T *__restrict__ z
     }
 }
 
+// ---- batch norm of a small tensor in one launch -----------------------------------------------------------------------
+// A tensor of at most 1024 rows is read in 2 us, but statistics, their merge and the elementwise pass are three dependent launches of
+// 4 us each.  Here one workgroup has all rows of 16 channels in its registers: 1024 threads = 16 chunks of 64 rows x the
+// row phases and channel vectors of the kernels above, so every sum has their terms in their order (and the
+// products that they contract, spelled out): results are the same to the last bit.
+// us, forward + backward, three launches each -> one each: fp32, 144 rows of 512 channels 24.0 -> 10.1, 576 of 256 22.9 -> 11.9; bf16, 400 of 512
+// 19.1 -> 12.1.  With two such rounds of chunks, beyond 1024 rows, the workgroups read too long (2025 of 128, fp32, 20.5 -> 22.5; 1568 of 512, bf16, 23.5
+// -> 27.6), and an arrival counter in place of the merge launch saved 1 us up to 128 chunks and cost 3 beyond: neither is used.
+constexpr int BS_CH = 16, BS_RPC = 64, BS_MAX_ROWS = 16 * BS_RPC;      // channels of a workgroup; rows per chunk (as col_reduce_chunks has them)
+
+// Which rows a thread holds: chunk k0, row phase ph, every PH-th row
+template <int V> struct SmallRows {
+    static constexpr int CG = BS_CH / V, PH = 4 * V, RW = BS_RPC / PH;      // channel vectors; phases; rows per chunk and phase
+    static_assert(CG * PH * 16 == 1024, "16 chunks at once");
+    int cg, ph, k0, c0;
+    __device__ __forceinline__ SmallRows() {
+        cg = threadIdx.x % CG; ph = threadIdx.x / CG % PH; k0 = threadIdx.x / (CG * PH);
+        c0 = (int)blockIdx.x * BS_CH + cg * V;
+    }
+    __device__ __forceinline__ int row(int u) const { return k0 * BS_RPC + ph + u * PH; }
+};
+// sum over the phases, in order, of chunk k = tid / 16 and channel tid % 16
+template <int PH> __device__ __forceinline__ float phase_sum(const float (*red)[BS_CH + 1]) {
+    float s = 0.f;
+#pragma unroll
+    for (int p = 0; p < PH; p++) s += red[(threadIdx.x / BS_CH) * PH + p][threadIdx.x % BS_CH];
+    return s;
+}
+
+template <typename T, int V>
+__global__ void __launch_bounds__(1024) bn_small_kernel(const T *__restrict__ z, const T *__restrict__ res, T *__restrict__ y, const float *__restrict__ gamma,
+                                                        const float *__restrict__ beta, float *__restrict__ mean, float *__restrict__ var,
+                                                        float *__restrict__ inv, int rows, int C, float eps, int relu) {
+    constexpr int PH = SmallRows<V>::PH, RW = SmallRows<V>::RW;
+    __shared__ float red[16 * PH][BS_CH + 1];
+    __shared__ float cmean[16][BS_CH], cm2[16][BS_CH], stat[2][BS_CH];
+    const SmallRows<V> own;
+    const int tid = threadIdx.x, nch = (rows + BS_RPC - 1) / BS_RPC, rw = rows - 1;
+    float v[RW][V], r[RW][V], ga[V], be[V];
+#pragma unroll
+    for (int u = 0; u < RW; u++) VecIO<T, V>::load(z + (size_t)min(own.row(u), rw) * C + own.c0, v[u]);
+    if (res) {
+#pragma unroll
+        for (int u = 0; u < RW; u++) VecIO<T, V>::load(res + (size_t)min(own.row(u), rw) * C + own.c0, r[u]);
+    }
+#pragma unroll
+    for (int e = 0; e < V; e++) { ga[e] = gamma[own.c0 + e]; be[e] = beta[own.c0 + e]; }
+    auto reduce_rows = [&](auto SECOND) {
+        float s[V], m[V];
+#pragma unroll
+        for (int e = 0; e < V; e++) { s[e] = 0.f; m[e] = decltype(SECOND)::value ? cmean[own.k0][own.cg * V + e] : 0.f; }
+#pragma unroll
+        for (int u = 0; u < RW; u++)
+            if (own.row(u) < rows) {
+#pragma unroll
+                for (int e = 0; e < V; e++) {
+                    const float d = v[u][e] - m[e];
+                    s[e] = decltype(SECOND)::value ? __builtin_fmaf(d, d, s[e]) : s[e] + d;
+                }
+            }
+#pragma unroll
+        for (int e = 0; e < V; e++) red[own.k0 * PH + own.ph][own.cg * V + e] = s[e];
+        __syncthreads();
+    };
+    const int k = tid / BS_CH, c = tid % BS_CH;
+    reduce_rows(std::false_type{});
+    if (k < 16) cmean[k][c] = phase_sum<PH>(red) / (float)max(1, min(BS_RPC, rows - k * BS_RPC));
+    __syncthreads();
+    reduce_rows(std::true_type{});
+    if (k < 16) cm2[k][c] = phase_sum<PH>(red);
+    __syncthreads();
+    if (tid < 64) {                                        // col_merge_stats_kernel's second half: a chunk is a phase here
+        const float before = (float)(c * BS_RPC), mine = (float)(c == nch - 1 ? rows - c * BS_RPC : BS_RPC);     // rows of lane c's chunk
+        const float q = mine / (before + mine);
+        RunStats t{0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < 16; i++)
+            if (i < nch) t.fold(lane_value(before, i), lane_value(q, i), cmean[i][c], cm2[i][c]);
+        const float vr = t.m2 / (float)rows, is = 1.f / sqrtf(vr + eps);
+        if (tid < BS_CH) {
+            const int gc = (int)blockIdx.x * BS_CH + c;
+            mean[gc] = t.mean; var[gc] = vr; inv[gc] = is;
+            stat[0][c] = t.mean; stat[1][c] = is;
+        }
+    }
+    __syncthreads();
+    float m[V], is[V];
+#pragma unroll
+    for (int e = 0; e < V; e++) { m[e] = stat[0][own.cg * V + e]; is[e] = stat[1][own.cg * V + e]; }
+#pragma unroll
+    for (int u = 0; u < RW; u++) {
+        float o[V];
+#pragma unroll
+        for (int e = 0; e < V; e++) {
+            float f = __builtin_fmaf((v[u][e] - m[e]) * is[e], ga[e], be[e]);
+            if (res) f += r[u][e];
+            if (relu) f = fmaxf(f, 0.f);
+            o[e] = f;
+        }
+        if (own.row(u) < rows) VecIO<T, V>::store(y + (size_t)own.row(u) * C + own.c0, o);
+    }
+}
+
+// the column sums and act_bn_bwd_kernel (bn)
+template <typename T, int V>
+__global__ void __launch_bounds__(1024) bn_small_bwd_kernel(const T *__restrict__ z, const T *__restrict__ dy, const T *__restrict__ y,
+                                                            const float *__restrict__ mean, const float *__restrict__ invstd,
+                                                            const float *__restrict__ gamma, float *__restrict__ dbeta, float *__restrict__ dgamma,
+                                                            T *__restrict__ dz, T *dres, int res_first, int rows, int C, int relu, float inv_m) {
+    constexpr int PH = SmallRows<V>::PH, RW = SmallRows<V>::RW;
+    __shared__ float red[2][16 * PH][BS_CH + 1];
+    __shared__ float csum[2][16][BS_CH], total[2][BS_CH];
+    const SmallRows<V> own;
+    const int tid = threadIdx.x, nch = (rows + BS_RPC - 1) / BS_RPC, rw = rows - 1;
+    float v[RW][V], g[RW][V], m[V], is[V], ga[V];
+#pragma unroll
+    for (int u = 0; u < RW; u++) {
+        const size_t i = (size_t)min(own.row(u), rw) * C + own.c0;
+        VecIO<T, V>::load(z + i, v[u]);
+        VecIO<T, V>::load(dy + i, g[u]);
+    }
+#pragma unroll
+    for (int e = 0; e < V; e++) { m[e] = mean[own.c0 + e]; is[e] = invstd[own.c0 + e]; ga[e] = gamma[own.c0 + e]; }
+    if (relu) {
+        float a[RW][V];
+#pragma unroll
+        for (int u = 0; u < RW; u++) VecIO<T, V>::load(y + (size_t)min(own.row(u), rw) * C + own.c0, a[u]);
+#pragma unroll
+        for (int u = 0; u < RW; u++)
+#pragma unroll
+            for (int e = 0; e < V; e++)
+                if (!(a[u][e] > 0.f)) g[u][e] = 0.f;
+    }
+    {
+        float s0[V], s1[V];
+#pragma unroll
+        for (int e = 0; e < V; e++) s0[e] = s1[e] = 0.f;
+#pragma unroll
+        for (int u = 0; u < RW; u++)
+            if (own.row(u) < rows) {
+#pragma unroll
+                for (int e = 0; e < V; e++) {
+                    s0[e] += g[u][e];
+                    s1[e] = __builtin_fmaf(g[u][e], (v[u][e] - m[e]) * is[e], s1[e]);
+                }
+            }
+        const int at = own.k0 * PH + own.ph;
+#pragma unroll
+        for (int e = 0; e < V; e++) { red[0][at][own.cg * V + e] = s0[e]; red[1][at][own.cg * V + e] = s1[e]; }
+    }
+    __syncthreads();
+    const int k = tid / BS_CH, c = tid % BS_CH;
+    if (k < 16) { csum[0][k][c] = phase_sum<PH>(red[0]); csum[1][k][c] = phase_sum<PH>(red[1]); }
+    __syncthreads();
+    if (tid < 2 * BS_CH) {                                 // in the order of the chunks
+        const int w = tid / BS_CH;
+        float s = 0.f;
+#pragma unroll
+        for (int p = 0; p < 16; p++) {
+            if (p < nch) s += csum[w][p][c];
+        }
+        total[w][c] = s;
+        (w ? dgamma : dbeta)[(int)blockIdx.x * BS_CH + c] = s;
+    }
+    __syncthreads();
+    float db[V], dg[V];
+#pragma unroll
+    for (int e = 0; e < V; e++) { db[e] = total[0][own.cg * V + e]; dg[e] = total[1][own.cg * V + e]; }
+#pragma unroll
+    for (int u = 0; u < RW; u++) {
+        if (own.row(u) >= rows) continue;
+        const size_t i = (size_t)own.row(u) * C + own.c0;
+        if (dres) {
+            if (res_first) {
+                VecIO<T, V>::store(dres + i, g[u]);
+            } else {
+                float a[V];
+                VecIO<T, V>::load(dres + i, a);
+#pragma unroll
+                for (int e = 0; e < V; e++) a[e] += g[u][e];
+                VecIO<T, V>::store(dres + i, a);
+            }
+        }
+        float o[V];
+#pragma unroll
+        for (int e = 0; e < V; e++) {
+#pragma clang fp contract(off)
+            const float xh = (v[u][e] - m[e]) * is[e];
+            o[e] = ga[e] * is[e] * __builtin_fmaf(-inv_m, xh * dg[e], g[u][e] - db[e] * inv_m);
+        }
+        VecIO<T, V>::store(dz + i, o);
+    }
+}
+
 // Zero-insertion of dz for a strided convolution: out[n][h*sh][w*sw][k] = dz[n][h][w][k], zero elsewhere,
 // on an [N][Hd][Wd][K] grid; the data-gradient is then a stride-1 convolution over `out`.  Bound by its stores; the 64-bit divisions
 // of an index into (n, h, w, k) took longer than those, so below 2^31 vectors all five are multiplications (WIDE otherwise).
@@ -1724,6 +1918,34 @@ sol_status launch_act_bn_bwd(const void *z, const void *dy, const void *y, const
                                static_cast<const T *>(z), static_cast<const T *>(dy), static_cast<const T *>(y), mean, invstd, gamma,
                                dbeta, dgamma, static_cast<T *>(dz), static_cast<T *>(dres), res_first, total / V, C, relu, bn, 1.f / rows);
     });
+    SOL_HIP(hipGetLastError());
+    return SOL_OK;
+}
+
+// whole vectors of channels, and the rows in one workgroup's registers
+bool bn_small_applies(int rows, int C) { return rows > 0 && rows <= BS_MAX_ROWS && C % BS_CH == 0; }
+
+sol_status launch_bn_small(const void *z, const void *res, void *y, const float *gamma, const float *beta, float *mean, float *var, float *invstd,
+                           int rows, int C, float eps, int relu, int dt, hipStream_t st) {
+    auto run = [&](auto t, auto vec) {
+        typedef decltype(t) T;
+        hipLaunchKernelGGL((bn_small_kernel<T, decltype(vec)::value>), dim3(C / BS_CH), dim3(1024), 0, st, static_cast<const T *>(z),
+                           static_cast<const T *>(res), static_cast<T *>(y), gamma, beta, mean, var, invstd, rows, C, eps, relu);
+    };
+    if (dt == SOL_BF16) run(bf16_t{}, std::integral_constant<int, 8>{}); else run(0.f, std::integral_constant<int, 4>{});
+    SOL_HIP(hipGetLastError());
+    return SOL_OK;
+}
+
+sol_status launch_bn_small_bwd(const void *z, const void *dy, const void *y, const float *mean, const float *invstd, const float *gamma, float *dbeta,
+                               float *dgamma, void *dz, void *dres, int res_first, int rows, int C, int relu, int dt, hipStream_t st) {
+    auto run = [&](auto t, auto vec) {
+        typedef decltype(t) T;
+        hipLaunchKernelGGL((bn_small_bwd_kernel<T, decltype(vec)::value>), dim3(C / BS_CH), dim3(1024), 0, st,
+                           static_cast<const T *>(z), static_cast<const T *>(dy), static_cast<const T *>(y), mean, invstd, gamma, dbeta, dgamma,
+                           static_cast<T *>(dz), static_cast<T *>(dres), res_first, rows, C, relu, 1.f / rows);
+    };
+    if (dt == SOL_BF16) run(bf16_t{}, std::integral_constant<int, 8>{}); else run(0.f, std::integral_constant<int, 4>{});
     SOL_HIP(hipGetLastError());
     return SOL_OK;
 }

@@ -1,0 +1,56 @@
+"""Batch norm of at most 1024 rows in one launch each way: against the checker, and bit for bit against the launches that longer tensors take."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2003_10688_amd import workloads as wl
+from test_gpu_training import compare, gpu_train, oracle_train, sol  # noqa: F401  (sol: the module fixture)
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [(1, 7, 9), (1, 8, 8), (5, 1, 13), (3, 11, 31), (4, 16, 16), (5, 5, 41)]       # 63, 64, 65, 1023, 1024 and 1025 rows
+
+
+def _net(c):
+    return [wl.conv(c, 1, p=0), wl.conv(c, 1, p=0, res=0), wl.gap(), wl.linear(8)]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: str(s[0] * s[1] * s[2]))
+@pytest.mark.parametrize("c", [16, 48])
+def test_step_against_checker(sol, dtype, shape, c):  # noqa: F811
+    n, h, w = shape
+    rng = np.random.default_rng([n, h, w, c])
+    layers = _net(c)
+    params = wl.make_params(layers, 16, 3, bf16=(dtype == "bf16"), bias_std=0.3)
+    x = rng.standard_normal((n, 16, h, w)).astype(np.float32)
+    if dtype == "bf16":
+        x = torch.from_numpy(x).to(torch.bfloat16).float().numpy()
+    for l, prm in zip(layers, params):      # a BN layer's bias has no effect on the loss
+        if l["kind"] == "conv":
+            prm["bias"] = np.zeros_like(prm["bias"])
+    labels = wl.make_labels(n, 8, 5)
+    got, want = gpu_train(sol, layers, params, x, labels, dtype)[1][0], oracle_train(layers, params, x, labels, dtype)[0]
+    compare(got, want, layers, dtype, elementwise=(dtype == "f32"))
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shape", [(1, 1, 1)] + SHAPES[:-1], ids=lambda s: str(s[0] * s[1] * s[2]))
+def test_forward_bits(sol, dtype, shape):  # noqa: F811
+    """The first 16 channels of a layer of 24 (no whole groups of 16: the general launches) are a layer of 16 with the same filters."""
+    n, h, w = shape
+    d = sol.BF16 if dtype == "bf16" else sol.F32
+    gen = torch.Generator().manual_seed(n * h * w)
+    x = torch.randn((n, 16, h, w), generator=gen).numpy()
+    params = wl.make_params(_net(24), 16, 3, bf16=(dtype == "bf16"), bias_std=0.3)
+    got = []
+    for c in (16, 24):
+        layers = [wl.conv(c, 1, p=0), wl.gap(), wl.linear(8)]
+        p = [{k: (v[:c] if isinstance(v, np.ndarray) else v) for k, v in params[0].items()}, {}, {"w": np.ones((8, c), np.float32), "bias": np.zeros(8, np.float32)}]
+        net = sol.Network(layers, x.shape, d, flags=sol.NET_TRAINING)
+        net.set_params(p)
+        net.forward(sol.to_device_nhwc(x, d))
+        torch.cuda.synchronize()
+        got.append([net.tensor(0, which).cpu().numpy()[:16] for which in (sol.NT_MEAN, sol.NT_VAR)] + [sol.to_host_nchw(net.layer_output(0))[:, :16]])
+    for a, b in zip(*got):
+        assert np.array_equal(a, b)
