@@ -193,7 +193,7 @@ def test_plan_fuses_stem_and_pool_only_when_it_may(sol):
     r_keep, ws_keep = fused(wk.layers, wk.in_shape, sol.BF16, sol.NET_KEEP_ACTIVATIONS)
     assert r_keep == list(range(n)) and ws_keep > ws
     assert fused(wk.layers, wk.in_shape, sol.BF16, sol.NET_TRAINING)[0] == list(range(n))
-    assert fused(wk.layers, wk.in_shape, sol.F32)[0] == list(range(n))                     # fp32: no stem kernel
+    assert fused(wk.layers, wk.in_shape, sol.F32)[0] == [0, 0] + list(range(2, n))         # fp32: the stem pair alone
     stem, pool = wl.conv(64, 7, 2, 3), wl.pool("max", 3, 2, 1)
     tail = [wl.conv(8, 1)]
     assert fused([stem, pool] + tail, (2, 3, 40, 40), sol.BF16)[0] == [0, 0, 2]
