@@ -273,6 +273,11 @@ void sol_debug_set_conv_tile(int tile);
 /* Which kernel the last convolution launched by the CALLING THREAD ran on (test aid): "small" (conv_small), "pre" (conv_pre), "chain"
  * (conv_chain), or "" for every other one.  Layers that one launch computes together do not count. */
 const char *sol_debug_conv_kernel(void);
+/* The tile id that the estimate of times takes for a convolution when none is asked for, with or without a residual and a fused 2x2 pool
+ * (NULL: none); gradient != 0: for the data gradient of an fp32 training network.  0: no estimate holds, another rule decides.
+ * Host code (test aid). */
+sol_status sol_debug_choose_conv_tile(const sol_tensor_desc *x, const sol_conv_desc *conv, int residual, const sol_pool_desc *pool, int gradient,
+                                      int *tile);
 
 /* Measured ceilings for the roofline report (benchmark aid; no layer arithmetic).
  *   sol_debug_probe_copy   a plain device-to-device copy of `bytes` (multiple of 16; 16-byte aligned, non-overlapping

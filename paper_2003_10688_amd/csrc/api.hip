@@ -65,30 +65,35 @@ struct PairOperand { const void *x2, *w2; const float *scale2, *shift2; int H2, 
 // input side of a pre-activation convolution / of a convolution that reads a channel prefix of a wider tensor
 struct InputSide { const float *pre_scale, *pre_shift; int ldx, cvalid; };   // NULL / NULL: no BN + ReLU; ldx 0: dense; cvalid 0: all channels real
 
+// sizes of a dense convolution without a pool
+static ConvArgs conv_args(const sol_tensor_desc &xd, const sol_conv_desc &cd) {
+    ConvArgs a;
+    memset(static_cast<void *>(&a), 0, sizeof(a));
+    a.N = xd.n; a.H = xd.h; a.W = xd.w; a.C = a.ldx = a.Cvalid = xd.c;
+    a.Cout = a.ldy = cd.cout; a.R = cd.kh; a.S = cd.kw; a.sh = cd.sh; a.sw = cd.sw; a.ph = cd.ph; a.pw = cd.pw;
+    a.Ho = a.Hy = out_size(xd.h, cd.kh, cd.sh, cd.ph); a.Wo = a.Wy = out_size(xd.w, cd.kw, cd.sw, cd.pw);
+    a.P = (int)((unsigned)xd.n * (unsigned)a.Ho * (unsigned)a.Wo);     // of 2^31 and more: refused before it is used
+    a.Kp = packed_k(cd, xd.dtype);
+    a.Ktot = cd.kh * cd.kw * cd.cin;
+    return a;
+}
+
 // Shared by sol_conv2d_fused and the network executor.
 static sol_status conv_fused_impl(const sol_tensor_desc &xd, const void *x, const sol_conv_desc &cd, const void *w,
                                   const float *scale, const float *shift, const void *res, int act,
                                   const sol_pool_desc *pool, void *y, int32_t *argmax, void *prepool, int tile,
                                   hipStream_t st, int ldy = 0,     // ldy: elements between output pixels in y, 0 = cout (dense)
                                   const PairOperand *pair = nullptr, const InputSide *ins = nullptr,
-                                  bool one_order = false,        // see launch_conv
+                                  SumOrder order = SUMS_ANY,     // see launch_conv
                                   bool planned = false) {         // called by a network's plan
     SOL_REQUIRE(cd.cin == xd.c, SOL_ERR_SHAPE, "conv cin %d != input channels %d", cd.cin, xd.c);
     SOL_REQUIRE(act == SOL_ACT_NONE || act == SOL_ACT_RELU, SOL_ERR_SHAPE, "bad activation %d", act);
     const int Ho = out_size(xd.h, cd.kh, cd.sh, cd.ph), Wo = out_size(xd.w, cd.kw, cd.sw, cd.pw);
     SOL_REQUIRE(xd.h + 2 * cd.ph >= cd.kh && xd.w + 2 * cd.pw >= cd.kw && Ho > 0 && Wo > 0, SOL_ERR_SHAPE,
                 "filter %dx%d larger than padded input %dx%d", cd.kh, cd.kw, xd.h + 2 * cd.ph, xd.w + 2 * cd.pw);
-    ConvArgs a;
-    memset(static_cast<void *>(&a), 0, sizeof(a));
-    a.N = xd.n; a.H = xd.h; a.W = xd.w; a.C = xd.c;
-    a.Cout = cd.cout; a.R = cd.kh; a.S = cd.kw; a.sh = cd.sh; a.sw = cd.sw; a.ph = cd.ph; a.pw = cd.pw;
-    a.Ho = Ho; a.Wo = Wo;
-    a.Kp = packed_k(cd, xd.dtype);
-    a.Ktot = cd.kh * cd.kw * cd.cin;
+    ConvArgs a = conv_args(xd, cd);
     a.act = act;
     a.res = res;
-    a.pool = 0;
-    a.Hy = Ho; a.Wy = Wo;
     if (pool && pool->kind != SOL_POOL_NONE) {
         SOL_TRY(check_pool(pool));
         if (pool_is_fusable(*pool)) {
@@ -105,7 +110,6 @@ static sol_status conv_fused_impl(const sol_tensor_desc &xd, const void *x, cons
             a.Hy = out_size(Ho, 3, 2, pool->ph); a.Wy = out_size(Wo, 3, 2, pool->pw);
         }
     }
-    a.ldy = cd.cout;
     if (ldy != 0 && ldy != cd.cout) {
         SOL_REQUIRE(ldy > cd.cout && ldy % 8 == 0 && cd.cout % 8 == 0, SOL_ERR_SHAPE,
                     "output pitch %d: a multiple of 8 above cout (%d, itself a multiple of 8)", ldy, cd.cout);
@@ -113,8 +117,6 @@ static sol_status conv_fused_impl(const sol_tensor_desc &xd, const void *x, cons
         a.ldy = ldy;
     }
     SOL_REQUIRE((double)xd.n * Ho * Wo * a.ldy < 2147483648.0, SOL_ERR_UNSUPPORTED, "output spans 2^31 elements or more");
-    a.ldx = xd.c;
-    a.Cvalid = xd.c;
     if (ins) {
         SOL_REQUIRE((ins->pre_scale == nullptr) == (ins->pre_shift == nullptr), SOL_ERR_NULL, "input-side scale and shift come together");
         SOL_REQUIRE(aligned16(ins->pre_scale) && aligned16(ins->pre_shift), SOL_ERR_ALIGN, "device pointers must be 16-byte aligned");
@@ -140,7 +142,7 @@ static sol_status conv_fused_impl(const sol_tensor_desc &xd, const void *x, cons
     const bool quad = a.pool == 1 || a.pool == 2;
     a.argmax = a.pool == 1 ? argmax : nullptr;
     a.prepool = quad ? prepool : nullptr;
-    a.P = quad ? xd.n * a.Hy * a.Wy * 4 : xd.n * Ho * Wo;
+    if (quad) a.P = xd.n * a.Hy * a.Wy * 4;
     a.dw = FastDiv((uint32_t)(quad ? a.Wy : Wo));
     a.dh = FastDiv((uint32_t)(quad ? a.Hy : Ho));
     if (a.pool == 3) return launch_conv_stem_pool(a, xd.dtype, pool->ph, st);   // one kernel, no tile choice
@@ -154,7 +156,7 @@ static sol_status conv_fused_impl(const sol_tensor_desc &xd, const void *x, cons
                                            pair->stride, st);
         return launch_conv_pair(a, pair->x2, pair->w2, pair->scale2, pair->shift2, pair->H2, pair->W2, pair->K2, pair->Kp2, pair->stride, st);
     }
-    return launch_conv(a, xd.dtype, tile, st, one_order);
+    return launch_conv(a, xd.dtype, tile, st, order);
 }
 
 static sol_status pool_impl(const sol_tensor_desc &xd, const void *x, const sol_pool_desc &pd, void *y, int32_t *argmax,
@@ -360,11 +362,7 @@ static sol_status plan_training(sol_network *net, Arena &ar) {
 
 // can this convolution layer run fused with the 3x3 stride-2 max pool `p` behind it (conv_stem_pool_kernel)?
 static bool stem_pool_plan_ok(const sol_tensor_desc &in, const sol_conv_desc &cd, const sol_layer &L, const sol_pool_desc &p) {
-    ConvArgs a;
-    memset(static_cast<void *>(&a), 0, sizeof(a));
-    a.N = in.n; a.H = in.h; a.W = in.w; a.C = in.c;
-    a.Cout = cd.cout; a.R = cd.kh; a.S = cd.kw; a.sh = cd.sh; a.sw = cd.sw; a.ph = cd.ph; a.pw = cd.pw;
-    a.Kp = packed_k(cd, in.dtype);
+    ConvArgs a = conv_args(in, cd);
     a.act = L.act;
     return L.res < 0 && stem_pool_applies(a, in.dtype, p);
 }
@@ -865,6 +863,23 @@ int sol_out_size(int in, int k, int stride, int pad) { return out_size(in, k, st
 // Debugging / sweeping aid: force the convolution tile for later calls of the calling thread (0 = automatic).
 void sol_debug_set_conv_tile(int tile) { g_tile_override = tile; }
 const char *sol_debug_conv_kernel(void) { return conv_kernel_of_thread(); }
+sol_status sol_debug_choose_conv_tile(const sol_tensor_desc *xd, const sol_conv_desc *cd, int residual, const sol_pool_desc *pool, int gradient, int *tile) {
+    SOL_TRY(check_tensor(xd, "x"));
+    SOL_TRY(check_conv(cd));
+    SOL_REQUIRE(tile, SOL_ERR_NULL, "tile is NULL");
+    ConvArgs a = conv_args(*xd, *cd);
+    SOL_REQUIRE(cd->cin == xd->c && xd->h + 2 * cd->ph >= cd->kh && xd->w + 2 * cd->pw >= cd->kw, SOL_ERR_SHAPE, "convolution does not fit its input");
+    SOL_REQUIRE((double)xd->n * a.Ho * a.Wo * cd->cout < 2147483648.0, SOL_ERR_UNSUPPORTED, "output spans 2^31 elements or more");
+    a.res = residual ? xd : nullptr;                       // not looked into
+    if (pool && pool->kind != SOL_POOL_NONE) {
+        SOL_REQUIRE(pool_is_fusable(*pool), SOL_ERR_UNSUPPORTED, "not a pool that any convolution can fuse");
+        a.pool = pool->kind == SOL_POOL_MAX ? 1 : 2;
+        a.Hy = a.Ho / 2; a.Wy = a.Wo / 2;
+        a.P = a.N * a.Hy * a.Wy * 4;
+    }
+    *tile = conv_choose_tile(a, xd->dtype, gradient ? SUMS_GRADIENT : SUMS_ANY);
+    return SOL_OK;
+}
 
 size_t sol_packed_weight_bytes(const sol_conv_desc *cd, sol_dtype dt) {
     if (!cd || cd->cout <= 0 || cd->cin <= 0 || cd->kh <= 0 || cd->kw <= 0) return 0;
@@ -1130,20 +1145,20 @@ static sol_status train_conv_fwd(const sol_network *net, const LayerPlan &lp, co
     const void *in = layer_in(net, lp.src, x, ws);
     const bool bn = lp.L.kind == SOL_LAYER_CONV && lp.L.has_bn;
     const float *bias = vec_ptr(net, lp, VEC_BIAS);
-    const bool one_order = lp.in.dtype == SOL_F32;
+    const SumOrder order = lp.in.dtype == SOL_F32 ? SUMS_CHAIN : SUMS_ANY;
     if (bn)
         return conv_fused_impl(lp.in, in, lp.cd, net->params + lp.w_off, nullptr, bias, nullptr, SOL_ACT_NONE, nullptr, ws + lp.z_off,
-                               nullptr, nullptr, tile, st, 0, nullptr, nullptr, one_order);
+                               nullptr, nullptr, tile, st, 0, nullptr, nullptr, order);
     const void *res = lp.res >= 0 ? layer_in(net, lp.res, x, ws) : nullptr;
     return conv_fused_impl(lp.in, in, lp.cd, net->params + lp.w_off, nullptr, bias, res, lp.L.act, nullptr, ws + lp.out_off, nullptr,
-                           nullptr, tile, st, 0, nullptr, nullptr, one_order);
+                           nullptr, tile, st, 0, nullptr, nullptr, order);
 }
 
 static sol_status train_conv_dgrad(const sol_network *net, const LayerPlan &lp, const void *g, unsigned char *ws, int tile,
                                    hipStream_t st) {
     void *dsrc = ws + net->layers[lp.src].dact_off;
     return conv_fused_impl(lp.dzd, g, lp.dcd, net->params + lp.wT_off, nullptr, nullptr, lp.src_first ? nullptr : dsrc, SOL_ACT_NONE,
-                           nullptr, dsrc, nullptr, nullptr, tile, st);
+                           nullptr, dsrc, nullptr, nullptr, tile, st, 0, nullptr, nullptr, lp.in.dtype == SOL_F32 ? SUMS_GRADIENT : SUMS_ANY);
 }
 
 // Forward with batch statistics: conv -> z (stored), statistics of the stored z, then BN + residual + act
@@ -1440,7 +1455,7 @@ static sol_status run_layers(sol_network *net, const void *x, void *y, void *wor
                 }
                 SOL_TRY(conv_fused_impl(lp.in, in, lp.cd, net->params + lp.w_off, scale, shift, res, lp.L.act,
                                         fused, conv_dst, nullptr, nullptr,
-                                        g_tile_override ? g_tile_override : lp.tile, st, ldy, nullptr, nullptr, false, true));
+                                        g_tile_override ? g_tile_override : lp.tile, st, ldy, nullptr, nullptr, SUMS_ANY, true));
                 if (lp.split_pool) SOL_TRY(pool_impl(lp.conv_out, conv_dst, lp.L.pool, out, nullptr, st));
                 break;
             }
@@ -1581,7 +1596,7 @@ static sol_status autotune_training(sol_network *net, const void *x, void *y, vo
             int best_tile = T_AUTO;
             const sol_tensor_desc &shape = dg ? lp.in : lp.conv_out;
             for (int cand : kTuneCandidates) {
-                if (tune_skips(cand, shape) || (!dg && lp.in.dtype == SOL_F32 && cand >= S_FIRST && cand <= S_LAST)) continue;   // (see launch_conv: one_order)
+                if (tune_skips(cand, shape) || (!dg && lp.in.dtype == SOL_F32 && cand >= S_FIRST && cand <= S_LAST)) continue;   // (see launch_conv: SUMS_CHAIN)
                 float ms = 0.f;
                 const sol_status cs = time_conv(i, dg, cand, &ms);
                 if (cs == SOL_ERR_HIP) { rs = cs; break; }

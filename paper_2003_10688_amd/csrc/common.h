@@ -159,7 +159,10 @@ bool gemm8_kernel_applies(const ConvArgs &a, int dt);
 sol_status launch_conv_gemm8(const ConvArgs &a, int tile, hipStream_t st);
 bool direct_kernel_applies(const ConvArgs &a, int dt);
 int direct_choose_pre_tile(const ConvArgs &a, int dt);
-int conv_choose_tile(const ConvArgs &a, int dt);         // conv_choose.hip
+// Which kernels an automatic choice may take, by the order in which they add up a reduction (fp32; see launch_conv, conv_choose_tile)
+enum SumOrder { SUMS_ANY, SUMS_CHAIN, SUMS_GRADIENT };
+int conv_choose_tile(const ConvArgs &a, int dt, SumOrder order);        // conv_choose.hip
+int conv_rule_tile(const ConvArgs &a, int dt);           // conv_igemm.hip
 float conv_tile_estimate(int tile, int dt, long P, int Cout, float kbytes, float res, float mbytes);
 sol_status launch_conv_direct(const ConvArgs &a, int dt, int tile, hipStream_t st);
 int direct_choose_pair_tile(const ConvArgs &a, int K2);
@@ -236,7 +239,7 @@ bool linear_kernel_applies(const ConvArgs &a, int dt);
 sol_status launch_linear(const ConvArgs &a, int dt, hipStream_t st);
 bool linear_stream_applies(const ConvArgs &a, int dt);   // up to 128 rows, weights streamed (linear.hip)
 sol_status launch_linear_stream(const ConvArgs &a, int dt, hipStream_t st);
-sol_status launch_conv(const ConvArgs &a, int dt, int tile_override, hipStream_t st, bool one_order = false);
+sol_status launch_conv(const ConvArgs &a, int dt, int tile_override, hipStream_t st, SumOrder order = SUMS_ANY);
 sol_status launch_pool(const PoolArgs &a, int dt, hipStream_t st);
 sol_status launch_dwconv(const DwArgs &a, int dt, hipStream_t st);
 sol_status launch_pack_dw(int C, int taps, int dt, const float *w, void *packed, hipStream_t st);

@@ -254,7 +254,8 @@ static bool dma_kernel_applies(const ConvArgs &a, int esize) {
     return a.R * a.S <= 32 && xb < 4294967296.0 && (double)a.Cout * a.Kp * esize < 4294967296.0;
 }
 
-static int choose_tile(const ConvArgs &a, int esize) {
+int conv_rule_tile(const ConvArgs &a, int dt) {
+    const int esize = (int)dtype_size(dt);
     const bool dma_ok = dma_kernel_applies(a, esize);
     const bool dma128 = dma_ok && a.C % (128 / esize) == 0, dma64 = dma_ok && a.C % (64 / esize) == 0;
     if (a.Cout <= 32 || !dma64) return a.C % (128 / esize) == 0 ? (a.Cout <= 32 ? T_128x32 : T_128x64)
@@ -273,7 +274,7 @@ static int choose_tile(const ConvArgs &a, int esize) {
 template <typename T> static sol_status launch_typed(const ConvArgs &a, int tile, hipStream_t st) {
     constexpr int BK = 128 / (int)sizeof(T);
     const bool vec = a.C % BK == 0;
-    if (tile == T_AUTO) tile = choose_tile(a, (int)sizeof(T));
+    if (tile == T_AUTO) tile = conv_rule_tile(a, sizeof(T) == 2 ? SOL_BF16 : SOL_F32);
     if (dma_tile_row_bytes(tile)) return launch_conv_dma(a, sizeof(T) == 2 ? SOL_BF16 : SOL_F32, tile, st);
     if (!vec) {
         switch (tile) {
@@ -301,9 +302,9 @@ const char *conv_kernel_of_thread() { return t_kernel; }
 // through registers before it is multiplied.  A pre-activated 1x1 convolution of whole chunks takes its fragments from memory
 // directly (conv_pre, bf16) or transforms them between LDS and the products (conv_direct, fp32); everything else, and a tile asked for, the
 // register-staged kernel, which transforms on the way to LDS.
-static sol_status launch_conv_staged(const ConvArgs &a, int dt, int tile, hipStream_t st, bool one_order) {
+static sol_status launch_conv_staged(const ConvArgs &a, int dt, int tile, hipStream_t st, SumOrder order) {
     if (tile == T_AUTO && pre_kernel_applies(a, dt)) { t_kernel = "pre"; return launch_conv_pre(a, st); }
-    if (tile == T_AUTO && !one_order)
+    if (tile == T_AUTO && order != SUMS_CHAIN)
         if (const int t = direct_choose_pre_tile(a, dt)) { t_kernel = "direct"; return launch_conv_direct(a, dt, t, st); }
     if (!(tile >= T_256x128 && tile <= T_64x128)) {
         SOL_REQUIRE(tile == T_AUTO || tile == T_NO_HALO, SOL_ERR_UNSUPPORTED,
@@ -316,15 +317,17 @@ static sol_status launch_conv_staged(const ConvArgs &a, int dt, int tile, hipStr
     SOL_FAIL(SOL_ERR_DTYPE, "unknown dtype %d", dt);
 }
 
-// one_order: the automatic choice leaves out the kernels that split a reduction by the size of the layer (the small tiles, the
-// weight-streaming linear kernel), so that in fp32, where every remaining one walks a reduction the same way, an output does not
-// depend on how many pixels or rows stand beside it, to the last bit.  The forward pass of an fp32 training step asks for it: a
+// SUMS_CHAIN: the automatic choice leaves out the kernels that split a reduction by the size of the layer (the small tiles, the
+// weight-streaming linear kernel), and the tile is conv_rule_tile's, whose bits the chain kernel repeats: in fp32 the order of an
+// output's sum does not change when kernels are added or estimates fitted anew.  The forward pass of an fp32 training step asks for it: a
 // pre-activation or pooling candidate within a rounding of its threshold, decided the other way, moves a whole term of a weight
 // gradient (9 images of 113x113, ResNet-18-shaped: up to 0.02 of a gradient's norm, 2.5 of its rms in one element).
-sol_status launch_conv(const ConvArgs &a, int dt, int tile_override, hipStream_t st, bool one_order) {
+// SUMS_GRADIENT: its data gradients, for the same reason; see gradient_tile (conv_choose.hip).
+sol_status launch_conv(const ConvArgs &a, int dt, int tile_override, hipStream_t st, SumOrder order) {
+    const bool one_order = order == SUMS_CHAIN;
     t_kernel = "";
     if (a.P <= 0) return SOL_OK;   // empty batch: nothing to do
-    if (a.pre_scale || a.ldx != a.C || a.Cvalid != a.C) return launch_conv_staged(a, dt, tile_override, st, one_order);
+    if (a.pre_scale || a.ldx != a.C || a.Cvalid != a.C) return launch_conv_staged(a, dt, tile_override, st, order);
     if (tile_override == T_AUTO && stem_kernel_applies(a, dt)) return launch_conv_stem(a, st);
     if (tile_override == T_AUTO && !one_order && small_kernel_applies(a, dt)) { t_kernel = "small"; return launch_conv_small(a, dt, st); }
     if (tile_override == T_AUTO && !one_order && linear_stream_applies(a, dt)) return launch_linear_stream(a, dt, st);
@@ -341,7 +344,7 @@ sol_status launch_conv(const ConvArgs &a, int dt, int tile_override, hipStream_t
         }
         return launch_linear(a, dt, st);
     }
-    if (tile_override == T_AUTO && !one_order) tile_override = conv_choose_tile(a, dt);
+    if (tile_override == T_AUTO && !one_order) tile_override = conv_choose_tile(a, dt, order);
     if (tile_override >= H_FIRST && tile_override <= H_LAST) {
         SOL_REQUIRE(halo_kernel_applies(a, dt), SOL_ERR_UNSUPPORTED,
                     "conv tile %d needs a bf16 3x3 stride-1 pad-1 convolution with Cin %% 64 == 0 and no fused pool", tile_override);
@@ -366,7 +369,7 @@ sol_status launch_conv(const ConvArgs &a, int dt, int tile_override, hipStream_t
         return launch_conv_dma(a, dt, tile_override, st);
     }
     // fewer than 192 tiles of 128x128 and 32-channel chunks: the ring kernel's 64x64 tile, or the same sums on smaller ones
-    if (one_order && dt == SOL_F32 && tile_override == T_AUTO && choose_tile(a, 4) == D_64x64_128x3 && chain_kernel_applies(a)) { t_kernel = "chain"; return launch_conv_chain(a, st); }
+    if (one_order && dt == SOL_F32 && tile_override == T_AUTO && conv_rule_tile(a, SOL_F32) == D_64x64_128x3 && chain_kernel_applies(a)) { t_kernel = "chain"; return launch_conv_chain(a, st); }
     if (dt == SOL_BF16) return launch_typed<bf16_t>(a, tile_override, st);
     if (dt == SOL_F32) return launch_typed<float>(a, tile_override, st);
     SOL_FAIL(SOL_ERR_DTYPE, "unknown dtype %d", dt);

@@ -312,6 +312,13 @@ def sol_debug_conv_kernel():
     return lib().sol_debug_conv_kernel().decode()
 
 
+def sol_debug_choose_conv_tile(xd, cd, residual=False, pool=None, gradient=False):
+    """Tile id that the estimate of times takes for a convolution (TensorDesc, ConvDesc), 0 where another rule decides; runs on the host."""
+    t = C.c_int(-1)
+    _check(lib().sol_debug_choose_conv_tile(C.byref(xd), C.byref(cd), C.c_int(int(residual)), C.byref(pool) if pool else None, C.c_int(int(gradient)), C.byref(t)))
+    return t.value
+
+
 def sol_debug_probe_copy(dst, src, stream=None):
     """Plain device-to-device copy of src into dst (uint8 tensors of equal size, a multiple of 16 bytes)."""
     assert dst.numel() * dst.element_size() == src.numel() * src.element_size()

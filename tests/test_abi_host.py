@@ -207,6 +207,38 @@ def test_plan_fuses_stem_and_pool_only_when_it_may(sol):
     assert L.sol_network_layer_fused_into(None, 0, C.byref(t)) == 1
 
 
+# tiles that add up a reduction alike (tests/test_gpu_grad_order.py): split over waves, staged in registers, ring kernel by pixels x bytes
+SUM_ORDERS = {"split": (81, 82, 83, 84, 85), "staged": tuple(range(1, 9)), "64x64": (15, 18, 33), "64x128": (24, 26), "128x64": (11, 12, 14, 16, 25, 32),
+              "128x128": (21, 22, 23)}
+# (batch, channels of the gradient, of the layer's input, filter): the order, and from which square image on it is
+GRADIENT_ORDERS = {
+    (1, 64, 64, 3): {2: "split", 111: "64x128"}, (1, 128, 64, 1): {2: "split", 74: "64x128", 111: "64x64"},
+    (1, 256, 256, 3): {2: "split", 75: "64x128", 111: "128x128"}, (1, 512, 512, 3): {2: "split", 55: "64x128", 78: "128x128"},
+    (1, 64, 256, 1): {2: "split", 23: "64x128", 55: "64x64", 78: "64x128", 111: "128x128"},
+    (9, 64, 64, 3): {2: "split", 37: "64x128"}, (9, 128, 64, 1): {2: "split", 25: "64x128", 37: "64x64"},
+    (9, 128, 128, 3): {2: "split", 32: "64x128", 53: "128x128"}, (9, 256, 256, 3): {2: "split", 25: "64x128", 37: "128x128", 86: "128x64"},
+    (9, 512, 512, 3): {2: "split", 19: "64x128", 26: "128x128", 61: "128x64"}, (9, 512, 256, 1): {2: "split", 19: "64x128", 37: "128x128", 86: "128x64"},
+    (9, 64, 256, 1): {2: "split", 8: "64x128", 19: "64x64", 26: "64x128", 37: "128x128", 86: "128x64"},
+    (9, 64, 32, 3): {2: "split", 37: "staged"}, (9, 48, 64, 3): {2: "64x64"},
+    (32, 128, 64, 1): {2: "split", 13: "64x128", 20: "64x64"}, (32, 128, 128, 3): {2: "split", 17: "64x128", 28: "128x128", 64: "128x64"},
+    (32, 64, 256, 1): {2: "split", 5: "64x128", 10: "64x64", 14: "64x128", 20: "128x128", 46: "128x64"},
+}
+
+
+def test_order_of_fp32_data_gradients_is_pinned(sol):
+    """The order in which an fp32 data gradient adds up decides its last bits, and through them where a training run ends: it must not
+    move when the estimates of times do."""
+    for (n, c, k, f), pins in GRADIENT_ORDERS.items():
+        want = None
+        for hw in range(2, 113):
+            want = pins.get(hw, want)
+            t = sol.sol_debug_choose_conv_tile(sol.TensorDesc(n, hw, hw, c, sol.F32), sol.ConvDesc(k, c, f, f, 1, 1, f // 2, f // 2), gradient=True)
+            assert t in SUM_ORDERS[want], (n, c, k, f, hw, t)
+    for hw in range(2, 80):                                 # bf16: the fastest estimate
+        xd, cd = sol.TensorDesc(9, hw, hw, 128, sol.BF16), sol.ConvDesc(64, 128, 3, 3, 1, 1, 1, 1)
+        assert sol.sol_debug_choose_conv_tile(xd, cd, gradient=True) == sol.sol_debug_choose_conv_tile(xd, cd)
+
+
 def test_concat_planning_and_validation(sol):
     """Channel concatenation layers: shapes, refusals, and which producers the plan lets write in place."""
     L = sol.lib()
