@@ -364,7 +364,7 @@ static sol_status plan_training(sol_network *net, Arena &ar) {
 static bool stem_pool_plan_ok(const sol_tensor_desc &in, const sol_conv_desc &cd, const sol_layer &L, const sol_pool_desc &p) {
     ConvArgs a = conv_args(in, cd);
     a.act = L.act;
-    return L.res < 0 && stem_pool_applies(a, in.dtype, p);
+    return L.res < 0 && !L.pre_bn && stem_pool_applies(a, in.dtype, p);
 }
 
 // The plan's own choice for a dense layer whose 3x3 convolution is c2: see dense_one_launch_pays

@@ -207,6 +207,26 @@ def test_plan_fuses_stem_and_pool_only_when_it_may(sol):
     assert L.sol_network_layer_fused_into(None, 0, C.byref(t)) == 1
 
 
+@pytest.mark.parametrize("k", [3, 7])
+@pytest.mark.parametrize("pad", [0, 1])
+def test_plan_leaves_a_pre_activated_stem_alone(sol, k, pad):
+    """The stem + pool kernel has no BN + ReLU on its input side: such a convolution and its pool stay two launches, as two layers and as one."""
+    L = sol.lib()
+    t, pool = C.c_int(-1), wl.pool("max", 3, 2, pad)
+    for dt in (sol.F32, sol.BF16):
+        for pre, want in ((False, 0), (True, 1)):
+            st, h = _create(sol, [wl.conv(64, k, 2, k // 2, pre_bn=pre), pool, wl.conv(8, 1)], (2, 3, 40, 40), dt)
+            assert st == 0 and L.sol_network_layer_fused_into(h, 1, C.byref(t)) == 0 and t.value == want
+            L.sol_network_destroy(h)
+        ws = []
+        for pre in (False, True):                          # the pool inside the layer: apart from it, the convolution's output needs a buffer
+            st, h = _create(sol, [wl.conv(64, k, 2, k // 2, pre_bn=pre, pool=wl.pool_desc("max", 3, 2, pad)), wl.conv(8, 1)], (2, 3, 40, 40), dt)
+            assert st == 0
+            ws.append(L.sol_network_workspace_bytes(h))
+            L.sol_network_destroy(h)
+        assert ws[1] >= ws[0] + 2 * 64 * 20 * 20 * (2 if dt == sol.BF16 else 4)
+
+
 # tiles that add up a reduction alike (tests/test_gpu_grad_order.py): split over waves, staged in registers, ring kernel by pixels x bytes
 SUM_ORDERS = {"split": (81, 82, 83, 84, 85), "staged": tuple(range(1, 9)), "64x64": (15, 18, 33), "64x128": (24, 26), "128x64": (11, 12, 14, 16, 25, 32),
               "128x128": (21, 22, 23)}

@@ -44,6 +44,25 @@ def test_stem_pool_planned(sol, dt, k, pad, case):  # noqa: F811
         assert rel_err(ys[False], ys[True]) <= 2 * TOL[dt]
 
 
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("k", [3, 7])
+@pytest.mark.parametrize("pad", [0, 1])
+@pytest.mark.parametrize("inside", [False, True])
+def test_pre_activated_stem(sol, dt, k, pad, inside):  # noqa: F811
+    """BN + ReLU on the stem's input side, with the pool behind it as a layer of its own and inside the layer."""
+    d = sol.BF16 if dt == "bf16" else sol.F32
+    pool = wl.pool_desc("max", 3, 2, pad)
+    layers = [wl.conv(64, k, s=2, p=k // 2, pre_bn=True, pool=pool)] if inside else [wl.conv(64, k, s=2, p=k // 2, pre_bn=True), wl.pool("max", 3, 2, pad)]
+    rng = np.random.default_rng([k, pad, 3])
+    x = _grid(rng.standard_normal((2, 3, 29, 34)), dt)
+    prm = wl.make_params(layers, 3, 5, bf16=(dt == "bf16"), bias_std=0.3)
+    net = sol.Network(layers, x.shape, d)
+    net.set_params(prm)
+    got = sol.to_host_nchw(net.forward(sol.to_device_nhwc(x, d)))
+    want = orc.network_forward(layers, prm, x, bf16=(dt == "bf16"), return_all=True)[0][-1]
+    assert rel_err(got.reshape(want.shape), want) <= TOL[dt]
+
+
 @pytest.mark.parametrize("k", [3, 7])
 def test_nothing_outside_a_window_counts(sol, k):  # noqa: F811
     """fp32: an infinity or a NaN reaches the outputs whose windows hold it, and no other."""
