@@ -248,9 +248,15 @@ __global__ void __launch_bounds__(512) conv_dense_kernel(const DenseArgs a) {
             for (int j = 0; j < PH; j++) Mma16<bf16_t>::run(acc[i][h * PH + j], fa[k][i], fb[u & 1][j]);
     };
     int rs = 0;                                            // ring slot of the current stage
-    auto step = [&](auto S, auto LAST, int c) __attribute__((always_inline)) {            // S: register set of chunk c + 1
-        constexpr bool last = decltype(LAST)::value;
-        wait_vmcnt<XR - (XR + U - 1) / U + (DW - 1) * (XR + 2)>();        // weight stage c: only what was issued after it is outstanding
+    // S: register set of chunk c + 1.  T: -1 inside the loop; t for the t-th step behind it, which asks for no more x; DX - 1 for the last
+    // chunk's, which may be any of those.
+    auto step = [&](auto S, auto T, int c) __attribute__((always_inline)) {
+        constexpr bool last = decltype(T)::value == DX - 1, loads = decltype(T)::value < 0;
+        // Weight stage c has landed once only what was issued after it is outstanding: what step c - DW asked for behind the stage's second half (x
+        // pieces but those of its first unit) and all of the DW - 1 steps since, of which t asked for weights alone.  (The prologue
+        // asked for more.)  Counted is what is in the program: a load whose registers nothing read would be taken out by the compiler, so none is written.
+        constexpr int t = decltype(T)::value < 0 ? 0 : decltype(T)::value, x_behind = t < DW ? (DW - t) * XR - (XR + U - 1) / U : 0;
+        wait_vmcnt<x_behind + (DW - 1) * 2>();
         __builtin_amdgcn_s_barrier();                      // ... for every wave; chunk c is in LDS; nobody still reads chunk c - 1
         // chunk c lies in buffer c & 1 = 1 - S & 1 (DX is even): an immediate offset, but for the last chunk
         constexpr int par = last ? 0 : (decltype(S)::value + 1) & 1;
@@ -269,11 +275,13 @@ __global__ void __launch_bounds__(512) conv_dense_kernel(const DenseArgs a) {
                     __builtin_amdgcn_sched_group_barrier(0x002, (28 * (end - first) + CA * PH - 1) / (CA * PH) + 1, 0);
                 });
             if constexpr (u < 2) issue_w_half(I);
+            keep_order();                                  // the count above
             if constexpr (last && u == 1) {                // the slots of all chunks but this one are free
 #pragma unroll
                 for (int e = DW + 1; e < NSW; e++) issue_w();
             }
-            if constexpr (!last) static_for<end - first>([&](auto J) { load_piece(S, std::integral_constant<int, first + decltype(J)::value>{}, c + 1 + DX); });
+            if constexpr (loads) static_for<end - first>([&](auto J) { load_piece(S, std::integral_constant<int, first + decltype(J)::value>{}, c + 1 + DX); });
+            keep_order();
             if constexpr (u + 1 < U) {
                 wait_lgkmcnt<last ? 0 : end - first>();
             } else {
@@ -290,11 +298,11 @@ __global__ void __launch_bounds__(512) conv_dense_kernel(const DenseArgs a) {
     // whole groups of DX iterations without a branch, so that the compiler can tell how many loads are outstanding where
     int c = 0;
     for (; c + DX < nc; c += DX)
-        static_for<DX>([&](auto S) { step(std::integral_constant<int, (decltype(S)::value + 1) % DX>{}, std::false_type{}, c + decltype(S)::value); });
+        static_for<DX>([&](auto S) { step(std::integral_constant<int, (decltype(S)::value + 1) % DX>{}, std::integral_constant<int, -1>{}, c + decltype(S)::value); });
     static_for<DX - 1>([&](auto S) {
-        if (c + decltype(S)::value + 1 < nc) step(std::integral_constant<int, (decltype(S)::value + 1) % DX>{}, std::false_type{}, c + decltype(S)::value);
+        if (c + decltype(S)::value + 1 < nc) step(std::integral_constant<int, (decltype(S)::value + 1) % DX>{}, S, c + decltype(S)::value);
     });
-    step(std::integral_constant<int, 0>{}, std::true_type{}, nc - 1);
+    step(std::integral_constant<int, 0>{}, std::integral_constant<int, DX - 1>{}, nc - 1);
     contract(std::integral_constant<int, U - 1>{});
     // what the rest needs of the thread's number is computed again: kept over the loop it is two registers too many for the largest patch
     int tid2 = tid;
