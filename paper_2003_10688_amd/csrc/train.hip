@@ -350,6 +350,13 @@ __global__ void __launch_bounds__(256) bn_apply_kernel(const T *__restrict__ z, 
 //   dres (+)= g                                   (when the layer has a residual input)
 //   dz = gamma invstd (g - dbeta / M - xhat dgamma / M),   xhat = (z - mean) invstd      (BN)
 //   dz = g                                                                               (no BN)
+// dz of one element, each rounding spelled out so that every kernel that computes it has the same bits.  FIXC: dbeta / M is rounded on its own,
+// as a product that leaves the loop over a thread's vectors is; otherwise it is a part of the fused subtraction.
+template <bool FIXC> __device__ __forceinline__ float bn_dz(float z, float g, float m, float is, float ga, float db, float dg, float inv_m) {
+#pragma clang fp contract(off)
+    const float xh = (z - m) * is, a = FIXC ? g - db * inv_m : __builtin_fmaf(-db, inv_m, g);
+    return ga * is * __builtin_fmaf(-inv_m, xh * dg, a);
+}
 template <typename T, int V, bool FIXC>
 __global__ void __launch_bounds__(256) act_bn_bwd_kernel(const T *__restrict__ z, const T *__restrict__ dy,
                                                          const T *__restrict__ y, const float *__restrict__ mean,
@@ -388,10 +395,7 @@ __global__ void __launch_bounds__(256) act_bn_bwd_kernel(const T *__restrict__ z
         if (bn) {
             VecIO<T, V>::load(z + i * V, t);
 #pragma unroll
-            for (int e = 0; e < V; e++) {
-                const float xh = (t[e] - m[e]) * is[e];
-                g[e] = ga[e] * is[e] * (g[e] - db[e] * inv_m - xh * dg[e] * inv_m);
-            }
+            for (int e = 0; e < V; e++) g[e] = bn_dz<FIXC>(t[e], g[e], m[e], is[e], ga[e], db[e], dg[e], inv_m);
         }
         VecIO<T, V>::store(dz + i * V, g);
     }
@@ -500,8 +504,8 @@ __global__ void __launch_bounds__(1024) bn_small_kernel(const T *__restrict__ z,
     }
 }
 
-// the column sums and act_bn_bwd_kernel (bn)
-template <typename T, int V>
+// the column sums and act_bn_bwd_kernel (bn; FIXC: as that kernel has it for this number of channels)
+template <typename T, int V, bool FIXC>
 __global__ void __launch_bounds__(1024) bn_small_bwd_kernel(const T *__restrict__ z, const T *__restrict__ dy, const T *__restrict__ y,
                                                             const float *__restrict__ mean, const float *__restrict__ invstd,
                                                             const float *__restrict__ gamma, float *__restrict__ dbeta, float *__restrict__ dgamma,
@@ -582,11 +586,7 @@ __global__ void __launch_bounds__(1024) bn_small_bwd_kernel(const T *__restrict_
         }
         float o[V];
 #pragma unroll
-        for (int e = 0; e < V; e++) {
-#pragma clang fp contract(off)
-            const float xh = (v[u][e] - m[e]) * is[e];
-            o[e] = ga[e] * is[e] * __builtin_fmaf(-inv_m, xh * dg[e], g[u][e] - db[e] * inv_m);
-        }
+        for (int e = 0; e < V; e++) o[e] = bn_dz<FIXC>(v[u][e], g[u][e], m[e], is[e], ga[e], db[e], dg[e], inv_m);
         VecIO<T, V>::store(dz + i, o);
     }
 }
@@ -1941,9 +1941,12 @@ sol_status launch_bn_small_bwd(const void *z, const void *dy, const void *y, con
                                float *dgamma, void *dz, void *dres, int res_first, int rows, int C, int relu, int dt, hipStream_t st) {
     auto run = [&](auto t, auto vec) {
         typedef decltype(t) T;
-        hipLaunchKernelGGL((bn_small_bwd_kernel<T, decltype(vec)::value>), dim3(C / BS_CH), dim3(1024), 0, st,
-                           static_cast<const T *>(z), static_cast<const T *>(dy), static_cast<const T *>(y), mean, invstd, gamma, dbeta, dgamma,
-                           static_cast<T *>(dz), static_cast<T *>(dres), res_first, rows, C, relu, 1.f / rows);
+        constexpr int V = decltype(vec)::value;
+        auto launch = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3(C / BS_CH), dim3(1024), 0, st, static_cast<const T *>(z), static_cast<const T *>(dy), static_cast<const T *>(y),
+                               mean, invstd, gamma, dbeta, dgamma, static_cast<T *>(dz), static_cast<T *>(dres), res_first, rows, C, relu, 1.f / rows);
+        };
+        if ((256 * V) % C == 0) launch(bn_small_bwd_kernel<T, V, true>); else launch(bn_small_bwd_kernel<T, V, false>);
     };
     if (dt == SOL_BF16) run(bf16_t{}, std::integral_constant<int, 8>{}); else run(0.f, std::integral_constant<int, 4>{});
     SOL_HIP(hipGetLastError());

@@ -1,4 +1,4 @@
-"""Batch norm of at most 1024 rows in one launch each way: against the checker, and bit for bit against the launches that longer tensors take."""
+"""Batch norm of at most 1024 rows in one launch each way: against the checker, and, forward and backward, bit for bit against the launches that longer tensors take."""
 import numpy as np
 import pytest
 import torch
@@ -54,3 +54,42 @@ def test_forward_bits(sol, dtype, shape):  # noqa: F811
         got.append([net.tensor(0, which).cpu().numpy()[:16] for which in (sol.NT_MEAN, sol.NT_VAR)] + [sol.to_host_nchw(net.layer_output(0))[:, :16]])
     for a, b in zip(*got):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("act", ["relu", "none"])
+@pytest.mark.parametrize("few,many", [(8, 16), (24, 48)])
+@pytest.mark.parametrize("shape", [(1, 1, 1)] + SHAPES[:-1], ids=lambda s: str(s[0] * s[1] * s[2]))
+def test_backward_bits(sol, dtype, act, few, many, shape):  # noqa: F811
+    """As above, backward: two layers of `many` channels against the general launches over the first `few` of them, which keep their
+    per-channel constants for all of a thread's vectors (8, as 16 would) or fetch them for each (24, as 48 would).  Layer 2 adds layer 1, which a
+    later layer reads too, so the gradient of its residual is added to what is there.  What layers 1 and 2 pass on reaches layer 0 through
+    identity filters, so its gradient is the sum of two dz; the last filters are so small that the logits are the biases."""
+    n, h, w = shape
+    d = sol.BF16 if dtype == "bf16" else sol.F32
+    lists = {c: [wl.conv(few, 1, p=0), wl.conv(c, 1, p=0), wl.conv(c, 1, p=0, src=0, res=1, act=act), wl.conv(8, 3, bn=False, act="none"),
+                 wl.conv(8, 1, p=0, src=1, res=3, bn=False, act="none"), wl.gap(), wl.linear(8)] for c in (few, many)}
+    gen = torch.Generator().manual_seed(n * h * w)
+    x = torch.randn((n, 16, h, w), generator=gen).numpy()
+    full = wl.make_params(lists[many], 16, 3, bf16=(dtype == "bf16"), bias_std=0.3)
+    for i in (1, 2):
+        full[i]["w"] = np.eye(many, few, dtype=np.float32).reshape(many, few, 1, 1)
+    full[6]["w"] = full[6]["w"] * np.float32(2.0 ** -40)
+    labels = torch.arange(n, dtype=torch.int32, device="cuda:0") % 8
+    got = []
+    for c, layers in lists.items():
+        p = [dict(prm) for prm in full]
+        for i in (1, 2):
+            p[i] = {k: v[:c] if isinstance(v, np.ndarray) else v for k, v in p[i].items()}
+        for i in (3, 4):
+            p[i]["w"] = p[i]["w"][:, :c]
+        net = sol.Network(layers, x.shape, d, flags=sol.NET_TRAINING)
+        net.set_params(p)
+        xd = sol.to_device_nhwc(x, d)
+        net.forward(xd)
+        net.backward(xd, labels)
+        torch.cuda.synchronize()
+        got.append([net.tensor(i, which).cpu().numpy()[:few] for i in (1, 2) for which in (sol.NT_GRAD_GAMMA, sol.NT_GRAD_BETA)]
+                   + [sol.to_host_nchw(net.layer_grad(i))[:, :few] for i in (2, 1, 0)])
+    for k, (a, b) in enumerate(zip(*got)):
+        assert np.array_equal(a, b) and (n * h * w == 1 or np.any(a)), k
