@@ -271,7 +271,7 @@ sol_status sol_network_forward_static(sol_network *net, const void *x, void *y, 
 void sol_debug_set_conv_tile(int tile);
 
 /* Which kernel the last convolution launched by the CALLING THREAD ran on (test aid): "small" (conv_small), "pre" (conv_pre), "chain"
- * (conv_chain), or "" for every other one.  Layers that one launch computes together do not count. */
+ * (conv_chain), "direct" (conv_direct on a pre-activated convolution), or "" for every other one.  Layers that one launch computes together do not count. */
 const char *sol_debug_conv_kernel(void);
 /* The tile id that the estimate of times takes for a convolution when none is asked for, with or without a residual and a fused 2x2 pool
  * (NULL: none); gradient != 0: for the data gradient of an fp32 training network.  0: no estimate holds, another rule decides.
@@ -373,9 +373,11 @@ sol_status sol_graph_launch(sol_graph *graph, void *hip_stream);
 void sol_graph_destroy(sol_graph *graph);
 
 /* Fused layer pairs (the paper's layer-chain fusion, Sec. III-A and IV), when a network keeps no activations
- * (flags 0), bf16:
- *   - a 7x7 stride-2 convolution of a 3-channel input with 64 filters, ReLU and no residual whose only consumer is
- *     a 3x3 stride-2 pad-1 max-pool LAYER runs in one kernel with that pool; the convolution's output is never stored;
+ * (flags 0), bf16 but for the first:
+ *   - a 7x7 or 3x3 stride-2 convolution, bf16 or fp32, of a 3-channel input with 64 filters, ReLU, no residual and no input-side BN
+ *     whose only consumer is a 3x3 stride-2 max-pool LAYER, unpadded or of pad 1, runs in one kernel with that pool (as it does with such a
+ *     pool of its own, sol_layer.pool).  The convolution's output is never stored: sol_network_layer_output refuses it, and a tile set for it
+ *     has no effect.  (sol_conv2d_fused itself takes the bf16 7x7 form with a pool of pad 1 alone.)
  *   - an unpadded 1x1 convolution (any stride) over a multiple of 64 channels without activation (a projection
  *     shortcut) whose only reader is the residual input of a later unpadded 1x1 stride-1 convolution over a multiple
  *     of 64 channels runs inside that convolution's launch; its output is never stored, and never rounded to the storage type either (the result differs from

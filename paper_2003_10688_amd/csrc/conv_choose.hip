@@ -12,6 +12,10 @@
 // On 2287 other layers the choice takes 1.014 (bf16) and 1.012 (fp32) times as long as the best of all tiles, where the rules of thumb that
 // stood here (thresholds on the number of 128x128 tiles) took 1.094 and 1.077 (geometric means); of the summed time 0.83 and 0.87; 721 layers
 // are faster by more than 5 %, 57 slower (11 by more than 10 %).  Tiles that change that by less than a ten-thousandth are left out.
+// Where it loses (of all 7500 layers timed, in bf16 33 by more than 10 % and 4 by more than 20, in fp32 5 and none): 1x1 layers whose tiles fill a
+// little more than a whole number of rounds, on G_128x128_k2 most often (us, rules of thumb -> here: 2 images of 54x54, 1024 -> 2048 channels, 40.6 ->
+// 52.4; 40 of 12x12, with residual, 43.6 -> 51.3); 1024 channels to 16 or 32 filters, where T_128x32 beats D_128x64_64x4 (20 of 58x58, 28.3
+// -> 35.1); 32 or 64 channels to many on D_64x64_64x4 (26 of 8x8, 64 -> 128, 4.1 -> 5.1).  The auto-tuner finds those.
 #include <math.h>
 
 #include "common.h"
@@ -137,7 +141,7 @@ int conv_choose_tile(const ConvArgs &a, int dt, SumOrder order) {
     for (int i = 0; i < nt; i++) {
         const TileCost &t = tab[i];
         if (t.rowb == 128 && !chunk128) continue;
-        if (t.maxw && (!halo || a.W > t.maxw || ((t.tile == H_256x64_x6s || t.tile == H_256x64_x6s2) && a.C != 64))) continue;
+        if (t.maxw && (!halo || a.W > t.maxw || (t.tile == H_256x64_x6s2 && a.C != 64))) continue;
         if (t.tile >= S_FIRST && !direct) continue;
         if (keep && !(rule >= S_FIRST ? t.tile >= S_FIRST : like && t.tile < S_FIRST && t.bp == like->bp && t.rowb == like->rowb)) continue;
         const float c = estimate(t, l, bt);

@@ -308,7 +308,7 @@ __global__ void __launch_bounds__(512) conv_dense_kernel(const DenseArgs a) {
     int tid2 = tid;
     asm volatile("" : "+v"(tid2));
     const int lane2 = tid2 & 63, lr2 = lane2 & 15, lg2 = lane2 >> 4;
-    // ---- t1: affine + ReLU in the accumulator layout (4 channels of one pixel per lane2), rounded to bf16, over the chunk buffers
+    // ---- t1: affine + ReLU in the accumulator layout (4 channels of one pixel per lane), rounded to bf16, over the chunk buffers
     __builtin_amdgcn_s_barrier();                          // the chunk buffers and the last chunk's weights are dead
     issue_w();
 #pragma unroll
@@ -351,7 +351,7 @@ __global__ void __launch_bounds__(512) conv_dense_kernel(const DenseArgs a) {
         acc2[b][0] = acc2[b][1] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     }
     // The pixel blocks of a wave lie 16 rows apart: one address (the slot permutation depends on row % 16), block b at an immediate
-    // offset; lanes whose tap is padding go to the zero row instead.  What bounded this loop was the arithmetic of its addresses (a lane2's
+    // offset; lanes whose tap is padding go to the zero row instead.  What bounded this loop was the arithmetic of its addresses (a lane's
     // validity in one register, tested for each tap: 25 VALU instructions for 5 reads and 6 MFMAs, 4700 of the 27000 cycles of a 96-row tile).
     unsigned zrow[NB];
 #pragma unroll

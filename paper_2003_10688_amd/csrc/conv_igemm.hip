@@ -241,12 +241,6 @@ static sol_status launch_cfg(ConvArgs a, hipStream_t st) {
     return SOL_OK;
 }
 
-// Tile of what conv_choose_tile leaves over (input channels that are not whole 64-byte chunks, operands of 2 GiB) and of the sums in
-// one order, from per-layer timing sweeps on MI355X.  Small-Cin layers
-// use the element-gather kernel; everything else the LDS-DMA ring kernel with
-//   - 64x64 tiles (many resident workgroups) for narrow outputs and for layers with few tiles,
-//   - 128x64 / 64x64 tiles, 64-byte rows x 4 stages (3-5 workgroups per CU) for the big HBM-bound layers,
-//   - 128x128 tiles, 128-byte rows x 2 stages for the mid-sized, reuse-heavy layers.
 // The LDS-DMA kernel keeps one validity bit per filter tap in a 32-bit mask and addresses both
 // operands with 32-bit byte offsets.
 static bool dma_kernel_applies(const ConvArgs &a, int esize) {
@@ -254,14 +248,20 @@ static bool dma_kernel_applies(const ConvArgs &a, int esize) {
     return a.R * a.S <= 32 && xb < 4294967296.0 && (double)a.Cout * a.Kp * esize < 4294967296.0;
 }
 
+// Tile by rules of thumb, for what conv_choose_tile leaves over (input channels that are not whole 64-byte chunks, more than 32 taps, operands of
+// 2 GiB and more, tile 99), and for the sums of fp32 training that keep their order (SUMS_CHAIN, gradient_tile), for whose sake the fp32 part is
+// not to be tuned.  From per-layer timing sweeps on MI355X: small-Cin layers
+// use the element-gather kernel; everything else the LDS-DMA ring kernel with
+//   - 64x64 tiles (many resident workgroups) for narrow outputs and for layers with few tiles,
+//   - 128x64 / 64x64 tiles, 64-byte rows x 4 stages (3-5 workgroups per CU) for the big HBM-bound layers,
+//   - 128x128 tiles, 128-byte rows x 2 stages for the mid-sized, reuse-heavy layers.
 int conv_rule_tile(const ConvArgs &a, int dt) {
     const int esize = (int)dtype_size(dt);
     const bool dma_ok = dma_kernel_applies(a, esize);
     const bool dma128 = dma_ok && a.C % (128 / esize) == 0, dma64 = dma_ok && a.C % (64 / esize) == 0;
-    if (a.Cout <= 32 || !dma64) return a.C % (128 / esize) == 0 ? (a.Cout <= 32 ? T_128x32 : T_128x64)
-                                                                 : (a.Cout <= 32 ? T_128x32 : T_128x64);
+    if (a.Cout <= 32 || !dma64) return a.Cout <= 32 ? T_128x32 : T_128x64;
     const bool wide = a.R * a.S > 1;
-    // chunks of 64 bytes, one channel tile: twice the pixels per weight row once there are four rounds of them (64 images of 55x55, us,
+    // bf16 operands of 2 GiB and more, chunks of 64 bytes, one channel tile: twice the pixels per weight row (64 images of 55x55, us,
     // 64 pixels / 128: 3x3 32 -> 64 22.8 / 17.6, 1x1 32 -> 64 11.2 / 8.9)
     if (a.Cout <= 64 && !dma128 && esize == 2 && a.P >= 128 * 1024) return D_128x64_64x4;
     if (a.Cout <= 64) return (wide && dma128) ? D_64x64_128x3 : D_64x64_64x4;

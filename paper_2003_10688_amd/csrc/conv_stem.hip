@@ -1,6 +1,6 @@
 // Fused stride-2 convolutions over 3-channel inputs (network stems: 7x7 pad 3 of the ResNet-shaped lists, 3x3 of
-// the depthwise-separable chain), bf16.  The text below describes the 7x7 case; a 3x3 filter pads each filter
-// row to 16 reduction elements instead of 32.
+// the depthwise-separable chain): on their own in bf16, with the 3x3 max pool behind them in bf16 and fp32 (further down).  The text below
+// describes the bf16 7x7 case; a 3x3 filter pads each filter row to 16 reduction elements instead of 32.
 //
 // With Cin = 3 the reduction index (r, s, c) has no 16-byte-contiguous runs in NHWC, so the generic
 // implicit GEMM has to gather single elements.  Here a workgroup instead stages the input patch of

@@ -308,7 +308,7 @@ def sol_debug_set_conv_tile(tile):
 
 
 def sol_debug_conv_kernel():
-    """Which kernel this thread's last convolution ran on: "small", "pre", "chain", or "" for every other one."""
+    """Which kernel this thread's last convolution ran on: "small", "pre", "chain", "direct" (pre-activated), or "" for every other one."""
     return lib().sol_debug_conv_kernel().decode()
 
 
