@@ -11,29 +11,36 @@ from test_gpu_parity import TOL, make_block, rel_err, run_block, sol  # noqa: F4
 pytestmark = pytest.mark.gpu
 
 CASES = [
-    # N, C, H, W, K, k, s, p, res, pool
-    (2, 64, 31, 31, 128, 3, 1, 1, True, None),      # widest image of the halo tiles, and one column more
-    (2, 64, 31, 32, 128, 3, 1, 1, True, None),
-    (1, 64, 17, 62, 64, 3, 1, 1, False, None),      # the same for the tiles of wide images
-    (1, 64, 17, 63, 64, 3, 1, 1, False, None),
-    (3, 128, 20, 62, 64, 3, 1, 1, True, None),      # wide, two chunks: not the single-chunk tile
-    (40, 256, 14, 14, 256, 3, 1, 1, False, None),   # enough 256-pixel tiles
-    (9, 32, 24, 23, 32, 3, 1, 1, False, None),      # rows of 64 bytes, few filters
-    (9, 32, 24, 24, 32, 3, 1, 1, False, "max"),
-    (5, 96, 19, 19, 40, 3, 2, 1, False, None),      # half a chunk over, ragged filters
-    (50, 64, 33, 33, 16, 1, 1, 0, True, None),      # many pixels, few filters
-    (20, 128, 28, 28, 512, 1, 1, 0, True, None),
-    (33, 256, 15, 15, 1000, 1, 1, 0, False, None),  # channels that no tile divides
-    (16, 512, 14, 14, 512, 3, 2, 1, False, None),
-    (30, 128, 30, 30, 128, 3, 1, 1, False, "avg"),
-    (12, 64, 26, 26, 33, 1, 2, 0, False, None),     # not a multiple of 4
+    # N, C, H, W, K, k, s, p, res, pool, and the tiles they run on, fp32 and bf16 (tests/test_choose_host.py sees to it that they do)
+    (2, 64, 31, 31, 128, 3, 1, 1, True, None, 83, 83), (2, 64, 31, 32, 128, 3, 1, 1, True, None, 83, 83),       # small tiles, odd and even rows
+    (1, 64, 17, 62, 64, 3, 1, 1, False, None, 82, 82), (1, 64, 17, 63, 64, 3, 1, 1, False, None, 82, 82),
+    (3, 128, 20, 62, 64, 3, 1, 1, True, None, 83, 83), (33, 64, 8, 8, 1000, 3, 2, 1, False, None, 83, 85),
+    # halo tiles: the widest image of each, and one column more
+    (53, 64, 20, 31, 96, 3, 1, 1, False, None, 83, 41), (53, 64, 20, 32, 96, 3, 1, 1, False, None, 83, 45),
+    (61, 128, 13, 31, 16, 3, 1, 1, False, None, 81, 48), (61, 128, 13, 32, 16, 3, 1, 1, False, None, 81, 81),
+    (14, 64, 31, 31, 40, 3, 1, 1, False, None, 85, 49), (14, 64, 31, 32, 40, 3, 1, 1, False, None, 85, 26),
+    (50, 64, 7, 62, 16, 3, 1, 1, False, None, 81, 45), (50, 64, 7, 63, 16, 3, 1, 1, False, None, 81, 83),       # one chunk of channels
+    (29, 128, 16, 62, 16, 3, 1, 1, False, None, 81, 50), (29, 128, 16, 63, 16, 3, 1, 1, False, None, 81, 83),   # two
+    (29, 128, 16, 62, 16, 3, 1, 1, True, None, 81, 50), (40, 256, 14, 14, 256, 3, 1, 1, False, None, 85, 48),
+    (9, 32, 24, 23, 32, 3, 1, 1, False, None, 83, 15), (9, 32, 24, 24, 32, 3, 1, 1, False, "max", 83, 15),      # rows of 64 bytes, few filters
+    (5, 96, 19, 19, 40, 3, 2, 1, False, None, 81, 15),                                                          # half a chunk over, ragged filters
+    (50, 64, 33, 33, 16, 1, 1, 0, True, None, 6, 6), (20, 32, 63, 63, 16, 1, 1, 0, False, None, 6, 14),         # many pixels, few filters
+    (13, 192, 47, 47, 16, 1, 1, 0, True, None, 6, 24), (13, 128, 35, 35, 33, 1, 2, 0, False, None, 81, 26),
+    (20, 128, 28, 28, 512, 1, 1, 0, True, None, 18, 21), (33, 256, 15, 15, 1000, 1, 1, 0, False, None, 18, 21),  # channels that no tile divides
+    (8, 128, 41, 41, 1000, 1, 2, 0, False, None, 18, 23), (33, 32, 64, 64, 96, 1, 2, 0, False, None, 6, 18),
+    (16, 512, 14, 14, 512, 3, 2, 1, False, None, 83, 84), (30, 128, 30, 30, 128, 3, 1, 1, False, "avg", 18, 61),
+    (20, 384, 25, 25, 1000, 1, 2, 0, False, None, 18, 61), (64, 192, 17, 17, 33, 3, 1, 1, False, None, 81, 65),
+    (33, 32, 39, 39, 1000, 1, 2, 0, False, None, 18, 66), (64, 96, 28, 28, 96, 1, 1, 0, False, None, 6, 67),
+    (12, 64, 26, 26, 33, 1, 2, 0, False, None, 82, 15),                                                         # not a multiple of 4
+    (3, 32, 61, 61, 33, 1, 2, 0, False, None, 33, 15), (5, 96, 56, 56, 32, 1, 1, 0, False, None, 24, 15),
+    (20, 32, 25, 25, 33, 1, 2, 0, False, None, 15, 15), (64, 64, 19, 19, 33, 1, 2, 0, True, None, 26, 15),
 ]
 
 
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
 @pytest.mark.parametrize("case", CASES)
 def test_choice_against_general_path(sol, dt, case):  # noqa: F811
-    N, C, H, W, K, k, s, p, res, pool = case
+    N, C, H, W, K, k, s, p, res, pool = case[:10]
     rng = np.random.default_rng([N, C, H, K, k, s])
     l, x, prm, r = make_block(sol, rng, dt, N, C, H, W, K, k, s, p, res=res, pool=wl.pool_desc(pool, 2, 2, 0) if pool else None)
     got = run_block(sol, dt, l, x, prm, r)[0]
