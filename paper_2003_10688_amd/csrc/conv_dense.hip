@@ -18,7 +18,7 @@
 // What bounds it: two waves per SIMD that meet at a barrier once per chunk issue one instruction in about nine cycles each, whatever its
 // kind, so a chunk costs what it has of instructions, and what runs beside one another inside a wave.  Against a version that ran a
 // chunk's fragment reads, BN + ReLU and MFMAs one behind the other, chose each stage's matrix anew, tested each tap of each lane
-// and waited for everything at the start: DenseNet-121-shaped pass, batch 64, 1250 -> 1093 us; one layer, 64 images, us, that version ->
+// and waited for everything at the start: DenseNet-121-shaped pass, batch 64, 1250 -> 1093 us (another card 1262 -> 1121); one layer, 64 images, us, that version ->
 // this: 56x56, 64 / 192 channels 44 / 60 -> 37 / 52; 28x28, 128 / 480: 15.4 / 22 -> 11 / 18; 14x14, 256 / 640: 11 / 14 -> 8.2 / 12; 7x7, 512 / 992: 10 / 13 -> 8.1 /
 // 11.  Cycles of a tile of 96 rows, 640 channels: start 5600 -> 4800, phase A 1410 -> 1210 a chunk (products alone 384, BN + ReLU alone
 // 500, LDS 650), t1 1050 -> 1400, phase B 6500 -> 3400 (products 1730), sums and output 2000 -> 2200.  Without effect there: constants of two
