@@ -1,4 +1,5 @@
-"""Batch norm of at most 1024 rows in one launch each way: against the checker, and, forward and backward, bit for bit against the launches that longer tensors take."""
+"""Batch norm of at most 1024 rows in one launch each way: against the oracle, and, forward and backward, bit for bit against the launches that
+longer tensors take."""
 import numpy as np
 import pytest
 import torch

@@ -1,5 +1,5 @@
 """The automatic choice of kernel and tile by estimated time: whatever it takes computes what the general path (the implicit-GEMM kernels
-alone, tile 99) and the checker compute, over the forms that it accepts and at the limits of the kernels it picks between."""
+alone, tile 99) and the oracle compute, over the forms that it accepts and at the limits of the kernels it picks between."""
 import numpy as np
 import pytest
 import torch
@@ -51,7 +51,7 @@ def test_choice_against_general_path(sol, dt, case):  # noqa: F811
         sol.sol_debug_set_conv_tile(0)
     # two sums of the same terms in different orders, both within the tolerance of the exact one
     assert rel_err(got, general) <= 2 * TOL[dt]
-    few = np.sort(rng.choice(N, min(N, 2), replace=False))             # the checker's loops take two images
+    few = np.sort(rng.choice(N, min(N, 2), replace=False))             # the oracle's loops take two images
     want = orc.fused_conv(x[few], prm, l, None if r is None else r[few], bf16=(dt == "bf16"))[0]
     assert rel_err(got[few], want) <= TOL[dt]
 

@@ -20,7 +20,7 @@ CASES = [
 @pytest.mark.parametrize("pad", [0, 1])
 @pytest.mark.parametrize("case", CASES, ids=lambda c: "x".join(map(str, c)))
 def test_stem_pool_planned(sol, dt, k, pad, case):  # noqa: F811
-    """Against the checker and against the plan that keeps every activation (convolution stored, then the pool): bit for bit in bf16, where
+    """Against the oracle and against the plan that keeps every activation (convolution stored, then the pool): bit for bit in bf16, where
     rounding before the maximum is the same; within two summation orders in fp32."""
     N, H, W, p = case
     d = sol.BF16 if dt == "bf16" else sol.F32
@@ -35,7 +35,7 @@ def test_stem_pool_planned(sol, dt, k, pad, case):  # noqa: F811
         ys[keep] = sol.to_host_nchw(net.forward(sol.to_device_nhwc(x, d)))
         torch.cuda.synchronize()
         assert net.fused_into(1) == (1 if keep else 0)
-    few = np.unique([0, N - 1])                                        # the checker's loops take two images
+    few = np.unique([0, N - 1])                                        # the oracle's loops take two images
     want = orc.network_forward(layers, prm, x[few], bf16=(dt == "bf16"), return_all=True)[0][-1]
     assert rel_err(ys[False][few].reshape(want.shape), want) <= TOL[dt]
     if dt == "bf16":
